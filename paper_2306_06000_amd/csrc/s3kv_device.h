@@ -351,30 +351,72 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
     return v;
 }
 
-// Partials that cross workgroups inside ONE launch (fused step) must not sit in a cache that
-// another XCD cannot see: they are written and read with volatile 64- and 128-bit vector accesses,
-// which on gfx950 are plain stores / loads marked to go through to memory-side coherence.  No cache
-// write-back or invalidate is needed then (those cost far more than the partials themselves).
+// Partials that cross workgroups inside ONE launch (fused step) must not sit in a cache that another XCD
+// cannot see: they are stored and loaded with the sc0 sc1 cache bits (write-through to, and read from,
+// memory-side coherence).  No cache write-back or invalidate is needed then (those cost far more than the
+// partials themselves).  The accesses are written as machine instructions because the two ways the compiler
+// offers are both slower than the exchange itself: `volatile` accesses carry the bits but each one is waited
+// for on its own (three memory round trips per partial stored and three per partial merged: a context of 1417
+// rows cut into 23 chunks took 27 us against 20 us in 12 chunks), and atomics are at most 64 bits wide.
+// A store is left in flight (chunk_arrived() drains the wave's memory counter before the count; the s_nop keeps
+// the data registers unwritten for the cycle that a store of more than 64 bits needs); loads wait inside
+// their own asm block, so that no register is ever the target of a load the compiler does not know of.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <bool COHERENT>
 __device__ __forceinline__ void put_partial4(float *p, const f32x4 v) {
-    if (COHERENT) *(volatile f32x4 *)p = v;
+    if (COHERENT) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
     else *(f32x4 *)p = v;
 }
 template <bool COHERENT>
 __device__ __forceinline__ void put_partial2(float *p, const f32x2 v) {
-    if (COHERENT) *(volatile f32x2 *)p = v;
+    if (COHERENT) asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
     else *(f32x2 *)p = v;
 }
 template <bool COHERENT>
 __device__ __forceinline__ f32x4 get_partial4(const float *p) {
-    if (COHERENT) return *(const volatile f32x4 *)p;
-    return *(const f32x4 *)p;
+    if (!COHERENT) return *(const f32x4 *)p;
+    f32x4 v;
+    asm volatile("global_load_dwordx4 %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p) : "memory");
+    return v;
 }
 template <bool COHERENT>
 __device__ __forceinline__ f32x2 get_partial2(const float *p) {
-    if (COHERENT) return *(const volatile f32x2 *)p;
-    return *(const f32x2 *)p;
+    if (!COHERENT) return *(const f32x2 *)p;
+    f32x2 v;
+    asm volatile("global_load_dwordx2 %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p) : "memory");
+    return v;
+}
+// Four partials at once, one memory round trip for all: (max, sum) at ml[u], eight accumulator values at acc[u].
+template <bool COHERENT>
+__device__ __forceinline__ void get_partials(const float *const (&ml)[4], const float *const (&acc)[4], f32x2 (&m)[4], f32x4 (&lo)[4],
+                                             f32x4 (&hi)[4]) {
+    if (!COHERENT) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            m[u] = *(const f32x2 *)ml[u];
+            lo[u] = *(const f32x4 *)acc[u];
+            hi[u] = *(const f32x4 *)(acc[u] + 4);
+        }
+        return;
+    }
+    asm volatile(
+        "global_load_dwordx2 %0, %12, off sc0 sc1\n\t"
+        "global_load_dwordx2 %1, %13, off sc0 sc1\n\t"
+        "global_load_dwordx2 %2, %14, off sc0 sc1\n\t"
+        "global_load_dwordx2 %3, %15, off sc0 sc1\n\t"
+        "global_load_dwordx4 %4, %16, off sc0 sc1\n\t"
+        "global_load_dwordx4 %5, %16, off offset:16 sc0 sc1\n\t"
+        "global_load_dwordx4 %6, %17, off sc0 sc1\n\t"
+        "global_load_dwordx4 %7, %17, off offset:16 sc0 sc1\n\t"
+        "global_load_dwordx4 %8, %18, off sc0 sc1\n\t"
+        "global_load_dwordx4 %9, %18, off offset:16 sc0 sc1\n\t"
+        "global_load_dwordx4 %10, %19, off sc0 sc1\n\t"
+        "global_load_dwordx4 %11, %19, off offset:16 sc0 sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]), "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]),
+          "=&v"(lo[2]), "=&v"(hi[2]), "=&v"(lo[3]), "=&v"(hi[3])
+        : "v"(ml[0]), "v"(ml[1]), "v"(ml[2]), "v"(ml[3]), "v"(acc[0]), "v"(acc[1]), "v"(acc[2]), "v"(acc[3])
+        : "memory");
 }
 
 // A wave has written its chunk's partial: count the chunk on the context's arrival counter.  Returns true
@@ -383,16 +425,15 @@ __device__ __forceinline__ f32x2 get_partial2(const float *p) {
 // Two orderings of "my partial is visible before my count, the others' partials are visible after theirs":
 //   merge_sync 0  the partials are written and read with the write-through / cache-bypassing accesses above,
 //                 so they are at the memory side once this wave's vector-memory counter has drained
-//                 (s_waitcnt 0); the counter is a relaxed device-scope atomic.  This rests on `volatile`
-//                 vector accesses being emitted with the sc0 sc1 cache bits on gfx950 (a host-side test
-//                 compiles these helpers and checks the bits in the emitted code).
+//                 (s_waitcnt 0); the counter is a relaxed device-scope atomic.  (A host-side test compiles
+//                 these helpers and checks the cache bits and the order in the emitted code.)
 //   merge_sync 1  the same accesses, ordered by the memory model instead: a device-scope release fence
 //                 before the count and an acquire fence in the wave that merges (L2 write-back and
 //                 invalidate on this device, which cost far more than the partials themselves).
 __device__ __forceinline__ bool chunk_arrived(const AttnArgs &a, unsigned int *cnt, int nchunks) {
     const int lane = threadIdx.x & 63;
     if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    else __builtin_amdgcn_s_waitcnt(0);  // this wave's partial stores have completed
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wave's partial stores have completed
     unsigned int old = 0;
     if (lane == 0) old = atomicAdd(cnt, 1u);
     old = __builtin_amdgcn_readfirstlane(old);
@@ -403,8 +444,8 @@ __device__ __forceinline__ bool chunk_arrived(const AttnArgs &a, unsigned int *c
 }
 
 // Merge the chunk partials of (sequence b, head h) for this lane's 8-element slice and store the
-// final output row slice; H is the head count of the partial and output arrays.  nchunks >= 2.  Four chunks are loaded per round so that the (cache
-// bypassing) loads of a round are in flight together.
+// final output row slice; H is the head count of the partial and output arrays.  nchunks >= 2.  Four chunks are loaded
+// per round, in one memory round trip.
 template <int D, bool COHERENT>
 __device__ __forceinline__ void merge_chunks(const AttnArgs &a, int H, int b, int h, int dl, int nchunks) {
     const int64_t p0 = ((int64_t)b * a.max_chunks) * H + h;
@@ -413,18 +454,24 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs &a, int H, int b, in
     float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0; c0 < nchunks; c0 += 4) {
         float mv[4], lv[4], av[4][8];
+        const float *mp[4], *ap[4];
+        f32x2 mlv[4];
+        f32x4 lo[4], hi[4];
 #pragma unroll
         for (int u = 0; u < 4; u++) {
             const int64_t pi = p0 + (int64_t)min(c0 + u, nchunks - 1) * H;
-            const f32x2 mlv = get_partial2<COHERENT>(ml + 2 * pi);
-            mv[u] = mlv[0];
-            lv[u] = mlv[1];
-            const float *pa = a.part_acc + pi * D + dl * 8;
-            const f32x4 lo = get_partial4<COHERENT>(pa), hi = get_partial4<COHERENT>(pa + 4);
+            mp[u] = ml + 2 * pi;
+            ap[u] = a.part_acc + pi * D + dl * 8;
+        }
+        get_partials<COHERENT>(mp, ap, mlv, lo, hi);
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            mv[u] = mlv[u][0];
+            lv[u] = mlv[u][1];
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                av[u][i] = lo[i];
-                av[u][4 + i] = hi[i];
+                av[u][i] = lo[u][i];
+                av[u][4 + i] = hi[u][i];
             }
         }
         float mn = mm;
