@@ -172,9 +172,9 @@ int s3_decode_attention(s3_arena *a, int32_t layer, int32_t n, const void *q, co
  * workgroup that delivers the last chunk of a context merges the chunks, so no second kernel runs.
  *   len_out   DEVICE [n] int32 or NULL: receives pos[b] + 1, the positions of the next step; must not
  *             be the same array as pos (S3_ERR_INVALID) - alternate between two arrays. */
-/* (Shared key/value heads: the same call, results and checks, as two or three launches on `stream`: the
+/* (Shared key/value heads: the same call, results and checks, as one to three launches on `stream`: the
  * append (folded into the attention kernel when the matrix-core kernel runs over 16-bit rows), the
- * attention kernel, and a merge of chunk partials.  An 8-bit cache rounds the new row to codes in the
+ * attention kernel, and, with the vector-ALU kernel, a merge of chunk partials.  An 8-bit cache rounds the new row to codes in the
  * same kernel that attends over it.) */
 int s3_decode_step(s3_arena *a, int32_t layer, int32_t n, const int32_t *slot_id, const int32_t *pos_host,
                    const int64_t *slot_off, const int32_t *pos, const void *q, const void *k_new,
@@ -340,12 +340,9 @@ int s3_kv_probe_bandwidth(s3_arena *a, size_t bytes, int32_t mode, int32_t reps,
  *                  caches, 8-bit rows) are ordered across workgroups: 0 (default) write-through partial
  *                  stores, a drained memory counter and a relaxed counter increment; 1 device-scope
  *                  release / acquire fences around the increment (slower; same results)
- *   "gqa_merge"    shared key/value heads, matrix-core kernel: 1 = multi-chunk contexts are finished inside the
- *                  attention launch (arrival counters, write-through partials), 0 (default) = by a merge launch;
- *                  same results; the launch-saving form measured slower (its partials bypass the caches)
- *   "gqa_dynamic"  shared key/value heads, matrix-core kernel: per cent of the work list that is dealt by stride
- *                  before the waves claim the remaining positions from a device-wide counter (1..99; 0, 100 or -1,
- *                  the default = all by stride: claims pay only on very long lists of long items); same results
+ *   "gqa_merge", "gqa_dynamic"  shared key/value heads, matrix-core kernel: accepted (0 or 1; -1..100) and kept for
+ *                  callers that set them, without effect: the kernel divides the rows of a batch evenly over its
+ *                  waves and always merges the pieces of a context inside the launch
  *   "gqa_stream"   shared key/value heads, matrix-core kernel: how K rows are read: 1 = with the streaming hint
  *                  (whole rows per load, operand layout through LDS), 0 = plain loads straight into operand layout,
  *                  -1 (default) = 1 if the launch's K rows exceed the 256 MB memory-side cache, else 0; same results

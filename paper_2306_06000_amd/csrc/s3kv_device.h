@@ -36,18 +36,36 @@ struct AttnArgs {
     int32_t *len_out;        // may be null
     unsigned int *arrivals;  // [n][n_hgb] chunk-arrival counters, zero between launches
     int32_t merge_sync;      // how chunks that meet inside one launch are ordered: see chunk_arrived()
-    int32_t merge_in_kernel; // matrix-core kernel for shared heads: chunks meet inside the launch (no merge launch follows)
     unsigned int *queue;     // [2] kernels with a dynamic work list: positions claimed, workgroups gone; zero between launches
     int32_t stream_k;        // matrix-core kernel for shared heads: K rows with the streaming hint (1), plain (0), by launch size (< 0)
-    int32_t dyn_list;        // matrix-core kernel for shared heads: per cent of the list dealt by stride before waves claim positions from `queue` (0: all by stride)
+    // matrix-core kernel for shared heads: how the rows are divided among the waves
+    int32_t group, nqb, columns;          // query heads per cached head, blocks of 16 of them, columns = H * nqb
+    int32_t wave_shares, team_shares;     // shares per column if every wave takes one, if teams of four waves do
+    int32_t max_shares;  // partial slots allow this many publishing units per column
+    int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
+    int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
 };
 
-__device__ __forceinline__ int checked_len(const AttnArgs &a, int b) {
-    const int64_t off = a.slot_off[b];
-    const int32_t raw = a.cur_len[b];
+__device__ __forceinline__ int checked_len(const AttnArgs &a, int64_t off, int32_t raw) {
     const int64_t len = (int64_t)raw + a.len_add;
     const bool ok = off >= 0 && raw >= 0 && len <= a.max_len && off + len <= a.n_tokens;
     return ok ? (int)len : 0;
+}
+__device__ __forceinline__ int checked_len(const AttnArgs &a, int b) { return checked_len(a, a.slot_off[b], a.cur_len[b]); }
+
+// Entries first .. first+E-1 of the device arrays (length 0 past the end of the batch).  No branch around a load:
+// all of them leave together and cost one memory round trip.
+template <int E>
+__device__ __forceinline__ void load_entries(const AttnArgs &a, int first, int64_t (&off)[E], int (&len)[E]) {
+    int32_t raw[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int b = min(first + e, a.n - 1);
+        off[e] = a.slot_off[b];
+        raw[e] = a.cur_len[b];
+    }
+#pragma unroll
+    for (int e = 0; e < E; e++) len[e] = first + e < a.n ? checked_len(a, off[e], raw[e]) : 0;
 }
 
 template <int CTRL>
@@ -211,16 +229,16 @@ template <int E>
 __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre) {
     const int lane = threadIdx.x & 63;
     const int ncls = a.ncls, chunk = a.chunk, n = a.n;
+    int64_t off[E];
     int len[E], cls[E], cnt[E];
     int mx = 0;
+    load_entries<E>(a, lane * E, off, len);
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const int b = lane * E + e;
-        len[e] = 0;
         if (b < n) {
-            len[e] = checked_len(a, b);
             len_s[b] = len[e];
-            off_s[b] = a.slot_off[b];
+            off_s[b] = off[e];
         }
         mx = max(mx, len[e]);
     }
@@ -245,6 +263,63 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         }
         if (lane == 63) pre[c * (n + 1) + n] = incl;
     }
+}
+
+// The view with one length class, built by the whole workgroup: of every E * threads entries, thread t owns E
+// neighbours; two barriers.  Returns the number of chunks.
+template <int E>
+__device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t *off_s, int *len_s, int *pre, int *wave_sums) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+    int total = 0;
+#pragma unroll 1
+    for (int base = 0; base < a.n; base += E * (int)blockDim.x) {
+        int64_t off[E];
+        int len[E], cnt[E], sum = 0;
+        load_entries<E>(a, base + tid * E, off, len);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            const int b = base + tid * E + e;
+            cnt[e] = (len[e] + chunk - 1) / chunk;
+            sum += cnt[e];
+            if (b < a.n) {
+                len_s[b] = len[e];
+                off_s[b] = off[e];
+            }
+        }
+        const int incl = wave_inclusive_scan(sum);
+        if (lane == 63) wave_sums[wave] = incl;
+        __syncthreads();
+        const int upto = wave_inclusive_scan(lane < nwaves ? wave_sums[lane] : 0);
+        int run = total + incl - sum + (wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0);
+        total += __builtin_amdgcn_readlane(upto, nwaves - 1);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            const int b = base + tid * E + e;
+            if (b < a.n) pre[b] = run;
+            run += cnt[e];
+        }
+        if (tid == 0) pre[a.n] = total;
+        __syncthreads();
+    }
+    return total;
+}
+
+// A view with one length class in chunks (tiles) of CHUNK rows.  Kept small: it runs once, out of a cold
+// instruction cache.
+template <int CHUNK>
+__device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dyn, int *wave_sums) {
+    int64_t *off_s = (int64_t *)dyn;
+    int *len_s = (int *)(dyn + (size_t)a.n * 8);
+    int *pre = len_s + ((a.n + 1) & ~1);
+    BatchView v;
+    v.off = off_s;
+    v.len = len_s;
+    v.pre = pre;
+    v.n = a.n;
+    v.ncls = 1;
+    v.total = a.n <= (int)blockDim.x ? block_view<1>(a, CHUNK, off_s, len_s, pre, wave_sums)
+                                     : block_view<4>(a, CHUNK, off_s, len_s, pre, wave_sums);
+    return v;
 }
 
 // One pass over the device arrays (each entry is read from global memory once and checked once),
@@ -278,6 +353,18 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         v.ncls = ncls;
         v.total = 0;
         for (int c = 0; c < ncls; c++) v.total += pre[c * (n + 1) + n];
+        return v;
+    }
+    if (ncls == 1) {
+        // One class: a scan over the workgroup (the general path below walks the entries three times and costs a
+        // batch of 1024 about 5 us before its first load).
+        BatchView v;
+        v.off = off_s;
+        v.len = len_s;
+        v.pre = pre;
+        v.n = n;
+        v.ncls = 1;
+        v.total = block_view<4>(a, chunk, off_s, len_s, pre, wave_sums);
         return v;
     }
     const int per = (n + nthreads - 1) / nthreads;
@@ -419,6 +506,17 @@ __device__ __forceinline__ void get_partials(const float *const (&ml)[4], const 
         : "memory");
 }
 
+// The same loads as relaxed system-scope atomics of 64 bits (sc0 sc1 as well): twice the instructions, but the
+// compiler tracks them, so any number of them stays in flight at once.
+__device__ __forceinline__ f32x2 get_coherent2(const float *p) {
+    const uint64_t v = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return __builtin_bit_cast(f32x2, v);
+}
+__device__ __forceinline__ f32x4 get_coherent4(const float *p) {
+    const f32x2 lo = get_coherent2(p), hi = get_coherent2(p + 2);
+    return (f32x4){lo[0], lo[1], hi[0], hi[1]};
+}
+
 // A wave has written its chunk's partial: count the chunk on the context's arrival counter.  Returns true
 // (to every lane) in the wave that delivered the LAST chunk of the context; that wave then merges the chunks,
 // and the counter is back at zero for the next launch.  Called by whole waves in uniform control flow.
@@ -521,6 +619,19 @@ __device__ __forceinline__ void split_rows(const Item &it, int ts, int TS, int &
     j1 = min(end, j0 + per);
 }
 
+// The first sequence whose range of a prefix-sum array holds position w: the number of entries b with pre[b + 1] <= w
+// (the sums are non-decreasing).  Whole waves, every lane with the same w.  The lanes test every ceil(n/64)-th
+// border at once and then the borders between two of those: two LDS round trips whatever the batch.
+__device__ __forceinline__ int find_sequence(const int *pre, int n, int w) {
+    const int lane = threadIdx.x & 63;
+    const int step = (n + 63) >> 6;
+    int e = (lane + 1) * step;
+    const int at = step * __builtin_popcountll(__builtin_amdgcn_ballot_w64(e <= n && pre[min(e, n)] <= w));
+    if (step == 1) return at;
+    e = at + lane + 1;
+    return at + __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < step - 1 && e <= n && pre[min(e, n)] <= w));
+}
+
 // Work-list position -> item.  Called by whole waves (every lane with the same `item`): the class
 // totals are read by the first lanes at once and the sequence is found by counting, lanes in parallel,
 // the entries whose inclusive prefix does not exceed the position (the prefix sums are non-decreasing,
@@ -542,12 +653,7 @@ __device__ __forceinline__ Item decode_item(const AttnArgs &a, const BatchView &
         w -= t;
     }
     const int *pre = v.pre + cls * (v.n + 1);
-    int lo = 0;
-    for (int base = 0; base < v.n; base += 64) {
-        const int b = base + lane;
-        const bool below = b < v.n && pre[b + 1] <= w;
-        lo += __builtin_popcountll(__builtin_amdgcn_ballot_w64(below));
-    }
+    int lo = find_sequence(pre, v.n, w);
     lo = min(lo, v.n - 1);  // a consistent view never needs this
     it.b = lo;
     it.c = w - pre[lo];

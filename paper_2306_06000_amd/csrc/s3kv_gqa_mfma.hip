@@ -9,9 +9,17 @@
 // per cached head; here both products run on MFMA and every (row, head) score is handled by
 // exactly one lane.
 //
-// One wave = one work item = (sequence, chunk of its context, K/V head, block of 16 query heads);
-// the four waves of a workgroup are independent (no barrier after the batch-view prologue).  Per
-// tile of 16 cached rows:
+// Work division.  A column is one (K/V head, block of 16 query heads); the rows of all contexts, laid end to
+// end in tiles of 16, are the same length for every column.  That length is cut into equal shares and a wave
+// takes one share of one column, across the borders of contexts, so the waves end together whatever the
+// lengths of the batch and a context is cut only where a share ends (see share_plan below for the number of
+// shares).  A context inside one share leaves as its final row; a piece of a longer one leaves as a partial
+// (max, sum, unnormalised row) and whoever delivers the last piece merges them inside this launch.  Until this
+// division the unit was a chunk of 128 or 256 rows, dealt by stride: nearly every context left partials (7 to
+// 14 % extra traffic), a second launch merged them (5 to 6 us of device time a step) and the last round of the
+// stride left units idle (16 query heads on one cached head of 256, 256 contexts of 32..1000 rows: 1216 chunks
+// on 1024 waves).
+// Per tile of 16 cached rows:
 //   * K: lane (r = lane % 16, g = lane / 16) holds 16 bytes (8 elements) of row r at element offset
 //     32*ks + 8*g, ks = 0 .. D/32-1 - loaded so directly with plain loads, or, in launches whose K rows
 //     exceed the memory-side cache, loaded in whole rows with the streaming hint and brought into that
@@ -36,20 +44,8 @@
 //     and a low part (the remainder, rounded), and the product is issued for both, which keeps the
 //     weights' error near 2^-16 (bfloat16) / 2^-22 (fp16) instead of 2^-9 / 2^-12: with one part only,
 //     values of magnitude 1e2 put the fp16 kernel outside the attention tolerance.
-// Accumulators: O^T block db holds O^T[d = 16*db + 4*g + i][head], fp32.  Results leave as the
-// final row (single-chunk contexts) or as a chunk partial (max, sum, unnormalised row).  Partials are
-// finished either by attn_merge_kernel (a second launch) or, with merge_in_kernel, inside this launch:
-// an arrival counter per (sequence, K/V head, query block), write-through partials, the wave that
-// delivers the last chunk merges.  Done at once after every item this tripled the kernel's time (with
-// one wave per item nothing hides the write-through and the counter's round trip); here the
-// publication of an item trails the wave's work by two items - the counter is bumped at the end of the
-// NEXT item, when the partial's stores have long completed, and its answer is looked at one item
-// later still - so a wave never waits for either.  It still loses to the merge launch and is not the
-// default: with 128-row chunks nearly every item leaves an 8 KiB partial, and written through to memory
-// (as partials that cross XCDs inside one launch must be) they cost more than the launch they save -
-// 32 query / 8 cached heads x 128, 256 sequences: kernel 74 -> 101 us, whole step 72 -> 89 us;
-// multi-query 16/1 x 256: 29 -> 65 us.  In a decode step the new row is read from k_new / v_new and
-// appended by the wave that owns it.
+// Accumulators: O^T block db holds O^T[d = 16*db + 4*g + i][head], fp32.  In a decode step the new row is read
+// from k_new / v_new and appended by the wave that owns it.
 #include <type_traits>
 
 #include "s3kv_device.h"
@@ -72,6 +68,20 @@ __device__ __forceinline__ f32x4 mfma_values(const u32x2 a, const u32x2 b, const
     if (DT == S3_F16)
         return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c, 0, 0, 0);
+}
+
+// V^T . P^T for RB blocks of 16 rows (two operand words each), P^T as its high and its low part.
+template <int DT, int RB>
+__device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const unsigned (&hi)[2 * RB], const unsigned (&lo)[2 * RB], f32x4 c) {
+    if constexpr (RB == 2) {
+        const u32x4 a = (u32x4){v[0], v[1], v[2], v[3]};
+        c = mfma_scores<DT>(a, (u32x4){hi[0], hi[1], hi[2], hi[3]}, c);
+        return mfma_scores<DT>(a, (u32x4){lo[0], lo[1], lo[2], lo[3]}, c);
+    } else {
+        const u32x2 a = (u32x2){v[0], v[1]};
+        c = mfma_values<DT>(a, (u32x2){hi[0], hi[1]}, c);
+        return mfma_values<DT>(a, (u32x2){lo[0], lo[1]}, c);
+    }
 }
 
 __device__ __forceinline__ unsigned pack_f16(float lo, float hi) {
@@ -98,6 +108,13 @@ __device__ __forceinline__ void store_out4(void *out, int out_dtype, int64_t e, 
         }
         *(u32x2 *)((uint16_t *)out + e) = w;
     }
+}
+
+// Sixteen lanes read four rows of sixteen 16-bit elements, lane i the four elements of row i / 4 at its own address;
+// lane i receives element i of each row.
+__device__ __forceinline__ u32x2 lds_transpose4(const char *p) {
+    typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(__attribute__((address_space(3))) void *)(void *)p));
 }
 
 // Two e4m3 codes (bytes 2*half, 2*half+1 of w) -> one 32-bit word of two DT elements, exact: every e4m3 value
@@ -127,22 +144,212 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
     t[3] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);
 }
 
-// A chunk whose partial this wave has written and whose arrival is still to be counted / answered.
-struct PendingChunk {
-    unsigned int *cnt;  // the context's arrival counter; null: nothing pending
-    int b, hq0, nheads, nchunks;
+// How a launch divides its rows: `shares` equal runs of tiles per column, share k = tiles
+// [k * base + min(k, rem), ...) with one tile more for the first `rem`.  team 1: every wave works for itself and
+// a piece of a context cut by a share's border goes to memory.  team 4: the four waves of a workgroup take four
+// consecutive shares of one column and first merge their pieces through LDS.
+struct SharePlan {
+    int tiles, shares, base, rem, team;
 };
 
-// The wave that delivered the last chunk of (sequence b, query heads hq0 .. hq0+nheads-1) merges their chunk
-// partials: 64/(D/8) heads per pass, each lane its 8-element slice.
+// Why the line between team 1 and team 4 lies at 256 rows a share: a piece costs a write-through store
+// and a read of its fp32 rows, 16 query heads x D x 4 bytes twice against D x 4 bytes (16-bit K and V) per
+// cached row, so with shares of r rows pieces add up to 2 * 2 * 16 / r of the traffic (two pieces a share; grouped
+// heads less, in the ratio of the group to 16): 6 % at a share of 1000 rows, 25 % at 256.  Four waves together
+// leave a quarter of that, but meet at barriers at the end of their share, and waves that stream rows of
+// adjacent cached heads (team 1: neighbouring waves are neighbouring columns) read whole cached rows between them.
+#define S3_TEAM_ROWS 256
+// A team's waves take at least this many rows each: below it, what a share costs whatever its length (the meeting in
+// LDS, the write-through, the count, the merge of the pieces) outweighs the rows.  Three contexts of 512..8192 rows,
+// 32q/8kv x 128, shares of 26 rows a wave: 163 us a pass, 53: 159, 71: 156, 106: 167, 213: 191.
+#define S3_TEAM_MIN_ROWS 64
+
+// tiles: tiles of TR rows per column.
+template <int TR>
+__device__ __forceinline__ SharePlan share_plan(const AttnArgs &a, int tiles) {
+    SharePlan sp;
+    sp.tiles = tiles;
+    sp.team = 1;
+    int shares;
+    if (a.share_rows > 0) {  // the caller fixed the longest piece
+        const int per = a.share_rows / TR;
+        shares = min((tiles + per - 1) / per, a.max_shares);
+    } else {
+        shares = min(a.wave_shares, a.max_shares);
+        if (a.team_lds && tiles < shares * (S3_TEAM_ROWS / TR)) {
+            sp.team = 4;
+            constexpr int LEAST = 4 * (S3_TEAM_MIN_ROWS / TR);
+            shares = 4 * min(min(a.team_shares, a.max_shares), (tiles + LEAST - 1) / LEAST);
+        }
+    }
+    sp.shares = max(1, min(shares, tiles));
+    sp.base = tiles / sp.shares;
+    sp.rem = tiles - sp.base * sp.shares;
+    return sp;
+}
+__device__ __forceinline__ int share_start(const SharePlan &sp, int k) { return k * sp.base + min(k, sp.rem); }
+__device__ __forceinline__ int share_of(const SharePlan &sp, int tile) {
+    const int cut = sp.rem * (sp.base + 1);
+    return tile < cut ? tile / (sp.base + 1) : sp.rem + (tile - cut) / sp.base;
+}
+// Publishing units (shares, or teams of four) that context b's tiles [t0, t1) touch: the first one and how many.
+__device__ __forceinline__ void pieces_of(const SharePlan &sp, int t0, int t1, int &first, int &count) {
+    const int sh = sp.team == 4 ? 2 : 0;
+    first = share_of(sp, t0) >> sh;
+    count = (share_of(sp, t1 - 1) >> sh) - first + 1;
+}
+
+// A context of which this wave or team has left a piece in memory: its pieces are `count` (0: nothing left), by the
+// publishing units first, first + 1, ...; unit u keeps its piece of context b in partial slot u + b (along the
+// shares either u or b grows from one piece to the next, so no two pieces meet).
+struct Pending {
+    int b, first, count;
+};
+
+// This wave (its team) has written the pieces p0 and p1 (count 0: none): count them on their contexts' arrival
+// counters, both in one round trip; bit k of the result: the last piece of p_k's context has arrived, and this wave
+// merges it.  See chunk_arrived() for the two orderings.
+__device__ __forceinline__ unsigned pieces_arrived(const AttnArgs &a, const Pending &p0, const Pending &p1, int columns, int col) {
+    const int lane = threadIdx.x & 63;
+    if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the partial stores have completed
+    const int count = lane == 0 ? p0.count : p1.count;
+    unsigned int *cnt = a.arrivals + (int64_t)(lane == 0 ? p0.b : p1.b) * columns + col;
+    bool mine = false;
+    if (lane < 2 && count != 0) {
+        mine = atomicAdd(cnt, 1u) == (unsigned int)(count - 1);
+        if (mine) atomicExch(cnt, 0u);  // leave the counter clean for the next launch
+    }
+    const unsigned who = (unsigned)__builtin_amdgcn_ballot_w64(mine);
+    if (a.merge_sync && who != 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return who;
+}
+
+// Running merge of pieces for EB x 4 consecutive elements: pieces c0, c0 + stride, ... below `count`, NP of them per
+// memory round trip.  ml / acc: the (max, sum) pair and the elements of piece 0; sml / sacc: floats from one piece to
+// the next.
+template <int EB, int NP>
+struct PieceMerge {
+    float m[EB], l[EB];
+    f32x4 o[EB];
+    __device__ __forceinline__ void run(const float *const (&ml)[EB], const float *const (&acc)[EB], int64_t sml, int64_t sacc, int c0,
+                                        int stride, int count) {
+#pragma unroll
+        for (int i = 0; i < EB; i++) {
+            m[i] = -INFINITY;
+            l[i] = 0.f;
+            o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll 1
+        for (int c = c0; c < count; c += NP * stride) {
+            f32x2 mv[EB][NP];
+            f32x4 av[EB][NP];
+#pragma unroll
+            for (int u = 0; u < NP; u++) {
+                const int cc = c + u * stride < count ? c + u * stride : c;  // (past the end: piece c again, weight 0)
+#pragma unroll
+                for (int i = 0; i < EB; i++) {
+                    mv[i][u] = get_coherent2(ml[i] + cc * sml);
+                    av[i][u] = get_coherent4(acc[i] + cc * sacc);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < EB; i++) {
+                float mn = m[i];
+#pragma unroll
+                for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[i][u][0]);
+                const float alpha = m[i] == -INFINITY ? 0.f : fast_exp2(m[i] - mn);
+                l[i] *= alpha;
+                o[i] *= alpha;
+#pragma unroll
+                for (int u = 0; u < NP; u++) {
+                    const float w = c + u * stride < count ? fast_exp2(mv[i][u][0] - mn) : 0.f;
+                    l[i] += w * mv[i][u][1];
+                    o[i] += w * av[i][u];
+                }
+                m[i] = mn;
+            }
+        }
+    }
+};
+
+// Merge the pieces of query heads hq0 .. hq0+nh-1 of a context and store the final rows; by a wave (nthr 64) or by
+// the four waves of a workgroup in step (nthr 256).  A workgroup with more threads than quads of elements deals the
+// pieces of a context of many over the spare threads, which meet in LDS (6 floats per thread).
+// Kept small: all of this runs once per launch and wave, i.e. out of a cold instruction cache (unrolled for every
+// shape, with the code around it, the kernel was 136 KB and a merge of four pieces took 3 us).
 template <int D>
-__device__ __forceinline__ void merge_pending(const AttnArgs &a, const PendingChunk &p, int lane) {
-    constexpr int LPH = D / 8, HPP = 64 / LPH;
-    for (int h0 = 0; h0 < p.nheads; h0 += HPP) {
-        const int h = h0 + lane / LPH;
-        if (h < p.nheads) merge_chunks<D, true>(a, a.Hq, p.b, p.hq0 + h, lane % LPH, p.nchunks);
+__device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p, int hq0, int nh, int tid, int nthr, float *lds) {
+    const int64_t row0 = ((int64_t)p.first + p.b) * a.Hq + hq0;
+    const int64_t sml = 2 * (int64_t)a.Hq, sacc = (int64_t)a.Hq * D;
+    const float *pml = (const float *)a.part_ml + 2 * row0, *pacc = a.part_acc + row0 * D;
+    char *out = (char *)a.out;
+    const int64_t out0 = ((int64_t)p.b * a.Hq + hq0) * D;
+    const int quads = nh * (D / 4);
+    if (nthr == 256 && quads <= 128 && p.count > 4) {
+        const int splits = min(8, 256 / quads);
+        const int split = tid / quads, e = tid - split * quads;
+        const float *const ml[1] = {pml + 2 * (e / (D / 4))};
+        const float *const acc[1] = {pacc + e * 4};
+        PieceMerge<1, 8> pm;
+        __syncthreads();  // an earlier merge has read the LDS
+        if (split < splits) {
+            pm.run(ml, acc, sml, sacc, split, splits, p.count);
+            *(f32x4 *)(lds + tid * 4) = pm.o[0];
+            *(f32x2 *)(lds + 1024 + tid * 2) = (f32x2){pm.m[0], pm.l[0]};
+        }
+        __syncthreads();
+        if (tid < quads) {
+            float m = -INFINITY, l = 0.f;
+            f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int k = 0; k < splits; k++) {  // (a split without a piece: max -inf, sum 0)
+                const f32x2 x = *(const f32x2 *)(lds + 1024 + (k * quads + tid) * 2);
+                const float mn = fmaxf(m, x[0]), alpha = m == -INFINITY ? 0.f : fast_exp2(m - mn), w = x[0] == -INFINITY && x[1] == 0.f ? 0.f : fast_exp2(x[0] - mn);
+                l = l * alpha + w * x[1];
+                o = o * alpha + w * *(const f32x4 *)(lds + (k * quads + tid) * 4);
+                m = mn;
+            }
+            store_out4(out, a.out_dtype, out0 + tid * 4, o * (1.f / l));
+        }
+        return;
+    }
+    constexpr int EB = D / 64, NP = EB == 4 ? 3 : 6;  // 12 or 6 quads per thread in flight
+#pragma unroll 1
+    for (int e0 = tid; e0 < quads; e0 += EB * nthr) {
+        const float *ml[EB], *acc[EB];
+#pragma unroll
+        for (int i = 0; i < EB; i++) {
+            const int e = e0 + i * nthr < quads ? e0 + i * nthr : e0;
+            ml[i] = pml + 2 * (e / (D / 4));
+            acc[i] = pacc + e * 4;
+        }
+        PieceMerge<EB, NP> pm;
+        pm.run(ml, acc, sml, sacc, 0, 1, p.count);
+#pragma unroll
+        for (int i = 0; i < EB; i++)
+            if (e0 + i * nthr < quads) store_out4(out, a.out_dtype, out0 + (e0 + i * nthr) * 4, pm.o[i] * (1.f / pm.l[i]));
     }
 }
+
+// 16 bytes at byte `off` of the buffer, zeros past its end.
+template <bool NT>
+__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, unsigned off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, NT ? 2 : 0);
+}
+
+// A context as a wave's share sees it.  All fields are wave-uniform.
+struct Segment {
+    int seq, t0, t_end;  // its index in the batch, its first tile, the tile after its last one in this share
+    int t1;              // the tile after its last one
+    int len;
+    int64_t off;
+};
+
+// Rows of a tile.  Cached rows of up to 128 bytes a head: 32, so that a wave's two register sets hold 8 KiB and the work
+// per tile (maximum, exponent reference, loop) is spread over twice the rows, and the second product runs at the
+// instruction's full 32 contraction slots; longer rows: 16 (the sets and the accumulators fill the registers).
+__host__ __device__ constexpr int gqa_tile_rows(int row_bytes) { return row_bytes <= 128 ? 32 : 16; }
 
 // KV8: the cache rows are e4m3 codes (one byte per element) and DT is the type of q; a 16-byte load then
 // holds 16 elements, which are widened (exactly) to DT in registers and feed two contraction steps.
@@ -150,388 +357,460 @@ template <int DT, int D, bool KV8>
 __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {
     constexpr int EB = KV8 ? 1 : 2;       // bytes per cached element
     constexpr int KS = D / 32;            // contraction steps of the score product
-    constexpr int KL = KV8 ? D / 64 : KS; // 16-byte K loads per lane and tile
     constexpr int DB = D / 16;            // 16-element blocks of an output row
     constexpr int PPR = D * EB / 16;      // 16-byte pieces per cached row of one head
-    constexpr int VL = 16 * PPR / 64;     // 16-byte loads per lane for a 16-row V tile
-    // LDS row stride of the V tile, bytes.  16-bit rows: 8 bytes of padding, so that the four lane groups' 16-bit
-    // gathers hit different banks.  8-bit rows: 16 bytes, so that rows stay 16-byte aligned and the four lane
-    // groups' 32-bit reads (rows 4g .. 4g+3, sixteen consecutive words each) cover the banks evenly.
-    constexpr int VSTRIDE = KV8 ? D + 16 : D * 2 + 8;
-    constexpr float RESCALE_LOG2 = 8.f;   // see the softmax step
-    extern __shared__ __align__(16) char dyn_lds[];  // the batch view
-    __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
-    // LDS row stride of the K tile: with 16 bytes of padding the 128-bit reads of sixteen rows cover every bank once
+    constexpr int TR = gqa_tile_rows(D * EB), RB = TR / 16;  // rows of a tile, in blocks of 16
+    constexpr int NL = TR * PPR / 64;     // 16-byte loads per lane for a tile of K or of V
+    constexpr int NK = D * EB / 64;       // 16-byte K operands per lane and row block
+    constexpr int RPL = 64 / PPR;         // rows per load instruction
+    // LDS row strides, bytes.  K: with 16 bytes of padding the 128-bit reads of sixteen rows cover every bank once.
+    // V, 16-bit rows: the transposing reads touch 32 consecutive bytes of sixteen rows, which 32 bytes of padding
+    // spread over all banks.  V, 8-bit rows: 16 bytes of padding, so that the four lane groups' 32-bit reads (rows
+    // 4g .. 4g+3, sixteen consecutive words each) cover the banks evenly.
     constexpr int KSTRIDE = D * EB + 16;
-    __shared__ __align__(16) char vtile[4][16 * VSTRIDE];
-    __shared__ __align__(16) char ktile[4][16 * KSTRIDE];
+    constexpr int VSTRIDE = KV8 ? D + 16 : D * 2 + 32;
+    constexpr float RESCALE_LOG2 = 8.f;   // see the softmax step
+    extern __shared__ __align__(16) char dyn_lds[];  // the batch view, then the teams' first pieces
+    __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
+    // A wave's LDS: the V and the K tile, or, once its share is done, one piece (16 heads x D floats, padded).
+    constexpr int PSTRIDE = D + 4;
+    constexpr int TILE_BYTES = TR * (VSTRIDE + KSTRIDE), PIECE_BYTES = 16 * PSTRIDE * 4;
+    __shared__ __align__(16) char wave_lds[4][TILE_BYTES > PIECE_BYTES ? TILE_BYTES : PIECE_BYTES];
+    __shared__ float2 piece_ml[8][16];  // team 4: (max, sum) of each wave's first (2w) and last (2w + 1) piece
+    __shared__ f32x4 piece_run[8][16];  // ... a piece's weight in its run of pieces, and the run's (max, sum, 1 / sum)
+    __shared__ int piece_b[8];          // ... and the context it belongs to, -1: none
+    __shared__ int merge_mine;
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
-    const int group = a.Hq / a.H;
-    const int nqb = (group + 15) / 16;  // blocks of 16 query heads per K/V head
-    const int per_seq = a.H * nqb;
-    const BatchView bv = build_batch_view(a, dyn_lds, wave_sums);
-    const int64_t total = (int64_t)bv.total * per_seq;
+    const int group = a.group, nqb = a.nqb, columns = a.columns;
+    const BatchView bv = build_tile_view<TR>(a, dyn_lds, wave_sums);  // pre[] counts tiles
     if (blockIdx.x == 0) {
         if (a.len_out)
             for (int b = threadIdx.x; b < a.n; b += 256) a.len_out[b] = a.cur_len[b] + 1;
     }
-    const bool ink = a.merge_in_kernel != 0;
-    // Dynamic work list: a wave takes its first item by its index and then claims positions from a device-wide
-    // counter, so that the waves end together whatever their items' lengths (the items of a ragged batch differ
-    // by a factor of five and a fixed stride leaves the sum of a dozen of them to chance).
-    // One device-wide counter serves a few million claims a second, far fewer than the waves of a large launch
-    // ask for, so only the END of the list is dealt that way: the first dyn_list per cent of the positions (whole
-    // rounds of the grid) go by stride.
-    // Not the default: measured +2.4 % and +3.6 % on 1024 and 2048 sequences of 32q/8kv x 128 with three quarters of
-    // the list by stride, -11 % on 1024 sequences with 8-bit rows (items half as long, claims twice as often) and
-    // -40 % on 256 sequences (three rounds of the grid).
-    const int static_pct = a.dyn_list > 0 ? a.dyn_list : 0;
-    const bool dyn = static_pct > 0 && static_pct < 100 && a.queue != nullptr;
-    if (ink) {  // no merge launch follows: the zero rows of empty or refused contexts are written here, by the workgroups in turn
-        for (int b = blockIdx.x; b < a.n; b += gridDim.x) {
-            if (bv.len[b] == 0) {
-                const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                for (int e = threadIdx.x; e < a.Hq * D / 8; e += 256) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
-            }
+    // the zero rows of empty or refused contexts, by the workgroups in turn
+#pragma unroll 1
+    for (int b = blockIdx.x; b < a.n; b += gridDim.x) {
+        if (bv.len[b] == 0) {
+            const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int e = threadIdx.x; e < a.Hq * D / 8; e += 256) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
         }
     }
-    // Chunks published by this wave whose bookkeeping is still due (wave-uniform): `told` has its partial in
-    // flight to memory, `counted` has been counted on its context's arrival counter and awaits the answer.
-    PendingChunk told, counted;
-    told.cnt = counted.cnt = nullptr;
-    unsigned int counted_old = 0;
-    auto settle = [&](bool drain) {
-        if (!told.cnt && !counted.cnt) return;
-        // everything this wave stored or loaded before the current item's results has completed: the loads were
-        // consumed, and the stores are older than they
-        __builtin_amdgcn_s_waitcnt(0);
-        for (int round = 0; round < (drain ? 2 : 1); round++) {
-            if (counted.cnt) {
-                if (__builtin_amdgcn_readfirstlane(counted_old) == (unsigned int)(counted.nchunks - 1)) {
-                    if (lane == 0) atomicExch(counted.cnt, 0u);  // leave the counter clean for the next launch
-                    if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                    merge_pending<D>(a, counted, lane);
-                }
-                counted.cnt = nullptr;
-            }
-            if (told.cnt) {
-                if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                if (lane == 0) counted_old = atomicAdd(told.cnt, 1u);
-                counted = told;
-                told.cnt = nullptr;
-            }
-        }
-    };
+    const int tiles = __builtin_amdgcn_readfirstlane(bv.total);
+    if (tiles == 0) return;  // the whole grid alike
+    const SharePlan sp = share_plan<TR>(a, tiles);
 
-    char *vt = vtile[wave];
-    char *kt = ktile[wave];
+    char *vt = wave_lds[wave];
+    char *kt = vt + TR * VSTRIDE;
+    // team 4: the first piece of each wave's share waits here (as many heads as the group has) while the share goes on
+    const int piece_heads = min(16, group);
+    float *first_piece = (float *)(dyn_lds + ((batch_view_bytes(a.n, 1) + 15) & ~(size_t)15)) + (size_t)wave * piece_heads * PSTRIDE;
+    float *last_piece = (float *)vt;
     const int64_t rstride = (int64_t)a.H * D * EB;
-    const unsigned rs32 = (unsigned)rstride;  // a cached row of all K/V heads: below 2^32 bytes
-    // SK: the K rows of this launch are more than the memory-side cache holds, so none of them survives until
-    // the next step and they are read with the streaming hint like the V rows; otherwise with plain loads (a batch
-    // whose K rows fit - 256 sequences of 32q/8kv x 128 - finds most of them still cached one step later: 0.76 of
-    // peak against 0.63 with the hint; a batch of 1024 the other way round, 0.66 against 0.63).
-    auto run_items = [&](auto stream_k_tag) {
-    constexpr bool SK = decltype(stream_k_tag)::value;
-    const int64_t n_waves = (int64_t)gridDim.x * 4;
-    // positions below t_static (at least one round: a wave's first item is always its own index) go by stride
-    const int64_t t_static = dyn ? max((int64_t)1, total * static_pct / 100 / n_waves) * n_waves : total;
-    int64_t item = (int64_t)blockIdx.x * 4 + wave;
-    while (item < total) {
-        // dynamic part of the work list: the position after this one is claimed now and looked at when this item is done
-        const bool claim_next = dyn && item + n_waves >= t_static;
-        unsigned int claimed = 0;
-        if (claim_next && lane == 0) claimed = atomicAdd(a.queue, 1u);
-        const Item it = decode_item(a, bv, item, per_seq);
-        const int hk = it.hgb / nqb, qb = it.hgb - hk * nqb;
-        const int start = it.c * it.clen, end = min(it.len, start + it.clen);
+    const unsigned rs32 = (unsigned)rstride;  // a cached row of all K/V heads: at most 64 KiB
+    // The K rows are read with the streaming hint, like the V rows, when this launch has more of them than the
+    // memory-side cache holds, so that none survives until the next step; else with plain loads (a batch whose K rows
+    // fit finds most of them still cached one step later: 256 sequences of 32q/8kv x 128 in chunks of 128 rows read
+    // at 0.76 of peak against 0.63 with the hint; a batch of 1024 the other way round, 0.66 against 0.63).
+    const bool stream_k = a.stream_k < 0 ? (int64_t)tiles * TR * rstride > ((int64_t)256 << 20) : a.stream_k != 0;
+
+    // (shares * columns tiles of at least 2 KiB lie in the arena: below 2^31 on any device)
+    const unsigned units = (unsigned)(sp.team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
+    const unsigned step = sp.team == 4 ? gridDim.x : gridDim.x * 4;
+#pragma unroll 1
+    for (unsigned unit = sp.team == 4 ? blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
+        const int pub = __builtin_amdgcn_readfirstlane(unit / columns);  // publishing unit: this wave's share or its team
+        const int col = __builtin_amdgcn_readfirstlane(unit - (unsigned)pub * columns);
+        const int share = sp.team == 4 ? pub * 4 + wave : pub;
+        const int hk = nqb == 1 ? col : col / nqb, qb = col - hk * nqb;
         const int head = qb * 16 + n;  // query head of this lane's column, within the group
         const bool head_ok = head < group;
         const int hq = hk * group + (head_ok ? head : group - 1);
+        const int hq0 = hk * group + qb * 16, nheads = min(16, group - qb * 16);
+        const int t_begin = share < sp.shares ? share_start(sp, share) : 0;
+        const int t_stop = share < sp.shares ? share_start(sp, share + 1) : 0;
+        // contexts this wave or team has left a piece of in memory: at most the first and the last one of its share
+        Pending pend0 = {0, 0, 0}, pend1 = {0, 0, 0};
+        if (sp.team == 4 && lane == 0) piece_b[2 * wave] = piece_b[2 * wave + 1] = -1;
 
-        u32x4 qop[KS];
+        if (t_begin < t_stop) {
+            // Two cursors run over the share's tiles: `ahead` issues the loads of a tile (of the next context, if there
+            // is one) into the register set that `now` has just reduced, two tiles on, so a wave has loads in flight from
+            // its first tile to its last.  A tile is read through a buffer descriptor that ends with the context's last
+            // row: rows past it, and the tiles after the last one of the share, cost no traffic and read as zeros.
+            // Row and column of a lane's 16 bytes never change: the addresses take no vector arithmetic.
+            unsigned voff[NL];
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-            // elements of contraction step ks held by lane group g: the same as the K operand's (a 16-byte K
-            // load of 8-bit rows covers 16 elements = steps 2j and 2j+1 of lane group g)
-            const int e0 = KV8 ? (ks >> 1) * 64 + g * 16 + (ks & 1) * 8 : ks * 32 + g * 8;
-            qop[ks] = *(const u32x4 *)(a.q + (((int64_t)it.b * a.Hq + hq) * D + e0) * 2);
-            if (!head_ok) qop[ks] = (u32x4){0u, 0u, 0u, 0u};  // padding columns: zero scores, never stored
-        }
-        char *kbase = a.kplane + it.off * rstride + (int64_t)hk * D * EB;
-        char *vbase = a.vplane + it.off * rstride + (int64_t)hk * D * EB;
-        // Decode step (len_add = 1): row len-1 is still only in k_new / v_new.  Every reader takes it from
-        // there; the wave of query block 0 whose chunk holds it also writes it into the arena (the append).
-        // (8-bit rows are quantised by the append kernel before this launch: nothing to take from k_new.)
-        const int jnew = (a.len_add && !KV8) ? it.len - 1 : -1;
-        const char *knew = a.k_new + ((int64_t)it.b * a.H + hk) * D * 2;
-        const char *vnew = a.v_new + ((int64_t)it.b * a.H + hk) * D * 2;
-
-        f32x4 o[DB];
-#pragma unroll
-        for (int db = 0; db < DB; db++) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        float m = -INFINITY, lsum = 0.f;
-
-        // Loads of one 16-row tile (rows past the chunk's end are clamped to its last row and masked later).
-        // V, and K when it streams (SK): whole rows per load instruction (16 bytes per lane, PPR lanes per row).
-        // K otherwise: the operand layout directly (row n, 16 bytes at 64 ks + 16 g).
-        auto load_tile = [&](int r0, u32x4 (&kld)[KL], u32x4 (&vv)[VL]) {
-            static_assert(KL == VL, "K and V tiles are loaded with the same pattern");
-            if (SK) {
-#pragma unroll
-                for (int i = 0; i < KL; i++) {
-                    const int idx = i * 64 + lane;
-                    const int rv = min(r0 + idx / PPR, end - 1);
-                    kld[i] = load16<true>((rv == jnew ? knew : kbase + (uint64_t)(unsigned)rv * rs32) + (idx % PPR) * 16);
-                }
-            } else {
-                const int rk = min(r0 + n, end - 1);
-                const char *krow = (rk == jnew ? knew : kbase + (uint64_t)(unsigned)rk * rs32) + g * 16;
-#pragma unroll
-                for (int ks = 0; ks < KL; ks++) kld[ks] = load16<false>(krow + ks * 64);
-            }
-#pragma unroll
-            for (int i = 0; i < VL; i++) {
-                const int idx = i * 64 + lane;
-                const int rv = min(r0 + idx / PPR, end - 1);
-                vv[i] = load16<true>((rv == jnew ? vnew : vbase + (uint64_t)(unsigned)rv * rs32) + (idx % PPR) * 16);
-            }
-        };
-        auto reduce_tile = [&](int r0, const u32x4 (&kld)[KL], const u32x4 (&vv)[VL]) {
-            if (qb == 0 && jnew >= r0 && jnew < r0 + 16 && jnew < end) {  // this tile holds the new row: append it
-                if (!SK && r0 + n == jnew) {
-#pragma unroll
-                    for (int ks = 0; ks < KL; ks++)
-                        *(u32x4 *)(kbase + (uint64_t)(unsigned)jnew * rs32 + g * 16 + ks * 64) = kld[ks];
-                }
-#pragma unroll
-                for (int i = 0; i < VL; i++) {
-                    const int idx = i * 64 + lane;
-                    if (r0 + idx / PPR == jnew) {
-                        if (SK) *(u32x4 *)(kbase + (uint64_t)(unsigned)jnew * rs32 + (idx % PPR) * 16) = kld[i];
-                        *(u32x4 *)(vbase + (uint64_t)(unsigned)jnew * rs32 + (idx % PPR) * 16) = vv[i];
-                    }
-                }
-            }
-            u32x4 kop[KL];
-            if (SK) {
-                // K tile through this wave's LDS buffer into operand layout, one 128-bit read per contraction load.
-                // (Loading the operand layout directly is 64 separate 16-byte cache accesses per instruction and
-                // fetches every 128-byte line twice, the second time from the L1 - which the streaming hint forgoes.)
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int i = 0; i < KL; i++) {
-                    const int idx = i * 64 + lane;
-                    *(u32x4 *)(kt + (idx / PPR) * KSTRIDE + (idx % PPR) * 16) = kld[i];
-                }
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int ks = 0; ks < KL; ks++) kop[ks] = *(const u32x4 *)(kt + n * KSTRIDE + ks * 64 + g * 16);
-                __builtin_amdgcn_wave_barrier();
-            } else {
-#pragma unroll
-                for (int ks = 0; ks < KL; ks++) kop[ks] = kld[ks];
-            }
-            f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-                u32x4 kk;
-                if (KV8) {
-                    const u32x4 raw = kop[ks >> 1];
-#pragma unroll
-                    for (int w = 0; w < 2; w++) {
-                        const unsigned word = raw[(ks & 1) * 2 + w];
-                        kk[2 * w] = widen2_e4m3<DT>(word, false);
-                        kk[2 * w + 1] = widen2_e4m3<DT>(word, true);
-                    }
-                } else {
-                    kk = kop[ks];
-                }
-                s = mfma_scores<DT>(kk, qop[ks], s);
-            }
-
-            float sv[4], mt = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                sv[i] = (r0 + 4 * g + i < end) ? s[i] * a.scale_log2e : -INFINITY;
-                mt = fmaxf(mt, sv[i]);
-            }
-            mt = fmaxf(mt, __shfl_xor(mt, 16));
-            mt = fmaxf(mt, __shfl_xor(mt, 32));
-            // Lazy reference: m is the exponent reference of the running sums, not necessarily the
-            // running maximum.  It moves (and the accumulators are rescaled) only when a tile's
-            // maximum exceeds it by more than RESCALE_LOG2, so p stays below 2^RESCALE_LOG2 and the
-            // rescale, which would otherwise run for almost every tile, runs for the first tile and
-            // then hardly ever.  (max, sum, row) leave the kernel consistent with whatever m is, which
-            // is all the merge of chunks needs.
-            const bool move = mt > m + RESCALE_LOG2;  // first tile: m = -inf
-            if (__builtin_amdgcn_ballot_w64(move) != 0) {
-                const float mn = move ? mt : m;
-                const float alpha = fast_exp2(m - mn);  // 1 where the reference stays, 0 on the first tile
-                lsum *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; db++) o[db] *= alpha;
-                m = mn;
-            }
-            float p[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                p[i] = fast_exp2(sv[i] - m);
-                lsum += p[i];
-            }
-
-            // The weights enter the second product as 16-bit operands: a high part (p rounded to the type) and
-            // a low part (what the high part misses, rounded again), two products per value block.  Together
-            // they carry about twice the type's mantissa, so the weighted sum is as exact as the fp32 weights
-            // allow, also for values of large magnitude (one rounded part alone is off by 2^-12 of |p v|).
-            u32x2 pop, pop_lo;
-            float r[4];
-            if (DT == S3_F16) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) r[i] = p[i] - (float)(_Float16)p[i];
-                pop[0] = pack_f16(p[0], p[1]);
-                pop[1] = pack_f16(p[2], p[3]);
-                pop_lo[0] = pack_f16(r[0], r[1]);
-                pop_lo[1] = pack_f16(r[2], r[3]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; i++) r[i] = p[i] - (float)(__bf16)p[i];
-                pop[0] = pack_bf16(p[0], p[1]);
-                pop[1] = pack_bf16(p[2], p[3]);
-                pop_lo[0] = pack_bf16(r[0], r[1]);
-                pop_lo[1] = pack_bf16(r[2], r[3]);
-            }
-
-            // V tile through this wave's LDS buffer.  The LDS unit serves one wave's operations in
-            // issue order; the wave barriers only keep the compiler from moving them across.
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int i = 0; i < VL; i++) {
-                const int idx = i * 64 + lane;
-                char *dst = vt + (idx / PPR) * VSTRIDE + (idx % PPR) * 16;
-                const u32x4 w = vv[i];
-                if (KV8) {
-                    *(u32x4 *)dst = w;
-                } else {
-                    *(u32x2 *)dst = (u32x2){w[0], w[1]};
-                    *(u32x2 *)(dst + 8) = (u32x2){w[2], w[3]};
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (KV8) {
-                // Four products at a time: this lane's operand row m = n of products 4q .. 4q+3 is output element
-                // d = 64q + 4n + j (j = 0..3), four consecutive codes = ONE 32-bit word per cached row; the words of
-                // rows 4g .. 4g+3 are transposed in registers into the four operands (codes of four rows at one d).
-#pragma unroll
-                for (int q4 = 0; q4 < DB / 4; q4++) {
-                    const unsigned *src = (const unsigned *)(vt + (4 * g) * VSTRIDE + q4 * 64) + n;
-                    unsigned t[4];
-                    transpose4x4_bytes(src[0], src[VSTRIDE / 4], src[2 * (VSTRIDE / 4)], src[3 * (VSTRIDE / 4)], t);
-#pragma unroll
-                    for (int j = 0; j < 4; j++) {
-                        const u32x2 vop = (u32x2){widen2_e4m3<DT>(t[j], false), widen2_e4m3<DT>(t[j], true)};
-                        o[4 * q4 + j] = mfma_values<DT>(vop, pop, o[4 * q4 + j]);
-                        o[4 * q4 + j] = mfma_values<DT>(vop, pop_lo, o[4 * q4 + j]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int db = 0; db < DB; db++) {
-                    const unsigned short *src = (const unsigned short *)(vt + (4 * g) * VSTRIDE) + db * 16 + n;
-                    const unsigned v0 = src[0], v1 = src[VSTRIDE / 2], v2 = src[2 * (VSTRIDE / 2)], v3 = src[3 * (VSTRIDE / 2)];
-                    const u32x2 vop = (u32x2){v0 | (v1 << 16), v2 | (v3 << 16)};
-                    o[db] = mfma_values<DT>(vop, pop, o[db]);
-                    o[db] = mfma_values<DT>(vop, pop_lo, o[db]);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-        };
-        // Two register sets used alternately: the next tile's loads are in flight while this one is reduced.
-        // The loop takes tiles in pairs for as long as a further tile follows the pair, so that every load in it is
-        // unconditional (the compiler then lets the other set's loads stay in flight at each wait); the last one
-        // or two tiles follow outside, and no tile beyond the chunk's end is ever loaded.
-        u32x4 k0[KL], v0[VL], k1[KL], v1[VL];
-        load_tile(start, k0, v0);
-        int r0 = start;
-        while (r0 + 32 < end) {
-            load_tile(r0 + 16, k1, v1);
-            reduce_tile(r0, k0, v0);
-            load_tile(r0 + 32, k0, v0);
-            reduce_tile(r0 + 16, k1, v1);
-            r0 += 32;
-        }
-        if (r0 + 16 < end) {
-            load_tile(r0 + 16, k1, v1);
-            reduce_tile(r0, k0, v0);
-            reduce_tile(r0 + 16, k1, v1);
-        } else {
-            reduce_tile(r0, k0, v0);
-        }
-
-        lsum += __shfl_xor(lsum, 16);
-        lsum += __shfl_xor(lsum, 32);
-        if (ink) settle(false);
-        if (head_ok) {
-            // Four consecutive output elements per store.  16-bit rows: accumulator block t holds elements
-            // 16t + 4g + i (i = 0..3).  8-bit rows (see the V product): register i of blocks 4q .. 4q+3 holds
-            // elements 64q + 16g + 4i + j.
-            auto piece = [&](int t, int &d0) -> f32x4 {
-                if (!KV8) {
-                    d0 = t * 16 + 4 * g;
-                    return o[t];
-                }
-                const int q4 = t / 4, i = t % 4;
-                d0 = q4 * 64 + 16 * g + 4 * i;
-                return (f32x4){o[4 * q4][i], o[4 * q4 + 1][i], o[4 * q4 + 2][i], o[4 * q4 + 3][i]};
+            for (int i = 0; i < NL; i++) voff[i] = (unsigned)(i * RPL + lane / PPR) * rs32 + (lane % PPR) * 16;
+            auto open = [&](int seq, int t) {  // the context of tile t, at or after `seq`
+                while (seq < a.n - 1 && __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) <= t) seq++;
+                Segment s;
+                s.seq = seq;
+                s.t0 = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
+                s.t1 = __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]);
+                s.t_end = min(t_stop, s.t1);
+                s.len = __builtin_amdgcn_readfirstlane(bv.len[seq]);
+                s.off = uniform64(bv.off[seq]);
+                return s;
             };
-            if (it.nchunks == 1) {
-                const float inv = 1.f / lsum;
-#pragma unroll
-                for (int t = 0; t < DB; t++) {
-                    int d0;
-                    const f32x4 v = piece(t, d0);
-                    store_out4(a.out, a.out_dtype, ((int64_t)it.b * a.Hq + hq) * D + d0, v * inv);
+            const int64_t head_byte = (int64_t)hk * D * EB;
+            Segment now = open(min(find_sequence(bv.pre, a.n, t_begin), a.n - 1), t_begin), ahead = now;
+            int t = t_begin, t_ahead = t_begin;
+            int rows_ahead = now.len - (t_begin - now.t0) * TR;  // rows of `ahead` from tile t_ahead on
+            int64_t at = (now.off + (t_begin - now.t0) * TR) * rstride + head_byte;
+            auto load_tile = [&](u32x4 (&kk)[NL], u32x4 (&vv)[NL]) {
+                if (t_ahead == ahead.t_end && t_ahead < t_stop) {
+                    ahead = open(ahead.seq + 1, t_ahead);
+                    at = ahead.off * rstride + head_byte;  // (a context is entered at its first row, but for a share's first)
+                    rows_ahead = ahead.len;
                 }
-            } else {
-                const int64_t pi = ((int64_t)it.b * a.max_chunks + it.c) * a.Hq + hq;
-                if (ink) {
-                    if (g == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){m, lsum});
+                const int bytes = t_ahead < t_stop ? (int)((unsigned)(min(TR, rows_ahead) - 1) * rs32 + D * EB) : 0;
+                const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(a.kplane + at, 0, bytes, 0x00020000);
+                const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(a.vplane + at, 0, bytes, 0x00020000);
+                if (stream_k) {
+#pragma unroll
+                    for (int i = 0; i < NL; i++) kk[i] = buffer_load16<true>(krs, voff[i]);
                 } else {
-                    if (g == 0) a.part_ml[pi] = make_float2(m, lsum);
+#pragma unroll
+                    for (int i = 0; i < NL; i++) kk[i] = buffer_load16<false>(krs, voff[i]);
                 }
 #pragma unroll
-                for (int t = 0; t < DB; t++) {
-                    int d0;
-                    const f32x4 v = piece(t, d0);
-                    if (ink) put_partial4<true>(a.part_acc + pi * D + d0, v);
-                    else *(f32x4 *)(a.part_acc + pi * D + d0) = v;
+                for (int i = 0; i < NL; i++) vv[i] = buffer_load16<true>(vrs, voff[i]);
+                t_ahead++;
+                at += TR * rstride;
+                rows_ahead -= TR;
+            };
+
+            u32x4 qop[KS];
+            u32x4 knew = (u32x4){0u, 0u, 0u, 0u}, vnew = knew;
+            f32x4 o[DB];
+            float m = -INFINITY, lsum = 0.f;
+            int jnew = -1;  // decode step: the row of `now` that is still only in k_new / v_new
+            auto enter = [&]() {  // start on context `now`
+#pragma unroll
+                for (int ks = 0; ks < KS; ks++) {
+                    // elements of contraction step ks held by lane group g: the same as the K operand's (a 16-byte K
+                    // load of 8-bit rows covers 16 elements = steps 2j and 2j+1 of lane group g)
+                    const int e0 = KV8 ? (ks >> 1) * 64 + g * 16 + (ks & 1) * 8 : ks * 32 + g * 8;
+                    qop[ks] = *(const u32x4 *)(a.q + (((int64_t)now.seq * a.Hq + hq) * D + e0) * 2);
+                    if (!head_ok) qop[ks] = (u32x4){0u, 0u, 0u, 0u};  // padding columns: zero scores, never stored
+                }
+                // Decode step (len_add = 1): row len-1 is still only in k_new / v_new.  Every reader takes it from
+                // there; the wave of query block 0 whose tile holds it also writes it into the arena (the append).
+                // (8-bit rows are quantised by the append kernel before this launch: nothing to take from k_new.)
+                if (!KV8 && a.len_add) {
+                    jnew = now.len - 1;
+                    if (jnew < (now.t_end - now.t0) * TR && lane < PPR) {  // in this share
+                        const int64_t at = ((int64_t)now.seq * a.H + hk) * D * 2 + lane * 16;
+                        knew = *(const u32x4 *)(a.k_new + at);
+                        vnew = *(const u32x4 *)(a.v_new + at);
+                    }
+                }
+#pragma unroll
+                for (int db = 0; db < DB; db++) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                m = -INFINITY;
+                lsum = 0.f;
+            };
+            auto reduce_tile = [&](int r0, const u32x4 (&kld)[NL], const u32x4 (&vv)[NL]) {
+                const int end = now.len;
+                // K and V tile through this wave's LDS buffer: K into operand layout, one 128-bit read per contraction
+                // load (loading the operand layout directly is 64 separate 16-byte cache accesses per instruction and
+                // fetches every 128-byte line twice), V transposed.  The LDS unit serves one wave's operations in
+                // issue order; the wave barriers only keep the compiler from moving them across.
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int i = 0; i < NL; i++) *(u32x4 *)(kt + (i * RPL + lane / PPR) * KSTRIDE + (lane % PPR) * 16) = kld[i];
+#pragma unroll
+                for (int i = 0; i < NL; i++) *(u32x4 *)(vt + (i * RPL + lane / PPR) * VSTRIDE + (lane % PPR) * 16) = vv[i];
+                if (!KV8 && jnew >= r0 && jnew < r0 + TR && lane < PPR) {  // this tile holds the new row
+                    __builtin_amdgcn_wave_barrier();
+                    *(u32x4 *)(kt + (jnew - r0) * KSTRIDE + lane * 16) = knew;
+                    *(u32x4 *)(vt + (jnew - r0) * VSTRIDE + lane * 16) = vnew;
+                    if (qb == 0) {  // append it
+                        const int64_t at = (now.off + jnew) * rstride + head_byte + lane * 16;
+                        *(u32x4 *)(a.kplane + at) = knew;
+                        *(u32x4 *)(a.vplane + at) = vnew;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                float sv[RB][4], mt = -INFINITY;
+#pragma unroll
+                for (int rb = 0; rb < RB; rb++) {
+                    f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < NK; j++) {
+                        const u32x4 raw = *(const u32x4 *)(kt + (rb * 16 + n) * KSTRIDE + j * 64 + g * 16);
+                        if (KV8) {
+#pragma unroll
+                            for (int half = 0; half < 2; half++) {
+                                u32x4 kk;
+#pragma unroll
+                                for (int w = 0; w < 2; w++) {
+                                    const unsigned word = raw[half * 2 + w];
+                                    kk[2 * w] = widen2_e4m3<DT>(word, false);
+                                    kk[2 * w + 1] = widen2_e4m3<DT>(word, true);
+                                }
+                                s = mfma_scores<DT>(kk, qop[2 * j + half < KS ? 2 * j + half : 0], s);
+                            }
+                        } else {
+                            s = mfma_scores<DT>(raw, qop[j], s);
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        sv[rb][i] = (r0 + rb * 16 + 4 * g + i < end) ? s[i] * a.scale_log2e : -INFINITY;
+                        mt = fmaxf(mt, sv[rb][i]);
+                    }
+                }
+                mt = fmaxf(mt, __shfl_xor(mt, 16));
+                mt = fmaxf(mt, __shfl_xor(mt, 32));
+                // Lazy reference: m is the exponent reference of the running sums, not necessarily the
+                // running maximum.  It moves (and the accumulators are rescaled) only when a tile's
+                // maximum exceeds it by more than RESCALE_LOG2, so p stays below 2^RESCALE_LOG2 and the
+                // rescale, which would otherwise run for almost every tile, runs for the first tile and
+                // then hardly ever.  (max, sum, row) leave the kernel consistent with whatever m is, which
+                // is all the merge of pieces needs.
+                const bool move = mt > m + RESCALE_LOG2;  // first tile: m = -inf
+                if (__builtin_amdgcn_ballot_w64(move) != 0) {
+                    const float mn = move ? mt : m;
+                    const float alpha = move ? fast_exp2(m - mn) : 1.f;  // 0 on the first tile
+                    lsum *= alpha;
+#pragma unroll
+                    for (int db = 0; db < DB; db++) o[db] *= alpha;
+                    m = mn;
+                }
+                const float ref = m == -INFINITY ? 0.f : m;  // only -inf scores so far: they weigh nothing
+                // The weights enter the second product as 16-bit operands: a high part (p rounded to the type) and
+                // a low part (what the high part misses, rounded again), two products per value block.  Together
+                // they carry about twice the type's mantissa, so the weighted sum is as exact as the fp32 weights
+                // allow, also for values of large magnitude (one rounded part alone is off by 2^-12 of |p v|).
+                // Contraction slots of lane group g: rows 4g .. 4g+3 of each row block.
+                unsigned hi[2 * RB], lo[2 * RB];
+#pragma unroll
+                for (int rb = 0; rb < RB; rb++) {
+                    float p[4], r[4];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        p[i] = fast_exp2(sv[rb][i] - ref);
+                        lsum += p[i];
+                        r[i] = DT == S3_F16 ? p[i] - (float)(_Float16)p[i] : p[i] - (float)(__bf16)p[i];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 2; i++) {
+                        hi[2 * rb + i] = DT == S3_F16 ? pack_f16(p[2 * i], p[2 * i + 1]) : pack_bf16(p[2 * i], p[2 * i + 1]);
+                        lo[2 * rb + i] = DT == S3_F16 ? pack_f16(r[2 * i], r[2 * i + 1]) : pack_bf16(r[2 * i], r[2 * i + 1]);
+                    }
+                }
+
+                if (KV8) {
+                    // Four products at a time: this lane's operand row m = n of products 4q .. 4q+3 is output element
+                    // d = 64q + 4n + j (j = 0..3), four consecutive codes = ONE 32-bit word per cached row; the words of
+                    // rows 4g .. 4g+3 are transposed in registers into the four operands (codes of four rows at one d).
+#pragma unroll
+                    for (int q4 = 0; q4 < DB / 4; q4++) {
+                        unsigned w[RB][4];
+#pragma unroll
+                        for (int rb = 0; rb < RB; rb++) {
+                            const unsigned *src = (const unsigned *)(vt + (rb * 16 + 4 * g) * VSTRIDE + q4 * 64) + n;
+                            transpose4x4_bytes(src[0], src[VSTRIDE / 4], src[2 * (VSTRIDE / 4)], src[3 * (VSTRIDE / 4)], w[rb]);
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            unsigned vop[2 * RB];
+#pragma unroll
+                            for (int rb = 0; rb < RB; rb++) {
+                                vop[2 * rb] = widen2_e4m3<DT>(w[rb][j], false);
+                                vop[2 * rb + 1] = widen2_e4m3<DT>(w[rb][j], true);
+                            }
+                            o[4 * q4 + j] = mfma_weights<DT, RB>(vop, hi, lo, o[4 * q4 + j]);
+                        }
+                    }
+                } else {
+                    const char *src = vt + (4 * g + (n >> 2)) * VSTRIDE + (n & 3) * 8;
+#pragma unroll
+                    for (int db = 0; db < DB; db++) {
+                        unsigned vop[2 * RB];
+#pragma unroll
+                        for (int rb = 0; rb < RB; rb++) {
+                            const u32x2 v4 = lds_transpose4(src + rb * 16 * VSTRIDE + db * 32);
+                            vop[2 * rb] = v4[0];
+                            vop[2 * rb + 1] = v4[1];
+                        }
+                        o[db] = mfma_weights<DT, RB>(vop, hi, lo, o[db]);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+            // The share's part of context `now` is done: its rows go through the tile buffers (free between tiles) into
+            // whole rows, and from there out as final rows (the whole context was here), to memory as a piece (counted
+            // and, by whoever is last, merged at the end of a share), or, in a team, to the wave's buffer of first pieces
+            // or nowhere: the last piece of a share stays where it is.
+            auto leave = [&]() {
+                lsum += __shfl_xor(lsum, 16);
+                lsum += __shfl_xor(lsum, 32);
+                const bool whole = t_begin <= now.t0 && now.t_end == now.t1;
+                const bool to_lds = !whole && sp.team == 4;
+                const float f = whole ? 1.f / lsum : 1.f;
+                __builtin_amdgcn_wave_barrier();
+                if (head_ok) {
+#pragma unroll
+                    for (int i = 0; i < DB; i++) {
+                        // 16-bit rows: accumulator block t holds elements 16t + 4g + i (i = 0..3).  8-bit rows (see the V
+                        // product): register i of blocks 4q .. 4q+3 holds elements 64q + 16g + 4i + j.
+                        const int q4 = i / 4, j = i % 4;
+                        const f32x4 v = KV8 ? (f32x4){o[4 * q4][j], o[4 * q4 + 1][j], o[4 * q4 + 2][j], o[4 * q4 + 3][j]} : o[i];
+                        *(f32x4 *)(last_piece + n * PSTRIDE + (KV8 ? q4 * 64 + 16 * g + 4 * j : i * 16 + 4 * g)) = v * f;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                const int slot = 2 * wave + (now.t_end == t_stop ? 1 : 0);
+                const int64_t row0 = (int64_t)(whole ? now.seq : pub + now.seq) * a.Hq + hq0;
+                if (to_lds) {
+                    if (head_ok && g == 0) piece_ml[slot][n] = make_float2(m, lsum);
+                    if (lane == 0) piece_b[slot] = now.seq;
+                } else if (!whole) {
+                    if (head_ok && g == 0) put_partial2<true>((float *)a.part_ml + 2 * (row0 + n), (f32x2){m, lsum});
+                    int first, count;
+                    pieces_of(sp, now.t0, now.t1, first, count);
+                    if (pend0.count == 0) pend0 = Pending{now.seq, first, count};
+                    else pend1 = Pending{now.seq, first, count};
+                }
+                if (!(to_lds && (slot & 1))) {
+#pragma unroll 1
+                    for (int e = lane; e < nheads * (D / 4); e += 64) {
+                        const int h = e / (D / 4), d = (e % (D / 4)) * 4;
+                        const f32x4 v = *(const f32x4 *)(last_piece + h * PSTRIDE + d);
+                        if (to_lds) *(f32x4 *)(first_piece + h * PSTRIDE + d) = v;
+                        else if (whole) store_out4(a.out, a.out_dtype, row0 * D + 4 * e, v);
+                        else put_partial4<true>(a.part_acc + row0 * D + 4 * e, v);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+
+            // One register set: reduce it, close the context if that was its last tile, refill the set.  The loop has ONE
+            // exit, at its bottom, and every trip issues the same loads in the same order (past the end of the share a
+            // half only waits for its set): the compiler derives how many loads may stay in flight at each wait from all
+            // paths that reach it.
+            auto half = [&](u32x4 (&kk)[NL], u32x4 (&vv)[NL]) {
+                if (t < t_stop) {
+                    reduce_tile((t - now.t0) * TR, kk, vv);
+                    t++;
+                    if (t == now.t_end) {
+                        leave();
+                        if (t < t_stop) {
+                            now = open(now.seq + 1, t);
+                            enter();
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NL; i++) asm volatile("" ::"v"(kk[i]), "v"(vv[i]));
+                }
+                load_tile(kk, vv);
+            };
+            u32x4 k0[NL], v0[NL], k1[NL], v1[NL];
+            load_tile(k0, v0);
+            enter();
+            load_tile(k1, v1);
+            do {
+                half(k0, v0);
+                half(k1, v1);
+            } while (t < t_stop);
+        }
+        if (sp.team == 4) {
+            __syncthreads();  // the pieces are in LDS
+            // Pieces of one context are neighbours: a run.  First the weight of every piece and the sum of every run ...
+            const int pb = piece_b[lane & 7];
+            int first8 = 0, count8 = 0;  // lane k: the publishing units of piece k's context
+            if (pb >= 0) pieces_of(sp, bv.pre[pb], bv.pre[pb + 1], first8, count8);
+            if (threadIdx.x < 128) {
+                const int k = threadIdx.x >> 4, h = threadIdx.x & 15;
+                const int mine = piece_b[k];
+                const float2 me = piece_ml[k][h];
+                float2 x[8];
+#pragma unroll
+                for (int j = 0; j < 8; j++) x[j] = piece_ml[j][h];
+                float m = me.x, l = 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    if (__builtin_amdgcn_readlane(pb, j) == mine) m = fmaxf(m, x[j].x);
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    if (__builtin_amdgcn_readlane(pb, j) == mine) l += fast_exp2(x[j].x - m) * x[j].y;
+                if (mine >= 0) piece_run[k][h] = (f32x4){fast_exp2(me.x - m), m, l, 1.f / l};
+            }
+            __syncthreads();
+            // ... then the rows, all threads together, every thread EB quads of elements at once
+            constexpr int EB = D / 64;
+            int h[EB], d[EB];
+#pragma unroll
+            for (int i = 0; i < EB; i++) {
+                const int e = min((int)threadIdx.x + i * 256, nheads * (D / 4) - 1);
+                h[i] = e / (D / 4);
+                d[i] = (e % (D / 4)) * 4;
+            }
+#pragma unroll 1
+            for (int k = 0; k < 8;) {
+                const int b = __builtin_amdgcn_readlane(pb, k);
+                if (b < 0) {
+                    k++;
+                    continue;
+                }
+                const int first = __builtin_amdgcn_readlane(first8, k), count = __builtin_amdgcn_readlane(count8, k);
+                f32x4 o[EB], r[EB];
+#pragma unroll
+                for (int i = 0; i < EB; i++) o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (; k < 8; k++) {
+                    const int kb = __builtin_amdgcn_readlane(pb, k);
+                    if (kb < 0) continue;
+                    if (kb != b) break;
+                    const float *src = (k & 1) ? (const float *)wave_lds[k >> 1] : first_piece + ((k >> 1) - wave) * piece_heads * PSTRIDE;
+#pragma unroll
+                    for (int i = 0; i < EB; i++) {
+                        r[i] = piece_run[k][h[i]];
+                        o[i] += r[i][0] * *(const f32x4 *)(src + h[i] * PSTRIDE + d[i]);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < EB; i++) {
+                    if ((int)threadIdx.x + i * 256 >= nheads * (D / 4)) continue;
+                    if (count == 1) {
+                        store_out4(a.out, a.out_dtype, ((int64_t)b * a.Hq + hq0 + h[i]) * D + d[i], o[i] * r[i][3]);
+                    } else {
+                        const int64_t pi = (int64_t)(pub + b) * a.Hq + hq0 + h[i];
+                        if (d[i] == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){r[i][1], r[i][2]});
+                        put_partial4<true>(a.part_acc + pi * D + d[i], o[i]);
+                    }
+                }
+                if (count > 1) {
+                    if (pend0.count == 0) pend0 = Pending{b, first, count};
+                    else pend1 = Pending{b, first, count};
                 }
             }
-        }
-        if (ink && it.nchunks > 1) {
-            told.cnt = a.arrivals + (int64_t)it.b * per_seq + it.hgb;
-            told.b = it.b;
-            told.hq0 = hk * group + qb * 16;
-            told.nheads = min(16, group - qb * 16);
-            told.nchunks = it.nchunks;
-        }
-        item = claim_next ? t_static + (int64_t)__builtin_amdgcn_readfirstlane(claimed) : item + n_waves;
-    }
-    };
-    // chunk counts bound the rows: (chunks - 1) * chunk < rows of a context <= chunks * chunk
-    const int64_t k_bytes = (int64_t)bv.total * a.chunk * rstride;
-    if (a.stream_k < 0 ? k_bytes > ((int64_t)256 << 20) : a.stream_k != 0) run_items(std::true_type{});
-    else run_items(std::false_type{});
-    if (ink) settle(true);  // the last one or two chunks of this wave
-    if (dyn && lane == 0) {
-        // the last wave to leave puts both counters back to zero for the next launch (a wave has made all its
-        // claims before it announces its exit)
-        const unsigned int gone = atomicAdd(a.queue + 1, 1u);
-        if (gone == (unsigned int)(gridDim.x * 4 - 1)) {
-            atomicExch(a.queue, 0u);
-            atomicExch(a.queue + 1, 0u);
+            if (pend0.count != 0) {  // uniform over the workgroup
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // every wave's stores are at the memory side ...
+                __syncthreads();                                            // ... before one of them counts the pieces
+                if (wave == 0) {
+                    const unsigned mine = pieces_arrived(a, pend0, pend1, columns, col);
+                    if (lane == 0) merge_mine = (int)mine;
+                }
+                __syncthreads();
+                const int mine = __builtin_amdgcn_readfirstlane(merge_mine);
+#pragma unroll 1
+                for (int k = 0; k < 2; k++)
+                    if ((mine >> k) & 1) merge_pieces<D>(a, k ? pend1 : pend0, hq0, nheads, threadIdx.x, 256, (float *)wave_lds);
+            }
+            __syncthreads();  // LDS is free for the next unit
+        } else {
+            if (pend0.count != 0 || pend1.count != 0) {
+                const unsigned mine = pieces_arrived(a, pend0, pend1, columns, col);
+#pragma unroll 1
+                for (int k = 0; k < 2; k++)
+                    if ((mine >> k) & 1) merge_pieces<D>(a, k ? pend1 : pend0, hq0, nheads, lane, 64, nullptr);
+            }
         }
     }
 }

@@ -552,9 +552,10 @@ static AttnArgs common_args(const s3_arena *a, const AttnCall &c, int row_heads,
 }
 
 // Library scratch: [arrival counters: cnt_bytes, fixed per arena kind, zero between launches]
-// [partial sums][partial (max, sum)], one partial per (sequence, chunk, head of q).
-static int place_scratch(s3_arena *a, AttnArgs &args, size_t cnt_bytes, const AttnCall &c) {
-    const size_t n_part = (size_t)args.n * args.max_chunks * args.Hq;
+// [partial sums][partial (max, sum)], `slots` partials per head of q (one per sequence and chunk, or as
+// gqa_partial_slots() counts them).
+static int place_scratch(s3_arena *a, AttnArgs &args, size_t cnt_bytes, size_t slots, const AttnCall &c) {
+    const size_t n_part = slots * args.Hq;
     const size_t acc_bytes = n_part * a->cfg.head_dim * sizeof(float);
     const size_t need = cnt_bytes + acc_bytes + n_part * sizeof(float2);
     char *base = nullptr;
@@ -580,6 +581,39 @@ static size_t counters_bytes(int n_hg) {
     return ((((size_t)(S3_MAX_BATCH + 1) * n_hg * sizeof(unsigned int)) + 255) & ~(size_t)255) + 256;  // + the work-list counters
 }
 
+// The matrix-core kernel's share of the scratch.  A piece of a context sits in slot (publishing unit + sequence),
+// so max_shares units need max_shares + n slots.  With the default division at most one unit per wave and column
+// (waves <= 8 per compute unit, see launch_gqa); with a caller's `chunk` as many as the longest contexts could need.
+// What fits the fixed buffer of s3_decode_step_static by its documented rule (chunks of `chunk` rows, or 128 / 256)
+// is held to that buffer's size by fewer shares, there and here alike, so that both calls divide their rows the same.
+static int64_t gqa_columns(const s3_arena *a) {
+    const int group = a->cfg.n_heads / a->cfg.n_kv_heads;
+    return (int64_t)a->cfg.n_kv_heads * ((group + 15) / 16);
+}
+static size_t gqa_slot_bytes(const s3_arena *a) {
+    return (size_t)a->cfg.n_heads * ((size_t)a->cfg.head_dim * sizeof(float) + sizeof(float2));
+}
+static bool gqa_fits_static(const s3_arena *a, int n) {
+    const int64_t columns = gqa_columns(a);
+    const int chunk = a->chunk > 0 ? a->chunk : n * columns >= 4096 ? 256 : 128;
+    const size_t max_chunks = (size_t)(a->cfg.max_len + chunk - 1) / chunk;
+    return counters_bytes((int)columns) + (size_t)n * max_chunks * gqa_slot_bytes(a) <= (size_t)S3_STATIC_SCRATCH_BYTES;
+}
+static int64_t gqa_max_shares(const s3_arena *a, int n) {
+    const int64_t columns = gqa_columns(a);
+    const int64_t waves = (int64_t)(a->num_cus > 0 ? a->num_cus : 256) * 8;
+    int64_t most = a->chunk > 0 ? (int64_t)n * (a->cfg.max_len + 31) / a->chunk + 1 : (waves + columns - 1) / columns;
+    if (gqa_fits_static(a, n)) {
+        const int64_t slots = (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes((int)columns)) / gqa_slot_bytes(a));
+        if (most > slots - n) most = slots - n;
+    }
+    return most < 1 ? 1 : most;
+}
+static size_t gqa_partial_slots(const s3_arena *a, int n) {
+    const int64_t shares = gqa_max_shares(a, n);
+    return shares > 1 ? (size_t)(shares + n) : 0;  // one share: no piece ever leaves its wave or team
+}
+
 // Scratch an attention call over n sequences needs at most: the launchers' layout with the smallest chunk
 // they may choose for any batch size (or the chunk the caller fixed).
 static size_t scratch_need(const s3_arena *a, int n) {
@@ -587,14 +621,20 @@ static size_t scratch_need(const s3_arena *a, int n) {
     const int kind = s3i_kernel_kind(a);
     int chunk = a->chunk;
     size_t cnt_bytes = 0;
+    if (kind == 2 || kind == 4) {
+        size_t most = 0;  // a smaller batch may take more slots: the fixed buffer's size bounds some and not others
+        for (int k = n; k >= 1; k = k > 64 ? k - 64 : k - 1) {
+            const size_t slots = gqa_partial_slots(a, k);
+            if (slots > most) most = slots;
+        }
+        return counters_bytes((int)gqa_columns(a)) + (most + 64) * gqa_slot_bytes(a);
+    }
     if (kind == 0 || kind == 3) {  // kernels that merge chunks themselves carry counters
         if (chunk <= 0) chunk = 1024;
         const int gh = kind == 3 ? 1024 / D : heads_per_load(D);
         cnt_bytes = counters_bytes((Hq + gh - 1) / gh);
-    } else {
-        if (chunk <= 0) chunk = (kind == 2 || kind == 4) ? 128 : 256;
-        if (kind == 2 || kind == 4)  // arrival counters (if chunks merge inside the launch) and the work-list counters
-            cnt_bytes = counters_bytes(a->cfg.n_kv_heads * ((Hq / a->cfg.n_kv_heads + 15) / 16));
+    } else if (chunk <= 0) {
+        chunk = 256;
     }
     const size_t max_chunks = (size_t)(a->cfg.max_len + chunk - 1) / chunk;
     const size_t n_part = (size_t)n * max_chunks * Hq;
@@ -669,47 +709,73 @@ static int launch_attn_kernels(s3_arena *a, attn_fn fn, int blocks, int threads,
     return S3_OK;
 }
 
-// Shared key/value heads.  Vector-ALU kernel: append as its own launch, attention, merge.  Matrix-core
-// kernel: attention (which appends the new row itself), merge; over 8-bit rows: quantising append launch,
-// attention, merge.
+// Shared key/value heads, matrix-core kernel: one launch (over 8-bit rows a quantising append before it).
+static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
+    const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
+    const bool eight_bit = s3i_kernel_kind(a) == 4;
+    attn_fn fn = eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D) : s3i_pick_gqa_mfma(a->cfg.kv_dtype, D);
+    if (!fn) return S3_ERR_INVALID;
+    if (c.static_scratch && !gqa_fits_static(a, c.n)) return S3_ERR_SCRATCH;
+    if (c.with_append && eight_bit) {  // 16-bit rows: the kernel appends by itself
+        const int arc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
+        if (arc != S3_OK) return arc;
+    }
+    const int64_t columns = gqa_columns(a);
+    AttnArgs args = common_args(a, c, Hkv, Hq, 16);  // (the kernel's batch view counts its own tiles)
+    args.ncls = 1;
+    args.stream_k = a->gqa_stream;
+    args.share_rows = a->chunk;
+    args.max_shares = (int32_t)gqa_max_shares(a, c.n);
+    int rc = place_scratch(a, args, counters_bytes((int)columns), gqa_partial_slots(a, c.n), c);
+    if (rc != S3_OK) return rc;
+    // LDS behind the view: the first pieces of a team's four waves.  A batch whose view leaves no room for them has
+    // thousands of contexts, i.e. long shares, and works without teams.
+    const size_t view = batch_view_lds(c.n, 1), group16 = Hq / Hkv < 16 ? Hq / Hkv : 16;
+    const size_t pieces = 4 * group16 * (size_t)(D + 4) * sizeof(float);
+    args.team_lds = c.n <= 1024;
+    const size_t dyn_lds = args.team_lds ? ((view + 15) & ~(size_t)15) + pieces : view;
+    int per_cu = 0;
+    rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
+    if (rc != S3_OK) return rc;
+    if (per_cu > 2) per_cu = 2;
+    const int cus = a->num_cus > 0 ? a->num_cus : 256;
+    args.group = Hq / Hkv;
+    args.nqb = (args.group + 15) / 16;
+    args.columns = (int32_t)columns;
+    const int64_t waves = (int64_t)cus * per_cu * 4;
+    args.wave_shares = (int32_t)(waves > columns ? waves / columns : 1);
+    args.team_shares = (int32_t)(waves > 4 * columns ? waves / (4 * columns) : 1);
+    const int blocks = a->grid_blocks > 0 ? a->grid_blocks : cus * per_cu;
+    return launch_attn_kernels(a, fn, blocks, 256, dyn_lds, c.stream, args, 0, !c.static_scratch);
+}
+
+// Shared key/value heads, vector-ALU kernel: append as its own launch, attention, merge.
 static int launch_gqa(s3_arena *a, const AttnCall &c) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
+    const int kind = s3i_kernel_kind(a);
+    // Variant indices of a shared-K/V arena: the shapes of the vector-ALU kernel, then the matrix-core kernel.
+    if (kind == 2 || kind == 4) return launch_gqa_mfma(a, c);
     const int group = Hq / Hkv;
     const int gq = group % 8 == 0 ? 8 : group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
-    // Variant indices of a shared-K/V arena: the shapes of the vector-ALU kernel, then the matrix-core kernel.
-    const int kind = s3i_kernel_kind(a);
-    const bool mfma = kind == 2 || kind == 4, eight_bit = kind == 4;
     int threads = 256;
-    attn_fn fn = eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D)
-                 : mfma    ? s3i_pick_gqa_mfma(a->cfg.kv_dtype, D)
-                           : s3i_pick_gqa(a->cfg.kv_dtype, D, gq, a->variant, &threads);
+    attn_fn fn = s3i_pick_gqa(a->cfg.kv_dtype, D, gq, a->variant, &threads);
     if (!fn) return S3_ERR_INVALID;
-    if (c.with_append && (!mfma || eight_bit)) {  // 16-bit rows: the matrix-core kernel appends by itself
+    if (c.with_append) {
         const int arc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
         if (arc != S3_OK) return arc;
     }
     const int GH = 512 / D;
-    // work items per chunk: (K/V head groups x query sub-blocks), or for the matrix-core kernel
-    // (K/V heads x blocks of 16 query heads), there one item per wave
-    const int per_seq = mfma ? Hkv * ((group + 15) / 16) : ((Hkv + GH - 1) / GH) * (group / gq);
+    const int per_seq = ((Hkv + GH - 1) / GH) * (group / gq);  // work items per chunk: K/V head groups x query sub-blocks
     // Few (sequence, head group) pairs: cut contexts finer so that the chip still has work everywhere.
-    const int chunk = a->chunk > 0 ? a->chunk
-                      : mfma     ? ((int64_t)c.n * per_seq >= 4096 ? 256 : 128)  // one wave per item: short items keep every SIMD busy
-                      : (int64_t)c.n * per_seq >= 2048 ? 1024 : (int64_t)c.n * per_seq >= 512 ? 512 : 256;
+    const int chunk = a->chunk > 0 ? a->chunk : (int64_t)c.n * per_seq >= 2048 ? 1024 : (int64_t)c.n * per_seq >= 512 ? 512 : 256;
     AttnArgs args = common_args(a, c, Hkv, Hq, chunk);
-    if (mfma && a->ncls <= 0) args.ncls = 1;  // items of at most 128 rows are all alike: no order to gain from (measured)
-    // matrix-core kernel: chunks of a context may meet inside the launch (one counter per sequence and item slot)
-    const bool ink = mfma && a->gqa_merge != 0;
-    args.merge_in_kernel = ink ? 1 : 0;
-    args.stream_k = a->gqa_stream;
-    args.dyn_list = mfma && a->gqa_dynamic > 0 ? a->gqa_dynamic : 0;
-    int rc = place_scratch(a, args, mfma ? counters_bytes(per_seq) : 0, c);
+    int rc = place_scratch(a, args, 0, (size_t)args.n * args.max_chunks, c);
     if (rc != S3_OK) return rc;
     const size_t dyn_lds = batch_view_lds(c.n, args.ncls);
     int blocks = 0;
     rc = stride_grid(a, (const void *)fn, threads, dyn_lds, 1, &blocks);
     if (rc != S3_OK) return rc;
-    return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, ink ? 0 : Hq, !c.static_scratch);
+    return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, Hq, !c.static_scratch);
 }
 
 // 8-bit cache rows: one kernel, which in a decode step also quantises and appends the new row, merges
@@ -721,7 +787,7 @@ static int launch_fp8(s3_arena *a, const AttnCall &c) {
     if (!fn) return S3_ERR_INVALID;
     AttnArgs args = common_args(a, c, H, H, a->chunk > 0 ? a->chunk : 1024);
     const int n_hg = (H + 1024 / D - 1) / (1024 / D);  // head groups: 1024/D heads per 128-bit wave load of bytes
-    int rc = place_scratch(a, args, counters_bytes(n_hg), c);
+    int rc = place_scratch(a, args, counters_bytes(n_hg), (size_t)args.n * args.max_chunks, c);
     if (rc != S3_OK) return rc;
     const size_t dyn_lds = batch_view_lds(c.n, args.ncls);
     int blocks = 0;
@@ -753,7 +819,7 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
         args.ncls = 4;
         while (args.ncls > 1 && batch_view_lds(c.n, args.ncls) > (size_t)96 * 1024) args.ncls--;
     }
-    int rc = place_scratch(a, args, counters_bytes(n_hg), c);
+    int rc = place_scratch(a, args, counters_bytes(n_hg), (size_t)args.n * args.max_chunks, c);
     if (rc != S3_OK) return rc;
     const int threads = s3i_variant_threads(variant, fused);  // the fused kernel adds an epilogue wave
     const size_t view = batch_view_lds(c.n, args.ncls);

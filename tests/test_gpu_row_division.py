@@ -1,0 +1,81 @@
+"""The matrix-core kernel divides the rows of a batch evenly over its waves, across the borders of contexts: every way
+a share can begin, end and be merged, against the fp32 oracle (max-abs 2e-3 / relative L2 1e-3, as everywhere).  Plus
+the cache bits of the loads that merge the pieces, read off the emitted code (no GPU needed for that one)."""
+import os
+import re
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2306_06000_amd import binding as s3
+from tests.harness import assert_close
+
+torch = pytest.importorskip("torch")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+FAMS = [
+    ("d64 group 3", 24, 8, 64, s3.S3_BF16, s3.S3_BF16, 1),
+    ("d128 group 4", 32, 8, 128, s3.S3_BF16, s3.S3_BF16, 2),
+    ("d128 group 24", 24, 1, 128, s3.S3_F16, s3.S3_F16, 2),
+    ("d256 group 16", 16, 1, 256, s3.S3_F16, s3.S3_F16, 2),
+    ("d64 e4m3 group 8", 8, 1, 64, s3.S3_E4M3, s3.S3_F16, 4),
+    ("d128 e4m3 group 2", 16, 8, 128, s3.S3_E4M3, s3.S3_BF16, 4),
+    ("d256 e4m3 group 2", 6, 3, 256, s3.S3_E4M3, s3.S3_F16, 4),
+]
+
+
+def batches():
+    rng = np.random.default_rng(5)
+    return [
+        ("one row", [1]),
+        ("one long context cut by every share", [2047]),
+        ("tile edges, empty first and last", [0, 15, 16, 17, 0, 31, 32, 33, 1, 63, 64, 65, 0]),
+        ("a long one between short ones", [3, 1900, 1, 1, 40]),
+        ("hundreds", [int(x) for x in rng.integers(0, 400, size=300)]),
+        ("more than fit a team's LDS", [int(x) for x in rng.integers(1, 12, size=1100)]),
+    ]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fam", FAMS, ids=[f[0] for f in FAMS])
+def test_even_division_over_batches(fam):
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    name, H, Hkv, D, kvt, act, kind = fam
+    for what, lens in batches():
+        rng = np.random.default_rng(len(lens) + D)
+        rig = EdgeRig(fam, lens, M=2048)
+        rig.put([rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens],
+                [rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens])
+        if kind == 1:  # fewer than four query heads per cached head: the matrix-core kernel on request
+            assert s3.s3_kv_set_param(rig.a, "variant", s3.s3_kv_get_param(rig.a, "n_variants")[1] - 1) == 0
+        n = len(lens)
+        q = rng.standard_normal((n, H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / {what}")
+        for grid in (1, 7):  # the division does not depend on the grid, nor do the bits
+            assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0
+            assert np.array_equal(rig.attend(q)[1], att), (name, what, grid)
+        assert s3.s3_kv_set_param(rig.a, "grid_blocks", 0) == 0
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
+        assert_close(step, rig.want(qb, longer), f"{name} / {what} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
+        rig.close()
+
+
+def test_merging_loads_bypass_the_caches(tmp_path):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc here")
+    src = tmp_path / "probe.hip"
+    src.write_text('#include "s3kv_device.h"\n__global__ void probe(const float *p, float *out) {\n'
+                   "    const f32x4 a = get_coherent4(p + 4 * threadIdx.x);\n    out[threadIdx.x] = a[0] + a[1] + a[2] + a[3];\n}\n")
+    asm = tmp_path / "probe.s"
+    subprocess.run([hipcc, "-O3", "-std=c++17", "--offload-arch=gfx950", "--cuda-device-only", "-S", "-I",
+                    os.path.join(ROOT, "paper_2306_06000_amd", "csrc"), "-I", os.path.join(ROOT, "include"), "-x", "hip", str(src), "-o", str(asm)],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    loads = re.findall(r"(?:global|flat)_load_dwordx[24] .*", asm.read_text())
+    assert loads and all("sc0" in x and "sc1" in x for x in loads), loads
