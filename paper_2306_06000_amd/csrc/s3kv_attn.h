@@ -10,9 +10,8 @@
 // lanes each, 768 contiguous bytes, the other four lanes of every sixteen idle); the lanes of a head
 // reduce their dot product with DPP row operations, keep a running maximum and sum in fp32, and
 // accumulate their 8-element slice of the output.  The TS waves of a workgroup that share a head group
-// split the chunk's tokens and merge through LDS; chunks of one context merge in a second kernel
-// (s3_decode_attention) or, in the fused step, in the epilogue wave of whichever workgroup delivers the
-// last chunk.  Score s_j = q.K_j * scale as in the section 2.1 equation of the S3 paper; softmax is
+// split the chunk's tokens and merge through LDS; chunks of one context merge in the epilogue wave of whichever
+// workgroup delivers the last chunk.  Score s_j = q.K_j * scale as in the section 2.1 equation of the S3 paper; softmax is
 // max-subtracted; everything after the 16-bit loads is fp32.
 #pragma once
 #include "s3kv_device.h"
@@ -29,11 +28,11 @@ struct HeadLanes {
 
 // One wave's share of an item: tokens [j0, j1) of head group hg, online softmax in fp32.
 // DT: element type of q/K/V.  D: head_dim.  U: tokens per load batch.  NT: non-temporal loads.
-// FUSED: row len-1 is still only in k_new / v_new: it is taken from there and, by the wave whose
-// range holds it, written into the arena (the append).
+// In a decode step row len-1 is still only in k_new / v_new: it is taken from there and, by the wave whose
+// range holds it, written into the arena (the append).  (k_new null: no such row.)
 // PF: software pipelining - the loads of the next batch of U tokens are issued before the current
 // batch is reduced, so the wave always has loads in flight (two register sets, used alternately).
-template <int DT, int D, int U, bool NT, bool FUSED>
+template <int DT, int D, int U, bool NT>
 struct TokenStream {
     static constexpr int LPH = HeadLanes<D>::LPH;
     static constexpr int GH = HeadLanes<D>::GH;
@@ -48,14 +47,14 @@ struct TokenStream {
         for (int u = 0; u < U; u++) {
             const int jj = min(j + u, j1 - 1);
             const char *src = kp + (int64_t)jj * rstride;
-            if (FUSED) src = (jj == jnew) ? knew : src;
+            src = (jj == jnew) ? knew : src;
             kk[u] = load16<NT>(src);
         }
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const int jj = min(j + u, j1 - 1);
             const char *src = vp + (int64_t)jj * rstride;
-            if (FUSED) src = (jj == jnew) ? vnew : src;
+            src = (jj == jnew) ? vnew : src;
             vv[u] = load16<NT>(src);
         }
     }
@@ -88,10 +87,10 @@ struct TokenStream {
     }
 };
 
-template <int DT, int D, int U, bool NT, bool FUSED, bool PF>
+template <int DT, int D, int U, bool NT, bool PF>
 __device__ __forceinline__ void wave_tokens(const AttnArgs &a, const Item &it, int hg, int j0, int j1, float &m,
                                             float &l, float (&acc)[8]) {
-    typedef TokenStream<DT, D, U, NT, FUSED> TS_t;
+    typedef TokenStream<DT, D, U, NT> TS_t;
     typedef HeadLanes<D> HL;
     const int lane = threadIdx.x & 63;
     const int g = lane / HL::LPH, dl = lane % HL::LPH;
@@ -107,10 +106,10 @@ __device__ __forceinline__ void wave_tokens(const AttnArgs &a, const Item &it, i
     TS_t st;
     st.kp = a.kplane + it.off * rstride + lane_byte;
     st.vp = a.vplane + it.off * rstride + lane_byte;
-    st.knew = FUSED ? a.k_new + in_byte : nullptr;
-    st.vnew = FUSED ? a.v_new + in_byte : nullptr;
+    st.knew = a.k_new + in_byte;
+    st.vnew = a.v_new + in_byte;
     st.rstride = rstride;
-    st.jnew = FUSED ? it.len - 1 : -1;
+    st.jnew = a.k_new ? it.len - 1 : -1;
     st.j1 = j1;
     st.scale_log2e = a.scale_log2e;
     st.qv = *(const u32x4 *)(a.q + in_byte);
@@ -139,7 +138,7 @@ __device__ __forceinline__ void wave_tokens(const AttnArgs &a, const Item &it, i
             }
         }
     }
-    if (FUSED && lane_ok && j0 <= st.jnew && st.jnew < j1) {  // the append: this wave owns the new row's slice
+    if (lane_ok && j0 <= st.jnew && st.jnew < j1) {  // the append: this wave owns the new row's slice
         *(u32x4 *)(a.kplane + (it.off + st.jnew) * rstride + lane_byte) = *(const u32x4 *)(a.k_new + in_byte);
         *(u32x4 *)(a.vplane + (it.off + st.jnew) * rstride + lane_byte) = *(const u32x4 *)(a.v_new + in_byte);
     }
@@ -177,11 +176,11 @@ __device__ __forceinline__ void wait_vm_then_read2(const char *s0, const char *s
         : "memory");
 }
 
-template <int DT, int D, int R, bool FUSED>
+template <int DT, int D, int R>
 __device__ __forceinline__ void wave_tokens_ring(const AttnArgs &a, const Item &it, int hg, int j0, int j1, char *ring,
                                                  float &m, float &l, float (&acc)[8]) {
     constexpr int U = 2;
-    typedef TokenStream<DT, D, U, true, FUSED> TS_t;
+    typedef TokenStream<DT, D, U, true> TS_t;
     typedef HeadLanes<D> HL;
     const int lane = threadIdx.x & 63;
     const int g = lane / HL::LPH, dl = lane % HL::LPH;
@@ -195,10 +194,10 @@ __device__ __forceinline__ void wave_tokens_ring(const AttnArgs &a, const Item &
     TS_t st;
     st.kp = a.kplane + it.off * rstride + lane_byte;
     st.vp = a.vplane + it.off * rstride + lane_byte;
-    st.knew = FUSED ? a.k_new + in_byte : nullptr;
-    st.vnew = FUSED ? a.v_new + in_byte : nullptr;
+    st.knew = a.k_new + in_byte;
+    st.vnew = a.v_new + in_byte;
     st.rstride = rstride;
-    st.jnew = FUSED ? it.len - 1 : -1;
+    st.jnew = a.k_new ? it.len - 1 : -1;
     st.j1 = j1;
     st.scale_log2e = a.scale_log2e;
     st.qv = *(const u32x4 *)(a.q + in_byte);
@@ -213,7 +212,7 @@ __device__ __forceinline__ void wave_tokens_ring(const AttnArgs &a, const Item &
         int issued = j0, islot = 0;     // next row to load and the slot it goes to
         auto issue = [&]() {
             const char *ks = st.kp + (int64_t)issued * rstride, *vs = st.vp + (int64_t)issued * rstride;
-            if (FUSED && issued == st.jnew) {
+            if (issued == st.jnew) {
                 ks = st.knew;
                 vs = st.vnew;
             }
@@ -238,7 +237,7 @@ __device__ __forceinline__ void wave_tokens_ring(const AttnArgs &a, const Item &
             st.reduce(j, kk, vv, m, l, acc);
         }
     }
-    if (FUSED && lane_ok && j0 <= st.jnew && st.jnew < j1) {
+    if (lane_ok && j0 <= st.jnew && st.jnew < j1) {
         *(u32x4 *)(a.kplane + (it.off + st.jnew) * rstride + lane_byte) = *(const u32x4 *)(a.k_new + in_byte);
         *(u32x4 *)(a.vplane + (it.off + st.jnew) * rstride + lane_byte) = *(const u32x4 *)(a.v_new + in_byte);
     }
@@ -278,7 +277,7 @@ __device__ __forceinline__ void emit_chunk(const AttnArgs &a, const Item &it, in
         store_out8(a.out, a.out_dtype, ((int64_t)it.b * a.H + h) * D + dl * 8, o);
         return;
     }
-    const int64_t pi = ((int64_t)it.b * a.max_chunks + it.c) * a.H + h;
+    const int64_t pi = (int64_t)(it.slot0 + it.c) * a.H + h;
     float *pml = (float *)a.part_ml + 2 * pi;
     float *pa = a.part_acc + pi * D + dl * 8;
     if (dl == 0) put_partial2<COHERENT>(pml, (f32x2){m, l});
@@ -286,46 +285,8 @@ __device__ __forceinline__ void emit_chunk(const AttnArgs &a, const Item &it, in
     put_partial4<COHERENT>(pa + 4, (f32x4){acc[4], acc[5], acc[6], acc[7]});
 }
 
-// Attention only (s3_decode_attention): TS*HS waves; the TS waves of a head group split the chunk's
-// tokens and merge through LDS; multi-chunk contexts are finished by attn_merge_kernel.
-template <int DT, int D, int TS, int HS, int U, bool NT, bool PF>
-__global__ void __launch_bounds__(TS *HS * 64) attn_partial_kernel(const AttnArgs a) {
-    constexpr int LPH = HeadLanes<D>::LPH, USED = HeadLanes<D>::USED, GH = HeadLanes<D>::GH;
-    constexpr int NW = TS * HS;
-    extern __shared__ __align__(16) char dyn_lds[];  // the batch view
-    __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
-    __shared__ float comb[TS > 1 ? NW : 1][10][64];
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ts = wave % TS, hs = wave / TS;
-    const int n_hg = (a.H + GH - 1) / GH;
-    const int n_hgb = (n_hg + HS - 1) / HS;
-    const BatchView bv = build_batch_view(a, dyn_lds, wave_sums);
-    const int64_t total = (int64_t)bv.total * n_hgb;
-
-    for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-        const Item it = decode_item(a, bv, item, n_hgb);
-        const int hg = it.hgb * HS + hs;
-        int j0, j1;
-        split_rows(it, ts, TS, j0, j1);
-        float m, l, acc[8];
-        wave_tokens<DT, D, U, NT, false, PF>(a, it, hg, j0, j1, m, l, acc);
-        if (TS > 1) {
-            comb[wave][0][lane] = m;
-            comb[wave][1][lane] = l;
-#pragma unroll
-            for (int i = 0; i < 8; i++) comb[wave][2 + i][lane] = acc[i];
-            __syncthreads();
-            if (ts == 0) combine_splits<TS>(comb, wave, lane, m, l, acc);
-        }
-        const int h = hg * GH + lane / LPH;
-        if (ts == 0 && h < a.H && lane % LPH < USED) emit_chunk<D, false>(a, it, h, lane % LPH, m, l, acc);
-        if (TS > 1) __syncthreads();  // comb is reused by the next item
-    }
-}
-
-// The whole layer-step in one launch (s3_decode_step): TS*HS compute waves plus ONE epilogue wave.
-// Compute waves stream their token shares (taking the new row from k_new / v_new and appending it),
+// The whole layer-step in one launch (s3_decode_step), or, without new rows (k_new null), attention alone
+// (s3_decode_attention): TS*HS compute waves plus ONE epilogue wave.  Compute waves stream their token shares (taking the new row from k_new / v_new and appending it),
 // drop (max, sum, weighted sum) into one of two LDS buffers and move on to the next item after a
 // single barrier.  The epilogue wave merges the splits, writes the output or the chunk partial,
 // announces the chunk on the context's arrival counter and, if it delivered the last chunk, merges
@@ -377,8 +338,8 @@ __global__ void __launch_bounds__((TS *HS + 1) * 64) attn_step_kernel(const Attn
             int j0, j1;
             split_rows(it, ts, TS, j0, j1);
             float m, l, acc[8];
-            if (R > 0) wave_tokens_ring<DT, D, R, true>(a, it, it.hgb * HS + hs, j0, j1, ring, m, l, acc);
-            else wave_tokens<DT, D, U, NT, true, PF>(a, it, it.hgb * HS + hs, j0, j1, m, l, acc);
+            if (R > 0) wave_tokens_ring<DT, D, R>(a, it, it.hgb * HS + hs, j0, j1, ring, m, l, acc);
+            else wave_tokens<DT, D, U, NT, PF>(a, it, it.hgb * HS + hs, j0, j1, m, l, acc);
             comb[parity][wave][0][lane] = m;
             comb[parity][wave][1][lane] = l;
 #pragma unroll
@@ -409,7 +370,7 @@ __global__ void __launch_bounds__((TS *HS + 1) * 64) attn_step_kernel(const Attn
                 if (chunk_arrived(a, cnt, it.nchunks)) {  // every chunk of this context has arrived
                     for (int s = 0; s < HS; s++) {
                         const int h = (it.hgb * HS + s) * GH + lane / LPH;
-                        if (h < a.H && dl_ok) merge_chunks<D, true>(a, a.H, it.b, h, lane % LPH, it.nchunks);
+                        if (h < a.H && dl_ok) merge_chunks<D, true>(a, it.slot0, a.H, it.b, h, lane % LPH, it.nchunks);
                     }
                 }
             }
@@ -447,7 +408,7 @@ __global__ void __launch_bounds__((TS *HS + 1) * 64) attn_step_kernel(const Attn
 template <int DT, int D, int TS, int U, bool DYN>
 __global__ void __launch_bounds__((TS + 1) * 64) attn_step_stream_kernel(const AttnArgs a) {
     typedef HeadLanes<D> HL;
-    typedef TokenStream<DT, D, U, true, true> TS_t;
+    typedef TokenStream<DT, D, U, true> TS_t;
     constexpr int LPH = HL::LPH, USED = HL::USED, GH = HL::GH;
     constexpr int NO_ROW = -0x40000000;  // "no new row in this share": equal to no row index
     extern __shared__ __align__(16) char dyn_lds[];  // the batch view
@@ -510,7 +471,7 @@ __global__ void __launch_bounds__((TS + 1) * 64) attn_step_stream_kernel(const A
                     kn_l = a.k_new + in_row;
                     vn_l = a.v_new + in_row;
                     stride_l = rstride;
-                    jnew_l = it_l.len - 1;
+                    jnew_l = a.k_new ? it_l.len - 1 : NO_ROW;
                 } else {  // no rows for this wave: its one batch reads the query row and is not reduced
                     kb_l = vb_l = kn_l = vn_l = a.q + in_row;
                     stride_l = 0;
@@ -557,7 +518,7 @@ __global__ void __launch_bounds__((TS + 1) * 64) attn_step_stream_kernel(const A
             auto adopt = [&]() {  // the reducer enters the item the loader has open
                 j_r = j0_l;
                 st.j1 = j1_l;
-                jnew_r = j0_l < j1_l ? it_l.len - 1 : NO_ROW;
+                jnew_r = j0_l < j1_l && a.k_new ? it_l.len - 1 : NO_ROW;
                 off_r = it_l.off;
                 st.qv = q_l;
                 lane_r = lane_l;
@@ -645,7 +606,7 @@ __global__ void __launch_bounds__((TS + 1) * 64) attn_step_stream_kernel(const A
                 if (it.nchunks > 1) {
                     unsigned int *cnt = a.arrivals + (int64_t)it.b * n_hgb + it.hgb;
                     if (chunk_arrived(a, cnt, it.nchunks)) {  // every chunk of this context has arrived
-                        if (h < a.H && dl_ok) merge_chunks<D, true>(a, a.H, it.b, h, lane % LPH, it.nchunks);
+                        if (h < a.H && dl_ok) merge_chunks<D, true>(a, it.slot0, a.H, it.b, h, lane % LPH, it.nchunks);
                     }
                 }
                 pos = pos1;
@@ -665,8 +626,8 @@ __global__ void __launch_bounds__((TS + 1) * 64) attn_step_stream_kernel(const A
     }
 }
 
-// One wave per (sequence, head group): merge the chunk partials of contexts longer than one
-// chunk; write zeros for empty contexts; leave single-chunk contexts (already final) alone.
+// Vector-ALU kernel for shared heads.  One wave per (sequence, head group): merge the chunk partials of contexts
+// longer than one chunk; write zeros for empty contexts; leave single-chunk contexts (already final) alone.
 template <int D>
 __global__ void __launch_bounds__(256) attn_merge_kernel(const AttnArgs a) {
     constexpr int LPH = HeadLanes<D>::LPH, USED = HeadLanes<D>::USED, GH = HeadLanes<D>::GH;
@@ -680,7 +641,7 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const AttnArgs a) {
     const int nchunks = chunks_of(a, b, a.chunk);
     if (nchunks == 1) return;
     if (nchunks > 1) {
-        merge_chunks<D, false>(a, a.H, b, h, dl, nchunks);
+        merge_chunks<D, false>(a, (int64_t)b * a.max_chunks, a.H, b, h, dl, nchunks);
         return;
     }
     const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -689,8 +650,6 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const AttnArgs a) {
 
 // Kernel shapes: (index, TS token splits, HS head groups per workgroup, U rows per load batch, NT, PF, R rows of
 // the LDS ring (0: rows in flight sit in registers), DYN dynamic work list, XS row stream carried across items);
-// R, DYN and XS concern the fused step kernel only (the attention-only kernel of such a shape is the register /
-// fixed-stride one).
 #define S3_VARIANTS(X)                            \
     X(0, 4, 1, 4, true, false, 0, false, false)   \
     X(1, 8, 1, 4, true, false, 0, false, false)   \
@@ -725,11 +684,10 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const AttnArgs a) {
 #define S3_DEFAULT_VARIANT_LARGE 13
 
 template <int DT, int D>
-static attn_fn pick_variant(int v, bool fused) {
+static attn_fn pick_variant(int v) {
     switch (v) {
 #define X(i, ts, hs, u, nt, pf, r, dyn, xs)                                                                       \
     case i:                                                                                                       \
-        if (!fused) return (attn_fn)attn_partial_kernel<DT, D, ts, hs, u, nt, pf>;                                  \
         if constexpr (xs) return (attn_fn)attn_step_stream_kernel<DT, D, ts * hs, u, dyn>; /* XS shapes: hs = 1 */ \
         else return (attn_fn)attn_step_kernel<DT, D, ts, hs, u, nt, pf, r, dyn>;
         S3_VARIANTS(X)

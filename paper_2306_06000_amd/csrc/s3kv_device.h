@@ -22,12 +22,15 @@ struct AttnArgs {
     const int64_t *slot_off;
     const int32_t *cur_len;  // rows to attend minus len_add
     void *out;
-    float *part_acc;   // [n][max_chunks][H][D]
-    float2 *part_ml;   // [n][max_chunks][H]  (running max in log2 units, sum)
+    // Partials: [slot][H][D] weighted sums and [slot][H] (running max in log2 units, sum).  Slot of a chunk: its
+    // position in the work list (one per chunk); vector-ALU kernel for shared heads: b * max_chunks + chunk.
+    float *part_acc;
+    float2 *part_ml;
     int64_t n_tokens;  // arena capacity N
     int32_t n, H, chunk, max_chunks, out_dtype, max_len;  // H: heads of a K/V row
     int32_t Hq;            // query heads (= H unless grouped-query / multi-query attention)
     int32_t ncls;          // length classes of the work order (1..8)
+    int32_t few_chunks;    // > 0: few contexts; cut them into about this many chunks (chunk: the longest allowed)
     int32_t len_add;    // 0: cur_len is the context length; 1 (fused step): cur_len is the append position
     float scale_log2e;  // scale * log2(e): scores are kept in log2 units so that exp is v_exp_f32
     // fused step only
@@ -211,6 +214,18 @@ __device__ __forceinline__ int wave_max_nonneg(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Rows per chunk of a batch of few contexts (total and longest: their rows).  Two bounds.  (1) `few_chunks` chunks in
+// all, so that every compute unit has an item and none has two (the host says how many, see few_chunks_for).
+// (2) A context's chunks are merged by one wave, a few per memory round trip, while a chunk's rows stream side by
+// side: a chunk of c rows costs about c / 10 of what merging one more chunk costs, so no finer than sqrt(10 * longest).
+// One context, 16 heads x 256 fp16, four layers, best chunk of a sweep: 410 rows 64 (36.6 us; whole 72.1), 1417 rows
+// 96 to 128 (51; 128), 8050 rows 256 to 384 (114; 181).
+__device__ __forceinline__ int few_chunk_rows(const AttnArgs &a, int total, int longest) {
+    const int even = total / a.few_chunks + 1;
+    const int least = (int)__builtin_amdgcn_sqrtf(10.f * (float)longest);
+    return min(a.chunk, (max(max(even, least), 32) + 15) & ~15);
+}
+
 // LDS picture of the batch built by every workgroup at kernel start (dynamic shared memory):
 //   off[n] (int64), len[n] (int32, 0 for refused entries), pre[ncls][n + 1] (int32)
 struct BatchView {
@@ -218,6 +233,7 @@ struct BatchView {
     const int *len;
     const int *pre;
     int n, ncls, total;
+    int chunk;  // rows per chunk
 };
 
 __device__ __forceinline__ size_t batch_view_bytes(int n, int ncls) {
@@ -226,9 +242,10 @@ __device__ __forceinline__ size_t batch_view_bytes(int n, int ncls) {
 
 // The one-wave build of the view: lane l owns entries l*E .. l*E+E-1 (n <= 64*E).
 template <int E>
-__device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre) {
+__device__ __forceinline__ int one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre) {
     const int lane = threadIdx.x & 63;
-    const int ncls = a.ncls, chunk = a.chunk, n = a.n;
+    const int ncls = a.ncls, n = a.n;
+    int chunk = a.chunk;
     int64_t off[E];
     int len[E], cls[E], cnt[E];
     int mx = 0;
@@ -243,6 +260,12 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         mx = max(mx, len[e]);
     }
     mx = wave_max_nonneg(mx);
+    if (a.few_chunks > 0) {
+        int rows = 0;
+#pragma unroll
+        for (int e = 0; e < E; e++) rows += len[e];
+        chunk = few_chunk_rows(a, __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63), mx);
+    }
 #pragma unroll
     for (int e = 0; e < E; e++) {
         cls[e] = class_of(len[e], mx, ncls);
@@ -263,6 +286,7 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         }
         if (lane == 63) pre[c * (n + 1) + n] = incl;
     }
+    return chunk;
 }
 
 // The view with one length class, built by the whole workgroup: of every E * threads entries, thread t owns E
@@ -317,6 +341,7 @@ __device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dy
     v.pre = pre;
     v.n = a.n;
     v.ncls = 1;
+    v.chunk = CHUNK;
     v.total = a.n <= (int)blockDim.x ? block_view<1>(a, CHUNK, off_s, len_s, pre, wave_sums)
                                      : block_view<4>(a, CHUNK, off_s, len_s, pre, wave_sums);
     return v;
@@ -339,13 +364,15 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         // E is a compile-time constant per batch size class: the per-entry work (two integer divisions) is
         // not spent on entries a small batch does not have.
         if (wave == 0) {
-            if (n <= 64) one_wave_view<1>(a, off_s, len_s, pre);
-            else if (n <= 128) one_wave_view<2>(a, off_s, len_s, pre);
-            else if (n <= 256) one_wave_view<4>(a, off_s, len_s, pre);
-            else one_wave_view<8>(a, off_s, len_s, pre);
+            const int rows = n <= 64    ? one_wave_view<1>(a, off_s, len_s, pre)
+                             : n <= 128 ? one_wave_view<2>(a, off_s, len_s, pre)
+                             : n <= 256 ? one_wave_view<4>(a, off_s, len_s, pre)
+                                        : one_wave_view<8>(a, off_s, len_s, pre);
+            if (lane == 0) wave_sums[0] = rows;
         }
         __syncthreads();
         BatchView v;
+        v.chunk = __builtin_amdgcn_readfirstlane(wave_sums[0]);
         v.off = off_s;
         v.len = len_s;
         v.pre = pre;
@@ -364,6 +391,7 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         v.pre = pre;
         v.n = n;
         v.ncls = 1;
+        v.chunk = chunk;
         v.total = block_view<4>(a, chunk, off_s, len_s, pre, wave_sums);
         return v;
     }
@@ -433,6 +461,7 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
     v.pre = pre;
     v.n = n;
     v.ncls = ncls;
+    v.chunk = chunk;
     v.total = 0;
     for (int c = 0; c < ncls; c++) v.total += pre[c * (n + 1) + n];
     return v;
@@ -541,12 +570,12 @@ __device__ __forceinline__ bool chunk_arrived(const AttnArgs &a, unsigned int *c
     return true;
 }
 
-// Merge the chunk partials of (sequence b, head h) for this lane's 8-element slice and store the
-// final output row slice; H is the head count of the partial and output arrays.  nchunks >= 2.  Four chunks are loaded
+// Merge the chunk partials of (sequence b, head h), in slots slot0, slot0 + 1, ..., for this lane's 8-element slice and
+// store the final output row slice; H is the head count of the partial and output arrays.  nchunks >= 2.  Four chunks are loaded
 // per round, in one memory round trip.
 template <int D, bool COHERENT>
-__device__ __forceinline__ void merge_chunks(const AttnArgs &a, int H, int b, int h, int dl, int nchunks) {
-    const int64_t p0 = ((int64_t)b * a.max_chunks) * H + h;
+__device__ __forceinline__ void merge_chunks(const AttnArgs &a, int64_t slot0, int H, int b, int h, int dl, int nchunks) {
+    const int64_t p0 = slot0 * H + h;
     const float *ml = (const float *)a.part_ml;
     float mm = -INFINITY, l = 0.f;
     float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -597,6 +626,7 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs &a, int H, int b, in
 // What a workgroup item is: chunk c of sequence b for head block hgb.
 struct Item {
     int b, c, nchunks, len, hgb;
+    int slot0;  // work-list position (partial slot) of the context's first chunk
     int clen;  // rows per chunk of this context: the context is cut into nchunks near-equal pieces
     int64_t off;
 };
@@ -642,6 +672,7 @@ __device__ __forceinline__ Item decode_item(const AttnArgs &a, const BatchView &
     const int lane = threadIdx.x & 63;
     int w = (int)(item / n_hgb);
     it.hgb = (int)(item - (int64_t)w * n_hgb);
+    it.slot0 = w;
     const int tot = lane < v.ncls ? v.pre[lane * (v.n + 1) + v.n] : 0;
     int cls = v.ncls - 1;
     for (int c = 0; c < v.ncls - 1; c++) {  // which class the item falls into
@@ -657,6 +688,7 @@ __device__ __forceinline__ Item decode_item(const AttnArgs &a, const BatchView &
     lo = min(lo, v.n - 1);  // a consistent view never needs this
     it.b = lo;
     it.c = w - pre[lo];
+    it.slot0 -= it.c;
     it.nchunks = pre[lo + 1] - pre[lo];
     it.len = v.len[lo];
     it.off = v.off[lo];
@@ -664,8 +696,9 @@ __device__ __forceinline__ Item decode_item(const AttnArgs &a, const BatchView &
         it.c = 0;
         it.nchunks = 1;
         it.len = 0;
+        it.slot0 = 0;
     }
-    it.clen = balanced_chunk_len(it.len, it.nchunks, a.chunk);
+    it.clen = balanced_chunk_len(it.len, it.nchunks, v.chunk);
     return it;
 }
 
@@ -682,6 +715,7 @@ __device__ __forceinline__ Item uniform_item(const Item &i) {
     o.b = __builtin_amdgcn_readfirstlane(i.b);
     o.c = __builtin_amdgcn_readfirstlane(i.c);
     o.nchunks = __builtin_amdgcn_readfirstlane(i.nchunks);
+    o.slot0 = __builtin_amdgcn_readfirstlane(i.slot0);
     o.len = __builtin_amdgcn_readfirstlane(i.len);
     o.hgb = __builtin_amdgcn_readfirstlane(i.hgb);
     o.clen = __builtin_amdgcn_readfirstlane(i.clen);

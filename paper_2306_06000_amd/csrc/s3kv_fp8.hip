@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(TS * 64) attn_fp8_kernel(const AttnArgs a) {
                 store_out8(a.out, a.out_dtype, e0, o0);
                 store_out8(a.out, a.out_dtype, e0 + 8, o1);
             } else {  // a chunk of a longer context: the partial goes out with write-through stores
-                const int64_t pi = ((int64_t)it.b * a.max_chunks + it.c) * a.H + h;
+                const int64_t pi = (int64_t)(it.slot0 + it.c) * a.H + h;
                 float *pa = a.part_acc + pi * D + dl * 16;
                 if (dl == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){mm, ll});
 #pragma unroll
@@ -259,8 +259,8 @@ __global__ void __launch_bounds__(TS * 64) attn_fp8_kernel(const AttnArgs a) {
             unsigned int *cnt = a.arrivals + (int64_t)it.b * n_hg + it.hgb;
             if (chunk_arrived(a, cnt, it.nchunks)) {
                 if (h_ok && tsub == 0) {
-                    merge_chunks<D, true>(a, a.H, it.b, h, 2 * dl, it.nchunks);
-                    merge_chunks<D, true>(a, a.H, it.b, h, 2 * dl + 1, it.nchunks);
+                    merge_chunks<D, true>(a, it.slot0, a.H, it.b, h, 2 * dl, it.nchunks);
+                    merge_chunks<D, true>(a, it.slot0, a.H, it.b, h, 2 * dl + 1, it.nchunks);
                 }
             }
         }

@@ -263,27 +263,27 @@ __global__ void __launch_bounds__(256) append_kernel(char *kplane, char *vplane,
 // attention: kernel choice and launchers
 // ------------------------------------------------------------------------------------------
 // Multi-head kernels, one translation unit per head dimension (s3kv_attn_inst.hip).
-attn_fn s3i_pick_mha_d64(int dt, int variant, bool fused);
-attn_fn s3i_pick_mha_d96(int dt, int variant, bool fused);
-attn_fn s3i_pick_mha_d128(int dt, int variant, bool fused);
-attn_fn s3i_pick_mha_d256(int dt, int variant, bool fused);
+attn_fn s3i_pick_mha_d64(int dt, int variant);
+attn_fn s3i_pick_mha_d96(int dt, int variant);
+attn_fn s3i_pick_mha_d128(int dt, int variant);
+attn_fn s3i_pick_mha_d256(int dt, int variant);
 attn_fn s3i_pick_merge_d64();
 attn_fn s3i_pick_merge_d96();
 attn_fn s3i_pick_merge_d128();
 attn_fn s3i_pick_merge_d256();
 int s3i_default_variant();
 int s3i_default_variant_large();
-int s3i_variant_threads(int variant, bool fused);
+int s3i_variant_threads(int variant);
 int s3i_variant_ring_bytes(int variant);
 int s3i_variant_dynamic(int variant);
 int s3i_variant_stream(int variant);
 
-static attn_fn pick_kernel(int dt, int d, int variant, bool fused) {
+static attn_fn pick_kernel(int dt, int d, int variant) {
     switch (d) {
-        case 64: return s3i_pick_mha_d64(dt, variant, fused);
-        case 96: return s3i_pick_mha_d96(dt, variant, fused);
-        case 128: return s3i_pick_mha_d128(dt, variant, fused);
-        case 256: return s3i_pick_mha_d256(dt, variant, fused);
+        case 64: return s3i_pick_mha_d64(dt, variant);
+        case 96: return s3i_pick_mha_d96(dt, variant);
+        case 128: return s3i_pick_mha_d128(dt, variant);
+        case 256: return s3i_pick_mha_d256(dt, variant);
         default: return nullptr;
     }
 }
@@ -614,13 +614,33 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
     return shares > 1 ? (size_t)(shares + n) : 0;  // one share: no piece ever leaves its wave or team
 }
 
+// Kernels whose chunks meet inside the launch (multi-head, 8-bit rows): chunks are of at most `chunk` rows (1024 unless
+// the caller says otherwise), and *few, if not 0, is how many chunks in all the kernel cuts a batch of few contexts into
+// (the lengths are on the device, so the rows per chunk are chosen there: few_chunk_rows).  Returns the partial slots.
+// n_hg: head groups, i.e. work items per chunk.  3/4 of an item per compute unit while the contexts themselves are
+// fewer than that (pieces do not divide evenly: with a full item per unit some unit would get two); beyond, whole
+// contexts are items enough.  Chunk fixed at 1024 -> this rule, 16 heads x 256 fp16, four layers: one context of 410
+// rows 74 -> 36 us, of 8050 rows 181 -> 112; 4 contexts of 500..1500 rows 129 -> 68, 8: 143 -> 102, 16: 207 -> 189;
+// 32 contexts of 32..1000 rows: 212, and 217 if the line were drawn above them.
+// As with gqa_max_shares, what the fixed buffer takes by its documented rule is held to its size.
+static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few) {
+    const int chunk = a->chunk > 0 ? a->chunk : 1024;
+    const int64_t whole = (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
+    const int64_t cus = a->num_cus > 0 ? a->num_cus : 256;
+    int64_t want = 0;
+    if (a->chunk <= 0 && n <= cus * 3 / 4 / n_hg) want = cus * 3 / 4 / n_hg;
+    const int64_t fixed = (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes(n_hg)) / slot_bytes);
+    if (whole <= fixed && want > fixed - n) want = fixed - n;
+    *few = want > 0 ? (int32_t)want : 0;
+    return (size_t)(want > 0 && want + n > whole ? want + n : whole);
+}
+
 // Scratch an attention call over n sequences needs at most: the launchers' layout with the smallest chunk
 // they may choose for any batch size (or the chunk the caller fixed).
 static size_t scratch_need(const s3_arena *a, int n) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads;
     const int kind = s3i_kernel_kind(a);
     int chunk = a->chunk;
-    size_t cnt_bytes = 0;
     if (kind == 2 || kind == 4) {
         size_t most = 0;  // a smaller batch may take more slots: the fixed buffer's size bounds some and not others
         for (int k = n; k >= 1; k = k > 64 ? k - 64 : k - 1) {
@@ -629,16 +649,21 @@ static size_t scratch_need(const s3_arena *a, int n) {
         }
         return counters_bytes((int)gqa_columns(a)) + (most + 64) * gqa_slot_bytes(a);
     }
+    const size_t slot_bytes = (size_t)Hq * ((size_t)D * sizeof(float) + sizeof(float2));
     if (kind == 0 || kind == 3) {  // kernels that merge chunks themselves carry counters
-        if (chunk <= 0) chunk = 1024;
-        const int gh = kind == 3 ? 1024 / D : heads_per_load(D);
-        cnt_bytes = counters_bytes((Hq + gh - 1) / gh);
-    } else if (chunk <= 0) {
-        chunk = 256;
+        const int gh = kind == 3 ? 1024 / D : heads_per_load(D), n_hg = (Hq + gh - 1) / gh;
+        size_t most = 0;
+        int32_t few;
+        for (int k = 1; k < n && k <= 1024; k++) {  // (more contexts than that are never "few")
+            const size_t slots = chunk_slots(a, k, n_hg, slot_bytes, &few);
+            if (slots > most) most = slots;
+        }
+        const size_t slots = chunk_slots(a, n, n_hg, slot_bytes, &few);
+        return counters_bytes(n_hg) + (slots > most ? slots : most) * slot_bytes;
     }
+    if (chunk <= 0) chunk = 256;
     const size_t max_chunks = (size_t)(a->cfg.max_len + chunk - 1) / chunk;
-    const size_t n_part = (size_t)n * max_chunks * Hq;
-    return cnt_bytes + n_part * ((size_t)D * sizeof(float) + sizeof(float2));
+    return (size_t)n * max_chunks * slot_bytes;
 }
 
 extern "C" int s3_kv_reserve_scratch(s3_arena *a, int32_t max_batch) {
@@ -778,6 +803,13 @@ static int launch_gqa(s3_arena *a, const AttnCall &c) {
     return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, Hq, !c.static_scratch);
 }
 
+// Scratch of a kernel whose chunks meet inside the launch.
+static int place_chunk_scratch(s3_arena *a, AttnArgs &args, int n_hg, const AttnCall &c) {
+    const size_t slot_bytes = (size_t)args.Hq * ((size_t)a->cfg.head_dim * sizeof(float) + sizeof(float2));
+    const size_t slots = chunk_slots(a, c.n, n_hg, slot_bytes, &args.few_chunks);
+    return place_scratch(a, args, counters_bytes(n_hg), slots, c);
+}
+
 // 8-bit cache rows: one kernel, which in a decode step also quantises and appends the new row, merges
 // chunks and publishes the new lengths.
 static int launch_fp8(s3_arena *a, const AttnCall &c) {
@@ -787,7 +819,7 @@ static int launch_fp8(s3_arena *a, const AttnCall &c) {
     if (!fn) return S3_ERR_INVALID;
     AttnArgs args = common_args(a, c, H, H, a->chunk > 0 ? a->chunk : 1024);
     const int n_hg = (H + 1024 / D - 1) / (1024 / D);  // head groups: 1024/D heads per 128-bit wave load of bytes
-    int rc = place_scratch(a, args, counters_bytes(n_hg), (size_t)args.n * args.max_chunks, c);
+    int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
     const size_t dyn_lds = batch_view_lds(c.n, args.ncls);
     int blocks = 0;
@@ -796,8 +828,8 @@ static int launch_fp8(s3_arena *a, const AttnCall &c) {
     return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, 0, !c.static_scratch);  // the kernel merges by itself
 }
 
-// Shared by s3_decode_attention (partial kernel + merge kernel) and s3_decode_step (with_append: one
-// kernel that also appends, merges and publishes the new lengths).
+// Shared by s3_decode_attention and s3_decode_step (with_append: the kernel also appends and publishes the new
+// lengths).
 static int launch_attention(s3_arena *a, const AttnCall &c) {
     if (a->cfg.n_kv_heads < a->cfg.n_heads) return launch_gqa(a, c);
     if (a->cfg.kv_dtype == S3_E4M3) return launch_fp8(a, c);
@@ -806,33 +838,31 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
     // merge), eight waves share an item's rows evenly, each with two batches of two rows in flight
     // alternately (1 % ahead of one batch of four rows on the ragged batch of 64, level on the others).
     const int variant = a->variant >= 0 ? a->variant : c.n > 128 ? s3i_default_variant_large() : s3i_default_variant();
-    const bool fused = c.with_append;
-    attn_fn fn = pick_kernel(a->cfg.kv_dtype, D, variant, fused);
+    attn_fn fn = pick_kernel(a->cfg.kv_dtype, D, variant);
     if (!fn) return S3_ERR_INVALID;
     const int GH = heads_per_load(D);
     const int n_hg = (H + GH - 1) / GH;
     AttnArgs args = common_args(a, c, H, H, a->chunk > 0 ? a->chunk : 1024);
-    args.len_out = c.len_out;
     // a dynamic work list is a longest-processing-time schedule only if the long items come first: four length
     // classes whatever the batch size (with a fixed stride, large batches did better without the classes' prologue)
-    if (a->ncls <= 0 && fused && s3i_variant_dynamic(variant)) {
+    if (a->ncls <= 0 && s3i_variant_dynamic(variant)) {
         args.ncls = 4;
         while (args.ncls > 1 && batch_view_lds(c.n, args.ncls) > (size_t)96 * 1024) args.ncls--;
     }
-    int rc = place_scratch(a, args, counters_bytes(n_hg), (size_t)args.n * args.max_chunks, c);
+    int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
-    const int threads = s3i_variant_threads(variant, fused);  // the fused kernel adds an epilogue wave
+    const int threads = s3i_variant_threads(variant);
     const size_t view = batch_view_lds(c.n, args.ncls);
-    const size_t dyn_lds = fused && s3i_variant_ring_bytes(variant) ? ((view + 15) & ~(size_t)15) + s3i_variant_ring_bytes(variant) : view;
+    const size_t dyn_lds = s3i_variant_ring_bytes(variant) ? ((view + 15) & ~(size_t)15) + s3i_variant_ring_bytes(variant) : view;
     int blocks = 0;
     // fixed stride: large batches balance better over two rounds of resident workgroups; a dynamic work list
     // needs exactly the resident ones
-    const int rounds = (fused && s3i_variant_dynamic(variant)) ? 1 : c.n > 128 ? 2 : 1;
+    const int rounds = s3i_variant_dynamic(variant) ? 1 : c.n > 128 ? 2 : 1;
     // the shapes that carry the row stream across items keep a compute unit's memory pipeline full from one
     // workgroup; a second resident one (their register count admits it) measured 2 % slower
-    rc = stride_grid(a, (const void *)fn, threads, dyn_lds, rounds, &blocks, fused && s3i_variant_stream(variant) ? 1 : 0);
+    rc = stride_grid(a, (const void *)fn, threads, dyn_lds, rounds, &blocks, s3i_variant_stream(variant) ? 1 : 0);
     if (rc != S3_OK) return rc;
-    return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, fused ? 0 : H, !c.static_scratch);
+    return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, 0, !c.static_scratch);  // the kernel merges by itself
 }
 
 extern "C" int s3_decode_attention(s3_arena *a, int32_t layer, int32_t n, const void *q, const int64_t *slot_off,

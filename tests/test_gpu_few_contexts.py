@@ -1,0 +1,45 @@
+"""Batches of few contexts are cut into chunks by a rule on their total and longest rows that runs on the device: both
+sides of its bounds (the smallest chunk, the longest, the number of contexts at which it ends) against the fp32 oracle,
+and the decode step against append + attention, bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2306_06000_amd import binding as s3
+from tests.harness import assert_close
+from tests.test_gpu_numeric_edges import EdgeRig
+
+pytestmark = pytest.mark.gpu
+
+FAMS = [
+    ("16 x 256", 16, 16, 256, s3.S3_F16, s3.S3_F16, 0),
+    ("12 x 128", 12, 12, 128, s3.S3_BF16, s3.S3_BF16, 0),
+    ("5 x 96", 5, 5, 96, s3.S3_BF16, s3.S3_BF16, 0),
+    ("3 x 64", 3, 3, 64, s3.S3_F16, s3.S3_F16, 0),
+    ("16 x 256 e4m3", 16, 16, 256, s3.S3_E4M3, s3.S3_F16, 3),
+    ("3 x 128 e4m3", 3, 3, 128, s3.S3_E4M3, s3.S3_BF16, 3),
+]
+
+
+@pytest.mark.parametrize("fam", FAMS, ids=[f[0] for f in FAMS])
+def test_few_contexts_are_cut_by_their_rows(fam):
+    name, H, Hkv, D, kvt, act, kind = fam
+    rng = np.random.default_rng(D + H)
+    per_load = 1024 // D if kind == 3 else 4 if D == 96 else 512 // D
+    last = 192 // -(-H // per_load)  # the largest batch the rule takes
+    for what, lens in (("one row", [1]), ("one piece", [31]), ("two pieces", [33]), ("one long", [2047]),
+                       ("mixed, empty ones", [0, 700, 1, 16, 17, 1500, 0]), ("the rule's last batch", [40] * (last - 1) + [1030]),
+                       ("the first beyond it", [40] * last + [1030])):
+        n = len(lens)
+        rig = EdgeRig(fam, lens, M=2048)
+        rig.put([rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens],
+                [rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens])
+        q = rng.standard_normal((n, H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / {what}")
+        assert np.array_equal(rig.attend(q)[1], att)
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
+        assert_close(step, rig.want(qb, longer), f"{name} / {what} / step")
+        if kind == 0:  # (8-bit rows: the step takes the new row in its last wave, in another order of sums)
+            assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
+        rig.close()
