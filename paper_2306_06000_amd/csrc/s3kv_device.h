@@ -45,6 +45,7 @@ struct AttnArgs {
     int32_t group, nqb, columns;          // query heads per cached head, blocks of 16 of them, columns = H * nqb
     int32_t wave_shares, team_shares;     // shares per column if every wave takes one, if teams of four waves do
     int32_t max_shares;  // partial slots allow this many publishing units per column
+    float merge_cost;    // time of merging one more piece of a context, in tiles streamed by one wave
     int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
     int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
 };
@@ -325,6 +326,21 @@ __device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t 
         if (tid == 0) pre[a.n] = total;
         __syncthreads();
     }
+    return total;
+}
+
+// Exclusive prefix sums of one value per entry (n <= threads, thread t brings entry t's) into pre[0..n]; returns the
+// total.  Whoever reads pre[] before has met a barrier since.
+__device__ __forceinline__ int block_prefix(int n, int mine, int *pre, int *wave_sums) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+    const int incl = wave_inclusive_scan(mine);
+    if (lane == 63) wave_sums[wave] = incl;
+    __syncthreads();
+    const int upto = wave_inclusive_scan(lane < nwaves ? wave_sums[lane] : 0);
+    const int total = __builtin_amdgcn_readlane(upto, nwaves - 1);
+    if (tid < n) pre[tid] = incl - mine + (wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0);
+    if (tid == 0) pre[n] = total;
+    __syncthreads();
     return total;
 }
 

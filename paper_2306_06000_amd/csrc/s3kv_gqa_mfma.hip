@@ -144,6 +144,26 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
     t[3] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);
 }
 
+// How a launch of few rows divides them (a batch of at most 256 contexts): every context by itself, into near-equal
+// chunks of at most `per` tiles, one wave a chunk, all at once.  Nothing is combined that the lengths do not force:
+// a context of one chunk is finished by its wave.  Lower bounds on `per`: all chunks of all columns fit the waves of
+// the grid; and the wave that merges a context reads its pieces a few per memory round trip while their tiles stream
+// side by side, so with `merge_cost` tiles' worth of time per piece (see launch_gqa_mfma) no finer than
+// sqrt(merge_cost * tiles of a context).  0: rows enough for even shares (below), that is, chunks would pass 64 KiB of K
+// rows, or contexts would average more than 12 pieces, which a team's four waves merge faster.
+// Per layer, chunks against even shares: 32q/8kv x 128, 19 contexts of about 80 rows 9.7 us and 16.2, 66 of 400..656
+// rows 35.3 and 37.7, 3 of 512..3000 rows (16 pieces each) 21.5 and 19.0; 12q/2kv x 128, 5 of 20..31 rows 7.3 and 11.7,
+// 17 of 1200..1455 rows 18.6 and 19.2; 64q/8kv x 128 e4m3, 22 of 2000..4793 rows 41.5 and 48.8.
+template <int TR, int ROW_BYTES>
+__device__ __forceinline__ int chunk_plan(const AttnArgs &a, int tiles) {
+    const int room = min(a.wave_shares - a.n, a.max_shares);  // chunks beyond one per context, per column
+    if (a.n > 256 || a.share_rows > 0 || a.max_shares <= 1 || room <= 0) return 0;
+    const int even = (tiles + room - 1) / room;
+    const float average = (float)tiles / (float)a.n;
+    const int per = max(even, (int)__builtin_amdgcn_sqrtf(a.merge_cost * 1.5f * average) + 1);
+    return per <= 65536 / ROW_BYTES / TR && average <= 12.f * (float)per ? per : 0;
+}
+
 // How a launch divides its rows: `shares` equal runs of tiles per column, share k = tiles
 // [k * base + min(k, rem), ...) with one tile more for the first `rem`.  team 1: every wave works for itself and
 // a piece of a context cut by a share's border goes to memory.  team 4: the four waves of a workgroup take four
@@ -225,57 +245,9 @@ __device__ __forceinline__ unsigned pieces_arrived(const AttnArgs &a, const Pend
     return who;
 }
 
-// Running merge of pieces for EB x 4 consecutive elements: pieces c0, c0 + stride, ... below `count`, NP of them per
-// memory round trip.  ml / acc: the (max, sum) pair and the elements of piece 0; sml / sacc: floats from one piece to
-// the next.
-template <int EB, int NP>
-struct PieceMerge {
-    float m[EB], l[EB];
-    f32x4 o[EB];
-    __device__ __forceinline__ void run(const float *const (&ml)[EB], const float *const (&acc)[EB], int64_t sml, int64_t sacc, int c0,
-                                        int stride, int count) {
-#pragma unroll
-        for (int i = 0; i < EB; i++) {
-            m[i] = -INFINITY;
-            l[i] = 0.f;
-            o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll 1
-        for (int c = c0; c < count; c += NP * stride) {
-            f32x2 mv[EB][NP];
-            f32x4 av[EB][NP];
-#pragma unroll
-            for (int u = 0; u < NP; u++) {
-                const int cc = c + u * stride < count ? c + u * stride : c;  // (past the end: piece c again, weight 0)
-#pragma unroll
-                for (int i = 0; i < EB; i++) {
-                    mv[i][u] = get_coherent2(ml[i] + cc * sml);
-                    av[i][u] = get_coherent4(acc[i] + cc * sacc);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < EB; i++) {
-                float mn = m[i];
-#pragma unroll
-                for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[i][u][0]);
-                const float alpha = m[i] == -INFINITY ? 0.f : fast_exp2(m[i] - mn);
-                l[i] *= alpha;
-                o[i] *= alpha;
-#pragma unroll
-                for (int u = 0; u < NP; u++) {
-                    const float w = c + u * stride < count ? fast_exp2(mv[i][u][0] - mn) : 0.f;
-                    l[i] += w * mv[i][u][1];
-                    o[i] += w * av[i][u];
-                }
-                m[i] = mn;
-            }
-        }
-    }
-};
-
 // Merge the pieces of query heads hq0 .. hq0+nh-1 of a context and store the final rows; by a wave (nthr 64) or by
-// the four waves of a workgroup in step (nthr 256).  A workgroup with more threads than quads of elements deals the
-// pieces of a context of many over the spare threads, which meet in LDS (6 floats per thread).
+// the four waves of a workgroup in step (nthr 256).  A workgroup with at least a thread per quad of elements
+// takes one quad a thread and deals the pieces over what threads are spare, which meet in LDS (6 floats per thread).
 // Kept small: all of this runs once per launch and wave, i.e. out of a cold instruction cache (unrolled for every
 // shape, with the code around it, the kernel was 136 KB and a merge of four pieces took 3 us).
 template <int D>
@@ -286,17 +258,41 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
     char *out = (char *)a.out;
     const int64_t out0 = ((int64_t)p.b * a.Hq + hq0) * D;
     const int quads = nh * (D / 4);
-    if (nthr == 256 && quads <= 128 && p.count > 4) {
+    if (nthr == 256 && quads <= 256 && p.count > 4) {
         const int splits = min(8, 256 / quads);
         const int split = tid / quads, e = tid - split * quads;
-        const float *const ml[1] = {pml + 2 * (e / (D / 4))};
-        const float *const acc[1] = {pacc + e * 4};
-        PieceMerge<1, 8> pm;
+        const float *ml = pml + 2 * (e / (D / 4)), *acc = pacc + e * 4;
         __syncthreads();  // an earlier merge has read the LDS
         if (split < splits) {
-            pm.run(ml, acc, sml, sacc, split, splits, p.count);
-            *(f32x4 *)(lds + tid * 4) = pm.o[0];
-            *(f32x2 *)(lds + 1024 + tid * 2) = (f32x2){pm.m[0], pm.l[0]};
+            constexpr int NP = 8;  // pieces per memory round trip
+            float m = -INFINITY, l = 0.f;
+            f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int c = split; c < p.count; c += NP * splits) {
+                f32x2 mv[NP];
+                f32x4 av[NP];
+#pragma unroll
+                for (int u = 0; u < NP; u++) {
+                    const int cc = c + u * splits < p.count ? c + u * splits : c;  // (past the end: piece c again, weight 0)
+                    mv[u] = get_coherent2(ml + cc * sml);
+                    av[u] = get_coherent4(acc + cc * sacc);
+                }
+                float mn = m;
+#pragma unroll
+                for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[u][0]);
+                const float alpha = m == -INFINITY ? 0.f : fast_exp2(m - mn);
+                l *= alpha;
+                o *= alpha;
+#pragma unroll
+                for (int u = 0; u < NP; u++) {
+                    const float w = c + u * splits < p.count ? fast_exp2(mv[u][0] - mn) : 0.f;
+                    l += w * mv[u][1];
+                    o += w * av[u];
+                }
+                m = mn;
+            }
+            *(f32x4 *)(lds + tid * 4) = o;
+            *(f32x2 *)(lds + 1024 + tid * 2) = (f32x2){m, l};
         }
         __syncthreads();
         if (tid < quads) {
@@ -314,21 +310,57 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
         }
         return;
     }
-    constexpr int EB = D / 64, NP = EB == 4 ? 3 : 6;  // 12 or 6 quads per thread in flight
+    // Whole waves in step, every lane EB quads: the piece is uniform, so its address is scalar and a lane adds one 32-bit
+    // offset per quad (at most 64 heads' rows of a piece: 64 KiB).
+    constexpr int EB = D == 256 ? 4 : 2, NP = D == 256 ? 3 : 6;
 #pragma unroll 1
     for (int e0 = tid; e0 < quads; e0 += EB * nthr) {
-        const float *ml[EB], *acc[EB];
+        unsigned eml[EB], eacc[EB];
+        float m[EB], l[EB];
+        f32x4 o[EB];
 #pragma unroll
         for (int i = 0; i < EB; i++) {
             const int e = e0 + i * nthr < quads ? e0 + i * nthr : e0;
-            ml[i] = pml + 2 * (e / (D / 4));
-            acc[i] = pacc + e * 4;
+            eml[i] = 2 * (e / (D / 4));
+            eacc[i] = 4 * e;
+            m[i] = -INFINITY;
+            l[i] = 0.f;
+            o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
         }
-        PieceMerge<EB, NP> pm;
-        pm.run(ml, acc, sml, sacc, 0, 1, p.count);
+#pragma unroll 1
+        for (int c = 0; c < p.count; c += NP) {
+            f32x2 mv[EB][NP];
+            f32x4 av[EB][NP];
+#pragma unroll
+            for (int u = 0; u < NP; u++) {
+                const int cc = c + u < p.count ? c + u : c;  // (past the end: piece c again, weight 0)
+                const float *um = pml + cc * sml, *ua = pacc + cc * sacc;
+#pragma unroll
+                for (int i = 0; i < EB; i++) {
+                    mv[i][u] = get_coherent2(um + eml[i]);
+                    av[i][u] = get_coherent4(ua + eacc[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < EB; i++) {
+                float mn = m[i];
+#pragma unroll
+                for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[i][u][0]);
+                const float alpha = m[i] == -INFINITY ? 0.f : fast_exp2(m[i] - mn);
+                l[i] *= alpha;
+                o[i] *= alpha;
+#pragma unroll
+                for (int u = 0; u < NP; u++) {
+                    const float w = c + u < p.count ? fast_exp2(mv[i][u][0] - mn) : 0.f;
+                    l[i] += w * mv[i][u][1];
+                    o[i] += w * av[i][u];
+                }
+                m[i] = mn;
+            }
+        }
 #pragma unroll
         for (int i = 0; i < EB; i++)
-            if (e0 + i * nthr < quads) store_out4(out, a.out_dtype, out0 + (e0 + i * nthr) * 4, pm.o[i] * (1.f / pm.l[i]));
+            if (e0 + i * nthr < quads) store_out4(out, a.out_dtype, out0 + (e0 + i * nthr) * 4, o[i] * (1.f / l[i]));
     }
 }
 
@@ -399,7 +431,15 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     }
     const int tiles = __builtin_amdgcn_readfirstlane(bv.total);
     if (tiles == 0) return;  // the whole grid alike
-    const SharePlan sp = share_plan<TR>(a, tiles);
+    const int per = chunk_plan<TR, D * EB>(a, tiles);
+    int chunks = 0;  // chunks of `per` tiles in a column; pre[] then counts them
+    SharePlan sp = {tiles, 1, tiles, 0, 1};
+    if (per == 0) {
+        sp = share_plan<TR>(a, tiles);
+    } else {
+        const int mine = (int)threadIdx.x < a.n ? (bv.len[threadIdx.x] + TR * per - 1) / (TR * per) : 0;
+        chunks = __builtin_amdgcn_readfirstlane(block_prefix(a.n, mine, (int *)bv.pre, wave_sums));
+    }
 
     char *vt = wave_lds[wave];
     char *kt = vt + TR * VSTRIDE;
@@ -416,23 +456,42 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     const bool stream_k = a.stream_k < 0 ? (int64_t)tiles * TR * rstride > ((int64_t)256 << 20) : a.stream_k != 0;
 
     // (shares * columns tiles of at least 2 KiB lie in the arena: below 2^31 on any device)
-    const unsigned units = (unsigned)(sp.team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
-    const unsigned step = sp.team == 4 ? gridDim.x : gridDim.x * 4;
+    const int team = per > 0 ? 1 : sp.team;
+    const unsigned units = (unsigned)(per > 0 ? chunks : team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
+    const unsigned step = team == 4 ? gridDim.x : gridDim.x * 4;
+    // (chunks: one wave on every compute unit before any unit gets a second one)
 #pragma unroll 1
-    for (unsigned unit = sp.team == 4 ? blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
+    for (unsigned unit = per > 0 ? wave * gridDim.x + blockIdx.x : team == 4 ? blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
         const int pub = __builtin_amdgcn_readfirstlane(unit / columns);  // publishing unit: this wave's share or its team
         const int col = __builtin_amdgcn_readfirstlane(unit - (unsigned)pub * columns);
-        const int share = sp.team == 4 ? pub * 4 + wave : pub;
         const int hk = nqb == 1 ? col : col / nqb, qb = col - hk * nqb;
         const int head = qb * 16 + n;  // query head of this lane's column, within the group
         const bool head_ok = head < group;
         const int hq = hk * group + (head_ok ? head : group - 1);
         const int hq0 = hk * group + qb * 16, nheads = min(16, group - qb * 16);
-        const int t_begin = share < sp.shares ? share_start(sp, share) : 0;
-        const int t_stop = share < sp.shares ? share_start(sp, share + 1) : 0;
+        // This wave's tiles, [t_begin, t_stop): of all contexts laid end to end, or (chunks) of context `seq`.
+        int t_begin = 0, t_stop = 0, seq = 0, chunk = 0, nchunks = 0;
+        if (per > 0) {
+            seq = min(find_sequence(bv.pre, a.n, pub), a.n - 1);
+            const int first = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
+            nchunks = __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) - first;
+            chunk = pub - first;
+            const int all = (__builtin_amdgcn_readfirstlane(bv.len[seq]) + TR - 1) / TR;
+            // near-equal pieces, none of them empty: the first all % nchunks have a tile more
+            const int base = all / max(nchunks, 1), rem = all - base * nchunks;
+            t_begin = chunk * base + min(chunk, rem);
+            t_stop = t_begin + base + (chunk < rem ? 1 : 0);
+        } else {
+            const int share = team == 4 ? pub * 4 + wave : pub;
+            if (share < sp.shares) {
+                t_begin = share_start(sp, share);
+                t_stop = share_start(sp, share + 1);
+                seq = min(find_sequence(bv.pre, a.n, t_begin), a.n - 1);
+            }
+        }
         // contexts this wave or team has left a piece of in memory: at most the first and the last one of its share
         Pending pend0 = {0, 0, 0}, pend1 = {0, 0, 0};
-        if (sp.team == 4 && lane == 0) piece_b[2 * wave] = piece_b[2 * wave + 1] = -1;
+        if (team == 4 && lane == 0) piece_b[2 * wave] = piece_b[2 * wave + 1] = -1;
 
         if (t_begin < t_stop) {
             // Two cursors run over the share's tiles: `ahead` issues the loads of a tile (of the next context, if there
@@ -444,18 +503,21 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
 #pragma unroll
             for (int i = 0; i < NL; i++) voff[i] = (unsigned)(i * RPL + lane / PPR) * rs32 + (lane % PPR) * 16;
             auto open = [&](int seq, int t) {  // the context of tile t, at or after `seq`
-                while (seq < a.n - 1 && __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) <= t) seq++;
                 Segment s;
+                s.t0 = 0;
+                if (per == 0) {
+                    while (seq < a.n - 1 && __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) <= t) seq++;
+                    s.t0 = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
+                }
                 s.seq = seq;
-                s.t0 = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
-                s.t1 = __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]);
-                s.t_end = min(t_stop, s.t1);
                 s.len = __builtin_amdgcn_readfirstlane(bv.len[seq]);
+                s.t1 = s.t0 + (s.len + TR - 1) / TR;
+                s.t_end = min(t_stop, s.t1);
                 s.off = uniform64(bv.off[seq]);
                 return s;
             };
             const int64_t head_byte = (int64_t)hk * D * EB;
-            Segment now = open(min(find_sequence(bv.pre, a.n, t_begin), a.n - 1), t_begin), ahead = now;
+            Segment now = open(seq, t_begin), ahead = now;
             int t = t_begin, t_ahead = t_begin;
             int rows_ahead = now.len - (t_begin - now.t0) * TR;  // rows of `ahead` from tile t_ahead on
             int64_t at = (now.off + (t_begin - now.t0) * TR) * rstride + head_byte;
@@ -650,7 +712,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 lsum += __shfl_xor(lsum, 16);
                 lsum += __shfl_xor(lsum, 32);
                 const bool whole = t_begin <= now.t0 && now.t_end == now.t1;
-                const bool to_lds = !whole && sp.team == 4;
+                const bool to_lds = !whole && team == 4;
                 const float f = whole ? 1.f / lsum : 1.f;
                 __builtin_amdgcn_wave_barrier();
                 if (head_ok) {
@@ -665,14 +727,14 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 }
                 __builtin_amdgcn_wave_barrier();
                 const int slot = 2 * wave + (now.t_end == t_stop ? 1 : 0);
-                const int64_t row0 = (int64_t)(whole ? now.seq : pub + now.seq) * a.Hq + hq0;
+                const int64_t row0 = (int64_t)(whole ? now.seq : per > 0 ? pub : pub + now.seq) * a.Hq + hq0;
                 if (to_lds) {
                     if (head_ok && g == 0) piece_ml[slot][n] = make_float2(m, lsum);
                     if (lane == 0) piece_b[slot] = now.seq;
                 } else if (!whole) {
                     if (head_ok && g == 0) put_partial2<true>((float *)a.part_ml + 2 * (row0 + n), (f32x2){m, lsum});
-                    int first, count;
-                    pieces_of(sp, now.t0, now.t1, first, count);
+                    int first = pub - chunk - seq, count = nchunks;  // (slot of the first piece: first + seq)
+                    if (per == 0) pieces_of(sp, now.t0, now.t1, first, count);
                     if (pend0.count == 0) pend0 = Pending{now.seq, first, count};
                     else pend1 = Pending{now.seq, first, count};
                 }
@@ -719,7 +781,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 half(k1, v1);
             } while (t < t_stop);
         }
-        if (sp.team == 4) {
+        if (team == 4) {
             __syncthreads();  // the pieces are in LDS
             // Pieces of one context are neighbours: a run.  First the weight of every piece and the sum of every run ...
             const int pb = piece_b[lane & 7];

@@ -767,6 +767,10 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     args.group = Hq / Hkv;
     args.nqb = (args.group + 15) / 16;
     args.columns = (int32_t)columns;
+    // What one more piece costs the wave that merges a context, in tiles streamed by one wave: a memory round trip of
+    // about two tiles brings two quads of elements a lane of six pieces (D 256: four quads of three).
+    const int eb = D == 256 ? 4 : 2, quads = (int)group16 * (D / 4), passes = (quads + 64 * eb - 1) / (64 * eb);
+    args.merge_cost = 2.f * passes / (eb == 4 ? 3 : 6);
     const int64_t waves = (int64_t)cus * per_cu * 4;
     args.wave_shares = (int32_t)(waves > columns ? waves / columns : 1);
     args.team_shares = (int32_t)(waves > 4 * columns ? waves / (4 * columns) : 1);
