@@ -222,9 +222,11 @@ __device__ __forceinline__ int wave_max_nonneg(int v) {
 // One context, 16 heads x 256 fp16, four layers, best chunk of a sweep: 410 rows 64 (36.6 us; whole 72.1), 1417 rows
 // 96 to 128 (51; 128), 8050 rows 256 to 384 (114; 181).
 __device__ __forceinline__ int few_chunk_rows(const AttnArgs &a, int total, int longest) {
+    if (longest <= 128) return a.chunk;  // a cut would save less than a merge costs (14 contexts of 30..68 rows: 7.8 us
+                                         // a layer whole, 8.4 in pieces of 32)
     const int even = total / a.few_chunks + 1;
     const int least = (int)__builtin_amdgcn_sqrtf(10.f * (float)longest);
-    return min(a.chunk, (max(max(even, least), 32) + 15) & ~15);
+    return min(a.chunk, (max(max(even, least), 64) + 15) & ~15);
 }
 
 // LDS picture of the batch built by every workgroup at kernel start (dynamic shared memory):
@@ -384,11 +386,11 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
                              : n <= 128 ? one_wave_view<2>(a, off_s, len_s, pre)
                              : n <= 256 ? one_wave_view<4>(a, off_s, len_s, pre)
                                         : one_wave_view<8>(a, off_s, len_s, pre);
-            if (lane == 0) wave_sums[0] = rows;
+            if (a.few_chunks > 0 && lane == 0) wave_sums[0] = rows;
         }
         __syncthreads();
         BatchView v;
-        v.chunk = __builtin_amdgcn_readfirstlane(wave_sums[0]);
+        v.chunk = a.few_chunks > 0 ? __builtin_amdgcn_readfirstlane(wave_sums[0]) : chunk;
         v.off = off_s;
         v.len = len_s;
         v.pre = pre;
