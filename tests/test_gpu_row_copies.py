@@ -1,0 +1,53 @@
+"""Row copies move spans of 256 or 1024 16-byte pieces per workgroup: sizes around those borders, whole and ragged,
+through every entry point that copies rows, byte for byte, with the neighbouring rows untouched."""
+import numpy as np
+import pytest
+
+from paper_2306_06000_amd import binding as s3
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("H,D,rows", [(1, 64, r) for r in (1, 31, 32, 33, 127, 128, 129, 300)] + [(3, 128, 85), (16, 256, 2), (16, 256, 129)])
+def test_rows_arrive_whole(H, D, rows):
+    layers, bytes_row = 2, H * D * 2
+    cfg = s3.make_config(layers, H, D, s3.S3_BF16, 64, 1024, 0, s3.S3_BF16)
+    bpt = s3.s3_kv_bytes_per_token(cfg)
+    mem = torch.full((2048 * bpt,), 0xA5, dtype=torch.uint8, device=DEV)
+    st, a = s3.s3_kv_arena_init(cfg, mem, mem.numel())
+    assert st == 0
+    rc, ids, offs, caps = s3.s3_kv_alloc(a, [rows, rows, rows])
+    assert rc == 3
+    stream = torch.cuda.current_stream().cuda_stream
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    src = [torch.randint(0, 256, (2, rows * bytes_row), dtype=torch.uint8, device=DEV, generator=g) for _ in range(layers)]
+    for layer in range(layers):  # slot 0 by the batched fill (with a shorter newcomer beside it), slot 1 by the single one
+        part = max(1, rows // 3)
+        assert s3.s3_kv_fill_batch(a, layer, ids[[0, 2]], np.array([rows, part], np.int32), [src[layer][0], src[layer][0]],
+                                   [src[layer][1], src[layer][1]], stream) == 0
+        assert s3.s3_kv_fill(a, int(ids[1]), layer, 0, rows, src[layer][0], src[layer][1], stream) == 0
+    planes = mem.view(2 * layers, -1)
+    want = torch.full_like(planes, 0xA5)
+    for layer in range(layers):
+        for w in range(2):
+            for slot, count in ((0, rows), (1, rows), (2, max(1, rows // 3))):
+                at = int(offs[slot]) * bytes_row
+                want[2 * layer + w, at:at + count * bytes_row] = src[layer][w][:count * bytes_row]
+    torch.cuda.synchronize()
+    assert torch.equal(planes, want)
+    stage = torch.full((s3.s3_kv_evict_bytes(a, rows) + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+    assert s3.s3_kv_gather_rows(a, int(ids[0]), rows, stage, stream) == 0
+    st, off, cap = s3.s3_kv_grow(a, int(ids[1]), rows, stream)
+    assert st == 0
+    torch.cuda.synchronize()
+    assert torch.equal(stage[:-64], torch.cat([src[p // 2][p % 2] for p in range(2 * layers)])) and (stage[-64:] == 0x5A).all()
+    for p in range(2 * layers):
+        assert torch.equal(planes[p, off * bytes_row:(off + rows) * bytes_row], src[p // 2][p % 2])
+    assert s3.s3_kv_scatter_rows(a, int(ids[2]), rows, stage, stream) == 0
+    torch.cuda.synchronize()
+    for p in range(2 * layers):
+        assert torch.equal(planes[p, int(offs[2]) * bytes_row:(int(offs[2]) + rows) * bytes_row], src[p // 2][p % 2])
+    s3.s3_kv_arena_destroy(a)
