@@ -867,7 +867,8 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
     AttnArgs args = common_args(a, c, H, H, a->chunk > 0 ? a->chunk : 1024);
     // a dynamic work list is a longest-processing-time schedule only if the long items come first: four length
     // classes whatever the batch size (with a fixed stride, large batches did better without the classes' prologue)
-    if (a->ncls <= 0 && s3i_variant_dynamic(variant)) {
+    // (attention alone: without them; 953 contexts of 11 rows, 12 x 128, lost 7 us a layer to the classes' prologue)
+    if (a->ncls <= 0 && c.with_append && s3i_variant_dynamic(variant)) {
         args.ncls = 4;
         while (args.ncls > 1 && batch_view_lds(c.n, args.ncls) > (size_t)96 * 1024) args.ncls--;
     }
