@@ -44,12 +44,10 @@ def parse():
     ap.add_argument("--grid-blocks", type=int, default=0)
     ap.add_argument("--classes", type=int, default=0, help="length classes of the longest-first work order (0: library default)")
     ap.add_argument("--merge-sync", type=int, default=0, help="1: fence-ordered merge of chunks inside a launch")
-    ap.add_argument("--gqa-merge", type=int, default=-1, help="shared heads, matrix-core kernel: 1 = chunks merge inside "
-                    "the attention launch, 0 = merge launch (-1: library default)")
+    ap.add_argument("--gqa-merge", type=int, default=-1, help="accepted by the library without effect")
     ap.add_argument("--gqa-stream", type=int, default=-1, help="shared heads, matrix-core kernel: K rows read with the "
                     "streaming hint (1), with plain loads (0), by launch size (-1, the library's default)")
-    ap.add_argument("--gqa-dynamic", type=int, default=-1, help="shared heads, matrix-core kernel: per cent of the work "
-                    "list dealt by stride before waves claim positions (0 or -1, the default: all by stride)")
+    ap.add_argument("--gqa-dynamic", type=int, default=-1, help="accepted by the library without effect")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-kernel-events", action="store_true", help="skip pass 2 (no events anywhere: for counter runs)")
     ap.add_argument("--c3-bytes", type=float, default=200e9)
@@ -337,7 +335,7 @@ def run_workload(name, args, torch, cpu_budget_s):
         achieved = per_launch_bytes / (avg_us * 1e-6) / 1e9 if avg_us > 0 else 0.0
         kind = s3.s3_kv_get_param(eng.arena, "kernel_kind")[1]
         kernel = {1: "attn_gqa_kernel", 2: "attn_gqa_mfma_kernel", 3: "attn_fp8_kernel", 4: "attn_gqa_mfma_kernel"}.get(
-            kind, "attn_partial_kernel" if args.unfused else "attn_step_kernel")
+            kind, "attn_step_kernel")
         traffic, traffic_ref = read_traffic(kernel, name)
         res["roofline"] = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1),
                            "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBPS, 4),
