@@ -681,7 +681,7 @@ static size_t scratch_need(const s3_arena *a, int n) {
     }
     if (chunk <= 0) chunk = 256;
     const size_t max_chunks = (size_t)(a->cfg.max_len + chunk - 1) / chunk;
-    return (size_t)n * max_chunks * slot_bytes;
+    return counters_bytes((int)gqa_columns(a)) + (size_t)n * max_chunks * slot_bytes;
 }
 
 extern "C" int s3_kv_reserve_scratch(s3_arena *a, int32_t max_batch) {
@@ -816,7 +816,10 @@ static int launch_gqa(s3_arena *a, const AttnCall &c) {
     // Few (sequence, head group) pairs: cut contexts finer so that the chip still has work everywhere.
     const int chunk = a->chunk > 0 ? a->chunk : (int64_t)c.n * per_seq >= 2048 ? 1024 : (int64_t)c.n * per_seq >= 512 ? 512 : 256;
     AttnArgs args = common_args(a, c, Hkv, Hq, chunk);
-    int rc = place_scratch(a, args, 0, (size_t)args.n * args.max_chunks, c);
+    // The arena's scratch keeps the matrix-core kernel's counter region (zero between launches) in front of the
+    // partials: both kernels of a shared-head arena may run in turn (the "variant" parameter).  The fixed buffer of
+    // s3_decode_step_static is cleared whenever its layout changes and needs no such room.
+    int rc = place_scratch(a, args, c.static_scratch ? 0 : counters_bytes((int)gqa_columns(a)), (size_t)args.n * args.max_chunks, c);
     if (rc != S3_OK) return rc;
     const size_t dyn_lds = batch_view_lds(c.n, args.ncls);
     int blocks = 0;

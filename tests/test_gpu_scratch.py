@@ -1,0 +1,33 @@
+"""The arena's scratch (arrival counters, then chunk partials) over calls that lay it out differently: every call must
+find its counters at zero whatever ran before it on the arena."""
+import numpy as np
+import pytest
+
+from paper_2306_06000_amd import binding as s3
+from tests.harness import assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,Hkv,D,kvt", [(32, 8, 128, s3.S3_BF16), (16, 1, 256, s3.S3_F16), (8, 2, 64, s3.S3_F16)])
+def test_both_kernels_of_a_shared_head_arena_in_turn(H, Hkv, D, kvt):
+    """Matrix cores, vector ALU with sequence 0 in many chunks (its partials come first in the scratch), matrix cores
+    again: all three against the oracle, and the third bit for bit the first."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    lens = [1000, 300, 0, 17, 1900]
+    rng = np.random.default_rng(60 + D)
+    rig = EdgeRig(("switch", H, Hkv, D, kvt, kvt, 2), lens, M=2048)
+    rig.put([rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens],
+            [rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens])
+    q = rng.standard_normal((len(lens), H, D), dtype=np.float32)
+    qb, first = rig.attend(q)
+    want = rig.want(qb)
+    assert_close(first, want, "matrix cores")
+    for chunk in (0, 32):
+        assert s3.s3_kv_set_param(rig.a, "variant", 0) == 0 and s3.s3_kv_get_param(rig.a, "kernel_kind") == (0, 1)
+        assert s3.s3_kv_set_param(rig.a, "chunk", chunk) == 0
+        assert_close(rig.attend(q)[1], want, f"vector ALU, chunk {chunk}")
+        assert s3.s3_kv_set_param(rig.a, "variant", -1) == 0 and s3.s3_kv_set_param(rig.a, "chunk", 0) == 0
+        assert np.array_equal(rig.attend(q)[1], first), f"matrix cores after the vector ALU, chunk {chunk}"
+    rig.close()
