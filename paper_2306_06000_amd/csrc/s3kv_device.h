@@ -96,6 +96,10 @@ __device__ __forceinline__ float group_sum(float v) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Exponent reference of a set of scores whose maximum is m: m, or 0 if every score is -inf, so that exp2(score - reference)
+// is 0 for them and not NaN (such rows, a chunk of them or a piece weigh nothing beside rows with finite scores).
+__device__ __forceinline__ float exp_reference(float m) { return m == -INFINITY ? 0.f : m; }
+
 // Note: __builtin_bit_cast applied directly to a vector-element expression (v[i]) reads element 0
 // with this compiler, so elements are always copied into a scalar first.
 template <int DT>
@@ -622,13 +626,13 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs &a, int64_t slot0, i
         float mn = mm;
 #pragma unroll
         for (int u = 0; u < 4; u++) mn = fmaxf(mn, mv[u]);  // repeats of the last chunk do not change the max
-        const float alpha = fast_exp2(mm - mn);
+        const float ref = exp_reference(mn), alpha = fast_exp2(mm - ref);
         l *= alpha;
 #pragma unroll
         for (int i = 0; i < 8; i++) o[i] *= alpha;
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            const float wgt = (c0 + u < nchunks) ? fast_exp2(mv[u] - mn) : 0.f;
+            const float wgt = (c0 + u < nchunks) ? fast_exp2(mv[u] - ref) : 0.f;
             l += wgt * lv[u];
 #pragma unroll
             for (int i = 0; i < 8; i++) o[i] += wgt * av[u][i];

@@ -221,13 +221,13 @@ __global__ void __launch_bounds__(TS * 64) attn_fp8_kernel(const AttnArgs a) {
             float o[16], mm = -INFINITY, ll = 0.f;
 #pragma unroll
             for (int e = 0; e < 16; e++) o[e] = 0.f;
-            // a chunk has at least one row, so the maximum over its waves and lane groups is finite
             for (int t = 0; t < TS; t++)
                 for (int g = 0; g < tpw; g++) mm = fmaxf(mm, comb[t][0][lane + g * a.H * LPH]);
+            const float ref = exp_reference(mm);
             for (int t = 0; t < TS; t++)
                 for (int g = 0; g < tpw; g++) {
                     const int src = lane + g * a.H * LPH;
-                    const float wt = fast_exp2(comb[t][0][src] - mm);
+                    const float wt = fast_exp2(comb[t][0][src] - ref);
                     ll += wt * comb[t][1][src];
 #pragma unroll
                     for (int e = 0; e < 16; e++) o[e] += wt * comb[t][2 + e][src];

@@ -280,12 +280,12 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
                 float mn = m;
 #pragma unroll
                 for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[u][0]);
-                const float alpha = m == -INFINITY ? 0.f : fast_exp2(m - mn);
+                const float ref = exp_reference(mn), alpha = fast_exp2(m - ref);
                 l *= alpha;
                 o *= alpha;
 #pragma unroll
                 for (int u = 0; u < NP; u++) {
-                    const float w = c + u * splits < p.count ? fast_exp2(mv[u][0] - mn) : 0.f;
+                    const float w = c + u * splits < p.count ? fast_exp2(mv[u][0] - ref) : 0.f;
                     l += w * mv[u][1];
                     o += w * av[u];
                 }
@@ -301,7 +301,7 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
 #pragma unroll 1
             for (int k = 0; k < splits; k++) {  // (a split without a piece: max -inf, sum 0)
                 const f32x2 x = *(const f32x2 *)(lds + 1024 + (k * quads + tid) * 2);
-                const float mn = fmaxf(m, x[0]), alpha = m == -INFINITY ? 0.f : fast_exp2(m - mn), w = x[0] == -INFINITY && x[1] == 0.f ? 0.f : fast_exp2(x[0] - mn);
+                const float mn = fmaxf(m, x[0]), ref = exp_reference(mn), alpha = fast_exp2(m - ref), w = fast_exp2(x[0] - ref);
                 l = l * alpha + w * x[1];
                 o = o * alpha + w * *(const f32x4 *)(lds + (k * quads + tid) * 4);
                 m = mn;
@@ -346,12 +346,12 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
                 float mn = m[i];
 #pragma unroll
                 for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[i][u][0]);
-                const float alpha = m[i] == -INFINITY ? 0.f : fast_exp2(m[i] - mn);
+                const float ref = exp_reference(mn), alpha = fast_exp2(m[i] - ref);
                 l[i] *= alpha;
                 o[i] *= alpha;
 #pragma unroll
                 for (int u = 0; u < NP; u++) {
-                    const float w = c + u < p.count ? fast_exp2(mv[i][u][0] - mn) : 0.f;
+                    const float w = c + u < p.count ? fast_exp2(mv[i][u][0] - ref) : 0.f;
                     l[i] += w * mv[i][u][1];
                     o[i] += w * av[i][u];
                 }
@@ -642,7 +642,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                     for (int db = 0; db < DB; db++) o[db] *= alpha;
                     m = mn;
                 }
-                const float ref = m == -INFINITY ? 0.f : m;  // only -inf scores so far: they weigh nothing
+                const float ref = exp_reference(m);
                 // The weights enter the second product as 16-bit operands: a high part (p rounded to the type) and
                 // a low part (what the high part misses, rounded again), two products per value block.  Together
                 // they carry about twice the type's mantissa, so the weighted sum is as exact as the fp32 weights
@@ -798,10 +798,11 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
 #pragma unroll
                 for (int j = 0; j < 8; j++)
                     if (__builtin_amdgcn_readlane(pb, j) == mine) m = fmaxf(m, x[j].x);
+                const float ref = exp_reference(m);
 #pragma unroll
                 for (int j = 0; j < 8; j++)
-                    if (__builtin_amdgcn_readlane(pb, j) == mine) l += fast_exp2(x[j].x - m) * x[j].y;
-                if (mine >= 0) piece_run[k][h] = (f32x4){fast_exp2(me.x - m), m, l, 1.f / l};
+                    if (__builtin_amdgcn_readlane(pb, j) == mine) l += fast_exp2(x[j].x - ref) * x[j].y;
+                if (mine >= 0) piece_run[k][h] = (f32x4){fast_exp2(me.x - ref), m, l, 1.f / l};
             }
             __syncthreads();
             // ... then the rows, all threads together, every thread EB quads of elements at once
