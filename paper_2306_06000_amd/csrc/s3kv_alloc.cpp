@@ -301,6 +301,7 @@ extern "C" int s3_kv_set_param(s3_arena *a, const char *name, int64_t value) {
     if (!strcmp(name, "chunk")) {
         if (value != 0 && (value < 32 || value > 2048 || value % 32)) return S3_ERR_INVALID;
         a->chunk = (int32_t)value;
+        a->scratch_batch = 0;
         return S3_OK;
     }
     if (!strcmp(name, "classes")) {
@@ -316,6 +317,7 @@ extern "C" int s3_kv_set_param(s3_arena *a, const char *name, int64_t value) {
     if (!strcmp(name, "variant")) {
         if (value < -1 || value >= s3i_variants_of(a)) return S3_ERR_INVALID;
         a->variant = (int32_t)value;
+        a->scratch_batch = 0;
         return S3_OK;
     }
     if (!strcmp(name, "gqa_merge")) {

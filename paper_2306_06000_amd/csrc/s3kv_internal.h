@@ -32,6 +32,7 @@ struct s3_arena {
     // split-K partials owned by the library
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
+    int32_t scratch_batch = 0;  // the scratch holds every batch up to this one (0: not known, e.g. after a change of "chunk")
 
     // optional timing of the attention kernels with events on the launch stream
     int32_t profile = 0;       // k > 0: bracket every k-th attention launch with events

@@ -569,6 +569,8 @@ static AttnArgs common_args(const s3_arena *a, const AttnCall &c, int row_heads,
     return args;
 }
 
+static size_t scratch_need(const s3_arena *a, int n);
+
 // Library scratch: [arrival counters: cnt_bytes, fixed per arena kind, zero between launches]
 // [partial sums][partial (max, sum)], `slots` partials per head of q (one per sequence and chunk, or as
 // gqa_partial_slots() counts them).
@@ -582,8 +584,15 @@ static int place_scratch(s3_arena *a, AttnArgs &args, size_t cnt_bytes, size_t s
         const int rc = static_scratch_for_call(cnt_bytes, c.stream, &base);
         if (rc != S3_OK) return rc;
     } else {
-        const int rc = ensure_scratch(a, need);
-        if (rc != S3_OK) return rc;
+        // The scratch moves only for a batch larger than any before (or after a change of "chunk" or "variant"): a
+        // smaller batch may need more than a larger one, since few contexts are cut finer, so a growth takes what
+        // every batch up to this one needs.  Recorded graphs keep its address.
+        if (args.n > a->scratch_batch || need > a->scratch_bytes) {
+            const size_t all = scratch_need(a, args.n);
+            const int rc = ensure_scratch(a, all > need ? all : need);
+            if (rc != S3_OK) return rc;
+            if (args.n > a->scratch_batch) a->scratch_batch = args.n;
+        }
         base = (char *)a->scratch;
     }
     args.arrivals = (unsigned int *)base;
@@ -653,40 +662,48 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }
 
-// Scratch an attention call over n sequences needs at most: the launchers' layout with the smallest chunk
-// they may choose for any batch size (or the chunk the caller fixed).
+// Vector-ALU kernel for shared heads: query heads per lane, and rows per chunk (few (sequence, head group) pairs: contexts
+// are cut finer so that the chip still has work everywhere).
+static int gqa_heads_per_lane(const s3_arena *a) {
+    const int group = a->cfg.n_heads / a->cfg.n_kv_heads;
+    return group % 8 == 0 ? 8 : group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
+}
+static int gqa_items_per_chunk(const s3_arena *a) {  // K/V head groups x query sub-blocks
+    const int GH = 512 / a->cfg.head_dim, group = a->cfg.n_heads / a->cfg.n_kv_heads;
+    return ((a->cfg.n_kv_heads + GH - 1) / GH) * (group / gqa_heads_per_lane(a));
+}
+static int gqa_chunk_rows(const s3_arena *a, int n) {
+    const int64_t items = (int64_t)n * gqa_items_per_chunk(a);
+    return a->chunk > 0 ? a->chunk : items >= 2048 ? 1024 : items >= 512 ? 512 : 256;
+}
+
+// Scratch the attention calls over 1 to n sequences need at most.
 static size_t scratch_need(const s3_arena *a, int n) {
-    const int D = a->cfg.head_dim, Hq = a->cfg.n_heads;
-    const int kind = s3i_kernel_kind(a);
-    int chunk = a->chunk;
-    if (kind == 2 || kind == 4) {
-        size_t most = 0;  // a smaller batch may take more slots: the fixed buffer's size bounds some and not others
-        for (int k = n; k >= 1; k = k > 64 ? k - 64 : k - 1) {
-            const size_t slots = gqa_partial_slots(a, k);
-            if (slots > most) most = slots;
-        }
-        return counters_bytes((int)gqa_columns(a)) + (most + 64) * gqa_slot_bytes(a);
-    }
+    const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, kind = s3i_kernel_kind(a);
     const size_t slot_bytes = (size_t)Hq * ((size_t)D * sizeof(float) + sizeof(float2));
-    if (kind == 0 || kind == 3) {  // kernels that merge chunks themselves carry counters
-        const int gh = kind == 3 ? 1024 / D : heads_per_load(D), n_hg = (Hq + gh - 1) / gh;
-        size_t most = 0;
+    const int gh = kind == 3 ? 1024 / D : heads_per_load(D), n_hg = (Hq + gh - 1) / gh;  // (kinds 0 and 3)
+    size_t most = 0;
+    for (int k = 1; k <= n; k++) {
         int32_t few;
-        for (int k = 1; k < n && k <= 1024; k++) {  // (more contexts than that are never "few")
-            const size_t slots = chunk_slots(a, k, n_hg, slot_bytes, &few);
-            if (slots > most) most = slots;
+        size_t slots;
+        if (kind == 2 || kind == 4) {
+            slots = gqa_partial_slots(a, k);
+        } else if (kind == 0 || kind == 3) {
+            slots = chunk_slots(a, k, n_hg, slot_bytes, &few);
+        } else {
+            const int chunk = gqa_chunk_rows(a, k);
+            slots = (size_t)k * ((a->cfg.max_len + chunk - 1) / chunk);
         }
-        const size_t slots = chunk_slots(a, n, n_hg, slot_bytes, &few);
-        return counters_bytes(n_hg) + (slots > most ? slots : most) * slot_bytes;
+        if (slots > most) most = slots;
     }
-    if (chunk <= 0) chunk = 256;
-    const size_t max_chunks = (size_t)(a->cfg.max_len + chunk - 1) / chunk;
-    return counters_bytes((int)gqa_columns(a)) + (size_t)n * max_chunks * slot_bytes;
+    return counters_bytes(kind == 0 || kind == 3 ? n_hg : (int)gqa_columns(a)) + most * slot_bytes;
 }
 
 extern "C" int s3_kv_reserve_scratch(s3_arena *a, int32_t max_batch) {
     if (!a || !a->base || max_batch < 1 || max_batch > S3_MAX_BATCH) return S3_ERR_INVALID;
-    return ensure_scratch(a, scratch_need(a, max_batch));
+    const int rc = ensure_scratch(a, scratch_need(a, max_batch));
+    if (rc == S3_OK && max_batch > a->scratch_batch) a->scratch_batch = max_batch;
+    return rc;
 }
 
 static size_t batch_view_lds(int n, int ncls) {
@@ -802,20 +819,14 @@ static int launch_gqa(s3_arena *a, const AttnCall &c) {
     const int kind = s3i_kernel_kind(a);
     // Variant indices of a shared-K/V arena: the shapes of the vector-ALU kernel, then the matrix-core kernel.
     if (kind == 2 || kind == 4) return launch_gqa_mfma(a, c);
-    const int group = Hq / Hkv;
-    const int gq = group % 8 == 0 ? 8 : group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
     int threads = 256;
-    attn_fn fn = s3i_pick_gqa(a->cfg.kv_dtype, D, gq, a->variant, &threads);
+    attn_fn fn = s3i_pick_gqa(a->cfg.kv_dtype, D, gqa_heads_per_lane(a), a->variant, &threads);
     if (!fn) return S3_ERR_INVALID;
     if (c.with_append) {
         const int arc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
         if (arc != S3_OK) return arc;
     }
-    const int GH = 512 / D;
-    const int per_seq = ((Hkv + GH - 1) / GH) * (group / gq);  // work items per chunk: K/V head groups x query sub-blocks
-    // Few (sequence, head group) pairs: cut contexts finer so that the chip still has work everywhere.
-    const int chunk = a->chunk > 0 ? a->chunk : (int64_t)c.n * per_seq >= 2048 ? 1024 : (int64_t)c.n * per_seq >= 512 ? 512 : 256;
-    AttnArgs args = common_args(a, c, Hkv, Hq, chunk);
+    AttnArgs args = common_args(a, c, Hkv, Hq, gqa_chunk_rows(a, c.n));
     // The arena's scratch keeps the matrix-core kernel's counter region (zero between launches) in front of the
     // partials: both kernels of a shared-head arena may run in turn (the "variant" parameter).  The fixed buffer of
     // s3_decode_step_static is cleared whenever its layout changes and needs no such room.

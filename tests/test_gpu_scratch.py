@@ -31,3 +31,27 @@ def test_both_kernels_of_a_shared_head_arena_in_turn(H, Hkv, D, kvt):
         assert s3.s3_kv_set_param(rig.a, "variant", -1) == 0 and s3.s3_kv_set_param(rig.a, "chunk", 0) == 0
         assert np.array_equal(rig.attend(q)[1], first), f"matrix cores after the vector ALU, chunk {chunk}"
     rig.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D,kvt,act,kind,n,M", [(16, 16, 256, s3.S3_F16, s3.S3_F16, 0, 30, 1024), (12, 12, 128, s3.S3_BF16, s3.S3_BF16, 0, 90, 256),
+                                                      (16, 16, 256, s3.S3_E4M3, s3.S3_F16, 3, 60, 1024), (32, 8, 128, s3.S3_BF16, s3.S3_BF16, 2, 300, 256),
+                                                      (16, 8, 128, s3.S3_F16, s3.S3_F16, 1, 300, 2048)])
+def test_a_smaller_batch_never_moves_the_scratch(H, Hkv, D, kvt, act, kind, n, M):
+    """The scratch grows for a larger batch only: its address is in recorded graphs.  (Few contexts are cut finer and
+    may need more room than many.)  A smaller "chunk" may move it."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    rig = EdgeRig(("grow", H, Hkv, D, kvt, act, kind), [1] * n, M=M)
+    rng = np.random.default_rng(n)
+    rig.put([rng.standard_normal((1, Hkv, D), dtype=np.float32)] * n, [rng.standard_normal((1, Hkv, D), dtype=np.float32)] * n)
+    q = rng.standard_normal((n, H, D), dtype=np.float32)
+    rig.attend(q)
+    held = s3.s3_kv_get_param(rig.a, "scratch_bytes")[1]
+    for k in [k for k in range(1, n) if k < 40 or k % 16 in (0, 1)]:
+        rig.attend(q[:k], lens=[1] * k)
+        assert s3.s3_kv_get_param(rig.a, "scratch_bytes")[1] == held, k
+    assert s3.s3_kv_reserve_scratch(rig.a, n) == 0 and s3.s3_kv_get_param(rig.a, "scratch_bytes")[1] == held
+    assert s3.s3_kv_set_param(rig.a, "chunk", 32) == 0
+    qb, got = rig.attend(q)
+    assert_close(got, rig.want(qb), "chunk 32")
+    rig.close()
