@@ -324,8 +324,11 @@ static int ensure_scratch(s3_arena *a, size_t need) {
         a->scratch_bytes = 0;
     }
     HIP_TRY(hipMalloc(&a->scratch, need));
+    // The arrival counters at its head must start at zero, for the call's own stream too: a memset of device memory need
+    // not be over when hipMemset returns, and a stream that does not wait for the default stream would overtake it.
+    HIP_TRY(hipMemset(a->scratch, 0, need));
+    HIP_TRY(hipStreamSynchronize(nullptr));
     a->scratch_bytes = need;
-    HIP_TRY(hipMemset(a->scratch, 0, need));  // the arrival counters at its head must start at zero
     return S3_OK;
 }
 

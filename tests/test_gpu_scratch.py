@@ -55,3 +55,26 @@ def test_a_smaller_batch_never_moves_the_scratch(H, Hkv, D, kvt, act, kind, n, M
     qb, got = rig.attend(q)
     assert_close(got, rig.want(qb), "chunk 32")
     rig.close()
+
+
+def test_the_first_call_of_an_arena_on_a_stream_of_its_own():
+    """Every call starts with no scratch: the counters are zero before a kernel on a stream that does not wait for the
+    default stream looks at them."""
+    import torch
+
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    lens = [1900, 3, 2000]
+    rng = np.random.default_rng(77)
+    rows = [rng.standard_normal((L, 8, 128), dtype=np.float32) for L in lens]
+    q = rng.standard_normal((3, 32, 128), dtype=np.float32)
+    side = torch.cuda.Stream()
+    for i in range(4):
+        rig = EdgeRig(("first", 32, 8, 128, s3.S3_BF16, s3.S3_BF16, 2), lens, M=2048)
+        rig.put(rows, rows)
+        torch.cuda.synchronize()
+        rig.stream = side.cuda_stream
+        with torch.cuda.stream(side):
+            qb, got = rig.attend(q)
+        assert_close(got, rig.want(qb), f"arena {i}")
+        rig.close()
