@@ -44,7 +44,7 @@ struct AttnArgs {
     // matrix-core kernel for shared heads: how the rows are divided among the waves
     int32_t group, nqb, columns;          // query heads per cached head, blocks of 16 of them, columns = H * nqb
     int32_t wave_shares, team_shares;     // shares per column if every wave takes one, if teams of four waves do
-    int32_t max_shares;  // partial slots allow this many publishing units per column
+    int32_t max_shares;  // partial slots allow this many publishing units per column (0: none, shares begin and end with contexts)
     float merge_cost;    // time of merging one more piece of a context, in tiles streamed by one wave
     int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
     int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
@@ -335,18 +335,23 @@ __device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t 
     return total;
 }
 
-// Exclusive prefix sums of one value per entry (n <= threads, thread t brings entry t's) into pre[0..n]; returns the
+// Exclusive prefix sums of the entries' chunks of `rows` rows (len: as the view holds it) into pre[0..n]; returns the
 // total.  Whoever reads pre[] before has met a barrier since.
-__device__ __forceinline__ int block_prefix(int n, int mine, int *pre, int *wave_sums) {
+__device__ __forceinline__ int chunk_prefix(int n, const int *len, int rows, int *pre, int *wave_sums) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
-    const int incl = wave_inclusive_scan(mine);
-    if (lane == 63) wave_sums[wave] = incl;
-    __syncthreads();
-    const int upto = wave_inclusive_scan(lane < nwaves ? wave_sums[lane] : 0);
-    const int total = __builtin_amdgcn_readlane(upto, nwaves - 1);
-    if (tid < n) pre[tid] = incl - mine + (wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0);
-    if (tid == 0) pre[n] = total;
-    __syncthreads();
+    int total = 0;
+#pragma unroll 1
+    for (int base = 0; base < n; base += blockDim.x) {
+        const int b = base + tid, mine = b < n ? (len[b] + rows - 1) / rows : 0;
+        const int incl = wave_inclusive_scan(mine);
+        if (lane == 63) wave_sums[wave] = incl;
+        __syncthreads();
+        const int upto = wave_inclusive_scan(lane < nwaves ? wave_sums[lane] : 0);
+        if (b < n) pre[b] = total + incl - mine + (wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0);
+        total += __builtin_amdgcn_readlane(upto, nwaves - 1);
+        if (tid == 0) pre[n] = total;
+        __syncthreads();
+    }
     return total;
 }
 

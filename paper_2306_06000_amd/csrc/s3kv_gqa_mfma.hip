@@ -156,8 +156,9 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
 // 17 of 1200..1455 rows 18.6 and 19.2; 64q/8kv x 128 e4m3, 22 of 2000..4793 rows 41.5 and 48.8.
 template <int TR, int ROW_BYTES>
 __device__ __forceinline__ int chunk_plan(const AttnArgs &a, int tiles) {
+    if (a.share_rows > 0) return a.share_rows / TR;   // the caller's choice (a multiple of 32)
     const int room = min(a.wave_shares - a.n, a.max_shares);  // chunks beyond one per context, per column
-    if (a.n > 256 || a.share_rows > 0 || a.max_shares <= 1 || room <= 0) return 0;
+    if (a.n > 256 || a.max_shares <= 1 || room <= 0) return 0;
     const int even = (tiles + room - 1) / room;
     const float average = (float)tiles / (float)a.n;
     const int per = max(even, (int)__builtin_amdgcn_sqrtf(a.merge_cost * 1.5f * average) + 1);
@@ -168,9 +169,17 @@ __device__ __forceinline__ int chunk_plan(const AttnArgs &a, int tiles) {
 // [k * base + min(k, rem), ...) with one tile more for the first `rem`.  team 1: every wave works for itself and
 // a piece of a context cut by a share's border goes to memory.  team 4: the four waves of a workgroup take four
 // consecutive shares of one column and first merge their pieces through LDS.
+// whole: both borders of a share move on to where the next context begins, so that no piece leaves a wave.
 struct SharePlan {
     int tiles, shares, base, rem, team;
+    bool whole;
 };
+
+// Whole contexts: where the fixed buffer has no room for pieces (max_shares 0, see s3i_gqa_max_shares); and for short
+// contexts, each of which a share's border would cut for about 4 us of counting and merging a launch: a share of c
+// contexts comes out longer or shorter by one of them, which pays while they average no more than 2c tiles (and none has
+// more than 256 rows).  32q/8kv x 128, 600 contexts of 1..30 rows: 20.6 us a layer, 25.9 cut; 1400 of 20..200: 138.0,
+// 138.1; 700 of 1..255 (outside the rule): 91.7, 85.8; 64q/8kv, 1010 of 20..200: 114.4, 118.9.
 
 // Why the line between team 1 and team 4 lies at 256 rows a share: a piece costs a write-through store
 // and a read of its fp32 rows, 16 query heads x D x 4 bytes twice against D x 4 bytes (16-bit K and V) per
@@ -190,17 +199,12 @@ __device__ __forceinline__ SharePlan share_plan(const AttnArgs &a, int tiles) {
     SharePlan sp;
     sp.tiles = tiles;
     sp.team = 1;
-    int shares;
-    if (a.share_rows > 0) {  // the caller fixed the longest piece
-        const int per = a.share_rows / TR;
-        shares = min((tiles + per - 1) / per, a.max_shares);
-    } else {
-        shares = min(a.wave_shares, a.max_shares);
-        if (a.team_lds && tiles < shares * (S3_TEAM_ROWS / TR)) {
-            sp.team = 4;
-            constexpr int LEAST = 4 * (S3_TEAM_MIN_ROWS / TR);
-            shares = 4 * min(min(a.team_shares, a.max_shares), (tiles + LEAST - 1) / LEAST);
-        }
+    sp.whole = a.max_shares == 0 || (a.max_len <= 256 && (int64_t)tiles * a.wave_shares <= 2 * (int64_t)a.n * a.n);
+    int shares = sp.whole ? a.wave_shares : min(a.wave_shares, a.max_shares);
+    if (a.team_lds && !sp.whole && tiles < shares * (S3_TEAM_ROWS / TR)) {
+        sp.team = 4;
+        constexpr int LEAST = 4 * (S3_TEAM_MIN_ROWS / TR);
+        shares = 4 * min(min(a.team_shares, a.max_shares), (tiles + LEAST - 1) / LEAST);
     }
     sp.shares = max(1, min(shares, tiles));
     sp.base = tiles / sp.shares;
@@ -433,12 +437,11 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     if (tiles == 0) return;  // the whole grid alike
     const int per = chunk_plan<TR, D * EB>(a, tiles);
     int chunks = 0;  // chunks of `per` tiles in a column; pre[] then counts them
-    SharePlan sp = {tiles, 1, tiles, 0, 1};
+    SharePlan sp = {tiles, 1, tiles, 0, 1, false};
     if (per == 0) {
         sp = share_plan<TR>(a, tiles);
     } else {
-        const int mine = (int)threadIdx.x < a.n ? (bv.len[threadIdx.x] + TR * per - 1) / (TR * per) : 0;
-        chunks = __builtin_amdgcn_readfirstlane(block_prefix(a.n, mine, (int *)bv.pre, wave_sums));
+        chunks = __builtin_amdgcn_readfirstlane(chunk_prefix(a.n, bv.len, TR * per, (int *)bv.pre, wave_sums));
     }
 
     char *vt = wave_lds[wave];
@@ -486,6 +489,10 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
             if (share < sp.shares) {
                 t_begin = share_start(sp, share);
                 t_stop = share_start(sp, share + 1);
+                if (sp.whole) {
+                    if (t_begin > 0) t_begin = __builtin_amdgcn_readfirstlane(bv.pre[min(find_sequence(bv.pre, a.n, t_begin - 1) + 1, a.n)]);
+                    t_stop = __builtin_amdgcn_readfirstlane(bv.pre[min(find_sequence(bv.pre, a.n, t_stop - 1) + 1, a.n)]);
+                }
                 seq = min(find_sequence(bv.pre, a.n, t_begin), a.n - 1);
             }
         }

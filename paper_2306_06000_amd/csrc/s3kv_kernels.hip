@@ -611,11 +611,15 @@ static size_t counters_bytes(int n_hg) {
     return ((((size_t)(S3_MAX_BATCH + 1) * n_hg * sizeof(unsigned int)) + 255) & ~(size_t)255) + 256;  // + the work-list counters
 }
 
-// The matrix-core kernel's share of the scratch.  A piece of a context sits in slot (publishing unit + sequence),
-// so max_shares units need max_shares + n slots.  With the default division at most one unit per wave and column
-// (waves <= 8 per compute unit, see launch_gqa); with a caller's `chunk` as many as the longest contexts could need.
+// The matrix-core kernel's share of the scratch.  Cut by the caller's `chunk`, contexts leave one piece per chunk.  With
+// the default division a piece of a context sits in slot (publishing unit + sequence), so max_shares units need
+// max_shares + n slots; at most one unit per wave and column (waves <= 8 per compute unit, see launch_gqa_mfma).
 // What fits the fixed buffer of s3_decode_step_static by its documented rule (chunks of `chunk` rows, or 128 / 256)
-// is held to that buffer's size by fewer shares, there and here alike, so that both calls divide their rows the same.
+// is held to that buffer's size, there and here alike, so that both calls divide their rows the same: by fewer
+// shares, or, where that would leave fewer of them than there are contexts, by shares of whole contexts (0; only
+// possible where no context is longer than a chunk).  32q/8kv x 128, contexts of 20..200 rows of at most 256, per layer:
+// 1900 contexts 232 us in the 108 shares that fit, 181 in whole contexts; 1990: 1201 us in 18 shares, 190; 2008: 21 ms
+// in one, 191.
 static int64_t gqa_columns(const s3_arena *a) {
     const int group = a->cfg.n_heads / a->cfg.n_kv_heads;
     return (int64_t)a->cfg.n_kv_heads * ((group + 15) / 16);
@@ -623,24 +627,26 @@ static int64_t gqa_columns(const s3_arena *a) {
 static size_t gqa_slot_bytes(const s3_arena *a) {
     return (size_t)a->cfg.n_heads * ((size_t)a->cfg.head_dim * sizeof(float) + sizeof(float2));
 }
-static bool gqa_fits_static(const s3_arena *a, int n) {
-    const int64_t columns = gqa_columns(a);
-    const int chunk = a->chunk > 0 ? a->chunk : n * columns >= 4096 ? 256 : 128;
-    const size_t max_chunks = (size_t)(a->cfg.max_len + chunk - 1) / chunk;
-    return counters_bytes((int)columns) + (size_t)n * max_chunks * gqa_slot_bytes(a) <= (size_t)S3_STATIC_SCRATCH_BYTES;
+// Chunks of the documented rule over n contexts, and how many the fixed buffer holds.
+static int64_t gqa_chunks(const s3_arena *a, int n) {
+    const int chunk = a->chunk > 0 ? a->chunk : n * gqa_columns(a) >= 4096 ? 256 : 128;
+    return (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
 }
-static int64_t gqa_max_shares(const s3_arena *a, int n) {
-    const int64_t columns = gqa_columns(a);
-    const int64_t waves = (int64_t)(a->num_cus > 0 ? a->num_cus : 256) * 8;
-    int64_t most = a->chunk > 0 ? (int64_t)n * (a->cfg.max_len + 31) / a->chunk + 1 : (waves + columns - 1) / columns;
-    if (gqa_fits_static(a, n)) {
-        const int64_t slots = (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes((int)columns)) / gqa_slot_bytes(a));
-        if (most > slots - n) most = slots - n;
-    }
-    return most < 1 ? 1 : most;
+static int64_t gqa_static_slots(const s3_arena *a) {
+    return (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes((int)gqa_columns(a))) / gqa_slot_bytes(a));
+}
+static bool gqa_fits_static(const s3_arena *a, int n) { return gqa_chunks(a, n) <= gqa_static_slots(a); }
+// (not for callers of the library: a host test reads it)
+extern "C" int64_t s3i_gqa_max_shares(const s3_arena *a, int32_t n) {
+    const int64_t columns = gqa_columns(a), waves = (int64_t)(a->num_cus > 0 ? a->num_cus : 256) * 8;
+    const int64_t most = (waves + columns - 1) / columns;
+    if (!gqa_fits_static(a, n)) return most;
+    const int64_t fit = gqa_static_slots(a) - n;
+    return fit >= most ? most : fit >= n ? fit : 0;
 }
 static size_t gqa_partial_slots(const s3_arena *a, int n) {
-    const int64_t shares = gqa_max_shares(a, n);
+    if (a->chunk > 0) return (size_t)gqa_chunks(a, n);
+    const int64_t shares = s3i_gqa_max_shares(a, n);
     return shares > 1 ? (size_t)(shares + n) : 0;  // one share: no piece ever leaves its wave or team
 }
 
@@ -652,7 +658,7 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // contexts are items enough.  Chunk fixed at 1024 -> this rule, 16 heads x 256 fp16, four layers: one context of 410
 // rows 74 -> 36 us, of 8050 rows 181 -> 112; 4 contexts of 500..1500 rows 129 -> 68, 8: 143 -> 102, 16: 207 -> 189;
 // 32 contexts of 32..1000 rows: 212, and 217 if the line were drawn above them.
-// As with gqa_max_shares, what the fixed buffer takes by its documented rule is held to its size.
+// As with s3i_gqa_max_shares, what the fixed buffer takes by its documented rule is held to its size.
 static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few) {
     const int chunk = a->chunk > 0 ? a->chunk : 1024;
     const int64_t whole = (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
@@ -788,7 +794,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     args.ncls = 1;
     args.stream_k = a->gqa_stream;
     args.share_rows = a->chunk;
-    args.max_shares = (int32_t)gqa_max_shares(a, c.n);
+    args.max_shares = (int32_t)s3i_gqa_max_shares(a, c.n);
     int rc = place_scratch(a, args, counters_bytes((int)columns), gqa_partial_slots(a, c.n), c);
     if (rc != S3_OK) return rc;
     // LDS behind the view: the first pieces of a team's four waves.  A batch whose view leaves no room for them has

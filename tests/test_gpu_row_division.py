@@ -66,6 +66,40 @@ def test_even_division_over_batches(fam):
         rig.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [300, 600, 1007, 1100, 1999, 2008, 2009])
+def test_short_contexts_around_the_fixed_buffers_size(n):
+    """At most 256 rows a context, 32 query on 8 cached heads of 128: 2008 contexts fit the fixed buffer of
+    s3_decode_step_static whole, from 1005 on with fewer slots left than contexts.  Attention, the step and the static
+    step (refused beyond) agree bit for bit."""
+    from tests.test_gpu_numeric_edges import TDT, EdgeRig, device_bits, wl
+
+    H, Hkv, D, kvt = 32, 8, 128, s3.S3_BF16
+    rng = np.random.default_rng(n)
+    lens = [int(x) for x in rng.integers(0, 30, size=n)]
+    for b, L in ((0, 250), (n // 2, 16), (n - 2, 255), (n - 1, 0)):
+        lens[b] = L
+    rig = EdgeRig(("short", H, Hkv, D, kvt, kvt, 2), lens, M=256)
+    rows = rng.standard_normal((256, Hkv, D), dtype=np.float32)
+    rig.put([np.roll(rows, b, axis=0)[:L] for b, L in enumerate(lens)], [np.roll(rows, 2 * b, axis=0)[:L] for b, L in enumerate(lens)])
+    q = rng.standard_normal((n, H, D), dtype=np.float32)
+    qb, att = rig.attend(q)
+    assert_close(att, rig.want(qb), "attention")
+    k_new, v_new = (rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2))
+    qb, step = rig.step(q, k_new, v_new)
+    longer = [L + 1 for L in lens]
+    assert_close(step, rig.want(qb, longer), "step")
+    assert np.array_equal(rig.attend(q, lens=longer)[1], step)
+    out = torch.full((n, H, D), float("nan"), dtype=torch.float32, device="cuda:0")
+    args = [device_bits(wl.to_bits(x, kvt), TDT[kvt], "cuda:0") for x in (q, k_new, v_new)]
+    st = s3.s3_decode_step_static(rig.a, 0, n, rig.off_d, torch.tensor(lens, dtype=torch.int32, device="cuda:0"), *args, out, s3.S3_F32, 0.0,
+                                  None, rig.stream)
+    torch.cuda.synchronize()
+    assert st == (s3.S3_ERR_SCRATCH if n > 2008 else 0)
+    assert n > 2008 or np.array_equal(out.cpu().numpy(), step)
+    rig.close()
+
+
 def test_merging_loads_bypass_the_caches(tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
