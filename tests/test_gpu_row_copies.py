@@ -51,3 +51,26 @@ def test_rows_arrive_whole(H, D, rows):
     for p in range(2 * layers):
         assert torch.equal(planes[p, int(offs[2]) * bytes_row:(int(offs[2]) + rows) * bytes_row], src[p // 2][p % 2])
     s3.s3_kv_arena_destroy(a)
+
+
+def test_one_long_newcomer_among_short_ones():
+    """The grid of a batched fill is bounded over all newcomers: the long one's rows take several spans per workgroup."""
+    H, D, lens = 16, 256, [5, 1, 2048, 16, 33] + [3] * 11
+    cfg = s3.make_config(1, H, D, s3.S3_BF16, 64, 2048, 0, s3.S3_BF16)
+    bpt, row = s3.s3_kv_bytes_per_token(cfg), H * D * 2
+    mem = torch.full((sum(-(-n // 64) * 64 for n in lens) * bpt,), 0xA5, dtype=torch.uint8, device=DEV)
+    st, a = s3.s3_kv_arena_init(cfg, mem, mem.numel())
+    assert st == 0
+    rc, ids, offs, caps = s3.s3_kv_alloc(a, lens)
+    assert rc == len(lens)
+    stream = torch.cuda.current_stream().cuda_stream
+    src = [[torch.randint(0, 256, (n * row,), dtype=torch.uint8, device=DEV) for n in lens] for _ in range(2)]
+    assert s3.s3_kv_fill_batch(a, 0, ids, np.array(lens, np.int32), src[0], src[1], stream) == 0
+    torch.cuda.synchronize()
+    planes = mem.view(2, -1)
+    want = torch.full_like(planes, 0xA5)
+    for w in range(2):
+        for i, n in enumerate(lens):
+            want[w, int(offs[i]) * row:(int(offs[i]) + n) * row] = src[w][i]
+    assert torch.equal(planes, want)
+    s3.s3_kv_arena_destroy(a)
