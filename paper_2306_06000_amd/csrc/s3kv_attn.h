@@ -285,6 +285,11 @@ __device__ __forceinline__ void emit_chunk(const AttnArgs &a, const Item &it, in
     put_partial4<COHERENT>(pa + 4, (f32x4){acc[4], acc[5], acc[6], acc[7]});
 }
 
+// Mean rows of a context below which a dynamic list is walked with a fixed stride after all.  Two layers, one class:
+// 12 x 128, 953 contexts of 2..25 rows 48.0 us with claims, 39.5 without; 16 x 256, 1000 of 2..25 114.3 and 88.4; (with two
+// rows per register set) 32 x 128, 1000 of 5..60 134.8 and 138.5.
+#define S3_CLAIM_ROWS 24
+
 // The whole layer-step in one launch (s3_decode_step), or, without new rows (k_new null), attention alone
 // (s3_decode_attention): TS*HS compute waves plus ONE epilogue wave.  Compute waves stream their token shares (taking the new row from k_new / v_new and appending it),
 // drop (max, sum, weighted sum) into one of two LDS buffers and move on to the next item after a
@@ -329,7 +334,8 @@ __global__ void __launch_bounds__((TS *HS + 1) * 64) attn_step_kernel(const Attn
     }
 
     // a work list no longer than the grid deals every position at launch: nothing to claim, no counter traffic
-    const bool dyn = DYN && total > (int64_t)gridDim.x;
+    // (nor in a batch of very short contexts, whose items end before a claim is back; S3_CLAIM_ROWS)
+    const bool dyn = DYN && total > (int64_t)gridDim.x && !(a.class_rows > 0 && bv.mean < S3_CLAIM_ROWS);
     int parity = 0;
     int64_t item = blockIdx.x;
     while (item < total) {

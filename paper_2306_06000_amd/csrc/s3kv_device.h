@@ -30,6 +30,7 @@ struct AttnArgs {
     int32_t n, H, chunk, max_chunks, out_dtype, max_len;  // H: heads of a K/V row
     int32_t Hq;            // query heads (= H unless grouped-query / multi-query attention)
     int32_t ncls;          // length classes of the work order (1..8)
+    int32_t class_rows;    // > 0: one class if the contexts average fewer rows than this
     int32_t few_chunks;    // > 0: few contexts; cut them into about this many chunks (chunk: the longest allowed)
     int32_t len_add;    // 0: cur_len is the context length; 1 (fused step): cur_len is the append position
     float scale_log2e;  // scale * log2(e): scores are kept in log2 units so that exp is v_exp_f32
@@ -241,18 +242,19 @@ struct BatchView {
     const int *pre;
     int n, ncls, total;
     int chunk;  // rows per chunk
+    int mean;   // mean rows of a context (0 unless the launch asks for it with class_rows or few_chunks)
 };
 
 __device__ __forceinline__ size_t batch_view_bytes(int n, int ncls) {
     return (size_t)n * 8 + (size_t)((n + 1) & ~1) * 4 + (size_t)ncls * (n + 1) * 4;
 }
 
-// The one-wave build of the view: lane l owns entries l*E .. l*E+E-1 (n <= 64*E).
+// The one-wave build of the view: lane l owns entries l*E .. l*E+E-1 (n <= 64*E).  `how`, for the other waves: rows per
+// chunk, classes, mean rows of a context (where the launch asks for it).
 template <int E>
-__device__ __forceinline__ int one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre) {
-    const int lane = threadIdx.x & 63;
-    const int ncls = a.ncls, n = a.n;
-    int chunk = a.chunk;
+__device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre, int *how) {
+    const int lane = threadIdx.x & 63, n = a.n;
+    int chunk = a.chunk, ncls = a.ncls, mean = 0;
     int64_t off[E];
     int len[E], cls[E], cnt[E];
     int mx = 0;
@@ -267,11 +269,14 @@ __device__ __forceinline__ int one_wave_view(const AttnArgs &a, int64_t *off_s, 
         mx = max(mx, len[e]);
     }
     mx = wave_max_nonneg(mx);
-    if (a.few_chunks > 0) {
+    if (a.few_chunks > 0 || a.class_rows > 0) {
         int rows = 0;
 #pragma unroll
         for (int e = 0; e < E; e++) rows += len[e];
-        chunk = few_chunk_rows(a, __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63), mx);
+        rows = __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63);
+        if (a.few_chunks > 0) chunk = few_chunk_rows(a, rows, mx);
+        mean = rows / n;
+        if (mean < a.class_rows) ncls = 1;
     }
 #pragma unroll
     for (int e = 0; e < E; e++) {
@@ -293,13 +298,20 @@ __device__ __forceinline__ int one_wave_view(const AttnArgs &a, int64_t *off_s, 
         }
         if (lane == 63) pre[c * (n + 1) + n] = incl;
     }
-    return chunk;
+    if (lane == 0) {
+        how[0] = chunk;
+        how[1] = ncls;
+        how[2] = mean;
+    }
 }
 
 // The view with one length class, built by the whole workgroup: of every E * threads entries, thread t owns E
-// neighbours; two barriers.  Returns the number of chunks.
-template <int E>
-__device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t *off_s, int *len_s, int *pre, int *wave_sums) {
+// neighbours; two barriers.  Returns the number of chunks.  WITH_ROWS: `rows` receives the rows of all contexts, and if
+// they average `most` or more (most > 0) the scan ends there, lengths and offsets in place: -1, with the rows of the
+// longest in `longest`.  agg: 2 * S3_MAX_WAVES words that nobody writes before the next barrier after this.
+template <int E, bool WITH_ROWS>
+__device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t *off_s, int *len_s, int *pre, int *wave_sums,
+                                          int most, int *agg, int64_t *rows, int *longest) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
     int total = 0;
 #pragma unroll 1
@@ -319,7 +331,28 @@ __device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t 
         }
         const int incl = wave_inclusive_scan(sum);
         if (lane == 63) wave_sums[wave] = incl;
+        if (WITH_ROWS) {
+            int mine = 0, mx = 0;
+#pragma unroll
+            for (int e = 0; e < E; e++) {  // (a wave's rows: at most 256 contexts of 2^20)
+                mine += len[e];
+                mx = max(mx, len[e]);
+            }
+            mine = wave_inclusive_scan(mine);
+            mx = wave_max_nonneg(mx);
+            if (lane == 63) {
+                agg[wave] = mine;
+                agg[S3_MAX_WAVES + wave] = mx;
+            }
+        }
         __syncthreads();
+        if (WITH_ROWS) {
+            for (int w = 0; w < nwaves; w++) {
+                *rows += agg[w];
+                *longest = max(*longest, agg[S3_MAX_WAVES + w]);
+            }
+            if (most > 0 && base + E * (int)blockDim.x >= a.n && *rows >= (int64_t)most * a.n) return -1;
+        }
         const int upto = wave_inclusive_scan(lane < nwaves ? wave_sums[lane] : 0);
         int run = total + incl - sum + (wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0);
         total += __builtin_amdgcn_readlane(upto, nwaves - 1);
@@ -369,8 +402,9 @@ __device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dy
     v.n = a.n;
     v.ncls = 1;
     v.chunk = CHUNK;
-    v.total = a.n <= (int)blockDim.x ? block_view<1>(a, CHUNK, off_s, len_s, pre, wave_sums)
-                                     : block_view<4>(a, CHUNK, off_s, len_s, pre, wave_sums);
+    v.mean = 0;
+    v.total = a.n <= (int)blockDim.x ? block_view<1, false>(a, CHUNK, off_s, len_s, pre, wave_sums, 0, nullptr, nullptr, nullptr)
+                                     : block_view<4, false>(a, CHUNK, off_s, len_s, pre, wave_sums, 0, nullptr, nullptr, nullptr);
     return v;
 }
 
@@ -391,25 +425,26 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         // E is a compile-time constant per batch size class: the per-entry work (two integer divisions) is
         // not spent on entries a small batch does not have.
         if (wave == 0) {
-            const int rows = n <= 64    ? one_wave_view<1>(a, off_s, len_s, pre)
-                             : n <= 128 ? one_wave_view<2>(a, off_s, len_s, pre)
-                             : n <= 256 ? one_wave_view<4>(a, off_s, len_s, pre)
-                                        : one_wave_view<8>(a, off_s, len_s, pre);
-            if (a.few_chunks > 0 && lane == 0) wave_sums[0] = rows;
+            if (n <= 64) one_wave_view<1>(a, off_s, len_s, pre, wave_sums);
+            else if (n <= 128) one_wave_view<2>(a, off_s, len_s, pre, wave_sums);
+            else if (n <= 256) one_wave_view<4>(a, off_s, len_s, pre, wave_sums);
+            else one_wave_view<8>(a, off_s, len_s, pre, wave_sums);
         }
         __syncthreads();
         BatchView v;
-        v.chunk = a.few_chunks > 0 ? __builtin_amdgcn_readfirstlane(wave_sums[0]) : chunk;
+        v.chunk = __builtin_amdgcn_readfirstlane(wave_sums[0]);
         v.off = off_s;
         v.len = len_s;
         v.pre = pre;
         v.n = n;
-        v.ncls = ncls;
+        v.ncls = __builtin_amdgcn_readfirstlane(wave_sums[1]);
+        v.mean = __builtin_amdgcn_readfirstlane(wave_sums[2]);
         v.total = 0;
-        for (int c = 0; c < ncls; c++) v.total += pre[c * (n + 1) + n];
+        for (int c = 0; c < v.ncls; c++) v.total += pre[c * (n + 1) + n];
         return v;
     }
-    if (ncls == 1) {
+    int mean = 0, mx = 0;
+    if (ncls == 1 || a.class_rows > 0) {
         // One class: a scan over the workgroup (the general path below walks the entries three times and costs a
         // batch of 1024 about 5 us before its first load).
         BatchView v;
@@ -419,24 +454,29 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         v.n = n;
         v.ncls = 1;
         v.chunk = chunk;
-        v.total = block_view<4>(a, chunk, off_s, len_s, pre, wave_sums);
-        return v;
+        int64_t rows = 0;
+        v.total = a.class_rows > 0 ? block_view<4, true>(a, chunk, off_s, len_s, pre, wave_sums, ncls > 1 ? a.class_rows : 0,
+                                                         ncls > 1 ? pre + n + 1 : wave_sums + S3_MAX_WAVES, &rows, &mx)
+                                   : block_view<4, false>(a, chunk, off_s, len_s, pre, wave_sums, 0, nullptr, nullptr, nullptr);
+        v.mean = mean = __builtin_amdgcn_readfirstlane((int)(rows / n));
+        if (v.total >= 0) return v;
     }
     const int per = (n + nthreads - 1) / nthreads;
     const int b0 = min(n, tid * per), b1 = min(n, b0 + per);
-    int mx = 0;
-    for (int b = b0; b < b1; b++) {
-        const int len = checked_len(a, b);
-        len_s[b] = len;
-        off_s[b] = a.slot_off[b];
-        mx = max(mx, len);
-    }
+    if (a.class_rows == 0) {  // (else the scan above has done this)
+        for (int b = b0; b < b1; b++) {
+            const int len = checked_len(a, b);
+            len_s[b] = len;
+            off_s[b] = a.slot_off[b];
+            mx = max(mx, len);
+        }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) mx = max(mx, __shfl_xor(mx, d));
-    if (lane == 0) wave_sums[wave] = mx;
-    __syncthreads();
-    for (int i = 0; i < nwaves; i++) mx = max(mx, wave_sums[i]);
-    __syncthreads();  // wave_sums is reused below
+        for (int d = 32; d >= 1; d >>= 1) mx = max(mx, __shfl_xor(mx, d));
+        if (lane == 0) wave_sums[wave] = mx;
+        __syncthreads();
+        for (int i = 0; i < nwaves; i++) mx = max(mx, wave_sums[i]);
+        __syncthreads();  // wave_sums is reused below
+    }
     int cnt[S3_MAX_CLASSES], incl[S3_MAX_CLASSES];
 #pragma unroll
     for (int c = 0; c < S3_MAX_CLASSES; c++) cnt[c] = 0;
@@ -489,6 +529,7 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
     v.n = n;
     v.ncls = ncls;
     v.chunk = chunk;
+    v.mean = mean;
     v.total = 0;
     for (int c = 0; c < ncls; c++) v.total += pre[c * (n + 1) + n];
     return v;

@@ -877,6 +877,11 @@ static int launch_fp8(s3_arena *a, const AttnCall &c) {
     return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, 0, !c.static_scratch);  // the kernel merges by itself
 }
 
+// Mean rows of a context below which a dynamic list has one length class.  The rows decide, on the device, and not the
+// entry point.  One class against four, two layers, append + attention: 12 x 128, 300 contexts of 20..300 rows 64.3 us and
+// 59.2, 953 of 100..200 152.6 and 156.4, 953 of 2..25 48.1 and 51.5; 32 x 128, 1000 of 5..60 134.9 and 144.6; 16 x 256,
+// 512 of 40..1600 531 and 513.  (A batch beyond 512 that is found to need the classes pays 0.5 us for the look.)
+#define S3_CLASS_ROWS 128
 // Shared by s3_decode_attention and s3_decode_step (with_append: the kernel also appends and publishes the new
 // lengths).
 static int launch_attention(s3_arena *a, const AttnCall &c) {
@@ -892,12 +897,13 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
     const int GH = heads_per_load(D);
     const int n_hg = (H + GH - 1) / GH;
     AttnArgs args = common_args(a, c, H, H, a->chunk > 0 ? a->chunk : 1024);
-    // a dynamic work list is a longest-processing-time schedule only if the long items come first: four length
-    // classes whatever the batch size (with a fixed stride, large batches did better without the classes' prologue)
-    // (attention alone: without them; 953 contexts of 11 rows, 12 x 128, lost 7 us a layer to the classes' prologue)
-    if (a->ncls <= 0 && c.with_append && s3i_variant_dynamic(variant)) {
+    // A dynamic work list is a longest-processing-time schedule only if the long items come first: four length classes
+    // whatever the batch size (with a fixed stride, large batches did better without the classes' prologue), unless the
+    // contexts are so short that the prologue outweighs the order; see S3_CLASS_ROWS.
+    if (a->ncls <= 0 && s3i_variant_dynamic(variant)) {
         args.ncls = 4;
         while (args.ncls > 1 && batch_view_lds(c.n, args.ncls) > (size_t)96 * 1024) args.ncls--;
+        args.class_rows = S3_CLASS_ROWS;
     }
     int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
