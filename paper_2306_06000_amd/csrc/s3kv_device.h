@@ -44,6 +44,7 @@ struct AttnArgs {
     int32_t stream_k;        // matrix-core kernel for shared heads: K rows with the streaming hint (1), plain (0), by launch size (< 0)
     // matrix-core kernel for shared heads: how the rows are divided among the waves
     int32_t group, nqb, columns;          // query heads per cached head, blocks of 16 of them, columns = H * nqb
+    int32_t column_shift;                 // log2 of the columns, -1: no power of two
     int32_t wave_shares, team_shares;     // shares per column if every wave takes one, if teams of four waves do
     int32_t max_shares;  // partial slots allow this many publishing units per column (0: none, shares begin and end with contexts)
     float merge_cost;    // time of merging one more piece of a context, in tiles streamed by one wave
@@ -242,15 +243,15 @@ struct BatchView {
     const int *pre;
     int n, ncls, total;
     int chunk;  // rows per chunk
-    int mean;   // mean rows of a context (0 unless the launch asks for it with class_rows or few_chunks)
+    int mean;   // mean rows of a context (0 unless the launch asks for it with class_rows)
 };
 
 __device__ __forceinline__ size_t batch_view_bytes(int n, int ncls) {
     return (size_t)n * 8 + (size_t)((n + 1) & ~1) * 4 + (size_t)ncls * (n + 1) * 4;
 }
 
-// The one-wave build of the view: lane l owns entries l*E .. l*E+E-1 (n <= 64*E).  `how`, for the other waves: rows per
-// chunk, classes, mean rows of a context (where the launch asks for it).
+// The one-wave build of the view: lane l owns entries l*E .. l*E+E-1 (n <= 64*E).  `how`, for the other waves, where
+// the rows decide: rows per chunk, classes, mean rows of a context.
 template <int E>
 __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre, int *how) {
     const int lane = threadIdx.x & 63, n = a.n;
@@ -275,8 +276,15 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         for (int e = 0; e < E; e++) rows += len[e];
         rows = __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63);
         if (a.few_chunks > 0) chunk = few_chunk_rows(a, rows, mx);
-        mean = rows / n;
-        if (mean < a.class_rows) ncls = 1;
+        if (a.class_rows > 0) {
+            mean = rows / n;
+            if (mean < a.class_rows) ncls = 1;
+        }
+        if (lane == 0) {
+            how[0] = chunk;
+            how[1] = ncls;
+            how[2] = mean;
+        }
     }
 #pragma unroll
     for (int e = 0; e < E; e++) {
@@ -297,11 +305,6 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
             if (b < n) pre[c * (n + 1) + b] = incl - lsum + loc[e];
         }
         if (lane == 63) pre[c * (n + 1) + n] = incl;
-    }
-    if (lane == 0) {
-        how[0] = chunk;
-        how[1] = ncls;
-        how[2] = mean;
     }
 }
 
@@ -388,10 +391,10 @@ __device__ __forceinline__ int chunk_prefix(int n, const int *len, int rows, int
     return total;
 }
 
-// A view with one length class in chunks (tiles) of CHUNK rows.  Kept small: it runs once, out of a cold
-// instruction cache.
+// A view with one length class in chunks (tiles) of CHUNK rows; `longest` receives the rows of the longest context.  Kept
+// small: it runs once, out of a cold instruction cache.
 template <int CHUNK>
-__device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dyn, int *wave_sums) {
+__device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dyn, int *wave_sums, int &longest) {
     int64_t *off_s = (int64_t *)dyn;
     int *len_s = (int *)(dyn + (size_t)a.n * 8);
     int *pre = len_s + ((a.n + 1) & ~1);
@@ -403,8 +406,9 @@ __device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dy
     v.ncls = 1;
     v.chunk = CHUNK;
     v.mean = 0;
-    v.total = a.n <= (int)blockDim.x ? block_view<1, false>(a, CHUNK, off_s, len_s, pre, wave_sums, 0, nullptr, nullptr, nullptr)
-                                     : block_view<4, false>(a, CHUNK, off_s, len_s, pre, wave_sums, 0, nullptr, nullptr, nullptr);
+    int64_t rows = 0;
+    longest = 0;
+    v.total = block_view<4, true>(a, CHUNK, off_s, len_s, pre, wave_sums, 0, wave_sums + S3_MAX_WAVES, &rows, &longest);
     return v;
 }
 
@@ -432,13 +436,18 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         }
         __syncthreads();
         BatchView v;
-        v.chunk = __builtin_amdgcn_readfirstlane(wave_sums[0]);
         v.off = off_s;
         v.len = len_s;
         v.pre = pre;
         v.n = n;
-        v.ncls = __builtin_amdgcn_readfirstlane(wave_sums[1]);
-        v.mean = __builtin_amdgcn_readfirstlane(wave_sums[2]);
+        v.chunk = chunk;
+        v.ncls = ncls;
+        v.mean = 0;
+        if (a.few_chunks > 0 || a.class_rows > 0) {
+            v.chunk = __builtin_amdgcn_readfirstlane(wave_sums[0]);
+            v.ncls = __builtin_amdgcn_readfirstlane(wave_sums[1]);
+            v.mean = __builtin_amdgcn_readfirstlane(wave_sums[2]);
+        }
         v.total = 0;
         for (int c = 0; c < v.ncls; c++) v.total += pre[c * (n + 1) + n];
         return v;
@@ -556,20 +565,6 @@ __device__ __forceinline__ void put_partial2(float *p, const f32x2 v) {
     if (COHERENT) asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
     else *(f32x2 *)p = v;
 }
-template <bool COHERENT>
-__device__ __forceinline__ f32x4 get_partial4(const float *p) {
-    if (!COHERENT) return *(const f32x4 *)p;
-    f32x4 v;
-    asm volatile("global_load_dwordx4 %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p) : "memory");
-    return v;
-}
-template <bool COHERENT>
-__device__ __forceinline__ f32x2 get_partial2(const float *p) {
-    if (!COHERENT) return *(const f32x2 *)p;
-    f32x2 v;
-    asm volatile("global_load_dwordx2 %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p) : "memory");
-    return v;
-}
 // Four partials at once, one memory round trip for all: (max, sum) at ml[u], eight accumulator values at acc[u].
 template <bool COHERENT>
 __device__ __forceinline__ void get_partials(const float *const (&ml)[4], const float *const (&acc)[4], f32x2 (&m)[4], f32x4 (&lo)[4],
@@ -603,15 +598,19 @@ __device__ __forceinline__ void get_partials(const float *const (&ml)[4], const 
         : "memory");
 }
 
-// The same loads as relaxed system-scope atomics of 64 bits (sc0 sc1 as well): twice the instructions, but the
-// compiler tracks them, so any number of them stays in flight at once.
-__device__ __forceinline__ f32x2 get_coherent2(const float *p) {
-    const uint64_t v = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    return __builtin_bit_cast(f32x2, v);
+// The matrix-core kernel's loads of partials, as other workgroups of the launch wrote them: 16 or 8 bytes past every cache that another XCD does not see (sc0
+// sc1).  Through a buffer descriptor, so that what lies past its end (pieces that are not there, lanes without an element)
+// reads as zeros and costs no traffic and no branch: unlike plain loads these never hit a cache (pairs of 64-bit atomic
+// loads before, the last piece's repeated for those that are not there: 16q/1kv x 256, 3 contexts of 700..924 rows 17.7 us
+// a layer, now 16.7; 512 of 32..1000 81.4 and 78.9).  The compiler tracks them, so any number stays in flight.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t piece_buffer(const float *p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ f32x4 get_coherent4(const float *p) {
-    const f32x2 lo = get_coherent2(p), hi = get_coherent2(p + 2);
-    return (f32x4){lo[0], lo[1], hi[0], hi[1]};
+__device__ __forceinline__ f32x4 piece_load4(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 17));
+}
+__device__ __forceinline__ f32x2 piece_load2(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 17));
 }
 
 // A wave has written its chunk's partial: count the chunk on the context's arrival counter.  Returns true
@@ -638,6 +637,33 @@ __device__ __forceinline__ bool chunk_arrived(const AttnArgs &a, unsigned int *c
     return true;
 }
 
+// Matrix-core kernel.  A context of which this wave or team has left a piece in memory: its pieces are `count` (0:
+// nothing left), by the publishing units first, first + 1, ...; unit u keeps its piece of context b in partial slot u + b
+// (along the shares either u or b grows from one piece to the next, so no two pieces meet; chunks, which belong to one
+// context each, are counted so that u + b is the chunk's number).
+struct Pending {
+    int b, first, count;
+};
+
+// This wave (its team) has written the pieces p0 and p1 (count 0: none): count them on their contexts' arrival
+// counters, both in one round trip; bit k of the result: the last piece of p_k's context has arrived, and this wave
+// merges it.  See chunk_arrived() for the two orderings.
+__device__ __forceinline__ unsigned pieces_arrived(const AttnArgs &a, const Pending &p0, const Pending &p1, int columns, int col) {
+    const int lane = threadIdx.x & 63;
+    if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the partial stores have completed
+    const int count = lane == 0 ? p0.count : p1.count;
+    unsigned int *cnt = a.arrivals + (int64_t)(lane == 0 ? p0.b : p1.b) * columns + col;
+    bool mine = false;
+    if (lane < 2 && count != 0) {
+        mine = atomicAdd(cnt, 1u) == (unsigned int)(count - 1);
+        if (mine) atomicExch(cnt, 0u);  // leave the counter clean for the next launch
+    }
+    const unsigned who = (unsigned)__builtin_amdgcn_ballot_w64(mine);
+    if (a.merge_sync && who != 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    asm volatile("" ::: "memory");  // no piece is loaded before this
+    return who;
+}
 // Merge the chunk partials of (sequence b, head h), in slots slot0, slot0 + 1, ..., for this lane's 8-element slice and
 // store the final output row slice; H is the head count of the partial and output arrays.  nchunks >= 2.  Four chunks are loaded
 // per round, in one memory round trip.

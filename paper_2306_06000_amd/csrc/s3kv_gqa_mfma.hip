@@ -9,37 +9,34 @@
 // per cached head; here both products run on MFMA and every (row, head) score is handled by
 // exactly one lane.
 //
-// Work division.  A column is one (K/V head, block of 16 query heads); the rows of all contexts, laid end to
-// end in tiles of 16, are the same length for every column.  That length is cut into equal shares and a wave
-// takes one share of one column, across the borders of contexts, so the waves end together whatever the
-// lengths of the batch and a context is cut only where a share ends (see share_plan below for the number of
-// shares).  A context inside one share leaves as its final row; a piece of a longer one leaves as a partial
-// (max, sum, unnormalised row) and whoever delivers the last piece merges them inside this launch.  Until this
-// division the unit was a chunk of 128 or 256 rows, dealt by stride: nearly every context left partials (7 to
-// 14 % extra traffic), a second launch merged them (5 to 6 us of device time a step) and the last round of the
-// stride left units idle (16 query heads on one cached head of 256, 256 contexts of 32..1000 rows: 1216 chunks
-// on 1024 waves).
-// Per tile of 16 cached rows:
-//   * K: lane (r = lane % 16, g = lane / 16) holds 16 bytes (8 elements) of row r at element offset
-//     32*ks + 8*g, ks = 0 .. D/32-1 - loaded so directly with plain loads, or, in launches whose K rows
-//     exceed the memory-side cache, loaded in whole rows with the streaming hint and brought into that
-//     layout through a per-wave LDS buffer - : the A operand of
-//     v_mfma_f32_16x16x32 (row r, contraction slots of lane group g); Q^T is the B operand, loaded
-//     once per item with the same slot assignment (head = lane % 16), so whichever way the
-//     instruction numbers its contraction slots, both operands agree.  The accumulator holds
-//     S^T[row 4*g + i][head lane % 16], i < 4.
+// Work division.  A column is one (K/V head, block of 16 query heads); every column has the same rows, in tiles of 16
+// or 32.  Many rows: the contexts lie end to end, that length is cut into equal shares and a wave takes one share of one
+// column, across the borders of contexts, so the waves end together whatever the lengths of the batch and a context is
+// cut only where a share ends (share_plan).  Few rows: every context by itself is cut into chunks, each taken by one
+// wave or by the four waves of a workgroup (chunk_plan).  A context inside one share or chunk leaves as its final row; a
+// piece of a longer one leaves as a partial (max, sum, unnormalised row) and whoever delivers the last piece merges
+// them inside this launch.  Dealing chunks of 128 or 256 rows by stride instead let nearly every context leave partials
+// (7 to 14 % extra traffic), needed a second launch to merge them (5 to 6 us of device time a step) and left units idle
+// in the last round of the stride (16 query heads on one cached head of 256, 256 contexts of 32..1000 rows: 1216
+// chunks on 1024 waves).
+// Per tile:
+//   * K and V rows are loaded whole, 16 bytes a lane, two tiles ahead, and pass through a per-wave LDS buffer (row-major;
+//     the row strides are at the kernel's start).
+//   * K: lane (r = lane % 16, g = lane / 16) reads 16 bytes (8 elements) of row r at element offset 32*ks + 8*g,
+//     ks = 0 .. D/32-1: the A operand of v_mfma_f32_16x16x32 (row r, contraction slots of lane group g); Q^T is the B
+//     operand, loaded once per context with the same slot assignment (head = lane % 16), so whichever way the
+//     instruction numbers its contraction slots, both operands agree.  The accumulator holds S^T[row 4*g + i][head
+//     lane % 16], i < 4.
 //   * softmax: scale into log2 units, mask rows past the end, tile maximum per head (over the four
 //     registers, then across the four lane groups); the exponent reference m follows the maximum
 //     lazily (see the loop), p = exp2(s - m), running sum.
-//   * V: the accumulator layout of S^T is already the B-operand layout of v_mfma_f32_16x16x16
-//     (4 contraction slots = rows 4*g .. 4*g+3, column = head), so P^T needs no shuffle.  The A
-//     operand V^T (row of the product = output element d, contraction = cached rows) needs four
-//     cached rows at ONE d per lane, while memory holds eight d of one row per 16-byte load: the V
-//     tile goes through a per-wave LDS buffer (row-major, row stride padded by 8 bytes so that the
-//     four lane groups hit different banks) and is read back as 16-bit gathers.  With 8-bit rows a
-//     lane reads one 32-bit word (four consecutive d) from each of its four rows and transposes the
-//     4 x 4 codes in registers (eight v_perm_b32), which feeds four products at once; the products'
-//     operand rows are numbered accordingly (d = 64q + 4n + j) and the results leave in that order.
+//   * V: the accumulator layout of S^T is already the B-operand layout of the second product (rows 4*g .. 4*g+3 of a
+//     block of 16, column = head), so P^T needs no shuffle.  The A operand V^T (row of the product = output element d,
+//     contraction = cached rows) needs four cached rows at one d per lane, while memory holds eight d of one row per
+//     16-byte load: 16-bit rows come out of LDS through the transposing read (ds_read_b64_tr_b16).  With 8-bit rows a
+//     lane reads one 32-bit word (four consecutive d) from each of its four rows and transposes the 4 x 4 codes in
+//     registers (eight v_perm_b32), which feeds four products at once; the products' operand rows are numbered
+//     accordingly (d = 64q + 4n + j) and the results leave in that order.
 //   * p enters the second product as two 16-bit operands of the storage type, a high part (p rounded)
 //     and a low part (the remainder, rounded), and the product is issued for both, which keeps the
 //     weights' error near 2^-16 (bfloat16) / 2^-22 (fp16) instead of 2^-9 / 2^-12: with one part only,
@@ -144,25 +141,124 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
     t[3] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);
 }
 
+// Quotients of small whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here
+// all out of a cold instruction cache).  x / y rounded down: x < 2^20, so that half a unit in x, which keeps the product off
+// the whole numbers, is more than the error.  And a whole number not below x / y (by less than 2 above it), x < 2^28.
+__device__ __forceinline__ int quotient(int x, int y) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y)); }
+__device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x * __builtin_amdgcn_rcpf((float)y) * 1.000001f) + 1; }
+
 // How a launch of few rows divides them (a batch of at most 256 contexts): every context by itself, into near-equal
-// chunks of at most `per` tiles, one wave a chunk, all at once.  Nothing is combined that the lengths do not force:
-// a context of one chunk is finished by its wave.  Lower bounds on `per`: all chunks of all columns fit the waves of
-// the grid; and the wave that merges a context reads its pieces a few per memory round trip while their tiles stream
-// side by side, so with `merge_cost` tiles' worth of time per piece (see launch_gqa_mfma) no finer than
-// sqrt(merge_cost * tiles of a context).  0: rows enough for even shares (below), that is, chunks would pass 64 KiB of K
-// rows, or contexts would average more than 12 pieces, which a team's four waves merge faster.
-// Per layer, chunks against even shares: 32q/8kv x 128, 19 contexts of about 80 rows 9.7 us and 16.2, 66 of 400..656
-// rows 35.3 and 37.7, 3 of 512..3000 rows (16 pieces each) 21.5 and 19.0; 12q/2kv x 128, 5 of 20..31 rows 7.3 and 11.7,
-// 17 of 1200..1455 rows 18.6 and 19.2; 64q/8kv x 128 e4m3, 22 of 2000..4793 rows 41.5 and 48.8.
+// chunks of at most `per` tiles, one wave or a team of four waves a chunk, all at once.  Nothing is combined that the
+// lengths do not force: a context of one chunk is finished by its wave or team.  What bounds such a launch is a chain of
+// latencies (view and plan 2.5 us, rows a tile a microsecond and wave, the team's meeting in LDS 1, write-through and count
+// 1, merge 2 to 3) and, throughout, code that runs once out of a cold instruction cache.  A layer in microseconds, shares
+// across contexts or chunks by one wave -> this rule: 32q/8kv x 128, 3 contexts of 512..8192 rows 18.9 -> 16.2, 8 of
+// 32..2000 18.9 -> 15.3, 19 of 70..84 9.7 -> 8.1; 12q/2kv x 128, 17 of 1200..1455 19.8 -> 15.8; 16q/1kv x 256, 3 of
+// 700..924 25.0 -> 16.9, 30 of 32..1000 29.0 -> 18.1, 100 30.8 -> 22.8; 64q/8kv x 128 e4m3, 22 of 2000..4793 44.6 -> 41.7,
+// 25 of 60..1106 21.4 -> 18.9.
+#define S3_FEW_CONTEXTS 256
+struct ChunkPlan {
+    int units, least;  // per column: chunks that run at once, and tiles below which a chunk is not cut (0 units: no chunks)
+    int team;
+};
+// Tiles per chunk, if n / 4 * quarters chunks beyond tiles / per are allowed for (contexts do not divide evenly; 4: always enough).
+__device__ __forceinline__ int chunk_tiles(const AttnArgs &a, const ChunkPlan &p, int tiles, int quarters) {
+    const int room = min(p.units - ((a.n * quarters + 3) >> 2), a.max_shares);
+    return max(not_below(tiles, max(room, 1)), p.least);
+}
+// One wave a chunk: the wave that merges a context reads its pieces a few per memory round trip while their tiles stream
+// side by side, so with `merge_cost` tiles' worth of time per piece (see launch_gqa_mfma) no finer than sqrt(merge_cost *
+// tiles of a context); not for chunks beyond 64 KiB of K rows (shares then) or contexts of more than 12 pieces on average.
+// A team a chunk: no finer than sqrt(1.3 * tiles) or 8 tiles, and contexts of up to 14 tiles whole (one context of 1100
+// rows, 32q/8kv x 128, chunks of 4, 8, 12, 16 tiles: 12.6, 11.4, 12.4, 13.1 us; 3 of 512..8192: 18.7, 18.7, 16.8, 15.7, 24:
+// 16.6; 16q/1kv x 256, 3 of 700..924: 18.9, 17.8, 18.6, 19.4; 11 of 20..211 rows cut at 8 tiles 10.4, whole 9.5).
+// Between the two: the longest wave's tiles, and that a team's four waves merge groups of more than four heads faster
+// than one wave does, which small groups' teams lose again at their meeting (16q/8kv x 128 e4m3, 40 contexts of
+// 100..1500: waves with 5 tiles 22.1 us, with 5.75 in teams 23.6; 40q/5kv x 128, 30 of 100..2000: 8 tiles 28.8, 5.5 in teams
+// 24.0).  That no more than half a chunk a context is allowed for to begin with (the count on the device tells):
+// 40q/5kv 25.1 -> 24.2, 64q/8kv e4m3, 22 of 2000..4793, 43.3 -> 41.7.
 template <int TR, int ROW_BYTES>
-__device__ __forceinline__ int chunk_plan(const AttnArgs &a, int tiles) {
-    if (a.share_rows > 0) return a.share_rows / TR;   // the caller's choice (a multiple of 32)
-    const int room = min(a.wave_shares - a.n, a.max_shares);  // chunks beyond one per context, per column
-    if (a.n > 256 || a.max_shares <= 1 || room <= 0) return 0;
-    const int even = (tiles + room - 1) / room;
-    const float average = (float)tiles / (float)a.n;
-    const int per = max(even, (int)__builtin_amdgcn_sqrtf(a.merge_cost * 1.5f * average) + 1);
-    return per <= 65536 / ROW_BYTES / TR && average <= 12.f * (float)per ? per : 0;
+__device__ __forceinline__ ChunkPlan chunk_plan(const AttnArgs &a, int tiles, int longest) {
+    ChunkPlan one = {0, 0, 1}, four = {0, 0, 4};
+    if (a.max_shares <= 1) return one;
+    const float average = (float)tiles * __builtin_amdgcn_rcpf((float)a.n);
+    int per = 0;
+    if (a.wave_shares > a.n) {
+        one.units = a.wave_shares;
+        one.least = (int)__builtin_amdgcn_sqrtf(a.merge_cost * 1.5f * average) + 1;
+        per = chunk_tiles(a, one, tiles, 2);
+        if (per > 65536 / ROW_BYTES / TR || average > 12.f * (float)per) one.units = 0;
+    }
+    if (a.team_shares > a.n) {
+        four.units = a.team_shares;
+        const bool whole = longest <= 14;
+        four.least = whole ? longest : max(8, (int)__builtin_amdgcn_sqrtf(1.3f * average));
+        const int bonus = whole ? 8 : a.merge_cost < 0.5f ? -6 : 8;
+        if (chunk_tiles(a, four, tiles, 2) <= (one.units > 0 ? 4 * per + bonus : 4 * not_below(tiles, a.wave_shares) + 16)) return four;
+    }
+    return one;
+}
+
+// The view of few contexts, and how they are divided: every wave of the workgroup builds all of it by itself and writes the
+// same values to the same words, so that nothing waits at a barrier before its first load (a wave reads behind its own writes).
+// Lane l owns entries E*l .. E*l+E-1.
+template <int E, int TR, int ROW_BYTES>
+__device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int &tiles, int &longest, int &per, int &team) {
+    const int lane = threadIdx.x & 63;
+    BatchView v;
+    int64_t *off_s = (int64_t *)dyn;
+    int *len_s = (int *)(dyn + (size_t)a.n * 8), *pre = len_s + ((a.n + 1) & ~1);
+    v.off = off_s;
+    v.len = len_s;
+    v.pre = pre;
+    v.n = a.n;
+    v.ncls = 1;
+    v.mean = v.chunk = 0;
+    int64_t off[E];
+    int len[E], cnt[E], sum = 0, most = 0;
+    load_entries<E>(a, lane * E, off, len);
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        cnt[e] = (len[e] + TR - 1) / TR;
+        sum += cnt[e];
+        most = max(most, cnt[e]);
+    }
+    int incl = wave_inclusive_scan(sum);
+    tiles = __builtin_amdgcn_readlane(incl, 63);
+    ChunkPlan plan = {0, 0, 1};
+    longest = wave_max_nonneg(most);
+    per = a.share_rows / TR;  // the caller's choice (a multiple of 32)
+    if (per == 0) plan = chunk_plan<TR, ROW_BYTES>(a, tiles, longest);
+    team = plan.team;
+#pragma unroll 1
+    for (int quarters = 2; per > 0 || plan.units > 0; quarters++) {
+        if (plan.units > 0) per = chunk_tiles(a, plan, tiles, quarters);
+        sum = 0;
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            cnt[e] = quotient((len[e] + TR - 1) / TR + per - 1, per);
+            sum += cnt[e];
+        }
+        incl = wave_inclusive_scan(sum);
+        if (plan.units == 0 || quarters == 4 || __builtin_amdgcn_readlane(incl, 63) <= min(plan.units, a.max_shares + a.n)) break;
+    }
+    v.total = __builtin_amdgcn_readlane(incl, 63);
+    int run = incl - sum;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int b = lane * E + e;
+        if (b < a.n) {
+            off_s[b] = off[e];
+            len_s[b] = len[e];
+            pre[b] = run;
+        }
+        run += cnt[e];
+    }
+    if (lane == 63) pre[a.n] = v.total;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return v;
 }
 
 // How a launch divides its rows: `shares` equal runs of tiles per column, share k = tiles
@@ -191,15 +287,16 @@ struct SharePlan {
 // A team's waves take at least this many rows each: below it, what a share costs whatever its length (the meeting in
 // LDS, the write-through, the count, the merge of the pieces) outweighs the rows.  Three contexts of 512..8192 rows,
 // 32q/8kv x 128, shares of 26 rows a wave: 163 us a pass, 53: 159, 71: 156, 106: 167, 213: 191.
-#define S3_TEAM_MIN_ROWS 64
+#define S3_TEAM_MIN_ROWS 32
 
 // tiles: tiles of TR rows per column.
 template <int TR>
-__device__ __forceinline__ SharePlan share_plan(const AttnArgs &a, int tiles) {
+__device__ __forceinline__ SharePlan share_plan(const AttnArgs &a, int tiles, int longest) {
     SharePlan sp;
     sp.tiles = tiles;
     sp.team = 1;
-    sp.whole = a.max_shares == 0 || (a.max_len <= 256 && (int64_t)tiles * a.wave_shares <= 2 * (int64_t)a.n * a.n);
+    const bool few_rows = tiles < a.wave_shares * (S3_TEAM_ROWS / TR);
+    sp.whole = a.max_shares == 0 || (longest <= (few_rows ? 12 : 16) && (few_rows || (int64_t)tiles * a.wave_shares <= 2 * (int64_t)a.n * a.n));
     int shares = sp.whole ? a.wave_shares : min(a.wave_shares, a.max_shares);
     if (a.team_lds && !sp.whole && tiles < shares * (S3_TEAM_ROWS / TR)) {
         sp.team = 4;
@@ -223,32 +320,6 @@ __device__ __forceinline__ void pieces_of(const SharePlan &sp, int t0, int t1, i
     count = (share_of(sp, t1 - 1) >> sh) - first + 1;
 }
 
-// A context of which this wave or team has left a piece in memory: its pieces are `count` (0: nothing left), by the
-// publishing units first, first + 1, ...; unit u keeps its piece of context b in partial slot u + b (along the
-// shares either u or b grows from one piece to the next, so no two pieces meet).
-struct Pending {
-    int b, first, count;
-};
-
-// This wave (its team) has written the pieces p0 and p1 (count 0: none): count them on their contexts' arrival
-// counters, both in one round trip; bit k of the result: the last piece of p_k's context has arrived, and this wave
-// merges it.  See chunk_arrived() for the two orderings.
-__device__ __forceinline__ unsigned pieces_arrived(const AttnArgs &a, const Pending &p0, const Pending &p1, int columns, int col) {
-    const int lane = threadIdx.x & 63;
-    if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the partial stores have completed
-    const int count = lane == 0 ? p0.count : p1.count;
-    unsigned int *cnt = a.arrivals + (int64_t)(lane == 0 ? p0.b : p1.b) * columns + col;
-    bool mine = false;
-    if (lane < 2 && count != 0) {
-        mine = atomicAdd(cnt, 1u) == (unsigned int)(count - 1);
-        if (mine) atomicExch(cnt, 0u);  // leave the counter clean for the next launch
-    }
-    const unsigned who = (unsigned)__builtin_amdgcn_ballot_w64(mine);
-    if (a.merge_sync && who != 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return who;
-}
-
 // Merge the pieces of query heads hq0 .. hq0+nh-1 of a context and store the final rows; by a wave (nthr 64) or by
 // the four waves of a workgroup in step (nthr 256).  A workgroup with at least a thread per quad of elements
 // takes one quad a thread and deals the pieces over what threads are spare, which meet in LDS (6 floats per thread).
@@ -262,10 +333,12 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
     char *out = (char *)a.out;
     const int64_t out0 = ((int64_t)p.b * a.Hq + hq0) * D;
     const int quads = nh * (D / 4);
-    if (nthr == 256 && quads <= 256 && p.count > 4) {
+    if (nthr == 256 && quads <= 256 && p.count > 4 && (int64_t)p.count * sacc < (1 << 28)) {  // (below 1 GiB)
         const int splits = min(8, 256 / quads);
         const int split = tid / quads, e = tid - split * quads;
-        const float *ml = pml + 2 * (e / (D / 4)), *acc = pacc + e * 4;
+        const unsigned sml4 = (unsigned)sml * 4, sacc4 = (unsigned)sacc * 4, last = p.count - 1;
+        const __amdgpu_buffer_rsrc_t mls = piece_buffer(pml, last * sml4 + nh * 8), accs = piece_buffer(pacc, last * sacc4 + quads * 16);
+        const unsigned eml = 8 * (e / (D / 4)), eacc = 16 * e;
         __syncthreads();  // an earlier merge has read the LDS
         if (split < splits) {
             constexpr int NP = 8;  // pieces per memory round trip
@@ -277,10 +350,11 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
                 f32x4 av[NP];
 #pragma unroll
                 for (int u = 0; u < NP; u++) {
-                    const int cc = c + u * splits < p.count ? c + u * splits : c;  // (past the end: piece c again, weight 0)
-                    mv[u] = get_coherent2(ml + cc * sml);
-                    av[u] = get_coherent4(acc + cc * sacc);
+                    mv[u] = piece_load2(mls, (c + u * splits) * sml4 + eml);
+                    av[u] = piece_load4(accs, (c + u * splits) * sacc4 + eacc);
                 }
+#pragma unroll
+                for (int u = 0; u < NP; u++) mv[u][0] = c + u * splits < p.count ? mv[u][0] : -INFINITY;
                 float mn = m;
 #pragma unroll
                 for (int u = 0; u < NP; u++) mn = fmaxf(mn, mv[u][0]);
@@ -289,7 +363,7 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
                 o *= alpha;
 #pragma unroll
                 for (int u = 0; u < NP; u++) {
-                    const float w = c + u * splits < p.count ? fast_exp2(mv[u][0] - ref) : 0.f;
+                    const float w = fast_exp2(mv[u][0] - ref);
                     l += w * mv[u][1];
                     o += w * av[u];
                 }
@@ -324,9 +398,9 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
         f32x4 o[EB];
 #pragma unroll
         for (int i = 0; i < EB; i++) {
-            const int e = e0 + i * nthr < quads ? e0 + i * nthr : e0;
-            eml[i] = 2 * (e / (D / 4));
-            eacc[i] = 4 * e;
+            const int e = e0 + i * nthr;  // (past the last quad: past the end of a piece)
+            eml[i] = 8 * (e / (D / 4));
+            eacc[i] = 16 * e;
             m[i] = -INFINITY;
             l[i] = 0.f;
             o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -337,14 +411,19 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
             f32x4 av[EB][NP];
 #pragma unroll
             for (int u = 0; u < NP; u++) {
-                const int cc = c + u < p.count ? c + u : c;  // (past the end: piece c again, weight 0)
-                const float *um = pml + cc * sml, *ua = pacc + cc * sacc;
+                const bool there = c + u < p.count;
+                const __amdgpu_buffer_rsrc_t mls = piece_buffer(pml + (c + u) * sml, there ? nh * 8 : 0);
+                const __amdgpu_buffer_rsrc_t accs = piece_buffer(pacc + (c + u) * sacc, there ? quads * 16 : 0);
 #pragma unroll
                 for (int i = 0; i < EB; i++) {
-                    mv[i][u] = get_coherent2(um + eml[i]);
-                    av[i][u] = get_coherent4(ua + eacc[i]);
+                    mv[i][u] = piece_load2(mls, eml[i]);
+                    av[i][u] = piece_load4(accs, eacc[i]);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < NP; u++)
+#pragma unroll
+                for (int i = 0; i < EB; i++) mv[i][u][0] = c + u < p.count ? mv[i][u][0] : -INFINITY;
 #pragma unroll
             for (int i = 0; i < EB; i++) {
                 float mn = m[i];
@@ -355,7 +434,7 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
                 o[i] *= alpha;
 #pragma unroll
                 for (int u = 0; u < NP; u++) {
-                    const float w = c + u < p.count ? fast_exp2(mv[i][u][0] - ref) : 0.f;
+                    const float w = fast_exp2(mv[i][u][0] - ref);
                     l[i] += w * mv[i][u][1];
                     o[i] += w * av[i][u];
                 }
@@ -420,27 +499,28 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int group = a.group, nqb = a.nqb, columns = a.columns;
-    const BatchView bv = build_tile_view<TR>(a, dyn_lds, wave_sums);  // pre[] counts tiles
-    if (blockIdx.x == 0) {
-        if (a.len_out)
-            for (int b = threadIdx.x; b < a.n; b += 256) a.len_out[b] = a.cur_len[b] + 1;
-    }
-    // the zero rows of empty or refused contexts, by the workgroups in turn
-#pragma unroll 1
-    for (int b = blockIdx.x; b < a.n; b += gridDim.x) {
-        if (bv.len[b] == 0) {
-            const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (int e = threadIdx.x; e < a.Hq * D / 8; e += 256) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
+    // pre[] counts tiles, or (per > 0) chunks of `per` tiles
+    int tiles, longest, per, team = 1;  // (longest: tiles of the longest context)
+    BatchView bv;
+    if (a.n <= S3_FEW_CONTEXTS) {
+        bv = a.n <= 64 ? few_view<1, TR, D * EB>(a, dyn_lds, tiles, longest, per, team) : few_view<S3_FEW_CONTEXTS / 64, TR, D * EB>(a, dyn_lds, tiles, longest, per, team);
+    } else {
+        bv = build_tile_view<TR>(a, dyn_lds, wave_sums, longest);
+        tiles = __builtin_amdgcn_readfirstlane(bv.total);
+        longest = (__builtin_amdgcn_readfirstlane(longest) + TR - 1) / TR;
+        per = a.share_rows / TR;  // the caller's chunks (0: none)
+        if (per == 0) {
+            const ChunkPlan plan = chunk_plan<TR, D * EB>(a, tiles, longest);
+            if (plan.units > 0) per = chunk_tiles(a, plan, tiles, 4);
+            team = plan.team;
         }
     }
-    const int tiles = __builtin_amdgcn_readfirstlane(bv.total);
-    if (tiles == 0) return;  // the whole grid alike
-    const int per = chunk_plan<TR, D * EB>(a, tiles);
-    int chunks = 0;  // chunks of `per` tiles in a column; pre[] then counts them
     SharePlan sp = {tiles, 1, tiles, 0, 1, false};
+    int chunks = __builtin_amdgcn_readfirstlane(bv.total);
     if (per == 0) {
-        sp = share_plan<TR>(a, tiles);
-    } else {
+        sp = share_plan<TR>(a, tiles, longest);
+        team = sp.team;
+    } else if (a.n > S3_FEW_CONTEXTS) {
         chunks = __builtin_amdgcn_readfirstlane(chunk_prefix(a.n, bv.len, TR * per, (int *)bv.pre, wave_sums));
     }
 
@@ -459,13 +539,13 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     const bool stream_k = a.stream_k < 0 ? (int64_t)tiles * TR * rstride > ((int64_t)256 << 20) : a.stream_k != 0;
 
     // (shares * columns tiles of at least 2 KiB lie in the arena: below 2^31 on any device)
-    const int team = per > 0 ? 1 : sp.team;
-    const unsigned units = (unsigned)(per > 0 ? chunks : team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
+    const unsigned units = tiles == 0 ? 0u : (unsigned)(per > 0 ? chunks : team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
     const unsigned step = team == 4 ? gridDim.x : gridDim.x * 4;
     // (chunks: one wave on every compute unit before any unit gets a second one)
 #pragma unroll 1
-    for (unsigned unit = per > 0 ? wave * gridDim.x + blockIdx.x : team == 4 ? blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
-        const int pub = __builtin_amdgcn_readfirstlane(unit / columns);  // publishing unit: this wave's share or its team
+    for (unsigned unit = team == 4 ? blockIdx.x : per > 0 ? wave * gridDim.x + blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
+        // publishing unit: this wave's share or chunk, or its team's
+        const int pub = __builtin_amdgcn_readfirstlane(a.column_shift >= 0 ? unit >> a.column_shift : unit / columns);
         const int col = __builtin_amdgcn_readfirstlane(unit - (unsigned)pub * columns);
         const int hk = nqb == 1 ? col : col / nqb, qb = col - hk * nqb;
         const int head = qb * 16 + n;  // query head of this lane's column, within the group
@@ -481,9 +561,14 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
             chunk = pub - first;
             const int all = (__builtin_amdgcn_readfirstlane(bv.len[seq]) + TR - 1) / TR;
             // near-equal pieces, none of them empty: the first all % nchunks have a tile more
-            const int base = all / max(nchunks, 1), rem = all - base * nchunks;
+            const int base = quotient(all, max(nchunks, 1)), rem = all - base * nchunks;
             t_begin = chunk * base + min(chunk, rem);
             t_stop = t_begin + base + (chunk < rem ? 1 : 0);
+            if (team == 4) {  // a quarter each
+                const int quarter = (t_stop - t_begin) >> 2, more = (t_stop - t_begin) & 3;
+                t_begin += wave * quarter + min(wave, more);
+                t_stop = t_begin + quarter + (wave < more ? 1 : 0);
+            }
         } else {
             const int share = team == 4 ? pub * 4 + wave : pub;
             if (share < sp.shares) {
@@ -790,74 +875,109 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
         }
         if (team == 4) {
             __syncthreads();  // the pieces are in LDS
-            // Pieces of one context are neighbours: a run.  First the weight of every piece and the sum of every run ...
-            const int pb = piece_b[lane & 7];
-            int first8 = 0, count8 = 0;  // lane k: the publishing units of piece k's context
-            if (pb >= 0) pieces_of(sp, bv.pre[pb], bv.pre[pb + 1], first8, count8);
-            if (threadIdx.x < 128) {
-                const int k = threadIdx.x >> 4, h = threadIdx.x & 15;
-                const int mine = piece_b[k];
-                const float2 me = piece_ml[k][h];
-                float2 x[8];
-#pragma unroll
-                for (int j = 0; j < 8; j++) x[j] = piece_ml[j][h];
-                float m = me.x, l = 0.f;
-#pragma unroll
-                for (int j = 0; j < 8; j++)
-                    if (__builtin_amdgcn_readlane(pb, j) == mine) m = fmaxf(m, x[j].x);
-                const float ref = exp_reference(m);
-#pragma unroll
-                for (int j = 0; j < 8; j++)
-                    if (__builtin_amdgcn_readlane(pb, j) == mine) l += fast_exp2(x[j].x - ref) * x[j].y;
-                if (mine >= 0) piece_run[k][h] = (f32x4){fast_exp2(me.x - ref), m, l, 1.f / l};
-            }
-            __syncthreads();
-            // ... then the rows, all threads together, every thread EB quads of elements at once
-            constexpr int EB = D / 64;
-            int h[EB], d[EB];
-#pragma unroll
-            for (int i = 0; i < EB; i++) {
-                const int e = min((int)threadIdx.x + i * 256, nheads * (D / 4) - 1);
-                h[i] = e / (D / 4);
-                d[i] = (e % (D / 4)) * 4;
-            }
+            if (per > 0) {
+                // The quarters of one chunk, left where each wave wrote its last piece; waves 0 .. k-1 had rows.
+                const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < 4 && piece_b[2 * (lane & 3) + 1] >= 0));
+                if (k > 1 || nchunks > 1) {
 #pragma unroll 1
-            for (int k = 0; k < 8;) {
-                const int b = __builtin_amdgcn_readlane(pb, k);
-                if (b < 0) {
-                    k++;
-                    continue;
-                }
-                const int first = __builtin_amdgcn_readlane(first8, k), count = __builtin_amdgcn_readlane(count8, k);
-                f32x4 o[EB], r[EB];
+                    for (int e = threadIdx.x; e < nheads * (D / 4); e += 256) {
+                        const int h = e / (D / 4), d = (e % (D / 4)) * 4;
+                        float m = -INFINITY, l = 0.f;
+                        float2 x[4];
 #pragma unroll
-                for (int i = 0; i < EB; i++) o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-                for (; k < 8; k++) {
-                    const int kb = __builtin_amdgcn_readlane(pb, k);
-                    if (kb < 0) continue;
-                    if (kb != b) break;
-                    const float *src = (k & 1) ? (const float *)wave_lds[k >> 1] : first_piece + ((k >> 1) - wave) * piece_heads * PSTRIDE;
+                        for (int w = 0; w < 4; w++) {
+                            x[w] = w < k ? piece_ml[2 * w + 1][h] : make_float2(-INFINITY, 0.f);
+                            m = fmaxf(m, x[w].x);
+                        }
+                        const float ref = exp_reference(m);
+                        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int i = 0; i < EB; i++) {
-                        r[i] = piece_run[k][h[i]];
-                        o[i] += r[i][0] * *(const f32x4 *)(src + h[i] * PSTRIDE + d[i]);
+                        for (int w = 0; w < 4; w++) {
+                            if (w >= k) break;
+                            const float wt = fast_exp2(x[w].x - ref);
+                            l += wt * x[w].y;
+                            o += wt * *(const f32x4 *)((const float *)wave_lds[w] + h * PSTRIDE + d);
+                        }
+                        if (nchunks == 1) {
+                            store_out4(a.out, a.out_dtype, ((int64_t)seq * a.Hq + hq0) * D + 4 * e, o * (1.f / l));
+                        } else {
+                            const int64_t pi = (int64_t)pub * a.Hq + hq0 + h;
+                            if (d == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){m, l});
+                            put_partial4<true>(a.part_acc + pi * D + d, o);
+                        }
                     }
+                    if (nchunks > 1) pend0 = Pending{seq, pub - chunk - seq, nchunks};
                 }
+            } else {
+                // Pieces of one context are neighbours: a run.  First the weight of every piece and the sum of every run ...
+                const int pb = piece_b[lane & 7];
+                int first8 = 0, count8 = 0;  // lane k: the publishing units of piece k's context
+                if (pb >= 0) pieces_of(sp, bv.pre[pb], bv.pre[pb + 1], first8, count8);
+                if (threadIdx.x < 128) {
+                    const int k = threadIdx.x >> 4, h = threadIdx.x & 15;
+                    const int mine = piece_b[k];
+                    const float2 me = piece_ml[k][h];
+                    float2 x[8];
+#pragma unroll
+                    for (int j = 0; j < 8; j++) x[j] = piece_ml[j][h];
+                    float m = me.x, l = 0.f;
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        if (__builtin_amdgcn_readlane(pb, j) == mine) m = fmaxf(m, x[j].x);
+                    const float ref = exp_reference(m);
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        if (__builtin_amdgcn_readlane(pb, j) == mine) l += fast_exp2(x[j].x - ref) * x[j].y;
+                    if (mine >= 0) piece_run[k][h] = (f32x4){fast_exp2(me.x - ref), m, l, 1.f / l};
+                }
+                __syncthreads();
+                // ... then the rows, all threads together, every thread EB quads of elements at once
+                constexpr int EB = D / 64;
+                int h[EB], d[EB];
 #pragma unroll
                 for (int i = 0; i < EB; i++) {
-                    if ((int)threadIdx.x + i * 256 >= nheads * (D / 4)) continue;
-                    if (count == 1) {
-                        store_out4(a.out, a.out_dtype, ((int64_t)b * a.Hq + hq0 + h[i]) * D + d[i], o[i] * r[i][3]);
-                    } else {
-                        const int64_t pi = (int64_t)(pub + b) * a.Hq + hq0 + h[i];
-                        if (d[i] == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){r[i][1], r[i][2]});
-                        put_partial4<true>(a.part_acc + pi * D + d[i], o[i]);
-                    }
+                    const int e = min((int)threadIdx.x + i * 256, nheads * (D / 4) - 1);
+                    h[i] = e / (D / 4);
+                    d[i] = (e % (D / 4)) * 4;
                 }
-                if (count > 1) {
-                    if (pend0.count == 0) pend0 = Pending{b, first, count};
-                    else pend1 = Pending{b, first, count};
+#pragma unroll 1
+                for (int k = 0; k < 8;) {
+                    const int b = __builtin_amdgcn_readlane(pb, k);
+                    if (b < 0) {
+                        k++;
+                        continue;
+                    }
+                    const int first = __builtin_amdgcn_readlane(first8, k), count = __builtin_amdgcn_readlane(count8, k);
+                    f32x4 o[EB], r[EB];
+#pragma unroll
+                    for (int i = 0; i < EB; i++) o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (; k < 8; k++) {
+                        const int kb = __builtin_amdgcn_readlane(pb, k);
+                        if (kb < 0) continue;
+                        if (kb != b) break;
+                        const float *src = (k & 1) ? (const float *)wave_lds[k >> 1] : first_piece + ((k >> 1) - wave) * piece_heads * PSTRIDE;
+#pragma unroll
+                        for (int i = 0; i < EB; i++) {
+                            r[i] = piece_run[k][h[i]];
+                            o[i] += r[i][0] * *(const f32x4 *)(src + h[i] * PSTRIDE + d[i]);
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < EB; i++) {
+                        if ((int)threadIdx.x + i * 256 >= nheads * (D / 4)) continue;
+                        if (count == 1) {
+                            store_out4(a.out, a.out_dtype, ((int64_t)b * a.Hq + hq0 + h[i]) * D + d[i], o[i] * r[i][3]);
+                        } else {
+                            const int64_t pi = (int64_t)(pub + b) * a.Hq + hq0 + h[i];
+                            if (d[i] == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){r[i][1], r[i][2]});
+                            put_partial4<true>(a.part_acc + pi * D + d[i], o[i]);
+                        }
+                    }
+                    if (count > 1) {
+                        if (pend0.count == 0) pend0 = Pending{b, first, count};
+                        else pend1 = Pending{b, first, count};
+                    }
                 }
             }
             if (pend0.count != 0) {  // uniform over the workgroup
@@ -881,6 +1001,18 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 for (int k = 0; k < 2; k++)
                     if ((mine >> k) & 1) merge_pieces<D>(a, k ? pend1 : pend0, hq0, nheads, lane, 64, nullptr);
             }
+        }
+    }
+    // What belongs to no row, behind the work: the new lengths (the last workgroup has none in a launch of few rows) ...
+    if (a.len_out && blockIdx.x == gridDim.x - 1) {
+        for (int b = threadIdx.x; b < a.n; b += 256) a.len_out[b] = a.cur_len[b] + 1;
+    }
+    // ... and the zero rows of empty or refused contexts, by the workgroups in turn
+#pragma unroll 1
+    for (int b = blockIdx.x; b < a.n; b += gridDim.x) {
+        if (bv.len[b] == 0) {
+            const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int e = threadIdx.x; e < a.Hq * D / 8; e += 256) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
         }
     }
 }

@@ -815,6 +815,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     args.group = Hq / Hkv;
     args.nqb = (args.group + 15) / 16;
     args.columns = (int32_t)columns;
+    args.column_shift = (columns & (columns - 1)) == 0 ? __builtin_ctzll((unsigned long long)columns) : -1;
     // What one more piece costs the wave that merges a context, in tiles streamed by one wave: a memory round trip of
     // about two tiles brings two quads of elements a lane of six pieces (D 256: four quads of three).
     const int eb = D == 256 ? 4 : 2, quads = (int)group16 * (D / 4), passes = (quads + 64 * eb - 1) / (64 * eb);

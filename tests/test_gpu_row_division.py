@@ -1,11 +1,6 @@
 """The matrix-core kernel divides the rows of a batch evenly over its waves, across the borders of contexts: every way
-a share can begin, end and be merged, against the fp32 oracle (max-abs 2e-3 / relative L2 1e-3, as everywhere).  Plus
-the cache bits of the loads that merge the pieces, read off the emitted code (no GPU needed for that one)."""
-import os
-import re
-import shutil
-import subprocess
-
+a share can begin, end and be merged, against the fp32 oracle (max-abs 2e-3 / relative L2 1e-3, as everywhere); and few
+contexts into chunks, by one wave or four."""
 import numpy as np
 import pytest
 
@@ -13,8 +8,6 @@ from paper_2306_06000_amd import binding as s3
 from tests.harness import assert_close
 
 torch = pytest.importorskip("torch")
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-
 FAMS = [
     ("d64 group 3", 24, 8, 64, s3.S3_BF16, s3.S3_BF16, 1),
     ("d128 group 4", 32, 8, 128, s3.S3_BF16, s3.S3_BF16, 2),
@@ -100,16 +93,71 @@ def test_short_contexts_around_the_fixed_buffers_size(n):
     rig.close()
 
 
-def test_merging_loads_bypass_the_caches(tmp_path):
-    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
-    if not os.path.exists(hipcc):
-        pytest.skip("no hipcc here")
-    src = tmp_path / "probe.hip"
-    src.write_text('#include "s3kv_device.h"\n__global__ void probe(const float *p, float *out) {\n'
-                   "    const f32x4 a = get_coherent4(p + 4 * threadIdx.x);\n    out[threadIdx.x] = a[0] + a[1] + a[2] + a[3];\n}\n")
-    asm = tmp_path / "probe.s"
-    subprocess.run([hipcc, "-O3", "-std=c++17", "--offload-arch=gfx950", "--cuda-device-only", "-S", "-I",
-                    os.path.join(ROOT, "paper_2306_06000_amd", "csrc"), "-I", os.path.join(ROOT, "include"), "-x", "hip", str(src), "-o", str(asm)],
-                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
-    loads = re.findall(r"(?:global|flat)_load_dwordx[24] .*", asm.read_text())
-    assert loads and all("sc0" in x and "sc1" in x for x in loads), loads
+# (tiles of 16 rows, of 32 where a cached row of one head has at most 128 bytes; columns decide how many chunks run at once)
+FEW = [
+    ("a wave each, a row to a tile", [1, 15, 16, 17, 31, 32, 33]),
+    ("quarters: one to five tiles", [64, 65, 79, 80, 128, 129, 160, 161, 0]),
+    ("the longest whole one", [224, 223, 100, 448, 7]),
+    ("one beyond it", [225, 449, 100, 7]),
+    ("two long among short", [5, 2047, 40, 1700, 0, 1]),
+    ("64", [130 + 9 * (b % 7) for b in range(64)]),
+    ("65", [130 + 9 * (b % 7) for b in range(64)] + [1500]),
+    ("256", [(37 * b) % 160 for b in range(255)] + [900]),
+    ("257", [(37 * b) % 160 for b in range(256)] + [900]),
+    ("as many as run at once", [300] * 63 + [17]),
+    ("contexts that divide badly", [257] * 40 + [300] * 8),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fam", FAMS, ids=[f[0] for f in FAMS])
+def test_few_contexts_by_waves_and_teams(fam):
+    """Chunks of single contexts, each by one wave or by the four waves of a workgroup: tile and quarter edges, the
+    borders of the rule (contexts taken whole, one view entry or four per lane, the largest batch it takes), few and
+    many chunks, in both orderings of the merge and on grids that make a workgroup take many; launch after launch."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    name, H, Hkv, D, kvt, act, kind = fam
+    for what, lens in FEW:
+        rng = np.random.default_rng(len(lens) + D)
+        rig = EdgeRig(fam, lens, M=2048)
+        rig.put([rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens],
+                [rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens])
+        if kind == 1:
+            assert s3.s3_kv_set_param(rig.a, "variant", s3.s3_kv_get_param(rig.a, "n_variants")[1] - 1) == 0
+        q = rng.standard_normal((len(lens), H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / {what}")
+        for grid, sync in ((1, 0), (5, 1), (0, 1), (0, 0)):
+            assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0 and s3.s3_kv_set_param(rig.a, "merge_sync", sync) == 0
+            assert np.array_equal(rig.attend(q)[1], att), (name, what, grid, sync)
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, rng.standard_normal((len(lens), Hkv, D), dtype=np.float32), rng.standard_normal((len(lens), Hkv, D), dtype=np.float32))
+        assert_close(step, rig.want(qb, longer), f"{name} / {what} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
+        for chunk in (32, 96):
+            assert s3.s3_kv_set_param(rig.a, "chunk", chunk) == 0
+            assert_close(rig.attend(q, lens=longer)[1], rig.want(qb, longer), f"{name} / {what} / chunk {chunk}")
+        rig.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("sync,launches", [(0, 150), (1, 20)])
+def test_soak_of_the_matrix_core_merge(sync, launches):
+    """Many pieces that meet through counters and write-through partials on every compute unit, in shares across contexts
+    and in chunks: the same bits launch after launch, those of the oracle's tolerance."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    for H, Hkv, D, kvt, lens in ((32, 8, 128, s3.S3_BF16, [int(x) for x in np.random.default_rng(8).integers(200, 1000, size=300)]),
+                                 (32, 8, 128, s3.S3_BF16, [2040, 1500, 700]), (16, 1, 256, s3.S3_F16, [1024 - 3 * b for b in range(60)])):
+        rng = np.random.default_rng(len(lens))
+        rig = EdgeRig(("soak", H, Hkv, D, kvt, kvt, 2), lens, M=2048)
+        rows = rng.standard_normal((2048 + 300, Hkv, D), dtype=np.float32)
+        rig.put([rows[b:b + L] for b, L in enumerate(lens)], [rows[300 - b:300 - b + L] for b, L in enumerate(lens)])
+        q = rng.standard_normal((len(lens), H, D), dtype=np.float32)
+        assert s3.s3_kv_set_param(rig.a, "merge_sync", sync) == 0
+        qb, first = rig.attend(q)
+        assert_close(first, rig.want(qb), f"{len(lens)} contexts")
+        for i in range(launches):
+            assert np.array_equal(rig.attend(q)[1], first), (len(lens), i)
+        rig.close()

@@ -270,12 +270,12 @@ def test_compact_validation():
 
 
 def test_write_through_partials_carry_the_cache_bits_the_in_kernel_merge_relies_on(tmp_path):
-    """Chunks of one context that meet inside one launch exchange their partial sums through memory between
-    workgroups on different XCDs (each with its own L2).  The default ordering relies on `volatile` vector
-    stores and loads being emitted as write-through / cache-bypassing accesses on gfx950 (cache bits sc0 sc1)
-    and on the fence-based ordering emitting an L2 write-back before and an invalidate after the counter.
-    This compiles the library's own helpers and reads the bits off the emitted code, so that a compiler
-    change shows up here and not as a rare wrong merge."""
+    """Pieces of one context that meet inside one launch exchange their partial sums through memory between
+    workgroups on different XCDs (each with its own L2).  The default ordering relies on the partials being stored and
+    loaded past the caches (cache bits sc0 sc1), on the wave's memory counter being drained before the count, and on the
+    merging loads being waited for before they are used; the fence-based ordering on an L2 write-back before and an
+    invalidate after the counter.  This compiles the helpers that the kernels use and reads all of it off the emitted
+    code, so that a compiler change shows up here and not as a rare wrong merge."""
     import shutil
     import subprocess
 
@@ -290,15 +290,42 @@ __global__ void probe_put(float *p, float x) {
     put_partial4<true>(p + 4 * threadIdx.x, (f32x4){x, x, x, x});
     put_partial2<true>(p + 4096 + 2 * threadIdx.x, (f32x2){x, x});
 }
-__global__ void probe_get(const float *p, float *out) {
-    const f32x4 a = get_partial4<true>(p + 4 * threadIdx.x);
-    const f32x2 b = get_partial2<true>(p + 4096 + 2 * threadIdx.x);
+template <bool COHERENT>
+__device__ __forceinline__ void all(const float *p, float *out) {
+    const float *ml[4], *acc[4];
+    f32x2 m[4];
+    f32x4 lo[4], hi[4];
+    for (int u = 0; u < 4; u++) {
+        ml[u] = p + 2 * threadIdx.x + 1000 * u;
+        acc[u] = p + 8000 + 8 * threadIdx.x + 2000 * u;
+    }
+    get_partials<COHERENT>(ml, acc, m, lo, hi);
+    float s = 0.f;
+    for (int u = 0; u < 4; u++) s += m[u][0] + m[u][1] + lo[u][0] + lo[u][1] + lo[u][2] + lo[u][3] + hi[u][0] + hi[u][1] + hi[u][2] + hi[u][3];
+    out[threadIdx.x] = s;
+}
+__global__ void probe_get(const float *p, float *out) { all<true>(p, out); }
+__global__ void probe_cached_get(const float *p, float *out) { all<false>(p, out); }
+__global__ void probe_pieces(const float *p, float *out) {
+    const f32x4 a = piece_load4(piece_buffer(p, 4096), 16 * threadIdx.x);
+    const f32x2 b = piece_load2(piece_buffer(p + 8192, 2048), 8 * threadIdx.x);
     out[threadIdx.x] = a[0] + a[1] + a[2] + a[3] + b[0] + b[1];
 }
 __global__ void probe_plain(float *p, float x) { put_partial4<false>(p + 4 * threadIdx.x, (f32x4){x, x, x, x}); }
-__global__ void probe_arrive(AttnArgs a, unsigned int *cnt, int *flag) {
+template <int SYNC>
+__device__ __forceinline__ void arrive(AttnArgs a, unsigned int *cnt, int *flag) {
+    a.merge_sync = SYNC;
     if (chunk_arrived(a, cnt, 2)) flag[threadIdx.x] = 1;
 }
+template <int SYNC>
+__device__ __forceinline__ void arrive_pieces(AttnArgs a, int b, int *flag) {
+    a.merge_sync = SYNC;
+    flag[threadIdx.x] = pieces_arrived(a, Pending{b, 0, 2}, Pending{b + 1, 1, 3}, 8, 1);
+}
+__global__ void probe_drained_chunk(AttnArgs a, unsigned int *cnt, int *flag) { arrive<0>(a, cnt, flag); }
+__global__ void probe_fenced_chunk(AttnArgs a, unsigned int *cnt, int *flag) { arrive<1>(a, cnt, flag); }
+__global__ void probe_drained_piece(AttnArgs a, int b, int *flag) { arrive_pieces<0>(a, b, flag); }
+__global__ void probe_fenced_piece(AttnArgs a, int b, int *flag) { arrive_pieces<1>(a, b, flag); }
 ''')
     csrc = os.path.join(ROOT, "paper_2306_06000_amd", "csrc")
     asm = tmp_path / "probe.s"
@@ -315,16 +342,28 @@ __global__ void probe_arrive(AttnArgs a, unsigned int *cnt, int *flag) {
     put = body("probe_put")
     assert re.search(r"(global|flat)_store_dwordx4 .*\bsc0\b.*\bsc1\b", put), put
     assert re.search(r"(global|flat)_store_dwordx2 .*\bsc0\b.*\bsc1\b", put), put
-    get = body("probe_get")
-    assert re.search(r"(global|flat)_load_dwordx4 .*\bsc0\b.*\bsc1\b", get), get
-    assert re.search(r"(global|flat)_load_dwordx2 .*\bsc0\b.*\bsc1\b", get), get
     plain = body("probe_plain")
-    assert "_store_dwordx4" in plain and "sc0" not in plain  # the bits come from `volatile`, not from every store
-    arrive = body("probe_arrive")
-    # both orderings are in the code (merge_sync picks one at run time): the fenced one writes the L2 back before
-    # the count and invalidates after it; the default drains the wave's memory counter before the count
-    assert "buffer_wbl2" in arrive and "buffer_inv" in arrive and "global_atomic_add" in arrive
-    assert re.search(r"s_waitcnt vmcnt\(0\).*global_atomic_add", arrive, flags=re.S)
+    assert "_store_dwordx4" in plain and "sc0" not in plain  # the bits are the helper's, not every store's
+    # the merge of the multi-head and 8-bit kernels: all twelve loads past the caches, then a wait for all of them
+    get = body("probe_get")
+    loads = re.findall(r"global_load_dwordx[24] .*", get)
+    assert len(loads) == 12 and all("sc0" in x and "sc1" in x for x in loads), loads
+    behind = get[get.rindex(loads[-1]) + len(loads[-1]):].strip().splitlines()
+    assert re.match(r"\s*s_waitcnt vmcnt\(0\)", behind[0]), behind[:3]
+    assert "sc0" not in body("probe_cached_get")
+    # the matrix-core kernel's
+    loads = re.findall(r"(?:buffer|global|flat)_load_dwordx[24] .*", body("probe_pieces"))
+    assert len(loads) == 2 and all(x.startswith("buffer") and "sc0" in x and "sc1" in x for x in loads), loads
+    for what in ("chunk", "piece"):
+        # default: the wave's memory counter is drained right before the count, without any fence
+        drained = body("probe_drained_" + what)
+        assert "buffer_wbl2" not in drained and "buffer_inv" not in drained, drained
+        before = drained[:drained.index("global_atomic_add")]
+        assert re.search(r"s_waitcnt vmcnt\(0\) lgkmcnt\(0\)", before) and "_store_" not in before, drained
+        # fenced: the L2 is written back before the count and invalidated after it
+        fenced = body("probe_fenced_" + what)
+        at = fenced.index("global_atomic_add")
+        assert "buffer_wbl2" in fenced[:at] and "buffer_inv" in fenced[at:], fenced
 
 
 def test_calls_that_touch_rows_refuse_a_metadata_only_arena_without_any_device_call():
