@@ -141,10 +141,13 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
     t[3] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);
 }
 
-// Quotients of small whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here
-// all out of a cold instruction cache).  x / y rounded down: x < 2^20, so that half a unit in x, which keeps the product off
-// the whole numbers, is more than the error.  And a whole number not below x / y (by less than 2 above it), x < 2^28.
-__device__ __forceinline__ int quotient(int x, int y) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y)); }
+// Quotients of whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here all out
+// of a cold instruction cache).  x / y rounded down, exact for x below 2^24: the product is off by less than one, which the
+// remainder puts right.  And a whole number not below x / y, by less than 2 above it where x / y is below 2^19.
+__device__ __forceinline__ int quotient(int x, int y) {
+    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y)), r = x - q * y;
+    return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
+}
 __device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x * __builtin_amdgcn_rcpf((float)y) * 1.000001f) + 1; }
 
 // How a launch of few rows divides them (a batch of at most 256 contexts): every context by itself, into near-equal
@@ -232,7 +235,7 @@ __device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int 
     team = plan.team;
 #pragma unroll 1
     for (int quarters = 2; per > 0 || plan.units > 0; quarters++) {
-        if (plan.units > 0) per = chunk_tiles(a, plan, tiles, quarters);
+        if (plan.units > 0) per = min(chunk_tiles(a, plan, tiles, quarters), max(longest, 1));  // (small numbers for quotient())
         sum = 0;
 #pragma unroll
         for (int e = 0; e < E; e++) {
@@ -511,7 +514,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
         per = a.share_rows / TR;  // the caller's chunks (0: none)
         if (per == 0) {
             const ChunkPlan plan = chunk_plan<TR, D * EB>(a, tiles, longest);
-            if (plan.units > 0) per = chunk_tiles(a, plan, tiles, 4);
+            if (plan.units > 0) per = min(chunk_tiles(a, plan, tiles, 4), max(longest, 1));
             team = plan.team;
         }
     }
