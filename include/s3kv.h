@@ -337,16 +337,16 @@ int s3_kv_probe_bandwidth(s3_arena *a, size_t bytes, int32_t mode, int32_t reps,
  *   "grid_blocks"  workgroups launched (0 = library default)
  *   "variant"      kernel variant index, -1 = default (see get "n_variants"; arenas with shared
  *                  key/value heads have their own, shorter, list)
- *   "merge_sync"   how chunks of one context that meet inside ONE launch (s3_decode_step on multi-head
- *                  caches, 8-bit rows) are ordered across workgroups: 0 (default) write-through partial
+ *   "merge_sync"   how chunks of one context that meet inside ONE launch (every attention kernel but the vector-ALU
+ *                  one of shared heads) are ordered across workgroups: 0 (default) write-through partial
  *                  stores, a drained memory counter and a relaxed counter increment; 1 device-scope
  *                  release / acquire fences around the increment (slower; same results)
  *   "gqa_merge", "gqa_dynamic"  shared key/value heads, matrix-core kernel: accepted (0 or 1; -1..100) and kept for
- *                  callers that set them, without effect: the kernel divides the rows of a batch evenly over its
- *                  waves and always merges the pieces of a context inside the launch
- *   "gqa_stream"   shared key/value heads, matrix-core kernel: how K rows are read: 1 = with the streaming hint
- *                  (whole rows per load, operand layout through LDS), 0 = plain loads straight into operand layout,
- *                  -1 (default) = 1 if the launch's K rows exceed the 256 MB memory-side cache, else 0; same results
+ *                  callers that set them, without effect: the kernel divides the rows of a batch by their number and
+ *                  always merges the pieces of a context inside the launch
+ *   "gqa_stream"   shared key/value heads, matrix-core kernel: K rows are read with the streaming hint (1), with
+ *                  plain loads (0), or (-1, default) with the hint if the launch's K rows exceed the 256 MB
+ *                  memory-side cache; same results
  *   "profile"      k > 0: every k-th attention launch (counted from this call) carries HIP events that
  *                  take the kernel's own start and end times (hipExtLaunchKernel); 0: off; both reset the sums
  * get names: the above plus "default_variant", "kernel_kind" (0 multi-head kernels, 1 shared-K/V vector-ALU kernel,

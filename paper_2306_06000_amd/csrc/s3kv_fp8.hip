@@ -253,9 +253,9 @@ __global__ void __launch_bounds__(TS * 64) attn_fp8_kernel(const AttnArgs a) {
             }
         }
         if (ts == 0 && it.nchunks > 1) {
-            // Chunks meet through an arrival counter per (sequence, head group), as in the fused multi-head
-            // step: whoever delivers the last chunk merges them.  With the default chunk of 1024 rows this is
-            // rare, which is what makes it cheaper than a merge launch after every attention launch.
+            // Chunks meet through an arrival counter per (sequence, head group), as in the multi-head kernels:
+            // whoever delivers the last chunk merges them (a batch of few contexts is cut by its rows, a larger one only
+            // beyond 1024 rows a context), without a merge launch after every attention launch.
             unsigned int *cnt = a.arrivals + (int64_t)it.b * n_hg + it.hgb;
             if (chunk_arrived(a, cnt, it.nchunks)) {
                 if (h_ok && tsub == 0) {

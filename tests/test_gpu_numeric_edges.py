@@ -365,11 +365,11 @@ def test_worked_example_model_shape_runs_through_the_library():
 # ---------------------------------------------------------------- the merge inside one launch, many times
 @pytest.mark.parametrize("sync,launches,variant", [(0, 200, -1), (1, 40, -1), (0, 120, 10), (1, 20, 10), (0, 40, 12),
                                                    (0, 120, 14), (1, 20, 14), (0, 40, 16)])
-def test_soak_of_the_in_kernel_merge_equals_the_two_kernel_path(sync, launches, variant):
+def test_soak_of_the_in_kernel_merge(sync, launches, variant):
     """Many contexts of many chunks, a grid that covers every compute unit (all XCDs), the same step
-    launched again and again: the output of the fused step (chunks meet through arrival counters and
-    write-through partials inside the launch) must equal, bit for bit, the two-kernel path (partials with
-    plain stores, merged by a second launch) every time.  Stops at the first mismatch.  Also with the dynamic
+    launched again and again: chunks meet through arrival counters and write-through partials inside the launch.
+    The reference is append + attention, whose chunks meet in the same way: it is held to the oracle's tolerance, and
+    every launch of the step must equal it bit for bit.  Stops at the first mismatch.  Also with the dynamic
     work list (variant 10: positions claimed from a device-wide counter that every launch must leave at zero)
     and with rows staged through the LDS ring (variant 12), on grids smaller and larger than the list; and with
     the row stream carried from one item into the next (variants 14, 16: positions claimed two items ahead)."""
@@ -386,15 +386,19 @@ def test_soak_of_the_in_kernel_merge_equals_the_two_kernel_path(sync, launches, 
     assert s3.s3_kv_set_param(rig.a, "variant", variant) == 0
     cus = s3.s3_kv_get_param(rig.a, "num_cus")[1]
     assert cus >= 8
-    q, k_new, v_new = (device_bits(wl.normal_bits(rng, (n, H, D), dtype), TDT[dtype], DEV) for _ in range(3))
+    qb, kb, vb = (wl.normal_bits(rng, (n, H, D), dtype) for _ in range(3))
+    q, k_new, v_new = (device_bits(x, TDT[dtype], DEV) for x in (qb, kb, vb))
     pos_d = torch.tensor(lens, dtype=torch.int32, device=DEV)
     len1_d = pos_d + 1
     len_out = torch.zeros(n, dtype=torch.int32, device=DEV)
-    # reference: append, then attention + merge kernel
+    # reference: append, then attention; checked against the oracle
     assert s3.s3_kv_append(rig.a, 0, n, rig.off_d, pos_d, k_new, v_new, rig.stream) == 0
     ref = torch.empty((n, H, D), dtype=torch.float32, device=DEV)
     assert s3.s3_decode_attention(rig.a, 0, n, q, rig.off_d, len1_d, ref, s3.S3_F32, 0.0, rig.stream) == 0
     torch.cuda.synchronize()
+    for b, sid in enumerate(rig.ids.tolist()):
+        assert rig.o.append(sid, 0, lens[b], kb[b], vb[b]) == 0
+    assert_close(ref.cpu().numpy(), rig.want(qb, [L + 1 for L in lens]), "append + attention")
     out = torch.empty_like(ref)
     for grid in (0, 2 * cus, 8 * cus, 7, 100000):
         assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0
@@ -402,18 +406,19 @@ def test_soak_of_the_in_kernel_merge_equals_the_two_kernel_path(sync, launches, 
             out.fill_(float("nan"))
             assert s3.s3_decode_step(rig.a, 0, n, rig.off_d, pos_d, q, k_new, v_new, out, s3.S3_F32, 0.0, len_out,
                                      rig.stream) == 0
-            assert torch.equal(out, ref), f"merge_sync {sync} grid {grid}: launch {i} differs from the two-kernel path"
+            assert torch.equal(out, ref), f"merge_sync {sync} grid {grid}: launch {i} differs from append + attention"
     rig.close()
 
 
 @pytest.mark.parametrize("variant", [14, 15, 16, 17])
 @pytest.mark.parametrize("H,D,dtype", [(16, 256, s3.S3_F16), (12, 128, s3.S3_BF16), (8, 96, s3.S3_F16), (3, 64, s3.S3_BF16)])
-def test_row_stream_carried_across_items_equals_the_two_kernel_path(variant, H, D, dtype):
+def test_row_stream_carried_across_items(variant, H, D, dtype):
     """Kernel shapes whose waves start loading the rows of their next item while the current one is still being
     reduced.  Grids far smaller than the work list, so that every workgroup walks many items; contexts from one row
     up, so that the list holds items whose trailing waves have no rows at all, shares of a single load batch and
-    shares of many; chunk sizes from the smallest.  The fused step must leave the same rows and the same output
-    bits as append + attention + merge, launch after launch (the claim counters must come back to zero)."""
+    shares of many; chunk sizes from the smallest.  The step must leave the same output bits as append + attention, which
+    is checked against the oracle at every chunk size, launch after launch (the claim counters must come back to
+    zero)."""
     rng = np.random.default_rng(900 + variant)
     lens = [1, 2, 3, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 129, 255, 256, 257, 300, 511, 640, 777, 1000,
             4, 1, 66, 12]
@@ -422,10 +427,14 @@ def test_row_stream_carried_across_items_equals_the_two_kernel_path(variant, H, 
     rig.put([rng.standard_normal((L, H, D), dtype=np.float32) for L in lens],
             [rng.standard_normal((L, H, D), dtype=np.float32) for L in lens])
     assert s3.s3_kv_set_param(rig.a, "variant", variant) == 0
-    q, k_new, v_new = (device_bits(wl.normal_bits(rng, (n, H, D), dtype), TDT[dtype], DEV) for _ in range(3))
+    qb, kb, vb = (wl.normal_bits(rng, (n, H, D), dtype) for _ in range(3))
+    q, k_new, v_new = (device_bits(x, TDT[dtype], DEV) for x in (qb, kb, vb))
     pos_d = torch.tensor(lens, dtype=torch.int32, device=DEV)
     len_out = torch.zeros(n, dtype=torch.int32, device=DEV)
     assert s3.s3_kv_append(rig.a, 0, n, rig.off_d, pos_d, k_new, v_new, rig.stream) == 0
+    for b, sid in enumerate(rig.ids.tolist()):
+        assert rig.o.append(sid, 0, lens[b], kb[b], vb[b]) == 0
+    want = rig.want(qb, [L + 1 for L in lens])
     ref = torch.empty((n, H, D), dtype=torch.float32, device=DEV)
     out = torch.empty_like(ref)
     for chunk in (32, 64, 256):
@@ -433,6 +442,7 @@ def test_row_stream_carried_across_items_equals_the_two_kernel_path(variant, H, 
         assert s3.s3_kv_set_param(rig.a, "grid_blocks", 0) == 0
         assert s3.s3_decode_attention(rig.a, 0, n, q, rig.off_d, pos_d + 1, ref, s3.S3_F32, 0.0, rig.stream) == 0
         torch.cuda.synchronize()
+        assert_close(ref.cpu().numpy(), want, f"append + attention, chunk {chunk}")
         for grid in (1, 2, 5, 64, 0):
             assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0
             for i in range(3):
@@ -446,12 +456,11 @@ def test_row_stream_carried_across_items_equals_the_two_kernel_path(variant, H, 
 
 
 @pytest.mark.parametrize("fam", [FAMILIES[4], FAMILIES[5], FAMILIES[7]], ids=[FAMILIES[i][0] for i in (4, 5, 7)])
-def test_matrix_core_kernel_merging_chunks_inside_the_launch_equals_the_merge_launch(fam):
-    """The matrix-core kernel for shared heads can finish multi-chunk contexts itself (arrival counters, the
-    publication of a chunk trailing the wave's work by two items) instead of leaving them to a merge launch:
-    same bits as the two-launch path, for attention and for the decode step, on a dominant-key batch (chunks with
-    very different maxima), launch after launch (the counters must come back to zero), and within the tolerance
-    of the oracle."""
+def test_matrix_core_kernel_merging_chunks_inside_the_launch(fam):
+    """The matrix-core kernel for shared heads finishes multi-chunk contexts itself: within the tolerance of the oracle
+    for attention and for the decode step, on a dominant-key batch (chunks with very different maxima), launch after
+    launch (the counters must come back to zero).  The "gqa_merge" parameter is accepted, kept and without effect:
+    the same bits at both values."""
     name, H, Hkv, D, kvt, act, kind = fam
     rng = np.random.default_rng(900 + D + kind)
     lens = [300, 0, 301, 64, 1, 517, 129, 1000, 33]
@@ -494,11 +503,9 @@ STREAM_FAMILIES = [FAMILIES[4], FAMILIES[5], FAMILIES[7],
 
 @pytest.mark.parametrize("fam", STREAM_FAMILIES, ids=[f[0] for f in STREAM_FAMILIES])
 def test_matrix_core_kernel_streaming_k_rows_equals_plain_loads(fam):
-    """The matrix-core kernel reads K either straight into operand layout with plain loads or, when a launch's K
-    rows exceed the memory-side cache, in whole rows with the streaming hint and through LDS (`gqa_stream`): the
-    operands hold the same bits either way, so attention and the decode step (whose append takes the new row from
-    differently laid out registers) must give the same output bits, the appended row must read back the same, and
-    both must meet the oracle's tolerance."""
+    """The matrix-core kernel reads K rows with plain loads or, when a launch's K rows exceed the memory-side cache, with
+    the streaming hint (`gqa_stream`); both go the same way through LDS: attention and the decode step must give the same
+    output bits, the appended row must read back the same, and both must meet the oracle's tolerance."""
     name, H, Hkv, D, kvt, act, kind = fam
     rng = np.random.default_rng(950 + D + kind)
     lens = [300, 0, 301, 64, 1, 517, 129, 1000, 33, 15, 16, 17]
@@ -533,11 +540,10 @@ def test_matrix_core_kernel_streaming_k_rows_equals_plain_loads(fam):
 
 
 @pytest.mark.parametrize("fam", STREAM_FAMILIES[:3], ids=[f[0] for f in STREAM_FAMILIES[:3]])
-def test_matrix_core_kernel_claiming_the_end_of_its_work_list_equals_the_fixed_stride(fam):
-    """`gqa_dynamic`: the waves of the matrix-core kernel take the first part of the work list by stride and claim
-    the rest from a device-wide counter that every launch must leave at zero.  Grids far smaller than the list, so
-    that most positions are claimed; launch after launch; attention and decode step; same bits as the fixed
-    stride."""
+def test_matrix_core_kernel_on_small_grids_and_the_dynamic_parameter(fam):
+    """Grids far smaller than the work, so that every wave takes many chunks, launch after launch, attention (against
+    the oracle) and decode step: the same bits whatever the grid.  The "gqa_dynamic" parameter is accepted in its range,
+    refused outside it and without effect."""
     name, H, Hkv, D, kvt, act, kind = fam
     rng = np.random.default_rng(970 + D + kind)
     lens = [300, 0, 301, 64, 1, 517, 129, 1000, 33, 15, 16, 17, 700, 45]
@@ -559,7 +565,7 @@ def test_matrix_core_kernel_claiming_the_end_of_its_work_list_equals_the_fixed_s
                 _, got = rig.attend(q)
                 assert np.array_equal(got, ref), (name, grid, pct, rep)
     assert s3.s3_kv_set_param(rig.a, "gqa_dynamic", 101) == s3.S3_ERR_INVALID
-    # the decode step, half of the list claimed, against the step by stride on a twin arena
+    # the decode step on a twin arena, at another value of the parameter
     k_new = rng.standard_normal((n, Hkv, D), dtype=np.float32)
     v_new = rng.standard_normal((n, Hkv, D), dtype=np.float32)
     twin = EdgeRig(fam, lens, M=2048)
