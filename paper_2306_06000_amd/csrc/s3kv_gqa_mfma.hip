@@ -171,8 +171,9 @@ __device__ __forceinline__ int chunk_tiles(const AttnArgs &a, const ChunkPlan &p
 }
 // One wave a chunk: the wave that merges a context reads its pieces a few per memory round trip while their tiles stream
 // side by side, so with `merge_cost` tiles' worth of time per piece (see launch_gqa_mfma) no finer than sqrt(merge_cost *
-// tiles of a context); not for chunks beyond 64 KiB of K rows (shares then; 128 KiB beyond 256 contexts, most of them whole: 16q/1kv x 256,
-// 600 of 10..300 rows, chunks of 15 tiles 35.0 us, shares 42.3) or contexts of more than 12 pieces on average.
+// tiles of a context); not for chunks beyond 64 KiB of K rows (shares then; 128 KiB beyond 256 contexts of
+// sixteen heads of 256, whose pieces of 16 KiB cost shares most: 16q/1kv x 256, 600 of 10..300 rows, chunks of 15 tiles 35.0
+// us, shares 42.3; 12q/2kv x 128 e4m3, 702 of 145..518, outside the rule: 41.8, 40.3) or contexts of more than 12 pieces on average.
 // A team a chunk: no finer than sqrt(1.3 * tiles) or 8 tiles, and contexts of up to 14 tiles whole (one context of 1100
 // rows, 32q/8kv x 128, chunks of 4, 8, 12, 16 tiles: 12.6, 11.4, 12.4, 13.1 us; 3 of 512..8192: 18.7, 18.7, 16.8, 15.7, 24:
 // 16.6; 16q/1kv x 256, 3 of 700..924: 18.9, 17.8, 18.6, 19.4; 11 of 20..211 rows cut at 8 tiles 10.4, whole 9.5).
@@ -191,14 +192,14 @@ __device__ __forceinline__ ChunkPlan chunk_plan(const AttnArgs &a, int tiles, in
         one.units = a.wave_shares;
         one.least = (int)__builtin_amdgcn_sqrtf(a.merge_cost * 1.5f * average) + 1;
         per = chunk_tiles(a, one, tiles, 2);
-        if (per > (a.n > S3_FEW_CONTEXTS ? 131072 : 65536) / ROW_BYTES / TR || average > 12.f * (float)per) one.units = 0;
+        if (per > (a.n > S3_FEW_CONTEXTS && a.merge_cost > 2.f ? 131072 : 65536) / ROW_BYTES / TR || average > 12.f * (float)per) one.units = 0;
     }
     if (a.team_shares > a.n) {
         four.units = a.team_shares;
         const bool whole = longest <= 14;
         four.least = whole ? longest : max(8, (int)__builtin_amdgcn_sqrtf(1.3f * average));
         const int bonus = whole ? 8 : a.merge_cost < 0.5f ? -6 : 8;
-        if (chunk_tiles(a, four, tiles, 2) <= (one.units > 0 ? 4 * per + bonus : 4 * not_below(tiles, a.wave_shares) + 16)) return four;
+        if (min(chunk_tiles(a, four, tiles, 2), longest) <= (one.units > 0 ? 4 * per + bonus : 4 * not_below(tiles, a.wave_shares) + 16)) return four;
     }
     return one;
 }
