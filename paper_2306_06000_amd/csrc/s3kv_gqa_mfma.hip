@@ -191,7 +191,7 @@ __device__ __forceinline__ ChunkPlan chunk_plan(const AttnArgs &a, int tiles, in
     if (a.wave_shares > a.n) {
         one.units = a.wave_shares;
         one.least = (int)__builtin_amdgcn_sqrtf(a.merge_cost * 1.5f * average) + 1;
-        per = chunk_tiles(a, one, tiles, 2);
+        per = chunk_tiles(a, one, tiles, a.n > S3_FEW_CONTEXTS ? 4 : 2);
         if (per > (a.n > S3_FEW_CONTEXTS && a.merge_cost > 2.f ? 131072 : 65536) / ROW_BYTES / TR || average > 12.f * (float)per) one.units = 0;
     }
     if (a.team_shares > a.n) {
