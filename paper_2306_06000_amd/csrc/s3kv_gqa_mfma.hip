@@ -150,7 +150,7 @@ __device__ __forceinline__ int quotient(int x, int y) {
 }
 __device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x * __builtin_amdgcn_rcpf((float)y) * 1.000001f) + 1; }
 
-// How a launch of few rows divides them (a batch of at most 256 contexts): every context by itself, into near-equal
+// How a launch of few rows divides them: every context by itself, into near-equal
 // chunks of at most `per` tiles, one wave or a team of four waves a chunk, all at once.  Nothing is combined that the
 // lengths do not force: a context of one chunk is finished by its wave or team.  What bounds such a launch is a chain of
 // latencies (view and plan 2.5 us, rows a tile a microsecond and wave, the team's meeting in LDS 1, write-through and count
@@ -158,7 +158,9 @@ __device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x *
 // across contexts or chunks by one wave -> this rule: 32q/8kv x 128, 3 contexts of 512..8192 rows 18.9 -> 16.2, 8 of
 // 32..2000 18.9 -> 15.3, 19 of 70..84 9.7 -> 8.1; 12q/2kv x 128, 17 of 1200..1455 19.8 -> 15.8; 16q/1kv x 256, 3 of
 // 700..924 25.0 -> 16.9, 30 of 32..1000 29.0 -> 18.1, 100 30.8 -> 22.8; 64q/8kv x 128 e4m3, 22 of 2000..4793 44.6 -> 41.7,
-// 25 of 60..1106 21.4 -> 18.9.
+// 25 of 60..1106 21.4 -> 18.9; beyond 256 contexts 16q/1kv x 256, 300 of 2..40 37.0 -> 15.3, 12q/2kv x 128, 260 of 2..20
+// 21.4 -> 9.7.
+// Up to S3_FEW_CONTEXTS every wave builds the view for itself (four entries a lane), beyond the workgroup does.
 #define S3_FEW_CONTEXTS 256
 struct ChunkPlan {
     int units, least;  // per column: chunks that run at once, and tiles below which a chunk is not cut (0 units: no chunks)
@@ -173,7 +175,7 @@ __device__ __forceinline__ int chunk_tiles(const AttnArgs &a, const ChunkPlan &p
 // side by side, so with `merge_cost` tiles' worth of time per piece (see launch_gqa_mfma) no finer than sqrt(merge_cost *
 // tiles of a context); not for chunks beyond 64 KiB of K rows (shares then; 128 KiB beyond 256 contexts of
 // sixteen heads of 256, whose pieces of 16 KiB cost shares most: 16q/1kv x 256, 600 of 10..300 rows, chunks of 15 tiles 35.0
-// us, shares 42.3; 12q/2kv x 128 e4m3, 702 of 145..518, outside the rule: 41.8, 40.3) or contexts of more than 12 pieces on average.
+// us, shares 42.3; 12q/2kv x 128 e4m3, 702 of 145..518, outside the rule: 41.8, shares 37.5) or contexts of more than 12 pieces on average.
 // A team a chunk: no finer than sqrt(1.3 * tiles) or 8 tiles, and contexts of up to 14 tiles whole (one context of 1100
 // rows, 32q/8kv x 128, chunks of 4, 8, 12, 16 tiles: 12.6, 11.4, 12.4, 13.1 us; 3 of 512..8192: 18.7, 18.7, 16.8, 15.7, 24:
 // 16.6; 16q/1kv x 256, 3 of 700..924: 18.9, 17.8, 18.6, 19.4; 11 of 20..211 rows cut at 8 tiles 10.4, whole 9.5).
@@ -277,10 +279,11 @@ struct SharePlan {
 };
 
 // Whole contexts: where the fixed buffer has no room for pieces (max_shares 0, see s3i_gqa_max_shares); and for short
-// contexts, each of which a share's border would cut for about 4 us of counting and merging a launch: a share of c
-// contexts comes out longer or shorter by one of them, which pays while they average no more than 2c tiles (and none has
-// more than 256 rows).  32q/8kv x 128, 600 contexts of 1..30 rows: 20.6 us a layer, 25.9 cut; 1400 of 20..200: 138.0,
-// 138.1; 700 of 1..255 (outside the rule): 91.7, 85.8; 64q/8kv, 1010 of 20..200: 114.4, 118.9.
+// contexts, each of which a share's border would cut for about 4 us of counting and merging a launch (10 and more in teams):
+// a share of c contexts comes out longer or shorter by one of them, which pays while they average no more than 2c tiles and
+// none has more than 16, and instead of teams while none has more than 12.  32q/8kv x 128, 600 contexts of 1..30 rows: 20.6
+// us a layer, 25.9 cut; 1400 of 20..200: 138.0, 138.1; 700 of 1..255 (outside the rule): 91.7, 85.8; 400 of 10..60: 22.8, in
+// teams 26.6; 64q/8kv, 1010 of 20..200: 114.4, 118.9.
 
 // Why the line between team 1 and team 4 lies at 256 rows a share: a piece costs a write-through store
 // and a read of its fp32 rows, 16 query heads x D x 4 bytes twice against D x 4 bytes (16-bit K and V) per
@@ -290,8 +293,8 @@ struct SharePlan {
 // adjacent cached heads (team 1: neighbouring waves are neighbouring columns) read whole cached rows between them.
 #define S3_TEAM_ROWS 256
 // A team's waves take at least this many rows each: below it, what a share costs whatever its length (the meeting in
-// LDS, the write-through, the count, the merge of the pieces) outweighs the rows.  Three contexts of 512..8192 rows,
-// 32q/8kv x 128, shares of 26 rows a wave: 163 us a pass, 53: 159, 71: 156, 106: 167, 213: 191.
+// LDS, the write-through, the count, the merge of the pieces) outweighs the rows.  Shares of at least 32, 64, 128 rows,
+// 8q/1kv x 64, 300 contexts of 20..123 rows: 12.8, 15.2, 18.5 us a layer; 16q/1kv x 256, 300 of 20..200: 28.8, 31.8, 41.6.
 #define S3_TEAM_MIN_ROWS 32
 
 // tiles: tiles of TR rows per column.
