@@ -9,18 +9,20 @@
 // per cached head; here both products run on MFMA and every (row, head) score is handled by
 // exactly one lane.
 //
+// Two instances: workgroups of eight waves for launches of no more (context, column) pairs than compute units, which know
+// only chunks (eight_wave_plan), and workgroups of four for all others (chunk_plan, share_plan).
 // Work division.  A column is one (K/V head, block of 16 query heads); every column has the same rows, in tiles of 16
 // or 32.  Many rows: the contexts lie end to end, that length is cut into equal shares and a wave takes one share of one
 // column, across the borders of contexts, so the waves end together whatever the lengths of the batch and a context is
 // cut only where a share ends (share_plan).  Few rows: every context by itself is cut into chunks, each taken by one
-// wave or by the four waves of a workgroup (chunk_plan).  A context inside one share or chunk leaves as its final row; a
+// wave or by all waves of a workgroup (chunk_plan, eight_wave_plan).  A context inside one share or chunk leaves as its final row; a
 // piece of a longer one leaves as a partial (max, sum, unnormalised row) and whoever delivers the last piece merges
 // them inside this launch.  Dealing chunks of 128 or 256 rows by stride instead let nearly every context leave partials
 // (7 to 14 % extra traffic), needed a second launch to merge them (5 to 6 us of device time a step) and left units idle
 // in the last round of the stride (16 query heads on one cached head of 256, 256 contexts of 32..1000 rows: 1216
 // chunks on 1024 waves).
 // Per tile:
-//   * K and V rows are loaded whole, 16 bytes a lane, two tiles ahead, and pass through a per-wave LDS buffer (row-major;
+//   * K and V rows are loaded whole, 16 bytes a lane, one or two tiles ahead, and pass through a per-wave LDS buffer (row-major;
 //     the row strides are at the kernel's start).
 //   * K: lane (r = lane % 16, g = lane / 16) reads 16 bytes (8 elements) of row r at element offset 32*ks + 8*g,
 //     ks = 0 .. D/32-1: the A operand of v_mfma_f32_16x16x32 (row r, contraction slots of lane group g); Q^T is the B
@@ -150,7 +152,7 @@ __device__ __forceinline__ int quotient(int x, int y) {
 }
 __device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x * __builtin_amdgcn_rcpf((float)y) * 1.000001f) + 1; }
 
-// How a launch of few rows divides them: every context by itself, into near-equal
+// How a launch of few rows divides them (four waves a workgroup): every context by itself, into near-equal
 // chunks of at most `per` tiles, one wave or a team of four waves a chunk, all at once.  Nothing is combined that the
 // lengths do not force: a context of one chunk is finished by its wave or team.  What bounds such a launch is a chain of
 // latencies (view and plan 2.5 us, rows a tile a microsecond and wave, the team's meeting in LDS 1, write-through and count
@@ -161,7 +163,6 @@ __device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x *
 // 25 of 60..1106 21.4 -> 18.9; beyond 256 contexts 16q/1kv x 256, 300 of 2..40 37.0 -> 15.3, 12q/2kv x 128, 260 of 2..20
 // 21.4 -> 9.7.
 // Up to S3_FEW_CONTEXTS every wave builds the view for itself (four entries a lane), beyond the workgroup does.
-#define S3_FEW_CONTEXTS 256
 struct ChunkPlan {
     int units, least;  // per column: chunks that run at once, and tiles below which a chunk is not cut (0 units: no chunks)
     int team;
@@ -206,10 +207,26 @@ __device__ __forceinline__ ChunkPlan chunk_plan(const AttnArgs &a, int tiles, in
     return one;
 }
 
+// Teams of eight waves, where the (context, column) pairs are no more than the compute units (launch_gqa_mfma): one workgroup
+// a unit, all chunks at once.  With four waves a unit a wave's tile is a chain (rows into LDS, score products, maximum,
+// exponents, value products: 1 us at 16 rows x 256) that nothing else on its SIMD fills, and a chunk is as long as four such
+// chains; eight waves halve the chain and overlap two of them, and twice the pieces meet in LDS instead of memory.
+// Contexts of up to 22 tiles are whole: counting and merging their pieces costs more than the shorter chains give (16q/1kv x
+// 256, 16 contexts of 240..300 rows whole 14.0 us a layer, cut 14.6; of 360..450: 16.5, 14.9).  Longer ones in chunks of at
+// least a tile a wave, and no finer than sqrt(2 * tiles): 16 of 1000..2000 rows, factor 1, 2, 3: 20.0, 18.5, 18.8; 32q/8kv x
+// 128, 3 of 512..8192: 14.9, 14.1, 13.5; one of 8000 rows of 16q/1kv: 22.7, 23.1, 23.8; at least 8, 12, 16 tiles, 16q/1kv, 16 of 360..450:
+// 14.9, 15.4, 16.6.  Four waves by the rules above -> eight: 16q/1kv x 256, 256 contexts of 32..1000 rows 44.1 -> 37.2, 200 of
+// 1000..2000 86 -> 64, 3 of 32..1000 16.5 -> 14.8; the same of e4m3 rows, 200 of 32..1000, 31.5 -> 25.2; 32q/8kv x 128, 3 of
+// 512..8192 16.4 -> 14.1, 32 of 32..1000 20.9 -> 19.5; 8q/1kv x 64, 256 of 32..1000 16.5 -> 13.3.
+__device__ __forceinline__ ChunkPlan eight_wave_plan(const AttnArgs &a, int tiles, int longest) {
+    const float average = (float)tiles * __builtin_amdgcn_rcpf((float)a.n);
+    return ChunkPlan{a.team_shares, longest <= 22 ? longest : max(8, (int)__builtin_amdgcn_sqrtf(2.f * average)), 8};
+}
+
 // The view of few contexts, and how they are divided: every wave of the workgroup builds all of it by itself and writes the
 // same values to the same words, so that nothing waits at a barrier before its first load (a wave reads behind its own writes).
 // Lane l owns entries E*l .. E*l+E-1.
-template <int E, int TR, int ROW_BYTES>
+template <int E, int TR, int ROW_BYTES, int NW>
 __device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int &tiles, int &longest, int &per, int &team) {
     const int lane = threadIdx.x & 63;
     BatchView v;
@@ -235,7 +252,8 @@ __device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int 
     ChunkPlan plan = {0, 0, 1};
     longest = wave_max_nonneg(most);
     per = a.share_rows / TR;  // the caller's choice (a multiple of 32)
-    if (per == 0) plan = chunk_plan<TR, ROW_BYTES>(a, tiles, longest);
+    if (NW == 8) plan = eight_wave_plan(a, tiles, longest);
+    else if (per == 0) plan = chunk_plan<TR, ROW_BYTES>(a, tiles, longest);
     team = plan.team;
 #pragma unroll 1
     for (int quarters = 2; per > 0 || plan.units > 0; quarters++) {
@@ -329,11 +347,11 @@ __device__ __forceinline__ void pieces_of(const SharePlan &sp, int t0, int t1, i
 }
 
 // Merge the pieces of query heads hq0 .. hq0+nh-1 of a context and store the final rows; by a wave (nthr 64) or by
-// the four waves of a workgroup in step (nthr 256).  A workgroup with at least a thread per quad of elements
-// takes one quad a thread and deals the pieces over what threads are spare, which meet in LDS (6 floats per thread).
+// the four or eight (EIGHT) waves of a workgroup in step (nthr 256, 512).  Four waves with at least a thread per quad of elements
+// take one quad a thread and deals the pieces over what threads are spare, which meet in LDS (6 floats per thread).
 // Kept small: all of this runs once per launch and wave, i.e. out of a cold instruction cache (unrolled for every
 // shape, with the code around it, the kernel was 136 KB and a merge of four pieces took 3 us).
-template <int D>
+template <int D, bool EIGHT>
 __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p, int hq0, int nh, int tid, int nthr, float *lds) {
     const int64_t row0 = ((int64_t)p.first + p.b) * a.Hq + hq0;
     const int64_t sml = 2 * (int64_t)a.Hq, sacc = (int64_t)a.Hq * D;
@@ -341,7 +359,7 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
     char *out = (char *)a.out;
     const int64_t out0 = ((int64_t)p.b * a.Hq + hq0) * D;
     const int quads = nh * (D / 4);
-    if (nthr == 256 && quads <= 256 && p.count > 4 && (int64_t)p.count * sacc < (1 << 28)) {  // (below 1 GiB)
+    if (!EIGHT && nthr == 256 && quads <= 256 && p.count > 4 && (int64_t)p.count * sacc < (1 << 28)) {  // (below 1 GiB)
         const int splits = min(8, 256 / quads);
         const int split = tid / quads, e = tid - split * quads;
         const unsigned sml4 = (unsigned)sml * 4, sacc4 = (unsigned)sacc * 4, last = p.count - 1;
@@ -398,7 +416,7 @@ __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p
     }
     // Whole waves in step, every lane EB quads: the piece is uniform, so its address is scalar and a lane adds one 32-bit
     // offset per quad (at most 64 heads' rows of a piece: 64 KiB).
-    constexpr int EB = D == 256 ? 4 : 2, NP = D == 256 ? 3 : 6;
+    constexpr int EB = D == 256 && !EIGHT ? 4 : 2, NP = D == 256 && !EIGHT ? 3 : 6;
 #pragma unroll 1
     for (int e0 = tid; e0 < quads; e0 += EB * nthr) {
         unsigned eml[EB], eacc[EB];
@@ -476,8 +494,9 @@ __host__ __device__ constexpr int gqa_tile_rows(int row_bytes) { return row_byte
 
 // KV8: the cache rows are e4m3 codes (one byte per element) and DT is the type of q; a 16-byte load then
 // holds 16 elements, which are widened (exactly) to DT in registers and feed two contraction steps.
-template <int DT, int D, bool KV8>
-__global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {
+// NW: waves of a workgroup, 4 or 8.
+template <int DT, int D, bool KV8, int NW>
+__global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {
     constexpr int EB = KV8 ? 1 : 2;       // bytes per cached element
     constexpr int KS = D / 32;            // contraction steps of the score product
     constexpr int DB = D / 16;            // 16-element blocks of an output row
@@ -492,16 +511,19 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     // 4g .. 4g+3, sixteen consecutive words each) cover the banks evenly.
     constexpr int KSTRIDE = D * EB + 16;
     constexpr int VSTRIDE = KV8 ? D + 16 : D * 2 + 32;
+    constexpr bool CHUNKS = NW == 8;      // eight waves: chunks of contexts by teams, nothing else
+    // Register sets of rows on their way: two, or one where two do not fit two waves a SIMD (239 of 256 registers).
+    constexpr bool TWO_SETS = !(NW == 8 && D * EB == 512);
     constexpr float RESCALE_LOG2 = 8.f;   // see the softmax step
     extern __shared__ __align__(16) char dyn_lds[];  // the batch view, then the teams' first pieces
     __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
     // A wave's LDS: the V and the K tile, or, once its share is done, one piece (16 heads x D floats, padded).
     constexpr int PSTRIDE = D + 4;
     constexpr int TILE_BYTES = TR * (VSTRIDE + KSTRIDE), PIECE_BYTES = 16 * PSTRIDE * 4;
-    __shared__ __align__(16) char wave_lds[4][TILE_BYTES > PIECE_BYTES ? TILE_BYTES : PIECE_BYTES];
-    __shared__ float2 piece_ml[8][16];  // team 4: (max, sum) of each wave's first (2w) and last (2w + 1) piece
-    __shared__ f32x4 piece_run[8][16];  // ... a piece's weight in its run of pieces, and the run's (max, sum, 1 / sum)
-    __shared__ int piece_b[8];          // ... and the context it belongs to, -1: none
+    __shared__ __align__(16) char wave_lds[NW][TILE_BYTES > PIECE_BYTES ? TILE_BYTES : PIECE_BYTES];
+    __shared__ float2 piece_ml[2 * NW][16];  // teams: (max, sum) of each wave's first (2w) and last (2w + 1) piece
+    __shared__ f32x4 piece_run[CHUNKS ? 1 : 8][16];  // ... a piece's weight in its run of pieces, and the run's (max, sum, 1 / sum)
+    __shared__ int piece_b[2 * NW];          // ... and the context it belongs to, -1: none
     __shared__ int merge_mine;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -510,8 +532,8 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     // pre[] counts tiles, or (per > 0) chunks of `per` tiles
     int tiles, longest, per, team = 1;  // (longest: tiles of the longest context)
     BatchView bv;
-    if (a.n <= S3_FEW_CONTEXTS) {
-        bv = a.n <= 64 ? few_view<1, TR, D * EB>(a, dyn_lds, tiles, longest, per, team) : few_view<S3_FEW_CONTEXTS / 64, TR, D * EB>(a, dyn_lds, tiles, longest, per, team);
+    if (CHUNKS || a.n <= S3_FEW_CONTEXTS) {
+        bv = a.n <= 64 ? few_view<1, TR, D * EB, NW>(a, dyn_lds, tiles, longest, per, team) : few_view<S3_FEW_CONTEXTS / 64, TR, D * EB, NW>(a, dyn_lds, tiles, longest, per, team);
     } else {
         bv = build_tile_view<TR>(a, dyn_lds, wave_sums, longest);
         tiles = __builtin_amdgcn_readfirstlane(bv.total);
@@ -525,7 +547,9 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     }
     SharePlan sp = {tiles, 1, tiles, 0, 1, false};
     int chunks = __builtin_amdgcn_readfirstlane(bv.total);
-    if (per == 0) {
+    if (CHUNKS) {
+        per = max(per, 1);
+    } else if (per == 0) {
         sp = share_plan<TR>(a, tiles, longest);
         team = sp.team;
     } else if (a.n > S3_FEW_CONTEXTS) {
@@ -547,11 +571,11 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
     const bool stream_k = a.stream_k < 0 ? (int64_t)tiles * TR * rstride > ((int64_t)256 << 20) : a.stream_k != 0;
 
     // (shares * columns tiles of at least 2 KiB lie in the arena: below 2^31 on any device)
-    const unsigned units = tiles == 0 ? 0u : (unsigned)(per > 0 ? chunks : team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
-    const unsigned step = team == 4 ? gridDim.x : gridDim.x * 4;
+    const unsigned units = tiles == 0 ? 0u : (unsigned)(CHUNKS || per > 0 ? chunks : team == 4 ? (sp.shares + 3) / 4 : sp.shares) * columns;
+    const unsigned step = CHUNKS || team == 4 ? gridDim.x : gridDim.x * 4;
     // (chunks: one wave on every compute unit before any unit gets a second one)
 #pragma unroll 1
-    for (unsigned unit = team == 4 ? blockIdx.x : per > 0 ? wave * gridDim.x + blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
+    for (unsigned unit = CHUNKS || team == 4 ? blockIdx.x : per > 0 ? wave * gridDim.x + blockIdx.x : blockIdx.x * 4 + wave; unit < units; unit += step) {
         // publishing unit: this wave's share or chunk, or its team's
         const int pub = __builtin_amdgcn_readfirstlane(a.column_shift >= 0 ? unit >> a.column_shift : unit / columns);
         const int col = __builtin_amdgcn_readfirstlane(unit - (unsigned)pub * columns);
@@ -562,7 +586,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
         const int hq0 = hk * group + qb * 16, nheads = min(16, group - qb * 16);
         // This wave's tiles, [t_begin, t_stop): of all contexts laid end to end, or (chunks) of context `seq`.
         int t_begin = 0, t_stop = 0, seq = 0, chunk = 0, nchunks = 0;
-        if (per > 0) {
+        if (CHUNKS || per > 0) {
             seq = min(find_sequence(bv.pre, a.n, pub), a.n - 1);
             const int first = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
             nchunks = __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) - first;
@@ -572,8 +596,8 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
             const int base = quotient(all, max(nchunks, 1)), rem = all - base * nchunks;
             t_begin = chunk * base + min(chunk, rem);
             t_stop = t_begin + base + (chunk < rem ? 1 : 0);
-            if (team == 4) {  // a quarter each
-                const int quarter = (t_stop - t_begin) >> 2, more = (t_stop - t_begin) & 3;
+            if (CHUNKS || team == 4) {  // an equal part each
+                const int quarter = (t_stop - t_begin) / NW, more = (t_stop - t_begin) % NW;
                 t_begin += wave * quarter + min(wave, more);
                 t_stop = t_begin + quarter + (wave < more ? 1 : 0);
             }
@@ -591,11 +615,11 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
         }
         // contexts this wave or team has left a piece of in memory: at most the first and the last one of its share
         Pending pend0 = {0, 0, 0}, pend1 = {0, 0, 0};
-        if (team == 4 && lane == 0) piece_b[2 * wave] = piece_b[2 * wave + 1] = -1;
+        if ((CHUNKS || team == 4) && lane == 0) piece_b[2 * wave] = piece_b[2 * wave + 1] = -1;
 
         if (t_begin < t_stop) {
             // Two cursors run over the share's tiles: `ahead` issues the loads of a tile (of the next context, if there
-            // is one) into the register set that `now` has just reduced, two tiles on, so a wave has loads in flight from
+            // is one) into the register set that `now` has just moved to LDS, one tile a set on, so a wave has loads in flight from
             // its first tile to its last.  A tile is read through a buffer descriptor that ends with the context's last
             // row: rows past it, and the tiles after the last one of the share, cost no traffic and read as zeros.
             // Row and column of a lane's 16 bytes never change: the addresses take no vector arithmetic.
@@ -605,7 +629,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
             auto open = [&](int seq, int t) {  // the context of tile t, at or after `seq`
                 Segment s;
                 s.t0 = 0;
-                if (per == 0) {
+                if (!CHUNKS && per == 0) {
                     while (seq < a.n - 1 && __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) <= t) seq++;
                     s.t0 = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
                 }
@@ -674,8 +698,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 m = -INFINITY;
                 lsum = 0.f;
             };
-            auto reduce_tile = [&](int r0, const u32x4 (&kld)[NL], const u32x4 (&vv)[NL]) {
-                const int end = now.len;
+            auto stage_tile = [&](int r0, const u32x4 (&kld)[NL], const u32x4 (&vv)[NL]) {
                 // K and V tile through this wave's LDS buffer: K into operand layout, one 128-bit read per contraction
                 // load (loading the operand layout directly is 64 separate 16-byte cache accesses per instruction and
                 // fetches every 128-byte line twice), V transposed.  The LDS unit serves one wave's operations in
@@ -696,6 +719,9 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
+            };
+            auto reduce_tile = [&](int r0) {
+                const int end = now.len;
                 float sv[RB][4], mt = -INFINITY;
 #pragma unroll
                 for (int rb = 0; rb < RB; rb++) {
@@ -812,7 +838,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 lsum += __shfl_xor(lsum, 16);
                 lsum += __shfl_xor(lsum, 32);
                 const bool whole = t_begin <= now.t0 && now.t_end == now.t1;
-                const bool to_lds = !whole && team == 4;
+                const bool to_lds = !whole && (CHUNKS || team == 4);
                 const float f = whole ? 1.f / lsum : 1.f;
                 __builtin_amdgcn_wave_barrier();
                 if (head_ok) {
@@ -851,13 +877,21 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 __builtin_amdgcn_wave_barrier();
             };
 
-            // One register set: reduce it, close the context if that was its last tile, refill the set.  The loop has ONE
+            // One register set: into LDS, refill it, reduce the tile, close the context if that was its last one.  The loop has ONE
             // exit, at its bottom, and every trip issues the same loads in the same order (past the end of the share a
             // half only waits for its set): the compiler derives how many loads may stay in flight at each wait from all
             // paths that reach it.
             auto half = [&](u32x4 (&kk)[NL], u32x4 (&vv)[NL]) {
-                if (t < t_stop) {
-                    reduce_tile((t - now.t0) * TR, kk, vv);
+                const bool rows = t < t_stop;
+                if (rows) {
+                    stage_tile((t - now.t0) * TR, kk, vv);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NL; i++) asm volatile("" ::"v"(kk[i]), "v"(vv[i]));
+                }
+                load_tile(kk, vv);  // the set is in LDS: its next rows leave before this tile's products
+                if (rows) {
+                    reduce_tile((t - now.t0) * TR);
                     t++;
                     if (t == now.t_end) {
                         leave();
@@ -866,41 +900,37 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                             enter();
                         }
                     }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < NL; i++) asm volatile("" ::"v"(kk[i]), "v"(vv[i]));
                 }
-                load_tile(kk, vv);
             };
             u32x4 k0[NL], v0[NL], k1[NL], v1[NL];
             load_tile(k0, v0);
             enter();
-            load_tile(k1, v1);
+            if (TWO_SETS) load_tile(k1, v1);
             do {
                 half(k0, v0);
-                half(k1, v1);
+                if (TWO_SETS) half(k1, v1);
             } while (t < t_stop);
         }
-        if (team == 4) {
+        if (CHUNKS || team == 4) {
             __syncthreads();  // the pieces are in LDS
-            if (per > 0) {
-                // The quarters of one chunk, left where each wave wrote its last piece; waves 0 .. k-1 had rows.
-                const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < 4 && piece_b[2 * (lane & 3) + 1] >= 0));
+            if (CHUNKS || per > 0) {
+                // The parts of one chunk, left where each wave wrote its last piece; waves 0 .. k-1 had rows.
+                const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < NW && piece_b[2 * (lane & (NW - 1)) + 1] >= 0));
                 if (k > 1 || nchunks > 1) {
 #pragma unroll 1
-                    for (int e = threadIdx.x; e < nheads * (D / 4); e += 256) {
+                    for (int e = threadIdx.x; e < nheads * (D / 4); e += NW * 64) {
                         const int h = e / (D / 4), d = (e % (D / 4)) * 4;
                         float m = -INFINITY, l = 0.f;
-                        float2 x[4];
+                        float2 x[NW];
 #pragma unroll
-                        for (int w = 0; w < 4; w++) {
+                        for (int w = 0; w < NW; w++) {
                             x[w] = w < k ? piece_ml[2 * w + 1][h] : make_float2(-INFINITY, 0.f);
                             m = fmaxf(m, x[w].x);
                         }
                         const float ref = exp_reference(m);
                         f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int w = 0; w < 4; w++) {
+                        for (int w = 0; w < NW; w++) {
                             if (w >= k) break;
                             const float wt = fast_exp2(x[w].x - ref);
                             l += wt * x[w].y;
@@ -916,7 +946,7 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                     }
                     if (nchunks > 1) pend0 = Pending{seq, pub - chunk - seq, nchunks};
                 }
-            } else {
+            } else if constexpr (!CHUNKS) {
                 // Pieces of one context are neighbours: a run.  First the weight of every piece and the sum of every run ...
                 const int pb = piece_b[lane & 7];
                 int first8 = 0, count8 = 0;  // lane k: the publishing units of piece k's context
@@ -999,41 +1029,41 @@ __global__ void __launch_bounds__(256, D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(co
                 const int mine = __builtin_amdgcn_readfirstlane(merge_mine);
 #pragma unroll 1
                 for (int k = 0; k < 2; k++)
-                    if ((mine >> k) & 1) merge_pieces<D>(a, k ? pend1 : pend0, hq0, nheads, threadIdx.x, 256, (float *)wave_lds);
+                    if ((mine >> k) & 1) merge_pieces<D, CHUNKS>(a, k ? pend1 : pend0, hq0, nheads, threadIdx.x, NW * 64, (float *)wave_lds);
             }
             __syncthreads();  // LDS is free for the next unit
-        } else {
+        } else if constexpr (!CHUNKS) {
             if (pend0.count != 0 || pend1.count != 0) {
                 const unsigned mine = pieces_arrived(a, pend0, pend1, columns, col);
 #pragma unroll 1
                 for (int k = 0; k < 2; k++)
-                    if ((mine >> k) & 1) merge_pieces<D>(a, k ? pend1 : pend0, hq0, nheads, lane, 64, nullptr);
+                    if ((mine >> k) & 1) merge_pieces<D, false>(a, k ? pend1 : pend0, hq0, nheads, lane, 64, nullptr);
             }
         }
     }
     // What belongs to no row, behind the work: the new lengths (the last workgroup has none in a launch of few rows) ...
     if (a.len_out && blockIdx.x == gridDim.x - 1) {
-        for (int b = threadIdx.x; b < a.n; b += 256) a.len_out[b] = a.cur_len[b] + 1;
+        for (int b = threadIdx.x; b < a.n; b += NW * 64) a.len_out[b] = a.cur_len[b] + 1;
     }
     // ... and the zero rows of empty or refused contexts, by the workgroups in turn
 #pragma unroll 1
     for (int b = blockIdx.x; b < a.n; b += gridDim.x) {
         if (bv.len[b] == 0) {
             const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (int e = threadIdx.x; e < a.Hq * D / 8; e += 256) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
+            for (int e = threadIdx.x; e < a.Hq * D / 8; e += NW * 64) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
         }
     }
 }
 
 attn_fn s3i_pick_gqa_mfma(int dt, int d) {
     if (dt == S3_F16) {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_F16, 64, false>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_F16, 128, false>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_F16, 256, false>;
+        if (d == 64) return attn_gqa_mfma_kernel<S3_F16, 64, false, 4>;
+        if (d == 128) return attn_gqa_mfma_kernel<S3_F16, 128, false, 4>;
+        if (d == 256) return attn_gqa_mfma_kernel<S3_F16, 256, false, 4>;
     } else {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_BF16, 64, false>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_BF16, 128, false>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_BF16, 256, false>;
+        if (d == 64) return attn_gqa_mfma_kernel<S3_BF16, 64, false, 4>;
+        if (d == 128) return attn_gqa_mfma_kernel<S3_BF16, 128, false, 4>;
+        if (d == 256) return attn_gqa_mfma_kernel<S3_BF16, 256, false, 4>;
     }
     return nullptr;
 }
@@ -1041,13 +1071,25 @@ attn_fn s3i_pick_gqa_mfma(int dt, int d) {
 // The same kernel over 8-bit (e4m3) rows; act is the type of q.
 attn_fn s3i_pick_gqa_mfma8(int act, int d) {
     if (act == S3_F16) {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_F16, 64, true>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_F16, 128, true>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_F16, 256, true>;
+        if (d == 64) return attn_gqa_mfma_kernel<S3_F16, 64, true, 4>;
+        if (d == 128) return attn_gqa_mfma_kernel<S3_F16, 128, true, 4>;
+        if (d == 256) return attn_gqa_mfma_kernel<S3_F16, 256, true, 4>;
     } else if (act == S3_BF16) {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_BF16, 64, true>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_BF16, 128, true>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_BF16, 256, true>;
+        if (d == 64) return attn_gqa_mfma_kernel<S3_BF16, 64, true, 4>;
+        if (d == 128) return attn_gqa_mfma_kernel<S3_BF16, 128, true, 4>;
+        if (d == 256) return attn_gqa_mfma_kernel<S3_BF16, 256, true, 4>;
     }
     return nullptr;
+}
+
+// Eight waves a workgroup; act: the type of q (and of the rows, unless they are e4m3: kv8).
+template <int ACT>
+static attn_fn pick_eight_waves(int d, bool kv8) {
+    if (d == 64) return kv8 ? attn_gqa_mfma_kernel<ACT, 64, true, 8> : attn_gqa_mfma_kernel<ACT, 64, false, 8>;
+    if (d == 128) return kv8 ? attn_gqa_mfma_kernel<ACT, 128, true, 8> : attn_gqa_mfma_kernel<ACT, 128, false, 8>;
+    if (d == 256) return kv8 ? attn_gqa_mfma_kernel<ACT, 256, true, 8> : attn_gqa_mfma_kernel<ACT, 256, false, 8>;
+    return nullptr;
+}
+attn_fn s3i_pick_gqa_mfma_wide(int act, int d, bool kv8) {
+    return act == S3_F16 ? pick_eight_waves<S3_F16>(d, kv8) : act == S3_BF16 ? pick_eight_waves<S3_BF16>(d, kv8) : nullptr;
 }

@@ -808,14 +808,25 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     args.team_lds = c.n <= 1024;
     const size_t dyn_lds = args.team_lds ? ((view + 15) & ~(size_t)15) + pieces : view;
     int per_cu = 0;
-    rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
-    if (rc != S3_OK) return rc;
-    if (per_cu > 2) per_cu = 2;
     const int cus = a->num_cus > 0 ? a->num_cus : 256;
     args.group = Hq / Hkv;
     args.nqb = (args.group + 15) / 16;
     args.columns = (int32_t)columns;
     args.column_shift = (columns & (columns - 1)) == 0 ? __builtin_ctzll((unsigned long long)columns) : -1;
+    // No more (context, column) pairs than compute units: workgroups of eight waves, one a unit, which take a context or a
+    // chunk of one (eight_wave_plan).  Beyond, pairs would wait for a unit of their own (32q/8kv x 128, 34 contexts of
+    // 32..1000 rows 22.0 us a layer against 21.5 with workgroups of four, 64 contexts 34.2 against 30.5).
+    if (a->chunk <= 0 && c.n <= S3_FEW_CONTEXTS && c.n * columns <= cus) {
+        attn_fn wide = s3i_pick_gqa_mfma_wide(a->cfg.act_dtype, D, eight_bit);
+        args.team_shares = (int32_t)(cus / columns);
+        rc = resident_per_cu((const void *)wide, 512, view, &per_cu);
+        if (rc != S3_OK) return rc;
+        const int blocks = a->grid_blocks > 0 ? a->grid_blocks : (int)(args.team_shares * columns);
+        return launch_attn_kernels(a, wide, blocks, 512, view, c.stream, args, 0, !c.static_scratch);
+    }
+    rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
+    if (rc != S3_OK) return rc;
+    if (per_cu > 2) per_cu = 2;
     // What one more piece costs the wave that merges a context, in tiles streamed by one wave: a memory round trip of
     // about two tiles brings two quads of elements a lane of six pieces (D 256: four quads of three).
     const int eb = D == 256 ? 4 : 2, quads = (int)group16 * (D / 4), passes = (quads + 64 * eb - 1) / (64 * eb);

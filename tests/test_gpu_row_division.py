@@ -161,3 +161,37 @@ def test_soak_of_the_matrix_core_merge(sync, launches):
         for i in range(launches):
             assert np.array_equal(rig.attend(q)[1], first), (len(lens), i)
         rig.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fam", FAMS, ids=[f[0] for f in FAMS])
+def test_eight_waves_a_workgroup_and_the_borders_of_their_rule(fam):
+    """Workgroups of eight waves take the launches of no more (context, column) pairs than compute units: the last batch of
+    the rule and the first beyond it, the longest whole context (22 tiles) and one row more, fewer tiles than waves, one
+    tile more than a wave each, a context cut as finely as it gets, and a long one where no unit is left to cut it for."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    name, H, Hkv, D, kvt, act, kind = fam
+    tile = 32 if D * (1 if kind == 4 else 2) <= 128 else 16
+    columns = Hkv * -(-(H // Hkv) // 16)
+    full = 256 // columns
+    for what, lens in (("a wave each, and one more", [8 * tile, 8 * tile + 1, 7 * tile - 1, 1, 0]), ("whole", [22 * tile, 5]),
+                       ("cut", [22 * tile + 1, 9]), ("finest", [2047]), ("a unit each", [(37 * b) % 150 for b in range(full - 1)] + [1300]),
+                       ("one more", [(37 * b) % 150 for b in range(full)] + [1300])):
+        rng = np.random.default_rng(len(lens) + D)
+        rig = EdgeRig(fam, lens, M=2048)
+        rig.put([rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens],
+                [rng.standard_normal((L, Hkv, D), dtype=np.float32) for L in lens])
+        if kind == 1:
+            assert s3.s3_kv_set_param(rig.a, "variant", s3.s3_kv_get_param(rig.a, "n_variants")[1] - 1) == 0
+        q = rng.standard_normal((len(lens), H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / {what}")
+        for grid, sync in ((3, 0), (0, 1), (0, 0)):  # the division depends on neither
+            assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0 and s3.s3_kv_set_param(rig.a, "merge_sync", sync) == 0
+            assert np.array_equal(rig.attend(q)[1], att), (name, what, grid, sync)
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, rng.standard_normal((len(lens), Hkv, D), dtype=np.float32), rng.standard_normal((len(lens), Hkv, D), dtype=np.float32))
+        assert_close(step, rig.want(qb, longer), f"{name} / {what} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
+        rig.close()
