@@ -349,7 +349,8 @@ int s3_kv_probe_bandwidth(s3_arena *a, size_t bytes, int32_t mode, int32_t reps,
  *                  memory-side cache; same results
  *   "profile"      k > 0: every k-th attention launch (counted from this call) carries HIP events that
  *                  take the kernel's own start and end times (hipExtLaunchKernel); 0: off; both reset the sums
- * get names: the above plus "default_variant", "kernel_kind" (0 multi-head kernels, 1 shared-K/V vector-ALU kernel,
+ * get names: the above plus "default_variant", "kernel_kind" (0 multi-head kernels, 1 shared-K/V vector-ALU kernel
+ * (with nothing set by the caller the matrix-core kernel takes its place for the batches that it serves faster),
  * 2 shared-K/V matrix-core kernel, 3 kernel for 8-bit rows, 4 matrix-core kernel over 8-bit rows with
  * shared heads: what the next attention launch uses), "n_variants", "n_grows",
  * "live_slots", "scratch_bytes", "num_cus" and,

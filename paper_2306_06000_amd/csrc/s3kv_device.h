@@ -834,4 +834,5 @@ append_fp8_fn s3i_pick_append_fp8(int act);
 attn_fn s3i_pick_gqa_mfma(int dt, int d);
 attn_fn s3i_pick_gqa_mfma8(int act, int d);  // the same over 8-bit (e4m3) rows, q of type act
 attn_fn s3i_pick_gqa_mfma_wide(int act, int d, bool kv8);  // both, 512 threads per workgroup, one work item per workgroup
+attn_fn s3i_pick_gqa_mfma3(int dt, int d, bool wide);  // 16-bit rows, weights in three parts; 256 threads, or (wide) 512
 #define S3_FEW_CONTEXTS 256  // contexts whose view every wave of that kernel builds by itself

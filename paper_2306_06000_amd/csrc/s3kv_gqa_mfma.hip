@@ -69,18 +69,18 @@ __device__ __forceinline__ f32x4 mfma_values(const u32x2 a, const u32x2 b, const
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c, 0, 0, 0);
 }
 
-// V^T . P^T for RB blocks of 16 rows (two operand words each), P^T as its high and its low part.
-template <int DT, int RB>
-__device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const unsigned (&hi)[2 * RB], const unsigned (&lo)[2 * RB], f32x4 c) {
-    if constexpr (RB == 2) {
-        const u32x4 a = (u32x4){v[0], v[1], v[2], v[3]};
-        c = mfma_scores<DT>(a, (u32x4){hi[0], hi[1], hi[2], hi[3]}, c);
-        return mfma_scores<DT>(a, (u32x4){lo[0], lo[1], lo[2], lo[3]}, c);
-    } else {
-        const u32x2 a = (u32x2){v[0], v[1]};
-        c = mfma_values<DT>(a, (u32x2){hi[0], hi[1]}, c);
-        return mfma_values<DT>(a, (u32x2){lo[0], lo[1]}, c);
+// c + V^T . P^T for RB blocks of 16 rows (two operand words each), P^T in PARTS parts, the highest first.  Three parts meet
+// before they are added, so that the running sum is rounded once a tile.
+template <int DT, int RB, int PARTS>
+__device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const unsigned (&p)[PARTS][2 * RB], f32x4 c) {
+    const f32x4 sum = c;
+    if (PARTS == 3) c = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = PARTS - 1; i >= 0; i--) {
+        if constexpr (RB == 2) c = mfma_scores<DT>((u32x4){v[0], v[1], v[2], v[3]}, (u32x4){p[i][0], p[i][1], p[i][2], p[i][3]}, c);
+        else c = mfma_values<DT>((u32x2){v[0], v[1]}, (u32x2){p[i][0], p[i][1]}, c);
     }
+    return PARTS == 3 ? sum + c : c;
 }
 
 __device__ __forceinline__ unsigned pack_f16(float lo, float hi) {
@@ -495,10 +495,11 @@ __host__ __device__ constexpr int gqa_tile_rows(int row_bytes) { return row_byte
 // KV8: the cache rows are e4m3 codes (one byte per element) and DT is the type of q; a 16-byte load then
 // holds 16 elements, which are widened (exactly) to DT in registers and feed two contraction steps.
 // NW: waves of a workgroup, 4 or 8.
-template <int DT, int D, bool KV8, int NW>
+template <int DT, int D, bool KV8, int NW, int PARTS = 2>
 __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {
     constexpr int EB = KV8 ? 1 : 2;       // bytes per cached element
     constexpr int KS = D / 32;            // contraction steps of the score product
+    constexpr int CH = KS < 4 ? KS : 4;   // ... in as many chains
     constexpr int DB = D / 16;            // 16-element blocks of an output row
     constexpr int PPR = D * EB / 16;      // 16-byte pieces per cached row of one head
     constexpr int TR = gqa_tile_rows(D * EB), RB = TR / 16;  // rows of a tile, in blocks of 16
@@ -725,7 +726,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 float sv[RB][4], mt = -INFINITY;
 #pragma unroll
                 for (int rb = 0; rb < RB; rb++) {
-                    f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    // (several short chains of products, added pairwise: a dot product's rounding, and its latency)
+                    f32x4 sc[CH];
+#pragma unroll
+                    for (int c = 0; c < CH; c++) sc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int j = 0; j < NK; j++) {
                         const u32x4 raw = *(const u32x4 *)(kt + (rb * 16 + n) * KSTRIDE + j * 64 + g * 16);
@@ -739,12 +743,18 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                                     kk[2 * w] = widen2_e4m3<DT>(word, false);
                                     kk[2 * w + 1] = widen2_e4m3<DT>(word, true);
                                 }
-                                s = mfma_scores<DT>(kk, qop[2 * j + half < KS ? 2 * j + half : 0], s);
+                                const int ks = 2 * j + half;
+                                sc[ks % CH] = mfma_scores<DT>(kk, qop[ks < KS ? ks : 0], sc[ks % CH]);
                             }
                         } else {
-                            s = mfma_scores<DT>(raw, qop[j], s);
+                            sc[j % CH] = mfma_scores<DT>(raw, qop[j], sc[j % CH]);
                         }
                     }
+#pragma unroll
+                    for (int c = CH / 2; c > 0; c /= 2)
+#pragma unroll
+                        for (int k = 0; k < c; k++) sc[k] += sc[k + c];
+                    const f32x4 s = sc[0];
 #pragma unroll
                     for (int i = 0; i < 4; i++) {
                         sv[rb][i] = (r0 + rb * 16 + 4 * g + i < end) ? s[i] * a.scale_log2e : -INFINITY;
@@ -772,22 +782,28 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 // The weights enter the second product as 16-bit operands: a high part (p rounded to the type) and
                 // a low part (what the high part misses, rounded again), two products per value block.  Together
                 // they carry about twice the type's mantissa, so the weighted sum is as exact as the fp32 weights
-                // allow, also for values of large magnitude (one rounded part alone is off by 2^-12 of |p v|).
+                // allow, also for values of large magnitude (one rounded part alone is off by 2^-12 of |p v|); a third part
+                // carries what fp32 holds beyond (see pick_three_parts).
                 // Contraction slots of lane group g: rows 4g .. 4g+3 of each row block.
-                unsigned hi[2 * RB], lo[2 * RB];
+                unsigned w16[PARTS][2 * RB];
 #pragma unroll
                 for (int rb = 0; rb < RB; rb++) {
-                    float p[4], r[4];
+                    float p[4];
 #pragma unroll
                     for (int i = 0; i < 4; i++) {
                         p[i] = fast_exp2(sv[rb][i] - ref);
+                        // (three fp16 parts: weights 64 times as large, below 2^14, so that the parts of one that counts
+                        // stay in the type's range; sum and row carry the factor alike)
+                        if (DT == S3_F16 && PARTS == 3) p[i] *= 64.f;
                         lsum += p[i];
-                        r[i] = DT == S3_F16 ? p[i] - (float)(_Float16)p[i] : p[i] - (float)(__bf16)p[i];
                     }
 #pragma unroll
-                    for (int i = 0; i < 2; i++) {
-                        hi[2 * rb + i] = DT == S3_F16 ? pack_f16(p[2 * i], p[2 * i + 1]) : pack_bf16(p[2 * i], p[2 * i + 1]);
-                        lo[2 * rb + i] = DT == S3_F16 ? pack_f16(r[2 * i], r[2 * i + 1]) : pack_bf16(r[2 * i], r[2 * i + 1]);
+                    for (int part = 0; part < PARTS; part++) {
+#pragma unroll
+                        for (int i = 0; i < 2; i++)
+                            w16[part][2 * rb + i] = DT == S3_F16 ? pack_f16(p[2 * i], p[2 * i + 1]) : pack_bf16(p[2 * i], p[2 * i + 1]);
+#pragma unroll
+                        for (int i = 0; i < 4; i++) p[i] = DT == S3_F16 ? p[i] - (float)(_Float16)p[i] : p[i] - (float)(__bf16)p[i];
                     }
                 }
 
@@ -811,7 +827,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                                 vop[2 * rb] = widen2_e4m3<DT>(w[rb][j], false);
                                 vop[2 * rb + 1] = widen2_e4m3<DT>(w[rb][j], true);
                             }
-                            o[4 * q4 + j] = mfma_weights<DT, RB>(vop, hi, lo, o[4 * q4 + j]);
+                            o[4 * q4 + j] = mfma_weights<DT, RB, PARTS>(vop, w16, o[4 * q4 + j]);
                         }
                     }
                 } else {
@@ -825,7 +841,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                             vop[2 * rb] = v4[0];
                             vop[2 * rb + 1] = v4[1];
                         }
-                        o[db] = mfma_weights<DT, RB>(vop, hi, lo, o[db]);
+                        o[db] = mfma_weights<DT, RB, PARTS>(vop, w16, o[db]);
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -1053,6 +1069,21 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
             for (int e = threadIdx.x; e < a.Hq * D / 8; e += NW * 64) store_out8(a.out, a.out_dtype, ((int64_t)b * a.Hq * D / 8 + e) * 8, z);
         }
     }
+}
+
+// Fewer than four query heads per cached head, 16-bit rows.  The vector-ALU kernel, which serves these where it is faster
+// (gqa_on_matrix_cores), keeps the weights in fp32; three parts keep as much.  Error against 64 bits, relative 2-norm, fp32 outputs, 16q/8kv
+// x 128 and 24q/8kv x 64 bf16: vector ALU 1.1e-7 to 2.4e-7, two parts 1.6e-6 to 2.4e-6, three 1.0e-7 to 2.1e-7 (no batch larger than the vector ALU's).
+template <int DT, int NW>
+static attn_fn pick_three_parts(int d) {
+    if (d == 64) return attn_gqa_mfma_kernel<DT, 64, false, NW, 3>;
+    if (d == 128) return attn_gqa_mfma_kernel<DT, 128, false, NW, 3>;
+    if (d == 256) return attn_gqa_mfma_kernel<DT, 256, false, NW, 3>;
+    return nullptr;
+}
+attn_fn s3i_pick_gqa_mfma3(int dt, int d, bool wide) {
+    if (dt == S3_F16) return wide ? pick_three_parts<S3_F16, 8>(d) : pick_three_parts<S3_F16, 4>(d);
+    return wide ? pick_three_parts<S3_BF16, 8>(d) : pick_three_parts<S3_BF16, 4>(d);
 }
 
 attn_fn s3i_pick_gqa_mfma(int dt, int d) {

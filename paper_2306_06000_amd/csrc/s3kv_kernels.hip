@@ -631,6 +631,37 @@ static int64_t gqa_columns(const s3_arena *a) {
 static size_t gqa_slot_bytes(const s3_arena *a) {
     return (size_t)a->cfg.n_heads * ((size_t)a->cfg.head_dim * sizeof(float) + sizeof(float2));
 }
+// Vector-ALU kernel for shared heads: query heads per lane, and rows per chunk (few (sequence, head group) pairs: contexts
+// are cut finer so that the chip still has work everywhere).
+static int gqa_heads_per_lane(const s3_arena *a) {
+    const int group = a->cfg.n_heads / a->cfg.n_kv_heads;
+    return group % 8 == 0 ? 8 : group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
+}
+static int gqa_items_per_chunk(const s3_arena *a) {  // K/V head groups x query sub-blocks
+    const int GH = 512 / a->cfg.head_dim, group = a->cfg.n_heads / a->cfg.n_kv_heads;
+    return ((a->cfg.n_kv_heads + GH - 1) / GH) * (group / gqa_heads_per_lane(a));
+}
+static int gqa_chunk_rows(const s3_arena *a, int n) {
+    const int64_t items = (int64_t)n * gqa_items_per_chunk(a);
+    return a->chunk > 0 ? a->chunk : items >= 2048 ? 1024 : items >= 512 ? 512 : 256;
+}
+
+// Fewer than four query heads per cached head, 16-bit rows, nothing set by the caller: which kernel serves a batch of n.  The
+// matrix cores win where the launch is a chain of latencies (one launch instead of three) and wherever the vector-ALU kernel
+// reads the rows once per query head (odd groups).  With two heads it reads them once, and a batch that fills the chip is
+// bound by memory either way: more (sequence, cached head) pairs than two a compute unit stay with it (of 256: than one).
+// us a layer, vector ALU and matrix cores: 16q/8kv x 128, 1 context of 20 rows 11.6, 6.8, 20 of 32..1000 27.9, 15.3, 64 of 100..200
+// 23.7, 15.9, 85 of 32..1000 41.5, 42.4; 64q/32kv x 128, 10 of 2..24 11.4, 8.0, 64 of 100..200 36.4, 43.3; 6q/3kv x 256, 20 of 32..1000 29.2, 14.4,
+// 300 of 2..40 17.7, 19.6; 24q/8kv x 64, 20 of 32..1000 25.0, 10.6, 700 of 32..1000 393, 130, 1000 of 2..25 32.2, 20.5.
+// (Both keep what fp32 weights hold, see pick_three_parts; an infinite cached value makes its output element infinite on the
+// vector ALU and NaN on the matrix cores.)
+static bool gqa_on_matrix_cores(const s3_arena *a, int n) {
+    const int kind = s3i_kernel_kind(a);
+    if (kind != 1 || a->variant >= 0 || a->chunk > 0) return kind == 2 || kind == 4;
+    const int64_t cus = a->num_cus > 0 ? a->num_cus : 256;
+    return a->cfg.n_heads / a->cfg.n_kv_heads == 3 || n * gqa_columns(a) <= (a->cfg.head_dim == 256 ? cus : 2 * cus);
+}
+
 // Chunks of the documented rule over n contexts, and how many the fixed buffer holds.
 static int64_t gqa_chunks(const s3_arena *a, int n) {
     const int chunk = a->chunk > 0 ? a->chunk : n * gqa_columns(a) >= 4096 ? 256 : 128;
@@ -639,7 +670,12 @@ static int64_t gqa_chunks(const s3_arena *a, int n) {
 static int64_t gqa_static_slots(const s3_arena *a) {
     return (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes((int)gqa_columns(a))) / gqa_slot_bytes(a));
 }
-static bool gqa_fits_static(const s3_arena *a, int n) { return gqa_chunks(a, n) <= gqa_static_slots(a); }
+// (kind 1: by the vector-ALU kernel's chunks, without counters, whichever kernel serves the batch)
+static bool gqa_fits_static(const s3_arena *a, int n) {
+    if (s3i_kernel_kind(a) != 1) return gqa_chunks(a, n) <= gqa_static_slots(a);
+    const int chunk = gqa_chunk_rows(a, n);
+    return (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk) <= (int64_t)(S3_STATIC_SCRATCH_BYTES / gqa_slot_bytes(a));
+}
 // (not for callers of the library: a host test reads it)
 extern "C" int64_t s3i_gqa_max_shares(const s3_arena *a, int32_t n) {
     const int64_t columns = gqa_columns(a), waves = (int64_t)(a->num_cus > 0 ? a->num_cus : 256) * 8;
@@ -675,21 +711,6 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }
 
-// Vector-ALU kernel for shared heads: query heads per lane, and rows per chunk (few (sequence, head group) pairs: contexts
-// are cut finer so that the chip still has work everywhere).
-static int gqa_heads_per_lane(const s3_arena *a) {
-    const int group = a->cfg.n_heads / a->cfg.n_kv_heads;
-    return group % 8 == 0 ? 8 : group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
-}
-static int gqa_items_per_chunk(const s3_arena *a) {  // K/V head groups x query sub-blocks
-    const int GH = 512 / a->cfg.head_dim, group = a->cfg.n_heads / a->cfg.n_kv_heads;
-    return ((a->cfg.n_kv_heads + GH - 1) / GH) * (group / gqa_heads_per_lane(a));
-}
-static int gqa_chunk_rows(const s3_arena *a, int n) {
-    const int64_t items = (int64_t)n * gqa_items_per_chunk(a);
-    return a->chunk > 0 ? a->chunk : items >= 2048 ? 1024 : items >= 512 ? 512 : 256;
-}
-
 // Scratch the attention calls over 1 to n sequences need at most.
 static size_t scratch_need(const s3_arena *a, int n) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, kind = s3i_kernel_kind(a);
@@ -699,7 +720,7 @@ static size_t scratch_need(const s3_arena *a, int n) {
     for (int k = 1; k <= n; k++) {
         int32_t few;
         size_t slots;
-        if (kind == 2 || kind == 4) {
+        if (kind != 0 && kind != 3 && gqa_on_matrix_cores(a, k)) {
             slots = gqa_partial_slots(a, k);
         } else if (kind == 0 || kind == 3) {
             slots = chunk_slots(a, k, n_hg, slot_bytes, &few);
@@ -786,7 +807,9 @@ static int launch_attn_kernels(s3_arena *a, attn_fn fn, int blocks, int threads,
 static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
     const bool eight_bit = s3i_kernel_kind(a) == 4;
-    attn_fn fn = eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D) : s3i_pick_gqa_mfma(a->cfg.kv_dtype, D);
+    const bool three_parts = !eight_bit && Hq / Hkv < 4;
+    attn_fn fn = three_parts ? s3i_pick_gqa_mfma3(a->cfg.kv_dtype, D, false)
+                 : eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D) : s3i_pick_gqa_mfma(a->cfg.kv_dtype, D);
     if (!fn) return S3_ERR_INVALID;
     if (c.static_scratch && !gqa_fits_static(a, c.n)) return S3_ERR_SCRATCH;
     if (c.with_append && eight_bit) {  // 16-bit rows: the kernel appends by itself
@@ -817,7 +840,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     // chunk of one (eight_wave_plan).  Beyond, pairs would wait for a unit of their own (32q/8kv x 128, 34 contexts of
     // 32..1000 rows 22.0 us a layer against 21.5 with workgroups of four, 64 contexts 34.2 against 30.5).
     if (a->chunk <= 0 && c.n <= S3_FEW_CONTEXTS && c.n * columns <= cus) {
-        attn_fn wide = s3i_pick_gqa_mfma_wide(a->cfg.act_dtype, D, eight_bit);
+        attn_fn wide = three_parts ? s3i_pick_gqa_mfma3(a->cfg.kv_dtype, D, true) : s3i_pick_gqa_mfma_wide(a->cfg.act_dtype, D, eight_bit);
         args.team_shares = (int32_t)(cus / columns);
         rc = resident_per_cu((const void *)wide, 512, view, &per_cu);
         if (rc != S3_OK) return rc;
@@ -841,9 +864,8 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
 // Shared key/value heads, vector-ALU kernel: append as its own launch, attention, merge.
 static int launch_gqa(s3_arena *a, const AttnCall &c) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
-    const int kind = s3i_kernel_kind(a);
     // Variant indices of a shared-K/V arena: the shapes of the vector-ALU kernel, then the matrix-core kernel.
-    if (kind == 2 || kind == 4) return launch_gqa_mfma(a, c);
+    if (gqa_on_matrix_cores(a, c.n)) return launch_gqa_mfma(a, c);
     int threads = 256;
     attn_fn fn = s3i_pick_gqa(a->cfg.kv_dtype, D, gqa_heads_per_lane(a), a->variant, &threads);
     if (!fn) return S3_ERR_INVALID;
