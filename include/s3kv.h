@@ -174,9 +174,9 @@ int s3_decode_attention(s3_arena *a, int32_t layer, int32_t n, const void *q, co
  *   len_out   DEVICE [n] int32 or NULL: receives pos[b] + 1, the positions of the next step; must not
  *             be the same array as pos (S3_ERR_INVALID) - alternate between two arrays. */
 /* (Shared key/value heads: the same call, results and checks, as one to three launches on `stream`: the
- * append (folded into the attention kernel when the matrix-core kernel runs over 16-bit rows), the
- * attention kernel, and, with the vector-ALU kernel, a merge of chunk partials.  An 8-bit cache rounds the new row to codes in the
- * same kernel that attends over it.) */
+ * append (folded into the attention kernel when the matrix-core kernel runs, but for large batches of 8-bit rows), the
+ * attention kernel, and, with the vector-ALU kernel, a merge of chunk partials.  An 8-bit multi-head cache rounds the new row
+ * to codes in the same kernel that attends over it.) */
 int s3_decode_step(s3_arena *a, int32_t layer, int32_t n, const int32_t *slot_id, const int32_t *pos_host,
                    const int64_t *slot_off, const int32_t *pos, const void *q, const void *k_new,
                    const void *v_new, void *out, int32_t out_dtype, float scale, int32_t *len_out, void *stream);

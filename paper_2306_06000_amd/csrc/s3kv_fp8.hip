@@ -25,40 +25,6 @@ __device__ __forceinline__ void widen4_e4m3(const unsigned w, float (&f)[4]) {
     f[3] = hi[1];
 }
 
-// Two fp32 values -> their e4m3 codes in one half of a 32-bit word (v_cvt_pk_fp8_f32 rounds to the nearest
-// code, ties to even, subnormal codes included).  Magnitudes are clamped to 448 first, so nothing depends on
-// the instruction's overflow mode, and NaN is forced to 0x7f afterwards (the clamp turns it into a number).
-template <bool HI>
-__device__ __forceinline__ unsigned quantize2_e4m3(const float x0, const float x1, const unsigned old) {
-    const float c0 = fminf(fmaxf(x0, -448.f), 448.f), c1 = fminf(fmaxf(x1, -448.f), 448.f);
-    unsigned w = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(c0, c1, (int)old, HI);
-    constexpr unsigned S = HI ? 16u : 0u;
-    if (x0 != x0) w = (w & ~(0xFFu << S)) | (0x7Fu << S);
-    if (x1 != x1) w = (w & ~(0xFF00u << S)) | (0x7F00u << S);
-    return w;
-}
-
-template <int ACT>
-__device__ __forceinline__ float widen16(const unsigned short h) {
-    if (ACT == S3_F16) return (float)__builtin_bit_cast(_Float16, h);
-    const unsigned w = (unsigned)h << 16;
-    return __builtin_bit_cast(float, w);
-}
-
-// 16 consecutive 16-bit elements (two 128-bit words) -> their 16 codes in element order.
-template <int ACT>
-__device__ __forceinline__ u32x4 quantize16(const u32x4 lo, const u32x4 hi) {
-    u32x4 out;
-#pragma unroll
-    for (int w = 0; w < 4; w++) {
-        const unsigned a = w < 2 ? lo[2 * w] : hi[2 * w - 4], c = w < 2 ? lo[2 * w + 1] : hi[2 * w - 3];
-        const unsigned lo2 = quantize2_e4m3<false>(widen16<ACT>((unsigned short)(a & 0xFFFFu)),
-                                                   widen16<ACT>((unsigned short)(a >> 16)), 0u);
-        out[w] = quantize2_e4m3<true>(widen16<ACT>((unsigned short)(c & 0xFFFFu)), widen16<ACT>((unsigned short)(c >> 16)), lo2);
-    }
-    return out;
-}
-
 // grid (n, 2): block (b, which) quantises one new row of H*D 16-bit elements into row off+pos.
 template <int ACT>
 __global__ void __launch_bounds__(256) append_fp8_kernel(char *kplane, char *vplane, const int64_t *slot_off,

@@ -44,7 +44,7 @@
 //     weights' error near 2^-16 (bfloat16) / 2^-22 (fp16) instead of 2^-9 / 2^-12: with one part only,
 //     values of magnitude 1e2 put the fp16 kernel outside the attention tolerance.
 // Accumulators: O^T block db holds O^T[d = 16*db + 4*g + i][head], fp32.  In a decode step the new row is read
-// from k_new / v_new and appended by the wave that owns it.
+// from k_new / v_new and appended by the wave that owns it (8-bit rows: with eight waves, else by a launch before).
 #include <type_traits>
 
 #include "s3kv_device.h"
@@ -216,7 +216,8 @@ __device__ __forceinline__ ChunkPlan chunk_plan(const AttnArgs &a, int tiles, in
 // least a tile a wave, and no finer than sqrt(2 * tiles): 16 of 1000..2000 rows, factor 1, 2, 3: 20.0, 18.5, 18.8; 32q/8kv x
 // 128, 3 of 512..8192: 14.9, 14.1, 13.5; one of 8000 rows of 16q/1kv: 22.7, 23.1, 23.8; at least 8, 12, 16 tiles, 16q/1kv, 16 of 360..450:
 // 14.9, 15.4, 16.6.  Four waves by the rules above -> eight: 16q/1kv x 256, 256 contexts of 32..1000 rows 44.1 -> 37.2, 200 of
-// 1000..2000 86 -> 64, 3 of 32..1000 16.5 -> 14.8; the same of e4m3 rows, 200 of 32..1000, 31.5 -> 25.2; 32q/8kv x 128, 3 of
+// 1000..2000 86 -> 64, 3 of 32..1000 16.5 -> 14.8; the same of e4m3 rows, 200 of 32..1000, 31.5 -> 25.1 (21.7 with
+// the append inside); 32q/8kv x 128, 3 of
 // 512..8192 16.4 -> 14.1, 32 of 32..1000 20.9 -> 19.5; 8q/1kv x 64, 256 of 32..1000 16.5 -> 13.3.
 __device__ __forceinline__ ChunkPlan eight_wave_plan(const AttnArgs &a, int tiles, int longest) {
     const float average = (float)tiles * __builtin_amdgcn_rcpf((float)a.n);
@@ -513,8 +514,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
     constexpr int KSTRIDE = D * EB + 16;
     constexpr int VSTRIDE = KV8 ? D + 16 : D * 2 + 32;
     constexpr bool CHUNKS = NW == 8;      // eight waves: chunks of contexts by teams, nothing else
-    // Register sets of rows on their way: two, or one where two do not fit two waves a SIMD (239 of 256 registers).
-    constexpr bool TWO_SETS = !(NW == 8 && D * EB == 512);
+    // Register sets of rows on their way: two, or one where two (with the new row of 8-bit rows) do not fit two waves a
+    // SIMD: 239 and 229 of 256 registers.
+    constexpr bool TWO_SETS = !(NW == 8 && D == 256);
+    constexpr bool APPENDS = !KV8 || CHUNKS;  // takes the new row of a decode step itself (else the host appends it first)
     constexpr float RESCALE_LOG2 = 8.f;   // see the softmax step
     extern __shared__ __align__(16) char dyn_lds[];  // the batch view, then the teams' first pieces
     __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
@@ -670,7 +673,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
             };
 
             u32x4 qop[KS];
-            u32x4 knew = (u32x4){0u, 0u, 0u, 0u}, vnew = knew;
+            u32x4 knew = (u32x4){0u, 0u, 0u, 0u}, vnew = knew, knew2 = knew, vnew2 = knew;  // (knew2, vnew2: 8-bit rows only)
             f32x4 o[DB];
             float m = -INFINITY, lsum = 0.f;
             int jnew = -1;  // decode step: the row of `now` that is still only in k_new / v_new
@@ -685,13 +688,17 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 }
                 // Decode step (len_add = 1): row len-1 is still only in k_new / v_new.  Every reader takes it from
                 // there; the wave of query block 0 whose tile holds it also writes it into the arena (the append).
-                // (8-bit rows are quantised by the append kernel before this launch: nothing to take from k_new.)
-                if (!KV8 && a.len_add) {
+                // (8-bit rows: the 16-bit row waits until its tile's turn, so that nothing in flight is waited for here.)
+                if (APPENDS && a.len_add) {
                     jnew = now.len - 1;
                     if (jnew < (now.t_end - now.t0) * TR && lane < PPR) {  // in this share
-                        const int64_t at = ((int64_t)now.seq * a.H + hk) * D * 2 + lane * 16;
+                        const int64_t at = ((int64_t)now.seq * a.H + hk) * D * 2 + lane * (KV8 ? 32 : 16);
                         knew = *(const u32x4 *)(a.k_new + at);
                         vnew = *(const u32x4 *)(a.v_new + at);
+                        if (KV8) {
+                            knew2 = *(const u32x4 *)(a.k_new + at + 16);
+                            vnew2 = *(const u32x4 *)(a.v_new + at + 16);
+                        }
                     }
                 }
 #pragma unroll
@@ -709,7 +716,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 for (int i = 0; i < NL; i++) *(u32x4 *)(kt + (i * RPL + lane / PPR) * KSTRIDE + (lane % PPR) * 16) = kld[i];
 #pragma unroll
                 for (int i = 0; i < NL; i++) *(u32x4 *)(vt + (i * RPL + lane / PPR) * VSTRIDE + (lane % PPR) * 16) = vv[i];
-                if (!KV8 && jnew >= r0 && jnew < r0 + TR && lane < PPR) {  // this tile holds the new row
+                if (APPENDS && jnew >= r0 && jnew < r0 + TR && lane < PPR) {  // this tile holds the new row
+                    if (KV8) {  // rounded to codes as the append kernel rounds it
+                        knew = quantize16<DT>(knew, knew2);
+                        vnew = quantize16<DT>(vnew, vnew2);
+                    }
                     __builtin_amdgcn_wave_barrier();
                     *(u32x4 *)(kt + (jnew - r0) * KSTRIDE + lane * 16) = knew;
                     *(u32x4 *)(vt + (jnew - r0) * VSTRIDE + lane * 16) = vnew;

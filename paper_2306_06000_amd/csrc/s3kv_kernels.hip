@@ -803,7 +803,7 @@ static int launch_attn_kernels(s3_arena *a, attn_fn fn, int blocks, int threads,
     return S3_OK;
 }
 
-// Shared key/value heads, matrix-core kernel: one launch (over 8-bit rows a quantising append before it).
+// Shared key/value heads, matrix-core kernel: one launch (with workgroups of four over 8-bit rows an append before it).
 static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
     const bool eight_bit = s3i_kernel_kind(a) == 4;
@@ -812,10 +812,6 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
                  : eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D) : s3i_pick_gqa_mfma(a->cfg.kv_dtype, D);
     if (!fn) return S3_ERR_INVALID;
     if (c.static_scratch && !gqa_fits_static(a, c.n)) return S3_ERR_SCRATCH;
-    if (c.with_append && eight_bit) {  // 16-bit rows: the kernel appends by itself
-        const int arc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
-        if (arc != S3_OK) return arc;
-    }
     const int64_t columns = gqa_columns(a);
     AttnArgs args = common_args(a, c, Hkv, Hq, 16);  // (the kernel's batch view counts its own tiles)
     args.ncls = 1;
@@ -846,6 +842,13 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
         if (rc != S3_OK) return rc;
         const int blocks = a->grid_blocks > 0 ? a->grid_blocks : (int)(args.team_shares * columns);
         return launch_attn_kernels(a, wide, blocks, 512, view, c.stream, args, 0, !c.static_scratch);
+    }
+    // Workgroups of four over 8-bit rows: the append is its own launch.  (Taken into the kernel, as it is with eight waves, the
+    // rounding of 16 codes a lane in the middle of the row stream costs a long launch more than the 5 us: 32q/8kv x 128, 1024
+    // contexts of 32..1000 rows 208.9 us, folded 212.2; 24q/8kv x 64, 500 of 5..60 18.1, 18.4.)
+    if (c.with_append && eight_bit) {
+        rc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
+        if (rc != S3_OK) return rc;
     }
     rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
     if (rc != S3_OK) return rc;
