@@ -50,6 +50,8 @@ struct AttnArgs {
     float merge_cost;    // time of merging one more piece of a context, in tiles streamed by one wave
     int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
     int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
+    // 8-bit multi-head rows
+    int32_t unit_chunks;  // > 0: cut the contexts into as many chunks as run at once, which is this many
 };
 
 __device__ __forceinline__ int checked_len(const AttnArgs &a, int64_t off, int32_t raw) {
@@ -269,6 +271,16 @@ __device__ __forceinline__ int few_chunk_rows(const AttnArgs &a, int total, int 
     return min(a.chunk, (max(max(even, least), 64) + 15) & ~15);
 }
 
+// Rows per chunk of a batch of 8-bit rows whose contexts are fewer than the workgroups that run at once (host:
+// chunk_slots): the shortest whose chunks all run at once.  `units` less the `n * quarters / 4` chunks by which contexts
+// do not divide evenly; whether that was enough is counted (unit_chunks).  Bounds as in few_chunk_rows.
+__device__ __forceinline__ int unit_chunk_rows(const AttnArgs &a, int total, int longest, int quarters) {
+    if (longest <= 128) return a.chunk;
+    const int even = total / max(a.unit_chunks - ((a.n * quarters + 3) >> 2), 1) + 1;
+    const int least = (int)__builtin_amdgcn_sqrtf(10.f * (float)longest);
+    return min(a.chunk, (max(max(even, least), 64) + 15) & ~15);
+}
+
 // LDS picture of the batch built by every workgroup at kernel start (dynamic shared memory):
 //   off[n] (int64), len[n] (int32, 0 for refused entries), pre[ncls][n + 1] (int32)
 struct BatchView {
@@ -286,7 +298,7 @@ __device__ __forceinline__ size_t batch_view_bytes(int n, int ncls) {
 
 // The one-wave build of the view: lane l owns entries l*E .. l*E+E-1 (n <= 64*E).  `how`, for the other waves, where
 // the rows decide: rows per chunk, classes, mean rows of a context.
-template <int E>
+template <int E, bool UNITS>
 __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s, int *len_s, int *pre, int *how) {
     const int lane = threadIdx.x & 63, n = a.n;
     int chunk = a.chunk, ncls = a.ncls, mean = 0;
@@ -304,12 +316,23 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         mx = max(mx, len[e]);
     }
     mx = wave_max_nonneg(mx);
-    if (a.few_chunks > 0 || a.class_rows > 0) {
+    if (a.few_chunks > 0 || a.class_rows > 0 || (UNITS && a.unit_chunks > 0)) {
         int rows = 0;
 #pragma unroll
         for (int e = 0; e < E; e++) rows += len[e];
         rows = __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63);
         if (a.few_chunks > 0) chunk = few_chunk_rows(a, rows, mx);
+        if (UNITS && a.unit_chunks > 0) {
+#pragma unroll 1
+            for (int quarters = 2; quarters <= 4; quarters++) {
+                chunk = unit_chunk_rows(a, rows, mx, quarters);
+                if (chunk == a.chunk) break;
+                int count = 0;
+#pragma unroll
+                for (int e = 0; e < E; e++) count += (len[e] + chunk - 1) / chunk;
+                if (__builtin_amdgcn_readlane(wave_inclusive_scan(count), 63) <= a.unit_chunks) break;
+            }
+        }
         if (a.class_rows > 0) {
             mean = rows / n;
             if (mean < a.class_rows) ncls = 1;
@@ -448,6 +471,7 @@ __device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dy
 
 // One pass over the device arrays (each entry is read from global memory once and checked once),
 // then class-wise exclusive prefix sums of the chunk counts.
+template <bool UNITS = false>
 __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *dyn, int *wave_sums) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nthreads = blockDim.x, nwaves = nthreads >> 6;
@@ -463,10 +487,10 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         // E is a compile-time constant per batch size class: the per-entry work (two integer divisions) is
         // not spent on entries a small batch does not have.
         if (wave == 0) {
-            if (n <= 64) one_wave_view<1>(a, off_s, len_s, pre, wave_sums);
-            else if (n <= 128) one_wave_view<2>(a, off_s, len_s, pre, wave_sums);
-            else if (n <= 256) one_wave_view<4>(a, off_s, len_s, pre, wave_sums);
-            else one_wave_view<8>(a, off_s, len_s, pre, wave_sums);
+            if (n <= 64) one_wave_view<1, UNITS>(a, off_s, len_s, pre, wave_sums);
+            else if (n <= 128) one_wave_view<2, UNITS>(a, off_s, len_s, pre, wave_sums);
+            else if (n <= 256) one_wave_view<4, UNITS>(a, off_s, len_s, pre, wave_sums);
+            else one_wave_view<8, UNITS>(a, off_s, len_s, pre, wave_sums);
         }
         __syncthreads();
         BatchView v;
@@ -477,7 +501,7 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         v.chunk = chunk;
         v.ncls = ncls;
         v.mean = 0;
-        if (a.few_chunks > 0 || a.class_rows > 0) {
+        if (a.few_chunks > 0 || a.class_rows > 0 || (UNITS && a.unit_chunks > 0)) {
             v.chunk = __builtin_amdgcn_readfirstlane(wave_sums[0]);
             v.ncls = __builtin_amdgcn_readfirstlane(wave_sums[1]);
             v.mean = __builtin_amdgcn_readfirstlane(wave_sums[2]);

@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(TS * 64) attn_fp8_kernel(const AttnArgs a) {
     const int lane = threadIdx.x & 63, ts = threadIdx.x >> 6;
     const int tpw = (a.H < GH && GH % a.H == 0) ? GH / a.H : 1;  // rows per wave load
     const int n_hg = (a.H + GH - 1) / GH;
-    const BatchView bv = build_batch_view(a, dyn_lds, wave_sums);
+    const BatchView bv = build_batch_view<true>(a, dyn_lds, wave_sums);
     const int64_t total = (int64_t)bv.total * n_hg;
     // the new lengths, and a zero output row for empty or refused contexts, by the workgroups in turn
     for (int b = blockIdx.x; b < a.n; b += gridDim.x) {

@@ -699,7 +699,12 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // rows 74 -> 36 us, of 8050 rows 181 -> 112; 4 contexts of 500..1500 rows 129 -> 68, 8: 143 -> 102, 16: 207 -> 189;
 // 32 contexts of 32..1000 rows: 212, and 217 if the line were drawn above them.
 // As with s3i_gqa_max_shares, what the fixed buffer takes by its documented rule is held to its size.
-static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few) {
+// 8-bit rows, *units: beyond those batches, while the contexts' items are fewer than 0.7 of the two workgroups a compute unit
+// holds, contexts are cut until the chunks fill these (unit_chunk_rows): a workgroup streams 1000 rows in about 55 us whatever
+// the others do, and an item more than run at once starts only when another ends.  Contexts of 32..1000 rows, whole and cut, us
+// a layer: 16 heads x 256, 49 contexts 66.0 and 43.6, 64 68.3 and 54.8, 80 75.7 and 69.0, 96 (beyond the line) 90.2 and
+// 90.5, 112 97.4 and 98.4; 12 x 128, 97 64.3 and 39.6, 160 76.6 and 63.5.
+static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few, int32_t *units) {
     const int chunk = a->chunk > 0 ? a->chunk : 1024;
     const int64_t whole = (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
     const int64_t cus = a->num_cus > 0 ? a->num_cus : 256;
@@ -708,6 +713,10 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     const int64_t fixed = (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes(n_hg)) / slot_bytes);
     if (whole <= fixed && want > fixed - n) want = fixed - n;
     *few = want > 0 ? (int32_t)want : 0;
+    int64_t fill = s3i_kernel_kind(a) == 3 && a->chunk <= 0 && a->variant < 0 && want == 0 ? 2 * cus / n_hg : 0;
+    if (n * 10 > fill * 7 || (whole <= fixed && fill + n > fixed)) fill = 0;
+    *units = (int32_t)fill;
+    if (fill > want) want = fill;
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }
 
@@ -718,12 +727,12 @@ static size_t scratch_need(const s3_arena *a, int n) {
     const int gh = kind == 3 ? 1024 / D : heads_per_load(D), n_hg = (Hq + gh - 1) / gh;  // (kinds 0 and 3)
     size_t most = 0;
     for (int k = 1; k <= n; k++) {
-        int32_t few;
+        int32_t few, units;
         size_t slots;
         if (kind != 0 && kind != 3 && gqa_on_matrix_cores(a, k)) {
             slots = gqa_partial_slots(a, k);
         } else if (kind == 0 || kind == 3) {
-            slots = chunk_slots(a, k, n_hg, slot_bytes, &few);
+            slots = chunk_slots(a, k, n_hg, slot_bytes, &few, &units);
         } else {
             const int chunk = gqa_chunk_rows(a, k);
             slots = (size_t)k * ((a->cfg.max_len + chunk - 1) / chunk);
@@ -892,7 +901,7 @@ static int launch_gqa(s3_arena *a, const AttnCall &c) {
 // Scratch of a kernel whose chunks meet inside the launch.
 static int place_chunk_scratch(s3_arena *a, AttnArgs &args, int n_hg, const AttnCall &c) {
     const size_t slot_bytes = (size_t)args.Hq * ((size_t)a->cfg.head_dim * sizeof(float) + sizeof(float2));
-    const size_t slots = chunk_slots(a, c.n, n_hg, slot_bytes, &args.few_chunks);
+    const size_t slots = chunk_slots(a, c.n, n_hg, slot_bytes, &args.few_chunks, &args.unit_chunks);
     return place_scratch(a, args, counters_bytes(n_hg), slots, c);
 }
 

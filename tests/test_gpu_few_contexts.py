@@ -43,3 +43,26 @@ def test_few_contexts_are_cut_by_their_rows(fam):
         if kind == 0:  # (8-bit rows: the step takes the new row in its last wave, in another order of sums)
             assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
         rig.close()
+
+
+@pytest.mark.parametrize("fam,batches", [(FAMS[4], (49, 88, 90)), (FAMS[5], (193, 358, 360))], ids=["16 x 256 e4m3", "3 x 128 e4m3"])
+def test_eight_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
+    """Beyond the batches above, 8-bit rows are cut until their chunks fill two workgroups a compute unit, by a count on the
+    device: the first batch of that rule, the last and the first beyond it, with lengths that divide well and badly."""
+    name, H, Hkv, D, kvt, act, kind = fam
+    for n in batches:
+        for what, lens in (("even", [240] * n), ("badly", [129 + 3 * (b % 5) for b in range(n)]), ("short", [b % 40 for b in range(n)]),
+                           ("a long one", [1500] + [20 + b % 90 for b in range(n - 1)])):
+            rng = np.random.default_rng(n + D)
+            rig = EdgeRig(fam, lens, M=2048)
+            rows = rng.standard_normal((2048, Hkv, D), dtype=np.float32)
+            rig.put([np.roll(rows, b, axis=0)[:L] for b, L in enumerate(lens)], [np.roll(rows, 2 * b, axis=0)[:L] for b, L in enumerate(lens)])
+            q = rng.standard_normal((n, H, D), dtype=np.float32)
+            qb, att = rig.attend(q)
+            assert_close(att, rig.want(qb), f"{name} / {n} / {what}")
+            for grid in (7, 0):
+                assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0
+                assert np.array_equal(rig.attend(q)[1], att), (n, what, grid)
+            qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
+            assert_close(step, rig.want(qb, [L + 1 for L in lens]), f"{name} / {n} / {what} / step")
+            rig.close()
