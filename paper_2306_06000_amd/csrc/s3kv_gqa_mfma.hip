@@ -154,7 +154,8 @@ __device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x *
 
 // How a launch of few rows divides them (four waves a workgroup): every context by itself, into near-equal
 // chunks of at most `per` tiles, one wave or a team of four waves a chunk, all at once.  Nothing is combined that the
-// lengths do not force: a context of one chunk is finished by its wave or team.  What bounds such a launch is a chain of
+// lengths do not force: a context of one chunk is finished by its wave or team.  (The figures of few contexts were taken before
+// workgroups of eight took the launches of no more pairs than compute units.)  What bounds such a launch is a chain of
 // latencies (view and plan 2.5 us, rows a tile a microsecond and wave, the team's meeting in LDS 1, write-through and count
 // 1, merge 2 to 3) and, throughout, code that runs once out of a cold instruction cache.  A layer in microseconds, shares
 // across contexts or chunks by one wave -> this rule: 32q/8kv x 128, 3 contexts of 512..8192 rows 18.9 -> 16.2, 8 of
