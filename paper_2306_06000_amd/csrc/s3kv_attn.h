@@ -302,7 +302,8 @@ __device__ __forceinline__ void emit_chunk(const AttnArgs &a, const Item &it, in
 // unclaimed position from a device-wide counter (fetched by the epilogue wave one item ahead, so that the
 // round trip hides behind the streaming), which keeps every compute unit busy to the end whatever else
 // occupies some of them, and makes the longest-first order of the list a longest-processing-time schedule.
-template <int DT, int D, int TS, int HS, int U, bool NT, bool PF, int R, bool DYN>
+// UNITS: the view may cut the contexts into as many chunks as run at once (unit_chunk_rows).
+template <int DT, int D, int TS, int HS, int U, bool NT, bool PF, int R, bool DYN, bool UNITS = false>
 __global__ void __launch_bounds__((TS *HS + 1) * 64) attn_step_kernel(const AttnArgs a) {
     constexpr int LPH = HeadLanes<D>::LPH, USED = HeadLanes<D>::USED, GH = HeadLanes<D>::GH;
     constexpr int NWC = TS * HS;  // compute waves
@@ -316,7 +317,7 @@ __global__ void __launch_bounds__((TS *HS + 1) * 64) attn_step_kernel(const Attn
     const int ts = wave % TS, hs = wave / TS;
     const int n_hg = (a.H + GH - 1) / GH;
     const int n_hgb = (n_hg + HS - 1) / HS;
-    const BatchView bv = build_batch_view(a, dyn_lds, wave_sums);
+    const BatchView bv = build_batch_view<UNITS>(a, dyn_lds, wave_sums);
     const int64_t total = (int64_t)bv.total * n_hgb;
     char *ring = R > 0 ? dyn_lds + ((batch_view_bytes(a.n, a.ncls) + 15) & ~(size_t)15) + (size_t)(epilogue ? 0 : wave) * (R * 2048)
                        : nullptr;
@@ -689,9 +690,11 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const AttnArgs a) {
 #define S3_DEFAULT_VARIANT 4
 #define S3_DEFAULT_VARIANT_LARGE 13
 
+// (not a caller's choice: the default shape where the contexts are cut into as many chunks as run at once)
 template <int DT, int D>
 static attn_fn pick_variant(int v) {
     switch (v) {
+        case S3_UNIT_VARIANT: return (attn_fn)attn_step_kernel<DT, D, 8, 1, 2, true, true, 0, false, true>;
 #define X(i, ts, hs, u, nt, pf, r, dyn, xs)                                                                       \
     case i:                                                                                                       \
         if constexpr (xs) return (attn_fn)attn_step_stream_kernel<DT, D, ts * hs, u, dyn>; /* XS shapes: hs = 1 */ \

@@ -50,8 +50,9 @@ struct AttnArgs {
     float merge_cost;    // time of merging one more piece of a context, in tiles streamed by one wave
     int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
     int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
-    // 8-bit multi-head rows
-    int32_t unit_chunks;  // > 0: cut the contexts into as many chunks as run at once, which is this many
+    // multi-head kernels: > 0: cut the contexts into as many chunks as run at once, which is the low 16 bits, if they average
+    // as many rows as the high 16 bits say
+    int32_t unit_chunks;
 };
 
 __device__ __forceinline__ int checked_len(const AttnArgs &a, int64_t off, int32_t raw) {
@@ -271,14 +272,14 @@ __device__ __forceinline__ int few_chunk_rows(const AttnArgs &a, int total, int 
     return min(a.chunk, (max(max(even, least), 64) + 15) & ~15);
 }
 
-// Rows per chunk of a batch of 8-bit rows whose contexts are fewer than the workgroups that run at once (host:
-// chunk_slots): the shortest whose chunks all run at once.  `units` less the `n * quarters / 4` chunks by which contexts
-// do not divide evenly; whether that was enough is counted (unit_chunks).  Bounds as in few_chunk_rows.
-__device__ __forceinline__ int unit_chunk_rows(const AttnArgs &a, int total, int longest, int quarters) {
-    if (longest <= 128) return a.chunk;
-    const int even = total / max(a.unit_chunks - ((a.n * quarters + 3) >> 2), 1) + 1;
+// Rows per chunk of a batch whose contexts are fewer than the workgroups that run at once (host: chunk_slots): the shortest
+// whose chunks all run at once.  `units` less the `n * quarters / 4` chunks by which contexts do not divide evenly; whether
+// that was enough is counted (one_wave_view).  Bounds as in few_chunk_rows.
+__device__ __forceinline__ int unit_chunk_rows(const AttnArgs &a, int units, int total, int longest, int quarters, int most) {
+    if (longest <= 128) return most;
+    const int even = total / max(units - ((a.n * quarters + 3) >> 2), 1) + 1;
     const int least = (int)__builtin_amdgcn_sqrtf(10.f * (float)longest);
-    return min(a.chunk, (max(max(even, least), 64) + 15) & ~15);
+    return min(most, (max(max(even, least), 64) + 15) & ~15);
 }
 
 // LDS picture of the batch built by every workgroup at kernel start (dynamic shared memory):
@@ -322,15 +323,17 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         for (int e = 0; e < E; e++) rows += len[e];
         rows = __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63);
         if (a.few_chunks > 0) chunk = few_chunk_rows(a, rows, mx);
-        if (UNITS && a.unit_chunks > 0) {
+        if (UNITS && a.unit_chunks > 0 && rows >= (a.unit_chunks >> 16) * n) {
+            // (16-bit rows: chunks of up to 2048 rows, where whole contexts are as many as run at once)
+            const int units = a.unit_chunks & 0xFFFF, most = a.unit_chunks >> 16 > 0 ? 2 * a.chunk : a.chunk;
 #pragma unroll 1
             for (int quarters = 2; quarters <= 4; quarters++) {
-                chunk = unit_chunk_rows(a, rows, mx, quarters);
-                if (chunk == a.chunk) break;
+                chunk = unit_chunk_rows(a, units, rows, mx, quarters, most);
+                if (chunk == most) break;
                 int count = 0;
 #pragma unroll
                 for (int e = 0; e < E; e++) count += (len[e] + chunk - 1) / chunk;
-                if (__builtin_amdgcn_readlane(wave_inclusive_scan(count), 63) <= a.unit_chunks) break;
+                if (__builtin_amdgcn_readlane(wave_inclusive_scan(count), 63) <= units) break;
             }
         }
         if (a.class_rows > 0) {
@@ -876,6 +879,7 @@ __device__ __forceinline__ Item uniform_item(const Item &i) {
 }
 
 typedef void (*attn_fn)(const AttnArgs);
+#define S3_UNIT_VARIANT 1000  // see pick_variant()
 
 // Kernel for shared key/value heads (defined in s3kv_gqa.hip): gq query heads per K/V head and
 // lane (1, 2, 4 or 8), shape = index into its (waves, rows per load batch) table, < 0 for the

@@ -704,6 +704,10 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // the others do, and an item more than run at once starts only when another ends.  Contexts of 32..1000 rows, whole and cut, us
 // a layer: 16 heads x 256, 49 contexts 66.0 and 43.6, 64 68.3 and 54.8, 80 75.7 and 69.0, 96 (beyond the line) 90.2 and
 // 90.5, 112 97.4 and 98.4; 12 x 128, 97 64.3 and 39.6, 160 76.6 and 63.5.
+// 16-bit rows: the same from half an item to one and a half a compute unit, where the contexts average 400 rows (700 where the
+// rule for few contexts serves them well too, and beyond 9/8 items), with chunks of up to 2048 rows: 64 x 96, 24 contexts of
+// 64..1500 rows 85.4 and 78.8, 8 39.7 and 35.0; 16 x 256, 20 of 800..2000 94.0 and 78.2, 25 of 32..1000 49.1 and 42.0, 40 62.7 and
+// 62.7; 12 x 128, 65 of 512..2048 102.5 and 89.0; short ones pay up to 0.3 us for the look (25 of 60..300 18.8 and 19.0).
 static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few, int32_t *units) {
     const int chunk = a->chunk > 0 ? a->chunk : 1024;
     const int64_t whole = (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
@@ -713,9 +717,17 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     const int64_t fixed = (int64_t)((S3_STATIC_SCRATCH_BYTES - counters_bytes(n_hg)) / slot_bytes);
     if (whole <= fixed && want > fixed - n) want = fixed - n;
     *few = want > 0 ? (int32_t)want : 0;
-    int64_t fill = s3i_kernel_kind(a) == 3 && a->chunk <= 0 && a->variant < 0 && want == 0 ? 2 * cus / n_hg : 0;
-    if (n * 10 > fill * 7 || (whole <= fixed && fill + n > fixed)) fill = 0;
-    *units = (int32_t)fill;
+    const bool free_choice = a->chunk <= 0 && a->variant < 0;
+    int64_t fill = free_choice ? 2 * cus / n_hg : 0, rows = 0;  // (rows: what the contexts average at least)
+    if (s3i_kernel_kind(a) == 3) {
+        if (want > 0 || n * 10 > fill * 7) fill = 0;
+    } else {
+        const int64_t items = (int64_t)n * n_hg;
+        rows = want > 0 || items > cus * 9 / 8 ? 700 : 400;
+        if (n > 128 || items < cus / 2 || items > cus * 3 / 2) fill = 0;
+    }
+    if (whole <= fixed && fill + n > fixed) fill = 0;
+    *units = fill > 0 ? (int32_t)(fill | rows << 16) : 0;
     if (fill > want) want = fill;
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }
@@ -953,6 +965,7 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
     }
     int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
+    if (args.unit_chunks > 0) fn = pick_kernel(a->cfg.kv_dtype, D, S3_UNIT_VARIANT);
     const int threads = s3i_variant_threads(variant);
     const size_t view = batch_view_lds(c.n, args.ncls);
     const size_t dyn_lds = s3i_variant_ring_bytes(variant) ? ((view + 15) & ~(size_t)15) + s3i_variant_ring_bytes(variant) : view;

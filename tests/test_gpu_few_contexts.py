@@ -66,3 +66,26 @@ def test_eight_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
             qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
             assert_close(step, rig.want(qb, [L + 1 for L in lens]), f"{name} / {n} / {what} / step")
             rig.close()
+
+
+@pytest.mark.parametrize("fam,batches", [(FAMS[0], (15, 16, 25, 48)), (FAMS[1], (43, 65, 128)), (FAMS[2], (64, 100))],
+                         ids=["16 x 256", "12 x 128", "5 x 96"])
+def test_sixteen_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
+    """16-bit rows, half an item to one and a half a compute unit: contexts that average enough rows are cut into as many
+    chunks as run at once, others as before; both sides of that average, and contexts longer than a chunk may be."""
+    name, H, Hkv, D, kvt, act, kind = fam
+    for n in batches:
+        for what, lens in (("long", [700 + 9 * (b % 7) for b in range(n)]), ("below the average", [390] * n),
+                           ("one very long", [2047] + [600 + b % 90 for b in range(n - 1)])):
+            rng = np.random.default_rng(n + D)
+            rig = EdgeRig(fam, lens, M=2048)
+            rows = rng.standard_normal((2048, Hkv, D), dtype=np.float32)
+            rig.put([np.roll(rows, b, axis=0)[:L] for b, L in enumerate(lens)], [np.roll(rows, 2 * b, axis=0)[:L] for b, L in enumerate(lens)])
+            q = rng.standard_normal((n, H, D), dtype=np.float32)
+            qb, att = rig.attend(q)
+            assert_close(att, rig.want(qb), f"{name} / {n} / {what}")
+            qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
+            longer = [L + 1 for L in lens]
+            assert_close(step, rig.want(qb, longer), f"{name} / {n} / {what} / step")
+            assert np.array_equal(rig.attend(q, lens=longer)[1], step), (n, what)
+            rig.close()
