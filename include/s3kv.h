@@ -183,17 +183,17 @@ int s3_decode_step(s3_arena *a, int32_t layer, int32_t n, const int32_t *slot_id
 
 /* For callers that cannot allocate device memory: code recorded into a HIP graph, serving loops that must
  * never synchronise, harnesses that forbid hipMalloc.  Exactly s3_decode_step (same arguments, checks,
- * kernels and results), except that the chunk partials and arrival counters live in a fixed buffer that is
- * part of the library's device image (S3_STATIC_SCRATCH_BYTES = 32 MiB, held by every GPU the library runs
+ * kernels and results), except that the chunk partials and arrival counters live in two fixed buffers that are
+ * part of the library's device image (S3_STATIC_SCRATCH_BYTES = 32 MiB each, held by every GPU the library runs
  * on until the process ends) instead of the arena's scratch: the call makes no hipMalloc, hipFree or other
  * allocating call and never synchronises.  A call that needs more - about
- * n * ceil(max_len / chunk) * n_heads * (4 * head_dim + 8) bytes plus the counters; 32 MiB hold the
+ * n * ceil(max_len / chunk) * n_heads * (4 * head_dim + 8) bytes plus the counters beyond 32 MiB, which hold the
  * 28-layer, 721-sequence GPT-J batch at the default chunk - returns S3_ERR_SCRATCH and launches nothing.
  * The "profile" parameter does not time these launches (its events are allocated).  All calls on one GPU,
- * from every arena, share the buffer and it keeps the last call's contents: the counters are left at zero
- * by every launch (and are cleared by a small kernel on `stream` whenever the previous call on this GPU laid
- * the buffer out differently), partials are always written before they are read; calls that overlap on one
- * GPU (two streams, two threads) race on it. */
+ * from every arena, share the buffers: the counters, which no partials ever reach, are left at zero by every
+ * launch, and partials are always written before they are read, so calls of any arenas and batch sizes may follow
+ * one another in any order, recorded into graphs or not; calls that overlap on one GPU (two streams, two
+ * threads) race. */
 int s3_decode_step_static(s3_arena *a, int32_t layer, int32_t n, const int32_t *slot_id, const int32_t *pos_host,
                           const int64_t *slot_off, const int32_t *pos, const void *q, const void *k_new,
                           const void *v_new, void *out, int32_t out_dtype, float scale, int32_t *len_out,

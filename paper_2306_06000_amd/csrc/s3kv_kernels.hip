@@ -338,71 +338,47 @@ static int ensure_scratch(s3_arena *a, size_t need) {
 
 // ---- the fixed scratch of s3_decode_step_static ------------------------------------------
 // Part of the library's device image: every GPU that loads the library holds its own copy at its own
-// address until the process ends.  In host code the array's name is only a handle for the runtime; the
-// device address is asked for once per device (with that device current) and only that address is ever
+// address until the process ends.  In host code the arrays' names are only handles for the runtime; the
+// device addresses are asked for once per device (with that device current) and only those are ever
 // handed to kernels.
+// The counters have memory of their own, which no call's partials reach whatever its arena or kernel: they are zero
+// in the device image and every launch leaves its own at zero, so launches of any layouts may follow one another,
+// recorded into graphs or not, and nothing has to be cleared.  (A call's counters and partials together are at most
+// S3_STATIC_SCRATCH_BYTES, see place_scratch, so either array holds its part.)
 static __device__ __align__(256) unsigned char s3_static_scratch[S3_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char s3_static_counters[S3_STATIC_SCRATCH_BYTES];
 
 #define S3_MAX_DEVICES 64
-struct StaticScratch {
-    void *ptr = nullptr;      // device address of s3_static_scratch on this device
-    size_t counter_bytes = 0; // counter region of the last call on this device (0: none yet)
+struct StaticScratch {  // device addresses on one device
+    char *partials = nullptr, *counters = nullptr;
 };
 static StaticScratch g_static[S3_MAX_DEVICES];
 static std::mutex g_static_guard;
 
-__global__ void __launch_bounds__(256) zero_words_kernel(unsigned int *p, size_t n) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
-}
-
-// The current device's entry, with the buffer's device address resolved (once per device).  Caller holds the guard.
-static int static_scratch_entry(StaticScratch **out) {
+// The current device's addresses, resolved once per device.
+static int static_scratch(StaticScratch *out) {
+    std::lock_guard<std::mutex> lock(g_static_guard);
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= S3_MAX_DEVICES) return S3_ERR_INVALID;
     StaticScratch &st = g_static[dev];
-    if (!st.ptr) {
-        void *p = nullptr;
+    if (!st.counters) {
+        void *p = nullptr, *c = nullptr;
         HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(s3_static_scratch)));
-        if (!p || ((uintptr_t)p & 255)) return S3_ERR_INVALID;
-        st.ptr = p;
+        HIP_TRY(hipGetSymbolAddress(&c, HIP_SYMBOL(s3_static_counters)));
+        if (!p || !c || ((uintptr_t)p & 255) || ((uintptr_t)c & 255)) return S3_ERR_INVALID;
+        st.partials = (char *)p;
+        st.counters = (char *)c;
     }
-    *out = &st;
+    *out = st;
     return S3_OK;
 }
 
-// Called when an arena is created over device memory: the address is then known before the first decode step
+// Called when an arena is created over device memory: the addresses are then known before the first decode step
 // (which may run where no runtime query is wanted, e.g. under graph capture).
 int s3i_static_scratch_setup() {
-    std::lock_guard<std::mutex> lock(g_static_guard);
-    StaticScratch *st = nullptr;
-    return static_scratch_entry(&st);
-}
-
-// Address of the current device's fixed scratch, laid out with cnt_bytes of arrival counters at its head.
-// The counters must be zero before a launch.  Every launch leaves them at zero, but the region may hold
-// partials of a call that laid the buffer out with fewer counter bytes (another arena kind): whenever the
-// counter region differs from the last call's on this device (the first call included) it is cleared by a
-// kernel on `stream` (a kernel, not a memset, so that the call can be recorded into a graph).
-static int static_scratch_for_call(size_t cnt_bytes, void *stream, char **out) {
-    std::lock_guard<std::mutex> lock(g_static_guard);
-    StaticScratch *entry = nullptr;
-    const int src = static_scratch_entry(&entry);
-    if (src != S3_OK) return src;
-    StaticScratch &st = *entry;
-    if (cnt_bytes != st.counter_bytes) {
-        const size_t clear = cnt_bytes > st.counter_bytes ? cnt_bytes : st.counter_bytes;
-        if (clear > 0) {
-            const size_t words = clear / sizeof(unsigned int);
-            hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + 1023) / 1024)), dim3(256), 0,
-                               (hipStream_t)stream, (unsigned int *)st.ptr, words);
-            HIP_TRY(hipGetLastError());
-        }
-        st.counter_bytes = cnt_bytes;
-    }
-    *out = (char *)st.ptr;
-    return S3_OK;
+    StaticScratch st;
+    return static_scratch(&st);
 }
 
 // ---- optional event timing of the attention kernels -------------------------------------
@@ -580,16 +556,19 @@ static size_t scratch_need(const s3_arena *a, int n);
 
 // Library scratch: [arrival counters: cnt_bytes, fixed per arena kind, zero between launches]
 // [partial sums][partial (max, sum)], `slots` partials per head of q (one per sequence and chunk, or as
-// gqa_partial_slots() counts them).
+// gqa_partial_slots() counts them).  (s3_decode_step_static: the counters in an array of their own.)
 static int place_scratch(s3_arena *a, AttnArgs &args, size_t cnt_bytes, size_t slots, const AttnCall &c) {
     const size_t n_part = slots * args.Hq;
     const size_t acc_bytes = n_part * a->cfg.head_dim * sizeof(float);
     const size_t need = cnt_bytes + acc_bytes + n_part * sizeof(float2);
-    char *base = nullptr;
-    if (c.static_scratch) {  // no allocation on this path: the fixed buffer holds the call, or the call is refused
+    char *counters = nullptr, *partials = nullptr;
+    if (c.static_scratch) {  // no allocation on this path: the fixed buffers hold the call, or the call is refused
         if (need > (size_t)S3_STATIC_SCRATCH_BYTES) return S3_ERR_SCRATCH;
-        const int rc = static_scratch_for_call(cnt_bytes, c.stream, &base);
+        StaticScratch st;
+        const int rc = static_scratch(&st);
         if (rc != S3_OK) return rc;
+        counters = st.counters;
+        partials = st.partials;
     } else {
         // The scratch moves only for a batch larger than any before (or after a change of "chunk" or "variant"): a
         // smaller batch may need more than a larger one, since few contexts are cut finer, so a growth takes what
@@ -600,12 +579,13 @@ static int place_scratch(s3_arena *a, AttnArgs &args, size_t cnt_bytes, size_t s
             if (rc != S3_OK) return rc;
             if (args.n > a->scratch_batch) a->scratch_batch = args.n;
         }
-        base = (char *)a->scratch;
+        counters = (char *)a->scratch;
+        partials = counters + cnt_bytes;
     }
-    args.arrivals = (unsigned int *)base;
-    args.queue = cnt_bytes >= 256 ? (unsigned int *)(base + cnt_bytes - 256) : nullptr;  // the last 256 bytes of the counter region
-    args.part_acc = (float *)(base + cnt_bytes);
-    args.part_ml = (float2 *)(base + cnt_bytes + acc_bytes);
+    args.arrivals = (unsigned int *)counters;
+    args.queue = cnt_bytes >= 256 ? (unsigned int *)(counters + cnt_bytes - 256) : nullptr;  // the last 256 bytes of the counter region
+    args.part_acc = (float *)partials;
+    args.part_ml = (float2 *)(partials + acc_bytes);
     return S3_OK;
 }
 
@@ -899,8 +879,8 @@ static int launch_gqa(s3_arena *a, const AttnCall &c) {
     }
     AttnArgs args = common_args(a, c, Hkv, Hq, gqa_chunk_rows(a, c.n));
     // The arena's scratch keeps the matrix-core kernel's counter region (zero between launches) in front of the
-    // partials: both kernels of a shared-head arena may run in turn (the "variant" parameter).  The fixed buffer of
-    // s3_decode_step_static is cleared whenever its layout changes and needs no such room.
+    // partials: both kernels of a shared-head arena run in turn (by the batch, or the "variant" parameter).  The fixed
+    // scratch of s3_decode_step_static has its counters elsewhere and needs no such room.
     int rc = place_scratch(a, args, c.static_scratch ? 0 : counters_bytes((int)gqa_columns(a)), (size_t)args.n * args.max_chunks, c);
     if (rc != S3_OK) return rc;
     const size_t dyn_lds = batch_view_lds(c.n, args.ncls);

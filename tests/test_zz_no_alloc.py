@@ -161,3 +161,55 @@ def test_static_scratch_step_recorded_in_a_graph_replays_exactly_with_the_dynami
         assert torch.equal(again, want)
     assert s3.s3_kv_get_param(rig.a, "scratch_bytes")[1] > 0  # (from the allocating reference call only)
     rig.close()
+
+
+def test_recorded_steps_of_different_kernels_and_arenas_replay_in_any_order():
+    """One recorded step per batch size and arena is what the entry point is for.  An arena of two query heads per cached
+    head changes its kernel with the batch, and the kernels and arenas lay their scratch out differently: whatever was
+    replayed or called before, every step finds its arrival counters at zero.  All of them have contexts in several
+    pieces, and their partials are large enough to cover every other step's counters."""
+    small_groups = ("two heads a cached head", 16, 8, 128, s3.S3_BF16, s3.S3_BF16, 1)
+    steps = []
+    for fam, n in ((small_groups, 20), (small_groups, 64), (small_groups, 65), (small_groups, 200), (FAMILIES[0], 12), (FAMILIES[5], 40),
+                   (FAMILIES[6], 30)):
+        name, H, Hkv, D, kvt, act, kind = fam
+        rng = np.random.default_rng(n + D)
+        lens = [1500 - 11 * b if b < 40 else 3 + b % 20 for b in range(n)]
+        rig = EdgeRig(fam, lens, M=2048)
+        rows = rng.standard_normal((2048, Hkv, D), dtype=np.float32)
+        rig.put([np.roll(rows, b, axis=0)[:L] for b, L in enumerate(lens)], [np.roll(rows, 3 * b, axis=0)[:L] for b, L in enumerate(lens)])
+        q, k, v = (device_bits(wl.normal_bits(rng, (n, h, D), act), TDT[act], DEV) for h in (H, Hkv, Hkv))
+        pos_d = torch.tensor(lens, dtype=torch.int32, device=DEV)
+        want = torch.full((n, H, D), float("nan"), dtype=torch.float32, device=DEV)
+        assert s3.s3_decode_step(rig.a, 0, n, rig.off_d, pos_d, q, k, v, want, s3.S3_F32, 0.0, None, rig.stream) == 0
+        out = torch.empty_like(want)
+
+        def call(rig=rig, n=n, pos_d=pos_d, args=(q, k, v, out)):
+            return s3.s3_decode_step_static(rig.a, 0, n, rig.off_d, pos_d, *args, s3.S3_F32, 0.0, None,
+                                            torch.cuda.current_stream().cuda_stream)
+
+        def check(what, out=out, want=want, name=f"{name}, {n} contexts"):
+            torch.cuda.synchronize()
+            assert torch.equal(out, want), (name, what)
+
+        out.fill_(float("nan"))
+        assert call() == 0  # (an eager call, then the recording: the host saw the same layout twice)
+        check("eager")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call() == 0
+        steps.append((rig, graph, call, check, out))
+    order = [0, 3, 0, 2, 1, 3, 1, 4, 0, 5, 2, 0, 6, 1, 2, 5, 3, 4, 6, 3, 5, 0]
+    for eager_between in (False, True):
+        for i, k in enumerate(order):
+            rig, graph, call, check, out = steps[k]
+            out.fill_(float("nan"))
+            graph.replay()
+            check(f"replay {i}")
+            if eager_between:
+                rig, graph, call, check, out = steps[order[-1 - i]]
+                out.fill_(float("nan"))
+                assert call() == 0
+                check(f"call after replay {i}")
+    for rig, *_ in steps:
+        rig.close()
