@@ -156,7 +156,9 @@ int s3_kv_append(s3_arena *a, int32_t layer, int32_t n, const int32_t *slot_id, 
  * over the sequence's own rows only (no padding).  cur_len[b] == 0 gives a zero row.
  * Arithmetic is fp32 (dot products, max-subtracted softmax, weighted sum); contexts are
  * cut into chunks whose partials (max, sum, weighted sum) are merged, inside the launch but for
- * the vector-ALU kernel of shared heads, where a second kernel does.
+ * the vector-ALU kernel of shared heads, where a second kernel does.  (An infinite cached value makes its
+ * output element infinite or NaN; NaN always with four and more query heads per cached head, whose weighted
+ * sum runs over weights split into two 16-bit parts.)
  *   q         DEVICE [n][H][D] kv_dtype (8-bit caches: act_dtype), 16-byte aligned
  *   slot_off  DEVICE [n] int64, cur_len DEVICE [n] int32
  *   out       DEVICE [n][H][D] of out_dtype (S3_F32, S3_F16 or S3_BF16), 16-byte aligned

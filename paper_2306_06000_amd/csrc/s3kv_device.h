@@ -99,6 +99,11 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
+// The value that lane `from` (uniform) holds.
+__device__ __forceinline__ float lane_value(float v, int from) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), from));
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Exponent reference of a set of scores whose maximum is m: m, or 0 if every score is -inf, so that exp2(score - reference)
@@ -896,5 +901,5 @@ append_fp8_fn s3i_pick_append_fp8(int act);
 attn_fn s3i_pick_gqa_mfma(int dt, int d);
 attn_fn s3i_pick_gqa_mfma8(int act, int d);  // the same over 8-bit (e4m3) rows, q of type act
 attn_fn s3i_pick_gqa_mfma_wide(int act, int d, bool kv8);  // both, 512 threads per workgroup, one work item per workgroup
-attn_fn s3i_pick_gqa_mfma3(int dt, int d, bool wide);  // 16-bit rows, weights in three parts; 256 threads, or (wide) 512
+attn_fn s3i_pick_gqa_few_heads(int dt, int d, int group, bool wide);  // 16-bit rows, two or three query heads per cached head; 256 threads, or (wide) 512
 #define S3_FEW_CONTEXTS 256  // contexts whose view every wave of that kernel builds by itself

@@ -9,6 +9,7 @@
 // per cached head; here both products run on MFMA and every (row, head) score is handled by
 // exactly one lane.
 //
+// With two or three query heads per cached head only the scores are a matrix product (GQ, pick_few_heads).
 // Two instances: workgroups of eight waves for launches of no more (context, column) pairs than compute units, which know
 // only chunks (eight_wave_plan), and workgroups of four for all others (chunk_plan, share_plan).
 // Work division.  A column is one (K/V head, block of 16 query heads); every column has the same rows, in tiles of 16
@@ -69,18 +70,25 @@ __device__ __forceinline__ f32x4 mfma_values(const u32x2 a, const u32x2 b, const
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c, 0, 0, 0);
 }
 
-// c + V^T . P^T for RB blocks of 16 rows (two operand words each), P^T in PARTS parts, the highest first.  Three parts meet
-// before they are added, so that the running sum is rounded once a tile.
-template <int DT, int RB, int PARTS>
-__device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const unsigned (&p)[PARTS][2 * RB], f32x4 c) {
-    const f32x4 sum = c;
-    if (PARTS == 3) c = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = PARTS - 1; i >= 0; i--) {
-        if constexpr (RB == 2) c = mfma_scores<DT>((u32x4){v[0], v[1], v[2], v[3]}, (u32x4){p[i][0], p[i][1], p[i][2], p[i][3]}, c);
-        else c = mfma_values<DT>((u32x2){v[0], v[1]}, (u32x2){p[i][0], p[i][1]}, c);
+// V^T . P^T for RB blocks of 16 rows (two operand words each), P^T as its high and its low part.
+template <int DT, int RB>
+__device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const unsigned (&hi)[2 * RB], const unsigned (&lo)[2 * RB], f32x4 c) {
+    if constexpr (RB == 2) {
+        const u32x4 a = (u32x4){v[0], v[1], v[2], v[3]};
+        c = mfma_scores<DT>(a, (u32x4){hi[0], hi[1], hi[2], hi[3]}, c);
+        return mfma_scores<DT>(a, (u32x4){lo[0], lo[1], lo[2], lo[3]}, c);
+    } else {
+        const u32x2 a = (u32x2){v[0], v[1]};
+        c = mfma_values<DT>(a, (u32x2){hi[0], hi[1]}, c);
+        return mfma_values<DT>(a, (u32x2){lo[0], lo[1]}, c);
     }
-    return PARTS == 3 ? sum + c : c;
+}
+
+// Between writes to LDS and reads of the same words by other lanes of the wave: the LDS unit serves the wave in issue order,
+// so it is only the compiler that must not move the one across the other, nor hand a lane the value it wrote itself.
+__device__ __forceinline__ void lds_exchange() {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ unsigned pack_f16(float lo, float hi) {
@@ -497,7 +505,9 @@ __host__ __device__ constexpr int gqa_tile_rows(int row_bytes) { return row_byte
 // KV8: the cache rows are e4m3 codes (one byte per element) and DT is the type of q; a 16-byte load then
 // holds 16 elements, which are widened (exactly) to DT in registers and feed two contraction steps.
 // NW: waves of a workgroup, 4 or 8.
-template <int DT, int D, bool KV8, int NW, int PARTS = 2>
+// GQ: 2 or 3, the query heads per cached head where these are so few: the scores on the matrix cores, the weighted rows on the
+// vector ALU with the weights in fp32 (pick_few_heads); 0: both products on the matrix cores.
+template <int DT, int D, bool KV8, int NW, int GQ = 0>
 __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {
     constexpr int EB = KV8 ? 1 : 2;       // bytes per cached element
     constexpr int KS = D / 32;            // contraction steps of the score product
@@ -518,13 +528,15 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
     // Register sets of rows on their way: two, or one where two (with the new row of 8-bit rows) do not fit two waves a
     // SIMD: 239 and 229 of 256 registers.
     constexpr bool TWO_SETS = !(NW == 8 && D == 256);
+    static_assert(GQ == 0 || !KV8, "8-bit rows: both products on the matrix cores");
     constexpr bool APPENDS = !KV8 || CHUNKS;  // takes the new row of a decode step itself (else the host appends it first)
-    constexpr float RESCALE_LOG2 = 8.f;   // see the softmax step
+    constexpr float RESCALE_LOG2 = GQ > 0 ? 0.f : 8.f;  // see the softmax step
     extern __shared__ __align__(16) char dyn_lds[];  // the batch view, then the teams' first pieces
     __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
     // A wave's LDS: the V and the K tile, or, once its share is done, one piece (16 heads x D floats, padded).
     constexpr int PSTRIDE = D + 4;
-    constexpr int TILE_BYTES = TR * (VSTRIDE + KSTRIDE), PIECE_BYTES = 16 * PSTRIDE * 4;
+    // (GQ: the piece, behind it what the lanes of each of the RPL rows of a load have summed)
+    constexpr int TILE_BYTES = TR * (VSTRIDE + KSTRIDE), PIECE_BYTES = GQ > 0 ? (GQ * PSTRIDE + RPL * GQ * D) * 4 : 16 * PSTRIDE * 4;
     __shared__ __align__(16) char wave_lds[NW][TILE_BYTES > PIECE_BYTES ? TILE_BYTES : PIECE_BYTES];
     __shared__ float2 piece_ml[2 * NW][16];  // teams: (max, sum) of each wave's first (2w) and last (2w + 1) piece
     __shared__ f32x4 piece_run[CHUNKS ? 1 : 8][16];  // ... a piece's weight in its run of pieces, and the run's (max, sum, 1 / sum)
@@ -676,6 +688,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
             u32x4 qop[KS];
             u32x4 knew = (u32x4){0u, 0u, 0u, 0u}, vnew = knew, knew2 = knew, vnew2 = knew;  // (knew2, vnew2: 8-bit rows only)
             f32x4 o[DB];
+            float acc[GQ > 0 ? GQ : 1][8];  // GQ: this lane's eight elements of the weighted sums, over its rows of every load
             float m = -INFINITY, lsum = 0.f;
             int jnew = -1;  // decode step: the row of `now` that is still only in k_new / v_new
             auto enter = [&]() {  // start on context `now`
@@ -702,8 +715,15 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                         }
                     }
                 }
+                if constexpr (GQ > 0) {
 #pragma unroll
-                for (int db = 0; db < DB; db++) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    for (int h = 0; h < GQ; h++)
+#pragma unroll
+                        for (int e = 0; e < 8; e++) acc[h][e] = 0.f;
+                } else {
+#pragma unroll
+                    for (int db = 0; db < DB; db++) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                }
                 m = -INFINITY;
                 lsum = 0.f;
             };
@@ -732,6 +752,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
+                if constexpr (GQ > 0) lds_exchange();
             };
             auto reduce_tile = [&](int r0) {
                 const int end = now.len;
@@ -780,42 +801,82 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 // maximum exceeds it by more than RESCALE_LOG2, so p stays below 2^RESCALE_LOG2 and the
                 // rescale, which would otherwise run for almost every tile, runs for the first tile and
                 // then hardly ever.  (max, sum, row) leave the kernel consistent with whatever m is, which
-                // is all the merge of pieces needs.
+                // is all the merge of pieces needs.  (GQ: the running maximum itself, so that no weight exceeds 1 and sums
+                // overflow no earlier than the vector-ALU kernel's; there is little to rescale.)
                 const bool move = mt > m + RESCALE_LOG2;  // first tile: m = -inf
                 if (__builtin_amdgcn_ballot_w64(move) != 0) {
                     const float mn = move ? mt : m;
                     const float alpha = move ? fast_exp2(m - mn) : 1.f;  // 0 on the first tile
                     lsum *= alpha;
+                    if constexpr (GQ > 0) {
 #pragma unroll
-                    for (int db = 0; db < DB; db++) o[db] *= alpha;
+                        for (int h = 0; h < GQ; h++) {
+                            const float f = lane_value(alpha, h);
+#pragma unroll
+                            for (int e = 0; e < 8; e++) acc[h][e] *= f;
+                        }
+                    } else {
+#pragma unroll
+                        for (int db = 0; db < DB; db++) o[db] *= alpha;
+                    }
                     m = mn;
                 }
                 const float ref = exp_reference(m);
+                if constexpr (GQ > 0) {
+                    // The weights pass through the K tile's place (its rows have been read) to the lanes that hold the rows.
+                    // All of it is fp32: a weight keeps its 24 bits however small it is, and an infinite value gives an
+                    // infinite element (a 16-bit part of a weight that is 0 or negative would make it NaN).
+                    float *pw = (float *)kt;
+#pragma unroll
+                    for (int rb = 0; rb < RB; rb++) {
+                        float p[4];
+#pragma unroll
+                        for (int i = 0; i < 4; i++) {
+                            p[i] = fast_exp2(sv[rb][i] - ref);
+                            if (n < GQ) pw[(rb * 16 + 4 * g + i) * 4 + n] = p[i];
+                        }
+                        lsum += (p[0] + p[1]) + (p[2] + p[3]);
+                    }
+                    lds_exchange();
+                    float sum[GQ][8];  // of this tile: the long sums are rounded once a tile
+#pragma unroll
+                    for (int h = 0; h < GQ; h++)
+#pragma unroll
+                        for (int e = 0; e < 8; e++) sum[h][e] = 0.f;
+#pragma unroll
+                    for (int i = 0; i < NL; i++) {
+                        const int row = i * RPL + lane / PPR;
+                        const f32x4 w = *(const f32x4 *)(pw + row * 4);
+                        const u32x4 v = *(const u32x4 *)(vt + row * VSTRIDE + (lane % PPR) * 16);
+#pragma unroll
+                        for (int h = 0; h < GQ; h++) axpy8<DT>(sum[h], w[h], v);
+                    }
+#pragma unroll
+                    for (int h = 0; h < GQ; h++)
+#pragma unroll
+                        for (int e = 0; e < 8; e++) acc[h][e] += sum[h][e];
+                    lds_exchange();
+                    return;
+                }
                 // The weights enter the second product as 16-bit operands: a high part (p rounded to the type) and
                 // a low part (what the high part misses, rounded again), two products per value block.  Together
                 // they carry about twice the type's mantissa, so the weighted sum is as exact as the fp32 weights
-                // allow, also for values of large magnitude (one rounded part alone is off by 2^-12 of |p v|); a third part
-                // carries what fp32 holds beyond (see pick_three_parts).
+                // allow, also for values of large magnitude (one rounded part alone is off by 2^-12 of |p v|).
                 // Contraction slots of lane group g: rows 4g .. 4g+3 of each row block.
-                unsigned w16[PARTS][2 * RB];
+                unsigned hi[2 * RB], lo[2 * RB];
 #pragma unroll
                 for (int rb = 0; rb < RB; rb++) {
-                    float p[4];
+                    float p[4], r[4];
 #pragma unroll
                     for (int i = 0; i < 4; i++) {
                         p[i] = fast_exp2(sv[rb][i] - ref);
-                        // (three fp16 parts: weights 64 times as large, below 2^14, so that the parts of one that counts
-                        // stay in the type's range; sum and row carry the factor alike)
-                        if (DT == S3_F16 && PARTS == 3) p[i] *= 64.f;
                         lsum += p[i];
+                        r[i] = DT == S3_F16 ? p[i] - (float)(_Float16)p[i] : p[i] - (float)(__bf16)p[i];
                     }
 #pragma unroll
-                    for (int part = 0; part < PARTS; part++) {
-#pragma unroll
-                        for (int i = 0; i < 2; i++)
-                            w16[part][2 * rb + i] = DT == S3_F16 ? pack_f16(p[2 * i], p[2 * i + 1]) : pack_bf16(p[2 * i], p[2 * i + 1]);
-#pragma unroll
-                        for (int i = 0; i < 4; i++) p[i] = DT == S3_F16 ? p[i] - (float)(_Float16)p[i] : p[i] - (float)(__bf16)p[i];
+                    for (int i = 0; i < 2; i++) {
+                        hi[2 * rb + i] = DT == S3_F16 ? pack_f16(p[2 * i], p[2 * i + 1]) : pack_bf16(p[2 * i], p[2 * i + 1]);
+                        lo[2 * rb + i] = DT == S3_F16 ? pack_f16(r[2 * i], r[2 * i + 1]) : pack_bf16(r[2 * i], r[2 * i + 1]);
                     }
                 }
 
@@ -839,7 +900,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                                 vop[2 * rb] = widen2_e4m3<DT>(w[rb][j], false);
                                 vop[2 * rb + 1] = widen2_e4m3<DT>(w[rb][j], true);
                             }
-                            o[4 * q4 + j] = mfma_weights<DT, RB, PARTS>(vop, w16, o[4 * q4 + j]);
+                            o[4 * q4 + j] = mfma_weights<DT, RB>(vop, hi, lo, o[4 * q4 + j]);
                         }
                     }
                 } else {
@@ -853,7 +914,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                             vop[2 * rb] = v4[0];
                             vop[2 * rb + 1] = v4[1];
                         }
-                        o[db] = mfma_weights<DT, RB, PARTS>(vop, w16, o[db]);
+                        o[db] = mfma_weights<DT, RB>(vop, hi, lo, o[db]);
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -869,7 +930,16 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 const bool to_lds = !whole && (CHUNKS || team == 4);
                 const float f = whole ? 1.f / lsum : 1.f;
                 __builtin_amdgcn_wave_barrier();
-                if (head_ok) {
+                float *sums = last_piece + GQ * PSTRIDE;  // (GQ)
+                if constexpr (GQ > 0) {
+#pragma unroll
+                    for (int h = 0; h < GQ; h++) {
+                        float *dst = sums + ((lane / PPR) * GQ + h) * D + (lane % PPR) * 8;
+                        *(f32x4 *)dst = (f32x4){acc[h][0], acc[h][1], acc[h][2], acc[h][3]};
+                        *(f32x4 *)(dst + 4) = (f32x4){acc[h][4], acc[h][5], acc[h][6], acc[h][7]};
+                    }
+                    lds_exchange();
+                } else if (head_ok) {
 #pragma unroll
                     for (int i = 0; i < DB; i++) {
                         // 16-bit rows: accumulator block t holds elements 16t + 4g + i (i = 0..3).  8-bit rows (see the V
@@ -892,12 +962,29 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                     if (pend0.count == 0) pend0 = Pending{now.seq, first, count};
                     else pend1 = Pending{now.seq, first, count};
                 }
-                if (!(to_lds && (slot & 1))) {
+                if (GQ > 0 || !(to_lds && (slot & 1))) {
 #pragma unroll 1
                     for (int e = lane; e < nheads * (D / 4); e += 64) {
                         const int h = e / (D / 4), d = (e % (D / 4)) * 4;
-                        const f32x4 v = *(const f32x4 *)(last_piece + h * PSTRIDE + d);
-                        if (to_lds) *(f32x4 *)(first_piece + h * PSTRIDE + d) = v;
+                        f32x4 v;
+                        if constexpr (GQ > 0) {
+                            f32x4 part[RPL];
+#pragma unroll
+                            for (int r = 0; r < RPL; r++) part[r] = *(const f32x4 *)(sums + (r * GQ + h) * D + d);
+#pragma unroll
+                            for (int r = RPL / 2; r > 0; r /= 2)
+#pragma unroll
+                                for (int k = 0; k < r; k++) part[k] += part[k + r];
+                            v = part[0];
+                            float by = lane_value(f, 0);
+#pragma unroll
+                            for (int k = 1; k < GQ; k++) by = h == k ? lane_value(f, k) : by;
+                            v *= by;
+                        } else {
+                            v = *(const f32x4 *)(last_piece + h * PSTRIDE + d);
+                        }
+                        if (GQ > 0 && to_lds && (slot & 1)) *(f32x4 *)(last_piece + h * PSTRIDE + d) = v;
+                        else if (to_lds) *(f32x4 *)(first_piece + h * PSTRIDE + d) = v;
                         else if (whole) store_out4(a.out, a.out_dtype, row0 * D + 4 * e, v);
                         else put_partial4<true>(a.part_acc + row0 * D + 4 * e, v);
                     }
@@ -1083,19 +1170,25 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
     }
 }
 
-// Fewer than four query heads per cached head, 16-bit rows.  The vector-ALU kernel, which serves these where it is faster
-// (gqa_on_matrix_cores), keeps the weights in fp32; three parts keep as much.  Error against 64 bits, relative 2-norm, fp32 outputs, 16q/8kv
-// x 128 and 24q/8kv x 64 bf16: vector ALU 1.1e-7 to 2.4e-7, two parts 1.6e-6 to 2.4e-6, three 1.0e-7 to 2.1e-7 (no batch larger than the vector ALU's).
+// Two or three query heads per cached head, 16-bit rows.  The vector-ALU kernel, which serves these where it is faster
+// (gqa_on_matrix_cores), keeps the weights in fp32, and so does this one: only the scores are a matrix product (2 or 3 of its
+// 16 columns in use), the weighted rows are 2 or 3 multiply-adds an element on the vector ALU, far below what it could issue
+// while the rows arrive.  Weights in 16-bit parts on the matrix cores lose what the smallest of them carry (three fp16 parts
+// end at 2^-31 of the largest weight: a value of 6e4 under a weight of e^-14 off by 1e-5), make infinite values NaN, and save
+// 0 to 6 % of a launch at 128 and 256 elements a head, 2 to 8 % at 64.
+// Error against 64 bits, relative 2-norm, fp32 outputs, 16q/8kv x 128, 64q/32kv x 128, 16q/8kv x 64, 6q/3kv x 256, 24q/8kv x
+// 64, 12q/4kv x 128, 9q/3kv x 256, 8 to 85 contexts: bf16 1.34e-7 to 1.53e-7 where the vector ALU has 1.58e-7 to 1.82e-7, fp16
+// 1.38e-7 to 1.61e-7 and 1.66e-7 to 1.85e-7; one context of 37 rows level (bf16 1.11e-7 to 1.36e-7, 1.13e-7 to 1.37e-7).
 template <int DT, int NW>
-static attn_fn pick_three_parts(int d) {
-    if (d == 64) return attn_gqa_mfma_kernel<DT, 64, false, NW, 3>;
-    if (d == 128) return attn_gqa_mfma_kernel<DT, 128, false, NW, 3>;
-    if (d == 256) return attn_gqa_mfma_kernel<DT, 256, false, NW, 3>;
+static attn_fn pick_few_heads(int d, int group) {
+    if (d == 64) return group == 2 ? attn_gqa_mfma_kernel<DT, 64, false, NW, 2> : attn_gqa_mfma_kernel<DT, 64, false, NW, 3>;
+    if (d == 128) return group == 2 ? attn_gqa_mfma_kernel<DT, 128, false, NW, 2> : attn_gqa_mfma_kernel<DT, 128, false, NW, 3>;
+    if (d == 256) return group == 2 ? attn_gqa_mfma_kernel<DT, 256, false, NW, 2> : attn_gqa_mfma_kernel<DT, 256, false, NW, 3>;
     return nullptr;
 }
-attn_fn s3i_pick_gqa_mfma3(int dt, int d, bool wide) {
-    if (dt == S3_F16) return wide ? pick_three_parts<S3_F16, 8>(d) : pick_three_parts<S3_F16, 4>(d);
-    return wide ? pick_three_parts<S3_BF16, 8>(d) : pick_three_parts<S3_BF16, 4>(d);
+attn_fn s3i_pick_gqa_few_heads(int dt, int d, int group, bool wide) {
+    if (dt == S3_F16) return wide ? pick_few_heads<S3_F16, 8>(d, group) : pick_few_heads<S3_F16, 4>(d, group);
+    return wide ? pick_few_heads<S3_BF16, 8>(d, group) : pick_few_heads<S3_BF16, 4>(d, group);
 }
 
 attn_fn s3i_pick_gqa_mfma(int dt, int d) {

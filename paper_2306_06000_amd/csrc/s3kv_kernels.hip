@@ -630,11 +630,11 @@ static int gqa_chunk_rows(const s3_arena *a, int n) {
 // matrix cores win where the launch is a chain of latencies (one launch instead of three) and wherever the vector-ALU kernel
 // reads the rows once per query head (odd groups).  With two heads it reads them once, and a batch that fills the chip is
 // bound by memory either way: more (sequence, cached head) pairs than two a compute unit stay with it (of 256: than one).
-// us a layer, vector ALU and matrix cores: 16q/8kv x 128, 1 context of 20 rows 11.6, 6.8, 20 of 32..1000 27.9, 15.3, 64 of 100..200
-// 23.7, 15.9, 85 of 32..1000 41.5, 42.4; 64q/32kv x 128, 10 of 2..24 11.4, 8.0, 64 of 100..200 36.4, 43.3; 6q/3kv x 256, 20 of 32..1000 29.2, 14.4,
-// 300 of 2..40 17.7, 19.6; 24q/8kv x 64, 20 of 32..1000 25.0, 10.6, 700 of 32..1000 393, 130, 1000 of 2..25 32.2, 20.5.
-// (Both keep what fp32 weights hold, see pick_three_parts; an infinite cached value makes its output element infinite on the
-// vector ALU and NaN on the matrix cores.)
+// us a layer, bf16, vector ALU and matrix cores: 16q/8kv x 128, 1 context of 30..40 rows 11.4, 6.8, 20 of 32..1000 28.0, 16.3,
+// 64 of 100..200 23.7, 16.2, 85 of 32..1000 41.5, 43.4; 64q/32kv x 128, 8 of 32..1000 27.9, 19.4, 64 of 100..200 35.9, 44.9;
+// 6q/3kv x 256, 20 of 32..1000 29.1, 15.2, 85 36.9, 34.4, 300 of 2..40 17.9, 18.1; 24q/8kv x 64, 20 of 32..1000 25.0, 13.0, 700 of
+// 32..1000 392, 133, 300 of 2..40 19.5, 13.7; 9q/3kv x 256, 700 of 32..1000 633, 206.
+// (Both keep the weights in fp32 and treat infinite values alike, see pick_few_heads.)
 static bool gqa_on_matrix_cores(const s3_arena *a, int n) {
     const int kind = s3i_kernel_kind(a);
     if (kind != 1 || a->variant >= 0 || a->chunk > 0) return kind == 2 || kind == 4;
@@ -808,8 +808,9 @@ static int launch_attn_kernels(s3_arena *a, attn_fn fn, int blocks, int threads,
 static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
     const bool eight_bit = s3i_kernel_kind(a) == 4;
-    const bool three_parts = !eight_bit && Hq / Hkv < 4;
-    attn_fn fn = three_parts ? s3i_pick_gqa_mfma3(a->cfg.kv_dtype, D, false)
+    const int group = Hq / Hkv;
+    const bool few_heads = !eight_bit && group < 4;
+    attn_fn fn = few_heads ? s3i_pick_gqa_few_heads(a->cfg.kv_dtype, D, group, false)
                  : eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D) : s3i_pick_gqa_mfma(a->cfg.kv_dtype, D);
     if (!fn) return S3_ERR_INVALID;
     if (c.static_scratch && !gqa_fits_static(a, c.n)) return S3_ERR_SCRATCH;
@@ -829,7 +830,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     const size_t dyn_lds = args.team_lds ? ((view + 15) & ~(size_t)15) + pieces : view;
     int per_cu = 0;
     const int cus = a->num_cus > 0 ? a->num_cus : 256;
-    args.group = Hq / Hkv;
+    args.group = group;
     args.nqb = (args.group + 15) / 16;
     args.columns = (int32_t)columns;
     args.column_shift = (columns & (columns - 1)) == 0 ? __builtin_ctzll((unsigned long long)columns) : -1;
@@ -837,7 +838,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     // chunk of one (eight_wave_plan).  Beyond, pairs would wait for a unit of their own (32q/8kv x 128, 34 contexts of
     // 32..1000 rows 22.0 us a layer against 21.5 with workgroups of four, 64 contexts 34.2 against 30.5).
     if (a->chunk <= 0 && c.n <= S3_FEW_CONTEXTS && c.n * columns <= cus) {
-        attn_fn wide = three_parts ? s3i_pick_gqa_mfma3(a->cfg.kv_dtype, D, true) : s3i_pick_gqa_mfma_wide(a->cfg.act_dtype, D, eight_bit);
+        attn_fn wide = few_heads ? s3i_pick_gqa_few_heads(a->cfg.kv_dtype, D, group, true) : s3i_pick_gqa_mfma_wide(a->cfg.act_dtype, D, eight_bit);
         args.team_shares = (int32_t)(cus / columns);
         rc = resident_per_cu((const void *)wide, 512, view, &per_cu);
         if (rc != S3_OK) return rc;
