@@ -8,6 +8,7 @@ from paper_2306_06000_amd import binding as s3
 from tests.harness import assert_close
 from tests.test_gpu_numeric_edges import EdgeRig
 
+torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 FAMS = [
@@ -89,3 +90,33 @@ def test_sixteen_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
             assert_close(step, rig.want(qb, longer), f"{name} / {n} / {what} / step")
             assert np.array_equal(rig.attend(q, lens=longer)[1], step), (n, what)
             rig.close()
+
+
+@pytest.mark.parametrize("H,D,kvt,n", [(12, 128, s3.S3_BF16, 128), (16, 256, s3.S3_F16, 20), (64, 96, s3.S3_BF16, 24), (32, 64, s3.S3_F16, 80)])
+def test_longer_chunks_sum_no_longer_runs(H, D, kvt, n):
+    """16-bit rows in chunks of up to 2048 rows: against 64 bits the outputs are as exact as in chunks of 1024."""
+    rng = np.random.default_rng(D)
+    lens = [int(x) for x in rng.integers(1000, 2048, size=n)]
+    rig = EdgeRig(("runs", H, H, D, kvt, kvt, 0), lens, M=2048)
+    K, V = [], []
+    for L in lens:
+        K.append(rng.standard_normal((L, H, D), dtype=np.float32))
+        V.append(rng.standard_normal((L, H, D), dtype=np.float32))
+    rig.put(K, V)
+    dt = {s3.S3_F16: torch.float16, s3.S3_BF16: torch.bfloat16}[kvt]
+
+    def stored(x):  # [rows][H][D] -> [H][rows][D] in 64 bits, as the cache holds it
+        return torch.from_numpy(x).to("cuda:0").to(dt).double().permute(1, 0, 2).contiguous()
+
+    q = rng.standard_normal((n, H, D), dtype=np.float32)
+    want = np.empty((n, H, D))
+    for b in range(n):
+        s = torch.matmul(stored(K[b]), stored(q[b][None]).permute(0, 2, 1).contiguous()).squeeze(2) / D**0.5
+        p = torch.softmax(s, dim=1)
+        want[b] = torch.matmul(p.unsqueeze(1), stored(V[b])).squeeze(1).cpu().numpy()
+    off = []
+    for chunk in (0, 1024):
+        assert s3.s3_kv_set_param(rig.a, "chunk", chunk) == 0
+        off.append(np.linalg.norm(rig.attend(q)[1] - want) / np.linalg.norm(want))
+    rig.close()
+    assert off[0] <= 1.03 * off[1], off  # (the division of the rows differs, and with it every rounding: 1 % either way)
