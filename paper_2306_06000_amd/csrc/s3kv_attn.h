@@ -137,7 +137,7 @@ __device__ __forceinline__ void wave_tokens(const AttnArgs &a, const Item &it, i
         // (the second run's first row; past the share's end: there is none)
         const int second = TWICE && j1 - j0 > 128 ? j0 + (j1 - j0 + 4 * U - 1) / (4 * U) * (2 * U) : j1;
         for (int j = j0; j < j1; j += 2 * U) {
-            if (TWICE && j == second) {
+            if (TWICE && __builtin_expect(j == second, 0)) {
                 place[0][lane] = m;
                 place[1][lane] = l;
                 m = -INFINITY;
@@ -156,7 +156,7 @@ __device__ __forceinline__ void wave_tokens(const AttnArgs &a, const Item &it, i
                 st.reduce(j + U, kb, vb, m, l, acc);
             }
         }
-        if (TWICE && second < j1) {
+        if (TWICE && __builtin_expect(second < j1, 0)) {
             const float m1 = place[0][lane], mm = fmaxf(m1, m), f1 = fast_exp2(m1 - mm), f = fast_exp2(m - mm);
             m = mm;
             l = f1 * place[1][lane] + f * l;

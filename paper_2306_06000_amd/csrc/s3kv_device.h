@@ -50,8 +50,8 @@ struct AttnArgs {
     float merge_cost;    // time of merging one more piece of a context, in tiles streamed by one wave
     int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
     int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
-    // multi-head kernels: > 0: cut the contexts into as many chunks as run at once, which is the low 16 bits, if they average
-    // as many rows as the high 16 bits say
+    // multi-head kernels: > 0: the chunks of a context's heads that run at once (low 16 bits); the contexts may be cut into as
+    // many, whatever their rows, or (16 bits and up: 1) as unit_rule() says
     int32_t unit_chunks;
 };
 
@@ -287,6 +287,37 @@ __device__ __forceinline__ int unit_chunk_rows(const AttnArgs &a, int units, int
     return min(most, (max(max(even, least), 64) + 15) & ~15);
 }
 
+// 16-bit rows: whether the chunk length above takes the place of few_chunk_rows, or of chunks of 1024 rows (a.chunk), which a
+// batch beyond the few contexts gets.  chunks: how many those would be; rows, longest: all rows, and those of the longest
+// context.  Two kinds of batch gain:
+// (1) few contexts whose chunks turn out more than the compute units (contexts do not divide evenly), so that some units get
+// two and the launch lasts as long as those: by more than an eighth at 400 rows a context, by any number at 1000.
+// (2) beyond the few, a longest chunk that outlasts the rest: u items a compute unit (2 * n / units) of r rows on average take
+// the time of u * r rows, a single one streams about twice as fast once the others are done, and the finer division costs as
+// much again where it shares out little: the line, measured, is longest / r = 2 * u^2, and 1.6.
+// us a layer without and with: (1) 16 x 256, 18 contexts of 1000..2047 rows 94.1, 79.4, 64 x 96, 10 of 400..1400 63.8, 50.5, 12 x
+// 128, 52 of 300..600 34.5, 29.7; below the line 64 x 96, 9 of 512..2048 52.1, 56.8.  (2) 16 x 256, 25 of 32..1000 46.4, 41.3, 12 x 128, 67 of 40..2000 with a long tail 48.5, 36.7; below the line 67 of 300..600 35.4, 39.1, 16 x 64, 98 of
+// 10..200 13.7, 17.0.  Over 4160 batches (five shapes, thirteen kinds of lengths, 9/16 to 7/4 items a compute unit) those cut
+// by (1) took 0.90 of their time, by (2) 0.85, at most 1.074.
+__device__ __forceinline__ bool unit_rule(const AttnArgs &a, int units, int chunks, int rows, int longest) {
+    if (a.few_chunks > 0)
+        return 8 * chunks <= 7 * units && rows >= 400 * a.n && (16 * chunks > 9 * units || (2 * chunks > units && rows >= 1000 * a.n));
+    const float most = (float)min(longest, a.chunk), all = (float)rows;
+    return 2 * a.n <= units && longest >= 512 && 5.f * most * (float)a.n >= 8.f * all && most * (float)units * (float)units >= 8.f * (float)a.n * all;
+}
+
+// ... and whether the contexts stay whole where they would otherwise be cut at 1024 rows.  From 4/3 items a compute unit, no
+// context so long that it outlasts the rest: if chunks of 1024 rows were more than run at once by a tenth, so that a second,
+// mostly empty round followed, or nearly as many (7/8 and up) of contexts that differ about twofold.  us a layer cut at 1024 and
+// whole: 64 x 96, 23 contexts of 400..1400 rows 106.1, 93.9, 23 of 64..1500 81.9, 77.2, 16 x 256, 46 of 200..1800 142.3, 137.7;
+// outside the rule 64 x 96, 20 of 900..1100 83.8, 100.2, 16 x 256, 44 of 1000..2047 180.5, 193.  Over the batches above 0.96, at
+// most 1.048.
+__device__ __forceinline__ bool whole_rule(const AttnArgs &a, int units, int chunks, int rows, int longest) {
+    if (a.few_chunks > 0 || 3 * a.n < 2 * units || longest <= a.chunk || 4 * longest > 7 * a.chunk) return false;
+    if (chunks > units) return 10 * chunks >= 11 * units;
+    return 8 * chunks >= 7 * units && 4 * longest * a.n >= 7 * rows && longest * a.n <= 2 * rows;
+}
+
 // LDS picture of the batch built by every workgroup at kernel start (dynamic shared memory):
 //   off[n] (int64), len[n] (int32, 0 for refused entries), pre[ncls][n + 1] (int32)
 struct BatchView {
@@ -328,17 +359,25 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         for (int e = 0; e < E; e++) rows += len[e];
         rows = __builtin_amdgcn_readlane(wave_inclusive_scan(rows), 63);
         if (a.few_chunks > 0) chunk = few_chunk_rows(a, rows, mx);
-        if (UNITS && a.unit_chunks > 0 && rows >= (a.unit_chunks >> 16) * n) {
-            // (16-bit rows: chunks of up to 2048 rows, where whole contexts are as many as run at once)
-            const int units = a.unit_chunks & 0xFFFF, most = a.unit_chunks >> 16 > 0 ? 2 * a.chunk : a.chunk;
-#pragma unroll 1
-            for (int quarters = 2; quarters <= 4; quarters++) {
-                chunk = unit_chunk_rows(a, units, rows, mx, quarters, most);
-                if (chunk == most) break;
-                int count = 0;
+        auto chunks_of = [&](int rows_each) {
+            int count = 0;
 #pragma unroll
-                for (int e = 0; e < E; e++) count += (len[e] + chunk - 1) / chunk;
-                if (__builtin_amdgcn_readlane(wave_inclusive_scan(count), 63) <= units) break;
+            for (int e = 0; e < E; e++) count += (len[e] + rows_each - 1) / rows_each;
+            return __builtin_amdgcn_readlane(wave_inclusive_scan(count), 63);
+        };
+        const int sixteen = a.unit_chunks >> 16;
+        if (UNITS && a.unit_chunks > 0 && (!sixteen || mx >= 400)) {
+            // (16-bit rows: chunks of up to 2048 rows, where whole contexts are as many as run at once)
+            const int units = a.unit_chunks & 0xFFFF, most = sixteen ? 2 * a.chunk : a.chunk;
+            const int before = sixteen && (a.few_chunks > 0 || 2 * n > units) ? chunks_of(chunk) : 0;  // (where a rule asks)
+            if (!sixteen || __builtin_expect(unit_rule(a, units, before, rows, mx), 0)) {
+#pragma unroll 1
+                for (int quarters = 2; quarters <= 4; quarters++) {
+                    chunk = unit_chunk_rows(a, units, rows, mx, quarters, most);
+                    if (chunk == most || chunks_of(chunk) <= units) break;
+                }
+            } else if (whole_rule(a, units, before, rows, mx)) {
+                chunk = most;
             }
         }
         if (a.class_rows > 0) {

@@ -684,10 +684,9 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // the others do, and an item more than run at once starts only when another ends.  Contexts of 32..1000 rows, whole and cut, us
 // a layer: 16 heads x 256, 49 contexts 66.0 and 43.6, 64 68.3 and 54.8, 80 75.7 and 69.0, 96 (beyond the line) 90.2 and
 // 90.5, 112 97.4 and 98.4; 12 x 128, 97 64.3 and 39.6, 160 76.6 and 63.5.
-// 16-bit rows: the same from half an item to one and a half a compute unit, where the contexts average 400 rows (700 where the
-// rule for few contexts serves them well too, and beyond 9/8 items), with chunks of up to 2048 rows: 64 x 96, 24 contexts of
-// 64..1500 rows 85.4 and 78.8, 8 39.7 and 35.0; 16 x 256, 20 of 800..2000 94.0 and 78.2, 25 of 32..1000 49.1 and 42.0, 40 62.7 and
-// 62.7; 12 x 128, 65 of 512..2048 102.5 and 89.0; short ones pay up to 0.3 us for the look (25 of 60..300 18.8 and 19.0).
+// 16-bit rows: the same with chunks of up to 2048 rows, where the rows say so on the device: from 9/16 to one item a compute unit
+// (unit_rule), and from 4/3 to 7/4 whole contexts (whole_rule), if contexts can be long enough at all.  Batches that the rules
+// leave alone pay 0.2 to 1.0 us for the look (half of them less than 0.6), which is why they are not asked in between, where only few gain.
 static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few, int32_t *units) {
     const int chunk = a->chunk > 0 ? a->chunk : 1024;
     const int64_t whole = (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
@@ -698,16 +697,16 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     if (whole <= fixed && want > fixed - n) want = fixed - n;
     *few = want > 0 ? (int32_t)want : 0;
     const bool free_choice = a->chunk <= 0 && a->variant < 0;
-    int64_t fill = free_choice ? 2 * cus / n_hg : 0, rows = 0;  // (rows: what the contexts average at least)
-    if (s3i_kernel_kind(a) == 3) {
+    int64_t fill = free_choice ? 2 * cus / n_hg : 0;
+    const bool eight_bit = s3i_kernel_kind(a) == 3;
+    if (eight_bit) {
         if (want > 0 || n * 10 > fill * 7) fill = 0;
     } else {
-        const int64_t items = (int64_t)n * n_hg;
-        rows = want > 0 || items > cus * 9 / 8 ? 700 : 400;
-        if (n > 128 || items < cus / 2 || items > cus * 3 / 2) fill = 0;
+        const bool cut = want > 0 ? n * 32 >= fill * 9 : n * 2 <= fill, uncut = n * 3 >= fill * 2 && n * 8 <= fill * 7;
+        if (n > 128 || !(cut ? a->cfg.max_len >= 400 : uncut && a->cfg.max_len > chunk)) fill = 0;
     }
     if (whole <= fixed && fill + n > fixed) fill = 0;
-    *units = fill > 0 ? (int32_t)(fill | rows << 16) : 0;
+    *units = fill > 0 ? (int32_t)(fill | (eight_bit ? 0 : 1 << 16)) : 0;
     if (fill > want) want = fill;
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }

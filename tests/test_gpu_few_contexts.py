@@ -5,8 +5,9 @@ import numpy as np
 import pytest
 
 from paper_2306_06000_amd import binding as s3
-from tests.harness import assert_close
-from tests.test_gpu_numeric_edges import EdgeRig
+from paper_2306_06000_amd import workloads as wl
+from tests.harness import assert_close, device_bits
+from tests.test_gpu_numeric_edges import TDT, EdgeRig
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -69,34 +70,59 @@ def test_eight_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
             rig.close()
 
 
-@pytest.mark.parametrize("fam,batches", [(FAMS[0], (15, 16, 25, 48)), (FAMS[1], (43, 65, 128)), (FAMS[2], (64, 100))],
-                         ids=["16 x 256", "12 x 128", "5 x 96"])
+@pytest.mark.parametrize("fam,batches", [(FAMS[0], (17, 18, 24, 25, 32, 33, 42, 43, 56, 57)), (FAMS[1], (47, 48, 64, 65, 85, 86, 114, 128)), (FAMS[2], (72, 96, 97, 128)),
+                                         (("16 x 64", 16, 16, 64, s3.S3_F16, s3.S3_F16, 0), (72, 97))], ids=["16 x 256", "12 x 128", "5 x 96", "16 x 64"])
 def test_sixteen_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
-    """16-bit rows, half an item to one and a half a compute unit: contexts that average enough rows are cut into as many
-    chunks as run at once, others as before; both sides of that average, and contexts longer than a chunk may be."""
+    """16-bit rows, 9/16 of an item to one and 4/3 to 7/4 items a compute unit: the first and the last batch of the host's
+    part of the rule, and those beside them, with lengths on either side of the device's part: few contexts whose chunks are
+    more than the units, by a little and by an eighth; a long tail, and lengths without one; contexts whole that would be cut
+    at 1024 rows; one longer than any chunk; empty ones between.  Attention against the
+    oracle; the step against both it and attention over the appended rows, through both of its entry points, bit for bit."""
     name, H, Hkv, D, kvt, act, kind = fam
+    top = 4096
+    rng = np.random.default_rng(D)
+    rows = rng.standard_normal((top + 130, Hkv, D), dtype=np.float32)
     for n in batches:
-        for what, lens in (("long", [700 + 9 * (b % 7) for b in range(n)]), ("below the average", [390] * n),
-                           ("one very long", [2047] + [600 + b % 90 for b in range(n - 1)])):
-            rng = np.random.default_rng(n + D)
-            rig = EdgeRig(fam, lens, M=2048)
-            rows = rng.standard_normal((2048, Hkv, D), dtype=np.float32)
-            rig.put([np.roll(rows, b, axis=0)[:L] for b, L in enumerate(lens)], [np.roll(rows, 2 * b, axis=0)[:L] for b, L in enumerate(lens)])
+        for what, lens in (("level", [700 + 9 * (b % 7) for b in range(n)]), ("above a thousand", [1010 + 9 * (b % 3) for b in range(n)]),
+                           ("below", [390] * n), ("a tail", [40 + 7 * (b % 30) for b in range(n - 2)] + [900, 1100]),
+                           ("a long tail", [60 + 5 * (b % 50) for b in range(n - 1)] + [3500]),
+                           ("up to 1500", [64 + (b * 131) % 1430 for b in range(n)]),
+                           ("with empty ones", [0 if b % 3 else 1300 for b in range(n)])):
+            if n not in batches[::2] and what not in ("above a thousand", "a tail", "up to 1500"):
+                continue
+            rig = EdgeRig(fam, lens, M=top)
+            rig.put([rows[b:b + L] for b, L in enumerate(lens)], [rows[n - b:n - b + L] for b, L in enumerate(lens)])
             q = rng.standard_normal((n, H, D), dtype=np.float32)
             qb, att = rig.attend(q)
             assert_close(att, rig.want(qb), f"{name} / {n} / {what}")
-            qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
+            assert s3.s3_kv_set_param(rig.a, "grid_blocks", 7) == 0
+            assert np.array_equal(rig.attend(q)[1], att), (n, what)
+            assert s3.s3_kv_set_param(rig.a, "grid_blocks", 0) == 0
+            k_new, v_new = (rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2))
+            qb, step = rig.step(q, k_new, v_new)
             longer = [L + 1 for L in lens]
             assert_close(step, rig.want(qb, longer), f"{name} / {n} / {what} / step")
             assert np.array_equal(rig.attend(q, lens=longer)[1], step), (n, what)
+            assert np.array_equal(static_step(rig, q, k_new, v_new), step), (n, what)
             rig.close()
 
 
-@pytest.mark.parametrize("H,D,kvt,n", [(12, 128, s3.S3_BF16, 128), (16, 256, s3.S3_F16, 20), (64, 96, s3.S3_BF16, 24), (32, 64, s3.S3_F16, 80)])
+def static_step(rig, q, k_new, v_new):
+    """s3_decode_step_static at pos = lens (again: the rows are there already)."""
+    n = len(rig.lens)
+    out = torch.full((n, rig.H, rig.D), float("nan"), dtype=torch.float32, device="cuda:0")
+    pos = torch.tensor(rig.lens, dtype=torch.int32, device="cuda:0")
+    args = [device_bits(wl.to_bits(x, rig.act), TDT[rig.act], "cuda:0") for x in (q, k_new, v_new)]
+    assert s3.s3_decode_step_static(rig.a, 0, n, rig.off_d, pos, *args, out, s3.S3_F32, 0.0, None, rig.stream) == 0
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("H,D,kvt,n", [(12, 128, s3.S3_BF16, 128), (16, 256, s3.S3_F16, 48), (64, 96, s3.S3_BF16, 24), (32, 64, s3.S3_F16, 96)])
 def test_longer_chunks_sum_no_longer_runs(H, D, kvt, n):
-    """16-bit rows in chunks of up to 2048 rows: against 64 bits the outputs are as exact as in chunks of 1024."""
+    """16-bit rows, whole contexts that would be cut at 1024 rows: against 64 bits the outputs are as exact as in such chunks."""
     rng = np.random.default_rng(D)
-    lens = [int(x) for x in rng.integers(1000, 2048, size=n)]
+    lens = [int(x) for x in rng.integers(1000, 1790, size=n)]
     rig = EdgeRig(("runs", H, H, D, kvt, kvt, 0), lens, M=2048)
     K, V = [], []
     for L in lens:
