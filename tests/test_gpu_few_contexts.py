@@ -47,7 +47,7 @@ def test_few_contexts_are_cut_by_their_rows(fam):
         rig.close()
 
 
-@pytest.mark.parametrize("fam,batches", [(FAMS[4], (49, 88, 90)), (FAMS[5], (193, 358, 360))], ids=["16 x 256 e4m3", "3 x 128 e4m3"])
+@pytest.mark.parametrize("fam,batches", [(FAMS[4], (49, 89, 90)), (FAMS[5], (193, 358, 359))], ids=["16 x 256 e4m3", "3 x 128 e4m3"])
 def test_eight_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
     """Beyond the batches above, 8-bit rows are cut until their chunks fill two workgroups a compute unit, by a count on the
     device: the first batch of that rule, the last and the first beyond it, with lengths that divide well and badly."""
@@ -68,6 +68,28 @@ def test_eight_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
             qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
             assert_close(step, rig.want(qb, [L + 1 for L in lens]), f"{name} / {n} / {what} / step")
             rig.close()
+
+
+def test_eight_bit_rows_in_the_longest_chunks():
+    """The chunks of the rule above grow to the 1024 rows that a chunk may have: contexts on either side of one and of two
+    such chunks, and more chunks than run at once, through every entry point."""
+    fam = ("2 x 64 e4m3", 2, 2, 64, s3.S3_E4M3, s3.S3_BF16, 3)
+    name, H, Hkv, D, kvt, act, kind = fam
+    n = 358
+    rng = np.random.default_rng(5)
+    rows = rng.standard_normal((4096 + n, Hkv, D), dtype=np.float32)
+    for what, lens in (("one chunk each", [1022 + b % 3 for b in range(n)]), ("two", [2047 + b % 3 for b in range(n)]),
+                       ("a few long ones", [4000, 2049, 3000] + [1030] * (n - 3))):
+        rig = EdgeRig(fam, lens, M=4096)
+        rig.put([rows[b:b + L] for b, L in enumerate(lens)], [rows[n - b:n - b + L] for b, L in enumerate(lens)])
+        q = rng.standard_normal((n, H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), what)
+        k_new, v_new = (rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2))
+        qb, step = rig.step(q, k_new, v_new)
+        assert_close(step, rig.want(qb, [L + 1 for L in lens]), what + " / step")
+        assert np.array_equal(static_step(rig, q, k_new, v_new), step), what
+        rig.close()
 
 
 @pytest.mark.parametrize("fam,batches", [(FAMS[0], (17, 18, 24, 25, 32, 33, 42, 43, 56, 57)), (FAMS[1], (47, 48, 64, 65, 85, 86, 114, 128)), (FAMS[2], (72, 96, 97, 128)),
