@@ -535,7 +535,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
     __shared__ int wave_sums[S3_MAX_CLASSES * S3_MAX_WAVES];
     // A wave's LDS: the V and the K tile, or, once its share is done, one piece (16 heads x D floats, padded).
     constexpr int PSTRIDE = D + 4;
-    // (GQ: the piece, behind it what the lanes of each of the RPL rows of a load have summed)
+    // (GQ: the piece, behind it what each of the RPL groups of lanes has summed)
     constexpr int TILE_BYTES = TR * (VSTRIDE + KSTRIDE), PIECE_BYTES = GQ > 0 ? (GQ * PSTRIDE + RPL * GQ * D) * 4 : 16 * PSTRIDE * 4;
     __shared__ __align__(16) char wave_lds[NW][TILE_BYTES > PIECE_BYTES ? TILE_BYTES : PIECE_BYTES];
     __shared__ float2 piece_ml[2 * NW][16];  // teams: (max, sum) of each wave's first (2w) and last (2w + 1) piece
@@ -823,7 +823,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 }
                 const float ref = exp_reference(m);
                 if constexpr (GQ > 0) {
-                    // The weights pass through the K tile's place (its rows have been read) to the lanes that hold the rows.
+                    // The weights pass through the K tile's place (its rows have been read) to the lanes that sum the rows: a lane
+                    // NL rows in a row, so that four weights are one word to write and to read.
                     // All of it is fp32: a weight keeps its 24 bits however small it is, and an infinite value gives an
                     // infinite element (a 16-bit part of a weight that is 0 or negative would make it NaN).
                     float *pw = (float *)kt;
@@ -833,8 +834,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
 #pragma unroll
                         for (int i = 0; i < 4; i++) {
                             p[i] = fast_exp2(sv[rb][i] - ref);
-                            if (n < GQ) pw[(rb * 16 + 4 * g + i) * 4 + n] = p[i];
                         }
+                        if (n < GQ) *(f32x4 *)(pw + n * TR + rb * 16 + 4 * g) = (f32x4){p[0], p[1], p[2], p[3]};
                         lsum += (p[0] + p[1]) + (p[2] + p[3]);
                     }
                     lds_exchange();
@@ -843,13 +844,18 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                     for (int h = 0; h < GQ; h++)
 #pragma unroll
                         for (int e = 0; e < 8; e++) sum[h][e] = 0.f;
+                    const int row = NL * (lane / PPR);
 #pragma unroll
-                    for (int i = 0; i < NL; i++) {
-                        const int row = i * RPL + lane / PPR;
-                        const f32x4 w = *(const f32x4 *)(pw + row * 4);
-                        const u32x4 v = *(const u32x4 *)(vt + row * VSTRIDE + (lane % PPR) * 16);
+                    for (int i4 = 0; i4 < NL; i4 += 4) {
+                        f32x4 w[GQ];
 #pragma unroll
-                        for (int h = 0; h < GQ; h++) axpy8<DT>(sum[h], w[h], v);
+                        for (int h = 0; h < GQ; h++) w[h] = *(const f32x4 *)(pw + h * TR + row + i4);
+#pragma unroll
+                        for (int i = 0; i < 4; i++) {
+                            const u32x4 v = *(const u32x4 *)(vt + (row + i4 + i) * VSTRIDE + (lane % PPR) * 16);
+#pragma unroll
+                            for (int h = 0; h < GQ; h++) axpy8<DT>(sum[h], w[h][i], v);
+                        }
                     }
 #pragma unroll
                     for (int h = 0; h < GQ; h++)
@@ -1174,11 +1180,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
 // (gqa_on_matrix_cores), keeps the weights in fp32, and so does this one: only the scores are a matrix product (2 or 3 of its
 // 16 columns in use), the weighted rows are 2 or 3 multiply-adds an element on the vector ALU, far below what it could issue
 // while the rows arrive.  Weights in 16-bit parts on the matrix cores lose what the smallest of them carry (three fp16 parts
-// end at 2^-31 of the largest weight: a value of 6e4 under a weight of e^-14 off by 1e-5), make infinite values NaN, and save
-// 0 to 6 % of a launch at 128 and 256 elements a head, 2 to 8 % at 64.
+// end at 2^-31 of the largest weight: a value of 6e4 under a weight of e^-14 off by 1e-5) and make infinite values NaN; they
+// were 2 to 8 % faster at 64 elements a head, level at 128, slower at 256.
 // Error against 64 bits, relative 2-norm, fp32 outputs, 16q/8kv x 128, 64q/32kv x 128, 16q/8kv x 64, 6q/3kv x 256, 24q/8kv x
-// 64, 12q/4kv x 128, 9q/3kv x 256, 8 to 85 contexts: bf16 1.34e-7 to 1.53e-7 where the vector ALU has 1.58e-7 to 1.82e-7, fp16
-// 1.38e-7 to 1.61e-7 and 1.66e-7 to 1.85e-7; one context of 37 rows level (bf16 1.11e-7 to 1.36e-7, 1.13e-7 to 1.37e-7).
+// 64, 12q/4kv x 128, 9q/3kv x 256, 8 to 85 contexts: bf16 1.33e-7 to 1.54e-7 where the vector ALU has 1.58e-7 to 1.82e-7, fp16
+// 1.38e-7 to 1.61e-7 and 1.66e-7 to 1.85e-7; one context of 37 rows level (bf16 1.11e-7 to 1.37e-7, 1.13e-7 to 1.37e-7).
 template <int DT, int NW>
 static attn_fn pick_few_heads(int d, int group) {
     if (d == 64) return group == 2 ? attn_gqa_mfma_kernel<DT, 64, false, NW, 2> : attn_gqa_mfma_kernel<DT, 64, false, NW, 3>;
