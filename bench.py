@@ -336,6 +336,8 @@ def run_workload(name, args, torch, cpu_budget_s):
         kind = s3.s3_kv_get_param(eng.arena, "kernel_kind")[1]
         kernel = {1: "attn_gqa_kernel", 2: "attn_gqa_mfma_kernel", 3: "attn_fp8_kernel", 4: "attn_gqa_mfma_kernel"}.get(
             kind, "attn_step_kernel")
+        if kind == 1 and s3.s3_kv_get_param(eng.arena, "variant")[1] < 0 and s3.s3_kv_get_param(eng.arena, "chunk")[1] == 0:
+            kernel = "attn_gqa_kernel or attn_gqa_mfma_kernel"  # by the batch, see s3_kv_get_param in s3kv.h
         traffic, traffic_ref = read_traffic(kernel, name)
         res["roofline"] = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1),
                            "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBPS, 4),
