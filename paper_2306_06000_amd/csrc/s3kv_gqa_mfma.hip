@@ -84,6 +84,16 @@ __device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const
     }
 }
 
+// Lane h (0, 1 or 2) of each sixteen lanes to the lanes of BANKS (four lanes a bit) of that sixteen; the others keep `old`.
+template <int BANKS>
+__device__ __forceinline__ float head_weight(const float old, const float from, const int h) {
+    const int a = __builtin_bit_cast(int, old), b = __builtin_bit_cast(int, from);
+    const int r = h == 0   ? __builtin_amdgcn_update_dpp(a, b, 0x150, 0xF, BANKS, false)  // row_newbcast:0
+                  : h == 1 ? __builtin_amdgcn_update_dpp(a, b, 0x151, 0xF, BANKS, false)
+                           : __builtin_amdgcn_update_dpp(a, b, 0x152, 0xF, BANKS, false);
+    return __builtin_bit_cast(float, r);
+}
+
 // Between writes to LDS and reads of the same words by other lanes of the wave: the LDS unit serves the wave in issue order,
 // so it is only the compiler that must not move the one across the other, nor hand a lane the value it wrote itself.
 __device__ __forceinline__ void lds_exchange() {
@@ -528,7 +538,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
     // Register sets of rows on their way: two, or one where two (with the new row of 8-bit rows) do not fit two waves a
     // SIMD: 239 and 229 of 256 registers.
     constexpr bool TWO_SETS = !(NW == 8 && D == 256);
-    static_assert(GQ == 0 || !KV8, "8-bit rows: both products on the matrix cores");
+    static_assert(GQ == 0 || (!KV8 && GQ <= 3 && NL * RPL == TR), "16-bit rows, two or three heads");
     constexpr bool APPENDS = !KV8 || CHUNKS;  // takes the new row of a decode step itself (else the host appends it first)
     constexpr float RESCALE_LOG2 = GQ > 0 ? 0.f : 8.f;  // see the softmax step
     extern __shared__ __align__(16) char dyn_lds[];  // the batch view, then the teams' first pieces
@@ -823,39 +833,45 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 }
                 const float ref = exp_reference(m);
                 if constexpr (GQ > 0) {
-                    // The weights pass through the K tile's place (its rows have been read) to the lanes that sum the rows: a lane
-                    // NL rows in a row, so that four weights are one word to write and to read.
                     // All of it is fp32: a weight keeps its 24 bits however small it is, and an infinite value gives an
                     // infinite element (a 16-bit part of a weight that is 0 or negative would make it NaN).
-                    float *pw = (float *)kt;
+                    // A lane sums the rows whose weights its sixteen lanes hold (lane h of them those of head h, rows 4g .. 4g+3
+                    // of each block), so that the weights come by a broadcast within the sixteen: at D 64 eight lanes
+                    // take either block's four rows, at D 256 two sixteens exchange their weights and share eight rows.
+                    float p[RB][4];
 #pragma unroll
                     for (int rb = 0; rb < RB; rb++) {
-                        float p[4];
+#pragma unroll
+                        for (int i = 0; i < 4; i++) p[rb][i] = fast_exp2(sv[rb][i] - ref);
+                        lsum += (p[rb][0] + p[rb][1]) + (p[rb][2] + p[rb][3]);
+                    }
+                    float w[GQ][NL];
+#pragma unroll
+                    for (int h = 0; h < GQ; h++) {
 #pragma unroll
                         for (int i = 0; i < 4; i++) {
-                            p[i] = fast_exp2(sv[rb][i] - ref);
+                            const float own = head_weight<0xF>(p[0][i], p[0][i], h);
+                            if constexpr (D == 256) {
+                                const auto both = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, own), __builtin_bit_cast(unsigned, own), false, false);
+                                const unsigned even = both[0], odd = both[1];
+                                w[h][i] = __builtin_bit_cast(float, even);
+                                w[h][NL - 4 + i] = __builtin_bit_cast(float, odd);
+                            } else {
+                                w[h][i] = D == 64 ? head_weight<0xC>(own, p[RB - 1][i], h) : own;
+                            }
                         }
-                        if (n < GQ) *(f32x4 *)(pw + n * TR + rb * 16 + 4 * g) = (f32x4){p[0], p[1], p[2], p[3]};
-                        lsum += (p[0] + p[1]) + (p[2] + p[3]);
                     }
-                    lds_exchange();
+                    const int row = D == 64 ? ((lane >> 3) & 1) * 16 + 4 * g : NL * (lane / PPR);
                     float sum[GQ][8];  // of this tile: the long sums are rounded once a tile
 #pragma unroll
                     for (int h = 0; h < GQ; h++)
 #pragma unroll
                         for (int e = 0; e < 8; e++) sum[h][e] = 0.f;
-                    const int row = NL * (lane / PPR);
 #pragma unroll
-                    for (int i4 = 0; i4 < NL; i4 += 4) {
-                        f32x4 w[GQ];
+                    for (int i = 0; i < NL; i++) {
+                        const u32x4 v = *(const u32x4 *)(vt + (row + i) * VSTRIDE + (lane % PPR) * 16);
 #pragma unroll
-                        for (int h = 0; h < GQ; h++) w[h] = *(const f32x4 *)(pw + h * TR + row + i4);
-#pragma unroll
-                        for (int i = 0; i < 4; i++) {
-                            const u32x4 v = *(const u32x4 *)(vt + (row + i4 + i) * VSTRIDE + (lane % PPR) * 16);
-#pragma unroll
-                            for (int h = 0; h < GQ; h++) axpy8<DT>(sum[h], w[h][i], v);
-                        }
+                        for (int h = 0; h < GQ; h++) axpy8<DT>(sum[h], w[h][i], v);
                     }
 #pragma unroll
                     for (int h = 0; h < GQ; h++)
@@ -1181,7 +1197,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
 // 16 columns in use), the weighted rows are 2 or 3 multiply-adds an element on the vector ALU, far below what it could issue
 // while the rows arrive.  Weights in 16-bit parts on the matrix cores lose what the smallest of them carry (three fp16 parts
 // end at 2^-31 of the largest weight: a value of 6e4 under a weight of e^-14 off by 1e-5) and make infinite values NaN; they
-// were 2 to 8 % faster at 64 elements a head, level at 128, slower at 256.
+// were up to 5 % faster with three heads at 64 and 128 elements a head, level or slower elsewhere.
 // Error against 64 bits, relative 2-norm, fp32 outputs, 16q/8kv x 128, 64q/32kv x 128, 16q/8kv x 64, 6q/3kv x 256, 24q/8kv x
 // 64, 12q/4kv x 128, 9q/3kv x 256, 8 to 85 contexts: bf16 1.33e-7 to 1.54e-7 where the vector ALU has 1.58e-7 to 1.82e-7, fp16
 // 1.38e-7 to 1.61e-7 and 1.66e-7 to 1.85e-7; one context of 37 rows level (bf16 1.11e-7 to 1.37e-7, 1.13e-7 to 1.37e-7).

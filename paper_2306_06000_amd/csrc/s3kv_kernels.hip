@@ -630,11 +630,11 @@ static int gqa_chunk_rows(const s3_arena *a, int n) {
 // matrix cores win where the launch is a chain of latencies (one launch instead of three) and wherever the vector-ALU kernel
 // reads the rows once per query head (odd groups).  With two heads it reads them once, and a batch that fills the chip is
 // bound by memory either way: more (sequence, cached head) pairs than two a compute unit stay with it (of 256: than one).
-// us a layer, bf16, vector ALU and matrix cores: 16q/8kv x 128, 1 context of 30..40 rows 11.4, 6.4, 20 of 32..1000 28.1, 15.8,
-// 64 of 100..200 23.7, 15.7, 85 of 32..1000 41.6, 42.1; 64q/32kv x 128, 8 of 32..1000 28.0, 18.8, 64 of 100..200 36.0, 43.8;
-// 6q/3kv x 256, 20 of 32..1000 29.1, 14.7, 85 36.9, 33.1 (beyond its line now level or faster too: 200 75.9, 70.1, 300 of 2..40
-// 17.7, 16.8); 24q/8kv x 64, 20 of 32..1000 25.1, 12.9, 700 of 32..1000 394, 132, 300 of 2..40 19.6, 13.5; 9q/3kv x 256, 700 of
-// 32..1000 634, 204.
+// us a layer, bf16, vector ALU and matrix cores: 16q/8kv x 128, 1 context of 30..40 rows 10.8, 6.0, 20 of 32..1000 27.9, 15.5,
+// 64 of 100..200 23.6, 15.4, 85 of 32..1000 41.4, 41.8; 64q/32kv x 128, 8 of 32..1000 27.9, 18.5, 64 of 100..200 35.7, 43.0;
+// 6q/3kv x 256, 20 of 32..1000 29.0, 14.6, 85 36.8, 32.8 (beyond its line now faster too: 200 75.5, 69.5, 300 of 2..40 17.8,
+// 16.4); 24q/8kv x 64, 20 of 32..1000 25.1, 12.4, 700 of 32..1000 392, 132, 300 of 2..40 19.5, 13.3; 9q/3kv x 256, 700 of
+// 32..1000 633, 203.
 // (Both keep the weights in fp32 and treat infinite values alike, see pick_few_heads.)
 static bool gqa_on_matrix_cores(const s3_arena *a, int n) {
     const int kind = s3i_kernel_kind(a);
