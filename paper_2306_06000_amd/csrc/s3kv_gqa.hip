@@ -105,13 +105,14 @@ __global__ void __launch_bounds__(TS * 64) attn_gqa_kernel(const AttnArgs a) {
             if (writer) {
                 float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 float mm = -INFINITY, ll = 0.f;
-                if (len > 0) {  // a chunk's rows start at wave 0, lane group 0, so the maximum is finite
+                if (len > 0) {
                     for (int t = 0; t < TS; t++)
                         for (int g = 0; g < tpw; g++) mm = fmaxf(mm, comb[t][0][lane + g * a.H * LPH]);
+                    const float ref = exp_reference(mm);  // (a chunk may hold nothing but scores of -inf)
                     for (int t = 0; t < TS; t++)
                         for (int g = 0; g < tpw; g++) {
                             const int src = lane + g * a.H * LPH;
-                            const float wt = fast_exp2(comb[t][0][src] - mm);
+                            const float wt = fast_exp2(comb[t][0][src] - ref);
                             ll += wt * comb[t][1][src];
 #pragma unroll
                             for (int e = 0; e < 8; e++) o[e] += wt * comb[t][2 + e][src];

@@ -14,6 +14,9 @@ FAMS = [
     ("matrix cores d256 group 16", 16, 1, 256, s3.S3_BF16, s3.S3_BF16, 2),
     ("matrix cores d64 e4m3", 8, 1, 64, s3.S3_E4M3, s3.S3_BF16, 4),
     ("8-bit rows d128", 4, 4, 128, s3.S3_E4M3, s3.S3_BF16, 3),
+    ("two heads a cached head d128", 16, 8, 128, s3.S3_BF16, s3.S3_BF16, 1),
+    ("three heads a cached head d64", 24, 8, 64, s3.S3_BF16, s3.S3_BF16, 1),
+    ("three heads a cached head d256", 6, 2, 256, s3.S3_BF16, s3.S3_BF16, 1),
 ]
 
 
