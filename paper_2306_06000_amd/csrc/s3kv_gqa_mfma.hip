@@ -243,11 +243,59 @@ __device__ __forceinline__ ChunkPlan eight_wave_plan(const AttnArgs &a, int tile
     return ChunkPlan{a.team_shares, longest <= 22 ? longest : max(8, (int)__builtin_amdgcn_sqrtf(2.f * average)), 8};
 }
 
+// The context that holds position w of the work list: its index, the position of its first chunk, its chunks, rows and
+// offset.  All fields are wave-uniform.
+struct Located {
+    int seq, first, count, len;
+    int64_t off;
+};
+// ... from the view in LDS
+__device__ __forceinline__ Located locate(const BatchView &v, int w) {
+    Located x;
+    x.seq = min(find_sequence(v.pre, v.n, w), v.n - 1);
+    x.first = __builtin_amdgcn_readfirstlane(v.pre[x.seq]);
+    x.count = __builtin_amdgcn_readfirstlane(v.pre[x.seq + 1]) - x.first;
+    x.len = __builtin_amdgcn_readfirstlane(v.len[x.seq]);
+    x.off = uniform64(v.off[x.seq]);
+    return x;
+}
+// ... from the registers that the view is made in (lane l: entries E*l .. E*l+E-1, `run` chunks before them): a ballot and
+// a few lane reads, where the same through LDS is six dependent round trips.
+template <int E>
+__device__ __forceinline__ Located locate(const int64_t (&off)[E], const int (&len)[E], const int (&cnt)[E], int run, int incl, int w) {
+    const int at = min(__builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= w)), 63);
+    Located x;
+    x.first = __builtin_amdgcn_readlane(run, at);
+    int e = 0;
+    x.count = __builtin_amdgcn_readlane(cnt[0], at);
+#pragma unroll
+    for (int k = 1; k < E; k++) {  // (an entry without chunks holds no position)
+        const int c = __builtin_amdgcn_readlane(cnt[k], at);
+        const bool on = e == k - 1 && w >= x.first + x.count;
+        x.first += on ? x.count : 0;
+        x.count = on ? c : x.count;
+        e = on ? k : e;
+    }
+    x.seq = at * E + e;
+    x.len = __builtin_amdgcn_readlane(len[0], at);
+    int lo = __builtin_amdgcn_readlane((int)off[0], at), hi = __builtin_amdgcn_readlane((int)(off[0] >> 32), at);
+#pragma unroll
+    for (int k = 1; k < E; k++) {
+        const int l = __builtin_amdgcn_readlane(len[k], at), a = __builtin_amdgcn_readlane((int)off[k], at),
+                  b = __builtin_amdgcn_readlane((int)(off[k] >> 32), at);
+        x.len = e == k ? l : x.len;
+        lo = e == k ? a : lo;
+        hi = e == k ? b : hi;
+    }
+    x.off = (int64_t)(((uint64_t)(unsigned)hi << 32) | (unsigned)lo);
+    return x;
+}
+
 // The view of few contexts, and how they are divided: every wave of the workgroup builds all of it by itself and writes the
 // same values to the same words, so that nothing waits at a barrier before its first load (a wave reads behind its own writes).
-// Lane l owns entries E*l .. E*l+E-1.
+// Lane l owns entries E*l .. E*l+E-1.  here: the context of position `w`, if there is one (eight waves: the first unit).
 template <int E, int TR, int ROW_BYTES, int NW>
-__device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int &tiles, int &longest, int &per, int &team) {
+__device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int &tiles, int &longest, int &per, int &team, int w, Located &here) {
     const int lane = threadIdx.x & 63;
     BatchView v;
     int64_t *off_s = (int64_t *)dyn;
@@ -289,6 +337,7 @@ __device__ __forceinline__ BatchView few_view(const AttnArgs &a, char *dyn, int 
     }
     v.total = __builtin_amdgcn_readlane(incl, 63);
     int run = incl - sum;
+    if (NW == 8) here = locate<E>(off, len, cnt, run, incl, w);
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const int b = lane * E + e;
@@ -559,8 +608,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
     // pre[] counts tiles, or (per > 0) chunks of `per` tiles
     int tiles, longest, per, team = 1;  // (longest: tiles of the longest context)
     BatchView bv;
+    Located here = {0, 0, 0, 0, 0};  // (eight waves: the context of the unit at hand)
     if (CHUNKS || a.n <= S3_FEW_CONTEXTS) {
-        bv = a.n <= 64 ? few_view<1, TR, D * EB, NW>(a, dyn_lds, tiles, longest, per, team) : few_view<S3_FEW_CONTEXTS / 64, TR, D * EB, NW>(a, dyn_lds, tiles, longest, per, team);
+        const int w = __builtin_amdgcn_readfirstlane(a.column_shift >= 0 ? blockIdx.x >> a.column_shift : blockIdx.x / columns);
+        bv = a.n <= 64 ? few_view<1, TR, D * EB, NW>(a, dyn_lds, tiles, longest, per, team, w, here)
+                       : few_view<S3_FEW_CONTEXTS / 64, TR, D * EB, NW>(a, dyn_lds, tiles, longest, per, team, w, here);
     } else {
         bv = build_tile_view<TR>(a, dyn_lds, wave_sums, longest);
         tiles = __builtin_amdgcn_readfirstlane(bv.total);
@@ -614,11 +666,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
         // This wave's tiles, [t_begin, t_stop): of all contexts laid end to end, or (chunks) of context `seq`.
         int t_begin = 0, t_stop = 0, seq = 0, chunk = 0, nchunks = 0;
         if (CHUNKS || per > 0) {
-            seq = min(find_sequence(bv.pre, a.n, pub), a.n - 1);
-            const int first = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
-            nchunks = __builtin_amdgcn_readfirstlane(bv.pre[seq + 1]) - first;
-            chunk = pub - first;
-            const int all = (__builtin_amdgcn_readfirstlane(bv.len[seq]) + TR - 1) / TR;
+            if (!CHUNKS) here = locate(bv, pub);
+            seq = here.seq;
+            nchunks = here.count;
+            chunk = pub - here.first;
+            const int all = (here.len + TR - 1) / TR;
             // near-equal pieces, none of them empty: the first all % nchunks have a tile more
             const int base = quotient(all, max(nchunks, 1)), rem = all - base * nchunks;
             t_begin = chunk * base + min(chunk, rem);
@@ -661,10 +713,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                     s.t0 = __builtin_amdgcn_readfirstlane(bv.pre[seq]);
                 }
                 s.seq = seq;
-                s.len = __builtin_amdgcn_readfirstlane(bv.len[seq]);
+                s.len = CHUNKS ? here.len : __builtin_amdgcn_readfirstlane(bv.len[seq]);
                 s.t1 = s.t0 + (s.len + TR - 1) / TR;
                 s.t_end = min(t_stop, s.t1);
-                s.off = uniform64(bv.off[seq]);
+                s.off = CHUNKS ? here.off : uniform64(bv.off[seq]);
                 return s;
             };
             const int64_t head_byte = (int64_t)hk * D * EB;
@@ -1168,6 +1220,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 for (int k = 0; k < 2; k++)
                     if ((mine >> k) & 1) merge_pieces<D, CHUNKS>(a, k ? pend1 : pend0, hq0, nheads, threadIdx.x, NW * 64, (float *)wave_lds);
             }
+            if (CHUNKS) break;  // (the grid has a workgroup for every chunk)
             __syncthreads();  // LDS is free for the next unit
         } else if constexpr (!CHUNKS) {
             if (pend0.count != 0 || pend1.count != 0) {

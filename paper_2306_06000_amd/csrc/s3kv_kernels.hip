@@ -842,7 +842,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
         args.team_shares = (int32_t)(cus / columns);
         rc = resident_per_cu((const void *)wide, 512, view, &per_cu);
         if (rc != S3_OK) return rc;
-        const int blocks = a->grid_blocks > 0 ? a->grid_blocks : (int)(args.team_shares * columns);
+        const int blocks = (int)(args.team_shares * columns);  // one chunk a workgroup
         return launch_attn_kernels(a, wide, blocks, 512, view, c.stream, args, 0, !c.static_scratch);
     }
     // Workgroups of four over 8-bit rows: the append is its own launch.  (Taken into the kernel, as it is with eight waves, the
