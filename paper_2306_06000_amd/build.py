@@ -11,7 +11,7 @@ HEAD_DIMS = (64, 96, 128, 256)
 UNITS = [("s3kv_attn_inst.hip", [f"-DS3_INST_D={d}"], f"s3kv_attn_d{d}.o") for d in HEAD_DIMS] + [
     (s, [], s + ".o") for s in ("s3kv_kernels.hip", "s3kv_gqa.hip", "s3kv_gqa_mfma.hip", "s3kv_fp8.hip", "s3kv_alloc.cpp",
                                 "s3kv_sched.cpp")]
-HEADERS = ["s3kv_internal.h", "s3kv_device.h", "s3kv_attn.h"]
+HEADERS = ["s3kv_internal.h", "s3kv_device.h", "s3kv_attn.h", "s3kv_attn_few.h"]
 
 
 def _hipcc() -> str:

@@ -2,7 +2,7 @@
 // compiler's command line); the library links one object per supported head dimension.
 #include <hip/hip_runtime.h>
 
-#include "s3kv_attn.h"
+#include "s3kv_attn_few.h"
 
 #ifndef S3_INST_D
 #error "compile with -DS3_INST_D=<head dimension>"
@@ -16,6 +16,10 @@ attn_fn S3_CAT(s3i_pick_mha_d, S3_INST_D)(int dt, int variant) {
     if (dt == S3_F16) return pick_variant<S3_F16, S3_INST_D>(variant);
     if (dt == S3_BF16) return pick_variant<S3_BF16, S3_INST_D>(variant);
     return nullptr;
+}
+
+attn_fn S3_CAT(s3i_pick_few_d, S3_INST_D)(int dt) {
+    return dt == S3_F16 ? (attn_fn)attn_few_kernel<S3_F16, S3_INST_D> : dt == S3_BF16 ? (attn_fn)attn_few_kernel<S3_BF16, S3_INST_D> : nullptr;
 }
 
 attn_fn S3_CAT(s3i_pick_merge_d, S3_INST_D)() { return (attn_fn)attn_merge_kernel<S3_INST_D>; }

@@ -51,7 +51,8 @@ struct AttnArgs {
     int32_t share_rows;  // > 0: at most this many rows a share (set by the caller)
     int32_t team_lds;    // the launch carries LDS for the pieces of teams of four waves
     // multi-head kernels: > 0: the chunks of a context's heads that run at once (low 16 bits); the contexts may be cut into as
-    // many, whatever their rows, or (16 bits and up: 1) as unit_rule() says
+    // many, whatever their rows, or (16 bits and up: 1) as unit_rule() says.  attn_few_kernel: chunks of a context's heads,
+    // few_chunks one a compute unit, unit_chunks two; columns head groups.
     int32_t unit_chunks;
 };
 
@@ -172,6 +173,13 @@ __device__ __forceinline__ void store_out8(void *out, int out_dtype, int64_t e, 
         }
         *(u32x4 *)((uint16_t *)out + e) = w;
     }
+}
+
+// One output element.
+__device__ __forceinline__ void store_out1(void *out, int out_dtype, int64_t e, const float v) {
+    if (out_dtype == S3_F32) ((float *)out)[e] = v;
+    else if (out_dtype == S3_F16) ((_Float16 *)out)[e] = (_Float16)v;
+    else ((uint16_t *)out)[e] = (uint16_t)f32_to_bf16_rne(v);
 }
 
 // Two fp32 values -> their e4m3 codes in one half of a 32-bit word (v_cvt_pk_fp8_f32 rounds to the nearest
@@ -669,6 +677,9 @@ template <bool COHERENT>
 __device__ __forceinline__ void put_partial2(float *p, const f32x2 v) {
     if (COHERENT) asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
     else *(f32x2 *)p = v;
+}
+__device__ __forceinline__ void put_partial1(float *p, const float v) {
+    asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
 }
 // Four partials at once, one memory round trip for all: (max, sum) at ml[u], eight accumulator values at acc[u].
 template <bool COHERENT>

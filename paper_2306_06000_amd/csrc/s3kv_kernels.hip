@@ -289,6 +289,10 @@ attn_fn s3i_pick_mha_d64(int dt, int variant);
 attn_fn s3i_pick_mha_d96(int dt, int variant);
 attn_fn s3i_pick_mha_d128(int dt, int variant);
 attn_fn s3i_pick_mha_d256(int dt, int variant);
+attn_fn s3i_pick_few_d64(int dt);
+attn_fn s3i_pick_few_d96(int dt);
+attn_fn s3i_pick_few_d128(int dt);
+attn_fn s3i_pick_few_d256(int dt);
 attn_fn s3i_pick_merge_d64();
 attn_fn s3i_pick_merge_d96();
 attn_fn s3i_pick_merge_d128();
@@ -313,6 +317,11 @@ static attn_fn pick_kernel(int dt, int d, int variant) {
 static attn_fn pick_merge(int d) {
     return d == 64 ? s3i_pick_merge_d64() : d == 96 ? s3i_pick_merge_d96() : d == 128 ? s3i_pick_merge_d128()
                                                                                        : s3i_pick_merge_d256();
+}
+
+static attn_fn pick_few(int dt, int d) {
+    return d == 64 ? s3i_pick_few_d64(dt) : d == 96 ? s3i_pick_few_d96(dt) : d == 128 ? s3i_pick_few_d128(dt)
+                                                                                      : d == 256 ? s3i_pick_few_d256(dt) : nullptr;
 }
 
 // Heads that one 128-bit wave load of 16-bit elements covers: 512/D, except that a 96-wide head takes a
@@ -688,6 +697,15 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // 16-bit rows: the same with chunks of up to 2048 rows, where the rows say so on the device: from 9/16 to one item a compute unit
 // (unit_rule), and from 4/3 to 7/4 whole contexts (whole_rule), if contexts can be long enough at all.  Batches that the rules
 // leave alone pay 0.2 to 1.0 us for the look (half of them less than 0.6), which is why they are not asked in between, where only few gain.
+//
+// Multi-head 16-bit rows, nothing set by the caller: attn_few_kernel serves batches of up to 3/4 of an item a compute unit
+// (and 64 contexts, a lane each), in up to 2 * cus / n_hg chunks.  Beyond, whole contexts fill most of the chip and the
+// streaming kernel's balance is as good or better: 16 x 256, 26 contexts of 500..1500 rows 87.6 us a layer, 75.7 here, but 40
+// of 32..1000 60.8, 63.8, 48 70.4, 83.5, 64 x 96, 18 of 20..200 12.8, 14.9.
+static bool on_few_kernel(const s3_arena *a, int n, int n_hg) {
+    const int64_t cus = a->num_cus > 0 ? a->num_cus : 256;
+    return s3i_kernel_kind(a) == 0 && a->chunk <= 0 && a->variant < 0 && n <= 64 && (int64_t)n * n_hg <= cus * 3 / 4;
+}
 static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few, int32_t *units) {
     const int chunk = a->chunk > 0 ? a->chunk : 1024;
     const int64_t whole = (int64_t)n * ((a->cfg.max_len + chunk - 1) / chunk);
@@ -709,6 +727,7 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     if (whole <= fixed && fill + n > fixed) fill = 0;
     *units = fill > 0 ? (int32_t)(fill | (eight_bit ? 0 : 1 << 16)) : 0;
     if (fill > want) want = fill;
+    if (on_few_kernel(a, n, n_hg)) want = 2 * cus / n_hg;  // (at most 2 MiB: in the fixed buffer always)
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }
 
@@ -946,6 +965,14 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
     }
     int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
+    if (on_few_kernel(a, c.n, n_hg)) {
+        const int cus = a->num_cus > 0 ? a->num_cus : 256;
+        args.few_chunks = cus / n_hg;
+        args.unit_chunks = 2 * cus / n_hg;
+        args.columns = n_hg;
+        args.column_shift = (n_hg & (n_hg - 1)) == 0 ? __builtin_ctz((unsigned)n_hg) : -1;
+        return launch_attn_kernels(a, pick_few(a->cfg.kv_dtype, D), args.unit_chunks * n_hg, 512, 0, c.stream, args, 0, !c.static_scratch);
+    }
     if (args.unit_chunks > 0) fn = pick_kernel(a->cfg.kv_dtype, D, S3_UNIT_VARIANT);
     const int threads = s3i_variant_threads(variant);
     const size_t view = batch_view_lds(c.n, args.ncls);

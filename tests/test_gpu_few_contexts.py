@@ -168,3 +168,39 @@ def test_longer_chunks_sum_no_longer_runs(H, D, kvt, n):
         off.append(np.linalg.norm(rig.attend(q)[1] - want) / np.linalg.norm(want))
     rig.close()
     assert off[0] <= 1.03 * off[1], off  # (the division of the rows differs, and with it every rounding: 1 % either way)
+
+
+FEW = [FAMS[0], FAMS[1], FAMS[2], ("3 x 128", 3, 3, 128, s3.S3_BF16, s3.S3_BF16, 0), ("16 x 64", 16, 16, 64, s3.S3_F16, s3.S3_F16, 0)]
+
+
+@pytest.mark.parametrize("fam", FEW, ids=[f[0] for f in FEW])
+def test_few_contexts_shares_and_pieces(fam):
+    """The kernel of few contexts at the edges of what a wave takes (a row, fours of them, twelve, thirteen, runs of 128) and of
+    what a merge takes (16 pieces a round trip, 32, more), with the new row first, inside and last in a four; the largest batches
+    of it and the first beyond; empty contexts between.  Attention against the oracle; the step bit for bit against attention over the
+    appended rows, through both of its entry points and with both orderings of the merge."""
+    name, H, Hkv, D, kvt, act, kind = fam
+    n_hg = -(-H // (4 if D == 96 else 512 // D))
+    last = min(64, 192 // n_hg)
+    rng = np.random.default_rng(7 * D + H)
+    top = 8192
+    rows = rng.standard_normal((top + 130, Hkv, D), dtype=np.float32)
+    cases = [[1], [7], [8], [9], [31], [32], [33], [63], [64], [65], [96], [97], [104], [128], [129], [256], [519], [2048], [4100], [8000],
+             [64] * 2, [65, 2], [0, 130], [3000, 40, 0, 700], [1500] * min(4, last), [100] * last, [40 + 37 * b for b in range(last)],
+             [700] * (last - 1) + [2100]] + ([[90] * (last + 1)] if last < 64 else [])
+    for lens in cases:
+        n = len(lens)
+        rig = EdgeRig(fam, lens, M=top)
+        rig.put([rows[b:b + L] for b, L in enumerate(lens)], [rows[n - b:n - b + L] for b, L in enumerate(lens)])
+        q = rng.standard_normal((n, H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / {lens[:4]} x {n}")
+        k_new, v_new = (rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2))
+        qb, step = rig.step(q, k_new, v_new)
+        longer = [L + 1 for L in lens]
+        assert_close(step, rig.want(qb, longer), f"{name} / {lens[:4]} x {n} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step), lens
+        assert np.array_equal(static_step(rig, q, k_new, v_new), step), lens
+        assert s3.s3_kv_set_param(rig.a, "merge_sync", 1) == 0
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step), lens
+        rig.close()
