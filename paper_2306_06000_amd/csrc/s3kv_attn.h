@@ -400,7 +400,7 @@ __global__ void __launch_bounds__((TS *HS + 1) * 64, UNITS ? 5 : 0) attn_step_ke
                 }
             }
             if (it.nchunks > 1) {
-                unsigned int *cnt = a.arrivals + (int64_t)it.b * n_hgb + it.hgb;
+                unsigned int *cnt = arrival_counter(a, it.b, n_hgb, it.hgb);
                 if (chunk_arrived(a, cnt, it.nchunks)) {  // every chunk of this context has arrived
                     for (int s = 0; s < HS; s++) {
                         const int h = (it.hgb * HS + s) * GH + lane / LPH;
@@ -638,7 +638,7 @@ __global__ void __launch_bounds__((TS + 1) * 64) attn_step_stream_kernel(const A
                     emit_chunk<D, true>(a, it, h, lane % LPH, m, l, acc);
                 }
                 if (it.nchunks > 1) {
-                    unsigned int *cnt = a.arrivals + (int64_t)it.b * n_hgb + it.hgb;
+                    unsigned int *cnt = arrival_counter(a, it.b, n_hgb, it.hgb);
                     if (chunk_arrived(a, cnt, it.nchunks)) {  // every chunk of this context has arrived
                         if (h < a.H && dl_ok) merge_chunks<D, true>(a, it.slot0, a.H, it.b, h, lane % LPH, it.nchunks);
                     }

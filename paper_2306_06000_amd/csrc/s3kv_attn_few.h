@@ -282,7 +282,7 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wave's stores are at the memory side ...
             __syncthreads();                                             // ... and all the others', before one of them counts
             if (wave == 0) {
-                unsigned int *cntp = a.arrivals + (seq * n_hg + hg) * 32;  // a cache line each
+                unsigned int *cntp = arrival_counter(a, seq, n_hg, hg);
                 unsigned int old = 0;
                 if (lane == 0) {
                     old = atomicAdd(cntp, 1u);

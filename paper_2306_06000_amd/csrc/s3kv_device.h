@@ -729,6 +729,14 @@ __device__ __forceinline__ f32x2 piece_load2(__amdgpu_buffer_rsrc_t r, unsigned 
     return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 17));
 }
 
+// The arrival counter of context b, head group (column) g of n_groups.  The counter region holds 4096 of each group; smaller
+// batches keep theirs apart, up to a cache line each (128 contexts), since atomics on one line wait for each other: eight
+// neighbouring counters, on which 200 workgroups counted, cost the last of them 2.5 us.
+__device__ __forceinline__ unsigned int *arrival_counter(const AttnArgs &a, int b, int n_groups, int g) {
+    const int apart = min(5, __builtin_clz((unsigned)(a.n - 1) | 1u) - 20);  // n << apart <= 4096
+    return a.arrivals + (((int64_t)b * n_groups + g) << apart);
+}
+
 // A wave has written its chunk's partial: count the chunk on the context's arrival counter.  Returns true
 // (to every lane) in the wave that delivered the LAST chunk of the context; that wave then merges the chunks,
 // and the counter is back at zero for the next launch.  Called by whole waves in uniform control flow.
@@ -769,7 +777,7 @@ __device__ __forceinline__ unsigned pieces_arrived(const AttnArgs &a, const Pend
     if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the partial stores have completed
     const int count = lane == 0 ? p0.count : p1.count;
-    unsigned int *cnt = a.arrivals + (int64_t)(lane == 0 ? p0.b : p1.b) * columns + col;
+    unsigned int *cnt = arrival_counter(a, lane == 0 ? p0.b : p1.b, columns, col);
     bool mine = false;
     if (lane < 2 && count != 0) {
         mine = atomicAdd(cnt, 1u) == (unsigned int)(count - 1);

@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(TS * 64) attn_fp8_kernel(const AttnArgs a) {
             // Chunks meet through an arrival counter per (sequence, head group), as in the multi-head kernels:
             // whoever delivers the last chunk merges them (a batch of few contexts is cut by its rows, a larger one only
             // beyond 1024 rows a context), without a merge launch after every attention launch.
-            unsigned int *cnt = a.arrivals + (int64_t)it.b * n_hg + it.hgb;
+            unsigned int *cnt = arrival_counter(a, it.b, n_hg, it.hgb);
             if (chunk_arrived(a, cnt, it.nchunks)) {
                 if (h_ok && tsub == 0) {
                     merge_chunks<D, true>(a, it.slot0, a.H, it.b, h, 2 * dl, it.nchunks);
