@@ -85,6 +85,24 @@ __device__ __forceinline__ float dpp_sum_step(float v) {
     return v + __builtin_bit_cast(float, moved);
 }
 
+// Sum, maximum over a lane and those that differ from it in the sixteen (rows of 16 lanes; WIDE: the half) they are in, without the
+// LDS unit: the swap brings the even rows (the lower half) of a value into one register, the odd ones (the upper) into another.
+template <bool WIDE, typename F>
+__device__ __forceinline__ float swap_rows(float v, F f) {
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto both = WIDE ? __builtin_amdgcn_permlane32_swap(u, u, false, false) : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a = both[0], b = both[1];
+    return f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+}
+__device__ __forceinline__ float max_over_rows(float v) {
+    const auto f = [](float a, float b) { return fmaxf(a, b); };
+    return swap_rows<true>(swap_rows<false>(v, f), f);
+}
+__device__ __forceinline__ float sum_over_rows(float v) {
+    const auto f = [](float a, float b) { return a + b; };
+    return swap_rows<true>(swap_rows<false>(v, f), f);
+}
+
 // Sum over groups of LANES adjacent lanes (4, 8, 16 or 32); every lane of a group gets the sum.
 template <int LANES>
 __device__ __forceinline__ float group_sum(float v) {
@@ -92,11 +110,7 @@ __device__ __forceinline__ float group_sum(float v) {
     v = dpp_sum_step<0x4E>(v);   // quad_perm [2,3,0,1]: lane ^ 2
     if (LANES >= 8) v = dpp_sum_step<0x141>(v);  // row_half_mirror: the other quad of each 8
     if (LANES >= 16) v = dpp_sum_step<0x140>(v);  // row_mirror: the other 8 of each 16
-    if (LANES >= 32) {
-        const int bits = __builtin_bit_cast(int, v);
-        const int other = __builtin_amdgcn_ds_swizzle(bits, 0x401F);  // lane ^ 16
-        v += __builtin_bit_cast(float, other);
-    }
+    if (LANES >= 32) v = swap_rows<false>(v, [](float a, float b) { return a + b; });  // lane ^ 16
     return v;
 }
 

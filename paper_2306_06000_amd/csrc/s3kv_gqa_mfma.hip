@@ -63,13 +63,6 @@ __device__ __forceinline__ f32x4 mfma_scores(const u32x4 a, const u32x4 b, const
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-template <int DT>
-__device__ __forceinline__ f32x4 mfma_values(const u32x2 a, const u32x2 b, const f32x4 c) {
-    if (DT == S3_F16)
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c, 0, 0, 0);
-}
-
 // V^T . P^T for RB blocks of 16 rows (two operand words each), P^T as its high and its low part.
 template <int DT, int RB>
 __device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const unsigned (&hi)[2 * RB], const unsigned (&lo)[2 * RB], f32x4 c) {
@@ -77,10 +70,8 @@ __device__ __forceinline__ f32x4 mfma_weights(const unsigned (&v)[2 * RB], const
         const u32x4 a = (u32x4){v[0], v[1], v[2], v[3]};
         c = mfma_scores<DT>(a, (u32x4){hi[0], hi[1], hi[2], hi[3]}, c);
         return mfma_scores<DT>(a, (u32x4){lo[0], lo[1], lo[2], lo[3]}, c);
-    } else {
-        const u32x2 a = (u32x2){v[0], v[1]};
-        c = mfma_values<DT>(a, (u32x2){hi[0], hi[1]}, c);
-        return mfma_values<DT>(a, (u32x2){lo[0], lo[1]}, c);
+    } else {  // sixteen rows: both parts in the 32 contraction slots of one product, the rows' operand twice
+        return mfma_scores<DT>((u32x4){v[0], v[1], v[0], v[1]}, (u32x4){hi[0], hi[1], lo[0], lo[1]}, c);
     }
 }
 
@@ -856,8 +847,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                         mt = fmaxf(mt, sv[rb][i]);
                     }
                 }
-                mt = fmaxf(mt, __shfl_xor(mt, 16));
-                mt = fmaxf(mt, __shfl_xor(mt, 32));
+                mt = max_over_rows(mt);
                 // Lazy reference: m is the exponent reference of the running sums, not necessarily the
                 // running maximum.  It moves (and the accumulators are rescaled) only when a tile's
                 // maximum exceeds it by more than RESCALE_LOG2, so p stays below 2^RESCALE_LOG2 and the
@@ -998,8 +988,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
             // and, by whoever is last, merged at the end of a share), or, in a team, to the wave's buffer of first pieces
             // or nowhere: the last piece of a share stays where it is.
             auto leave = [&]() {
-                lsum += __shfl_xor(lsum, 16);
-                lsum += __shfl_xor(lsum, 32);
+                lsum = sum_over_rows(lsum);
                 const bool whole = t_begin <= now.t0 && now.t_end == now.t1;
                 const bool to_lds = !whole && (CHUNKS || team == 4);
                 const float f = whole ? 1.f / lsum : 1.f;
