@@ -968,10 +968,8 @@ attn_fn s3i_pick_fp8(int act, int d, int shape, int *threads);
 typedef void (*append_fp8_fn)(char *, char *, const int64_t *, const int32_t *, const char *, const char *, int32_t,
                               int64_t, int32_t);
 append_fp8_fn s3i_pick_append_fp8(int act);
-// Matrix-core kernel for shared key/value heads (defined in s3kv_gqa_mfma.hip); 256 threads per
-// workgroup, one work item per wave.
-attn_fn s3i_pick_gqa_mfma(int dt, int d);
-attn_fn s3i_pick_gqa_mfma8(int act, int d);  // the same over 8-bit (e4m3) rows, q of type act
-attn_fn s3i_pick_gqa_mfma_wide(int act, int d, bool kv8);  // both, 512 threads per workgroup, one work item per workgroup
-attn_fn s3i_pick_gqa_few_heads(int dt, int d, int group, bool wide);  // 16-bit rows, two or three query heads per cached head; 256 threads, or (wide) 512
+// Matrix-core kernel for shared key/value heads (defined in s3kv_gqa_mfma.hip): q of type act, rows of the same or (kv8) e4m3
+// codes; 256 threads per workgroup, one work item per wave, or (wide) 512, one per workgroup; loop: more items than waves.
+attn_fn s3i_pick_gqa_mfma(int act, int d, bool kv8, bool wide, bool loop);
+attn_fn s3i_pick_gqa_few_heads(int dt, int d, int group, bool wide, bool loop);  // 16-bit rows, two or three query heads per cached head
 #define S3_FEW_CONTEXTS 256  // contexts whose view every wave of that kernel builds by itself

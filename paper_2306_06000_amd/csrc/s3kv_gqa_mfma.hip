@@ -557,7 +557,9 @@ __host__ __device__ constexpr int gqa_tile_rows(int row_bytes) { return row_byte
 // NW: waves of a workgroup, 4 or 8.
 // GQ: 2 or 3, the query heads per cached head where these are so few: the scores on the matrix cores, the weighted rows on the
 // vector ALU with the weights in fp32 (pick_few_heads); 0: both products on the matrix cores.
-template <int DT, int D, bool KV8, int NW, int GQ = 0>
+// LOOP: there may be more units than waves (teams); else every wave (team) takes one, and nothing is computed, and spilled, in
+// front of a loop for units that do not come (137 to 169 scalar registers spilled with it, 58 to 105 without).
+template <int DT, int D, bool KV8, int NW, int GQ = 0, bool LOOP = false>
 __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {
     constexpr int EB = KV8 ? 1 : 2;       // bytes per cached element
     constexpr int KS = D / 32;            // contraction steps of the score product
@@ -1209,7 +1211,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 for (int k = 0; k < 2; k++)
                     if ((mine >> k) & 1) merge_pieces<D, CHUNKS>(a, k ? pend1 : pend0, hq0, nheads, threadIdx.x, NW * 64, (float *)wave_lds);
             }
-            if (CHUNKS) break;  // (the grid has a workgroup for every chunk)
+            if (!LOOP) break;
             __syncthreads();  // LDS is free for the next unit
         } else if constexpr (!CHUNKS) {
             if (pend0.count != 0 || pend1.count != 0) {
@@ -1218,6 +1220,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
                 for (int k = 0; k < 2; k++)
                     if ((mine >> k) & 1) merge_pieces<D, false>(a, k ? pend1 : pend0, hq0, nheads, lane, 64, nullptr);
             }
+            if (!LOOP) break;
         }
     }
     // What belongs to no row, behind the work: the new lengths (the last workgroup has none in a launch of few rows) ...
@@ -1243,53 +1246,34 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa
 // Error against 64 bits, relative 2-norm, fp32 outputs, 16q/8kv x 128, 64q/32kv x 128, 16q/8kv x 64, 6q/3kv x 256, 24q/8kv x
 // 64, 12q/4kv x 128, 9q/3kv x 256, 8 to 85 contexts: bf16 1.33e-7 to 1.54e-7 where the vector ALU has 1.58e-7 to 1.82e-7, fp16
 // 1.38e-7 to 1.61e-7 and 1.66e-7 to 1.85e-7; one context of 37 rows level (bf16 1.11e-7 to 1.37e-7, 1.13e-7 to 1.37e-7).
-template <int DT, int NW>
+template <int DT, int NW, bool LOOP>
 static attn_fn pick_few_heads(int d, int group) {
-    if (d == 64) return group == 2 ? attn_gqa_mfma_kernel<DT, 64, false, NW, 2> : attn_gqa_mfma_kernel<DT, 64, false, NW, 3>;
-    if (d == 128) return group == 2 ? attn_gqa_mfma_kernel<DT, 128, false, NW, 2> : attn_gqa_mfma_kernel<DT, 128, false, NW, 3>;
-    if (d == 256) return group == 2 ? attn_gqa_mfma_kernel<DT, 256, false, NW, 2> : attn_gqa_mfma_kernel<DT, 256, false, NW, 3>;
+    if (d == 64) return group == 2 ? attn_gqa_mfma_kernel<DT, 64, false, NW, 2, LOOP> : attn_gqa_mfma_kernel<DT, 64, false, NW, 3, LOOP>;
+    if (d == 128) return group == 2 ? attn_gqa_mfma_kernel<DT, 128, false, NW, 2, LOOP> : attn_gqa_mfma_kernel<DT, 128, false, NW, 3, LOOP>;
+    if (d == 256) return group == 2 ? attn_gqa_mfma_kernel<DT, 256, false, NW, 2, LOOP> : attn_gqa_mfma_kernel<DT, 256, false, NW, 3, LOOP>;
     return nullptr;
 }
-attn_fn s3i_pick_gqa_few_heads(int dt, int d, int group, bool wide) {
-    if (dt == S3_F16) return wide ? pick_few_heads<S3_F16, 8>(d, group) : pick_few_heads<S3_F16, 4>(d, group);
-    return wide ? pick_few_heads<S3_BF16, 8>(d, group) : pick_few_heads<S3_BF16, 4>(d, group);
+template <int DT>
+static attn_fn pick_few_heads(int d, int group, bool wide, bool loop) {
+    return wide ? pick_few_heads<DT, 8, false>(d, group) : loop ? pick_few_heads<DT, 4, true>(d, group) : pick_few_heads<DT, 4, false>(d, group);
+}
+attn_fn s3i_pick_gqa_few_heads(int dt, int d, int group, bool wide, bool loop) {
+    return dt == S3_F16 ? pick_few_heads<S3_F16>(d, group, wide, loop) : pick_few_heads<S3_BF16>(d, group, wide, loop);
 }
 
-attn_fn s3i_pick_gqa_mfma(int dt, int d) {
-    if (dt == S3_F16) {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_F16, 64, false, 4>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_F16, 128, false, 4>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_F16, 256, false, 4>;
-    } else {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_BF16, 64, false, 4>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_BF16, 128, false, 4>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_BF16, 256, false, 4>;
-    }
+// act: the type of q (and of the rows, unless they are e4m3: kv8).
+template <int ACT, int NW, bool LOOP>
+static attn_fn pick_waves(int d, bool kv8) {
+    if (d == 64) return kv8 ? attn_gqa_mfma_kernel<ACT, 64, true, NW, 0, LOOP> : attn_gqa_mfma_kernel<ACT, 64, false, NW, 0, LOOP>;
+    if (d == 128) return kv8 ? attn_gqa_mfma_kernel<ACT, 128, true, NW, 0, LOOP> : attn_gqa_mfma_kernel<ACT, 128, false, NW, 0, LOOP>;
+    if (d == 256) return kv8 ? attn_gqa_mfma_kernel<ACT, 256, true, NW, 0, LOOP> : attn_gqa_mfma_kernel<ACT, 256, false, NW, 0, LOOP>;
     return nullptr;
 }
-
-// The same kernel over 8-bit (e4m3) rows; act is the type of q.
-attn_fn s3i_pick_gqa_mfma8(int act, int d) {
-    if (act == S3_F16) {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_F16, 64, true, 4>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_F16, 128, true, 4>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_F16, 256, true, 4>;
-    } else if (act == S3_BF16) {
-        if (d == 64) return attn_gqa_mfma_kernel<S3_BF16, 64, true, 4>;
-        if (d == 128) return attn_gqa_mfma_kernel<S3_BF16, 128, true, 4>;
-        if (d == 256) return attn_gqa_mfma_kernel<S3_BF16, 256, true, 4>;
-    }
-    return nullptr;
-}
-
-// Eight waves a workgroup; act: the type of q (and of the rows, unless they are e4m3: kv8).
 template <int ACT>
-static attn_fn pick_eight_waves(int d, bool kv8) {
-    if (d == 64) return kv8 ? attn_gqa_mfma_kernel<ACT, 64, true, 8> : attn_gqa_mfma_kernel<ACT, 64, false, 8>;
-    if (d == 128) return kv8 ? attn_gqa_mfma_kernel<ACT, 128, true, 8> : attn_gqa_mfma_kernel<ACT, 128, false, 8>;
-    if (d == 256) return kv8 ? attn_gqa_mfma_kernel<ACT, 256, true, 8> : attn_gqa_mfma_kernel<ACT, 256, false, 8>;
-    return nullptr;
+static attn_fn pick_waves(int d, bool kv8, bool wide, bool loop) {
+    return wide ? pick_waves<ACT, 8, false>(d, kv8) : loop ? pick_waves<ACT, 4, true>(d, kv8) : pick_waves<ACT, 4, false>(d, kv8);
 }
-attn_fn s3i_pick_gqa_mfma_wide(int act, int d, bool kv8) {
-    return act == S3_F16 ? pick_eight_waves<S3_F16>(d, kv8) : act == S3_BF16 ? pick_eight_waves<S3_BF16>(d, kv8) : nullptr;
+attn_fn s3i_pick_gqa_mfma(int act, int d, bool kv8, bool wide, bool loop) {
+    return act == S3_F16    ? pick_waves<S3_F16>(d, kv8, wide, loop)
+           : act == S3_BF16 ? pick_waves<S3_BF16>(d, kv8, wide, loop) : nullptr;
 }

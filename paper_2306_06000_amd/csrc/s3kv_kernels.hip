@@ -829,8 +829,10 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     const bool eight_bit = s3i_kernel_kind(a) == 4;
     const int group = Hq / Hkv;
     const bool few_heads = !eight_bit && group < 4;
-    attn_fn fn = few_heads ? s3i_pick_gqa_few_heads(a->cfg.kv_dtype, D, group, false)
-                 : eight_bit ? s3i_pick_gqa_mfma8(a->cfg.act_dtype, D) : s3i_pick_gqa_mfma(a->cfg.kv_dtype, D);
+    const auto pick = [&](bool wide, bool loop) {
+        return few_heads ? s3i_pick_gqa_few_heads(a->cfg.kv_dtype, D, group, wide, loop) : s3i_pick_gqa_mfma(a->cfg.act_dtype, D, eight_bit, wide, loop);
+    };
+    attn_fn fn = pick(false, false);
     if (!fn) return S3_ERR_INVALID;
     if (c.static_scratch && !gqa_fits_static(a, c.n)) return S3_ERR_SCRATCH;
     const int64_t columns = gqa_columns(a);
@@ -857,7 +859,7 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     // chunk of one (eight_wave_plan).  Beyond, pairs would wait for a unit of their own (32q/8kv x 128, 34 contexts of
     // 32..1000 rows 22.0 us a layer against 21.5 with workgroups of four, 64 contexts 34.2 against 30.5).
     if (a->chunk <= 0 && c.n <= S3_FEW_CONTEXTS && c.n * columns <= cus) {
-        attn_fn wide = few_heads ? s3i_pick_gqa_few_heads(a->cfg.kv_dtype, D, group, true) : s3i_pick_gqa_mfma_wide(a->cfg.act_dtype, D, eight_bit);
+        attn_fn wide = pick(true, false);
         args.team_shares = (int32_t)(cus / columns);
         rc = resident_per_cu((const void *)wide, 512, view, &per_cu);
         if (rc != S3_OK) return rc;
@@ -871,6 +873,8 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
         rc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
         if (rc != S3_OK) return rc;
     }
+    // Chunks of the caller's size, grids of the caller's, and more columns than waves: units beyond what runs at once.
+    if (a->chunk > 0 || a->grid_blocks > 0 || columns > 4 * cus) fn = pick(false, true);
     rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
     if (rc != S3_OK) return rc;
     if (per_cu > 2) per_cu = 2;
