@@ -328,10 +328,11 @@ __device__ __forceinline__ void emit_chunk(const AttnArgs &a, const Item &it, in
 // unclaimed position from a device-wide counter (fetched by the epilogue wave one item ahead, so that the
 // round trip hides behind the streaming), which keeps every compute unit busy to the end whatever else
 // occupies some of them, and makes the longest-first order of the list a longest-processing-time schedule.
-// UNITS: the view may cut the contexts into as many chunks as run at once (unit_chunk_rows): two workgroups of nine waves a
-// compute unit, five on one of its SIMDs.
+// UNITS: the view may cut the contexts into as many chunks as run at once (unit_chunk_rows).  It and the default shape of up to
+// 128 contexts are held to the 96 registers that let two workgroups of nine waves share a compute unit, five on one of its
+// SIMDs (64 x 96, 64 contexts of 32..1000 rows: 133 us a layer, with 101 registers 148).
 template <int DT, int D, int TS, int HS, int U, bool NT, bool PF, int R, bool DYN, bool UNITS = false>
-__global__ void __launch_bounds__((TS *HS + 1) * 64, UNITS ? 5 : 0) attn_step_kernel(const AttnArgs a) {
+__global__ void __launch_bounds__((TS *HS + 1) * 64, UNITS || (TS == 8 && U == 2 && PF && R == 0 && !DYN) ? 5 : 0) attn_step_kernel(const AttnArgs a) {
     constexpr int LPH = HeadLanes<D>::LPH, USED = HeadLanes<D>::USED, GH = HeadLanes<D>::GH;
     constexpr int NWC = TS * HS;  // compute waves
     extern __shared__ __align__(16) char dyn_lds[];  // the batch view, then the rings

@@ -21,14 +21,6 @@
 
 #include "s3kv_attn.h"
 
-// x / y rounded down, exact for x below 2^24: the product with the hardware's reciprocal is off by less than one, which the
-// remainder puts right (an integer division is forty instructions).
-__device__ __forceinline__ int few_quotient(int x, int y) {
-    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y)), r = x - q * y;
-    return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
-}
-
-
 // A wave's share of a chunk's rows, for one head group.
 template <int DT, int D>
 struct FewRows {
@@ -141,13 +133,13 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
             const int room = max(units - ((n * quarters + 3) >> 2), 1);
             const int even = (int)((float)total * __builtin_amdgcn_rcpf((float)room) * 1.000001f) + 1;  // (not below the quotient)
             const int per = min(max(even, least), longest);
-            cnt = few_quotient(len + per - 1, per);
+            cnt = quotient(len + per - 1, per);
             incl = wave_inclusive_scan(cnt);
             if (__builtin_amdgcn_readlane(incl, 63) <= units) break;
         }
     }
     const int chunks = __builtin_amdgcn_readlane(incl, 63);
-    const int w = __builtin_amdgcn_readfirstlane(a.column_shift >= 0 ? (int)(blockIdx.x >> a.column_shift) : few_quotient(blockIdx.x, n_hg));
+    const int w = __builtin_amdgcn_readfirstlane(a.column_shift >= 0 ? (int)(blockIdx.x >> a.column_shift) : quotient(blockIdx.x, n_hg));
     const int hg = blockIdx.x - w * n_hg;
     if (w < chunks) {
         // ---- the chunk of this workgroup: of context `seq`, near-equal pieces, none of them empty
@@ -156,7 +148,7 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
         const int all = __builtin_amdgcn_readlane(len, seq), chunk = w - first;
         const int64_t row0 = (int64_t)(((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)(off >> 32), seq) << 32) |
                                        (unsigned)__builtin_amdgcn_readlane((int)off, seq));
-        const int base = nchunks == 1 ? all : few_quotient(all, nchunks), rem = all - base * nchunks;
+        const int base = nchunks == 1 ? all : quotient(all, nchunks), rem = all - base * nchunks;
         const int start = chunk * base + min(chunk, rem), rows = base + (chunk < rem ? 1 : 0);
         const int eighth = rows >> 3, more = rows & 7;
         const int j0 = start + wave * eighth + min(wave, more), share = eighth + (wave < more ? 1 : 0);

@@ -235,6 +235,15 @@ __device__ __forceinline__ u32x4 load16(const char *p) {
     return NT ? __builtin_nontemporal_load((const u32x4 *)p) : *(const u32x4 *)p;
 }
 
+// Quotients of whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here all out
+// of a cold instruction cache).  x / y rounded down, exact for x below 2^24: the product is off by less than one, which the
+// remainder puts right.  And a whole number not below x / y, by less than 2 above it where x / y is below 2^19.
+__device__ __forceinline__ int quotient(int x, int y) {
+    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y)), r = x - q * y;
+    return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+__device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x * __builtin_amdgcn_rcpf((float)y) * 1.000001f) + 1; }
+
 // Work order of a launch: longest contexts first.  Contexts are put into `ncls` length classes
 // relative to the longest context of the batch; the work list holds the chunks of class 0 (the longest)
 // in batch order, then class 1, and so on.  Long items therefore start first and the short ones fill
@@ -249,7 +258,8 @@ __device__ __forceinline__ int chunks_of(const AttnArgs &a, int b, int chunk) {
 }
 
 __device__ __forceinline__ int class_of(int len, int max_len_seen, int ncls) {
-    return ncls - 1 - min(ncls - 1, len * ncls / (max_len_seen + 1));  // len * ncls < 2^31: len <= max_len <= 2^20
+    // (the order of the work only: a quotient off by one at a border costs nothing)
+    return ncls - 1 - min(ncls - 1, (int)((float)(len * ncls) * __builtin_amdgcn_rcpf((float)(max_len_seen + 1))));
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave with DPP row operations (no LDS round trips):
@@ -384,7 +394,7 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
         auto chunks_of = [&](int rows_each) {
             int count = 0;
 #pragma unroll
-            for (int e = 0; e < E; e++) count += (len[e] + rows_each - 1) / rows_each;
+            for (int e = 0; e < E; e++) count += quotient(len[e] + rows_each - 1, rows_each);
             return __builtin_amdgcn_readlane(wave_inclusive_scan(count), 63);
         };
         const int sixteen = a.unit_chunks >> 16;
@@ -415,7 +425,7 @@ __device__ __forceinline__ void one_wave_view(const AttnArgs &a, int64_t *off_s,
 #pragma unroll
     for (int e = 0; e < E; e++) {
         cls[e] = class_of(len[e], mx, ncls);
-        cnt[e] = (len[e] + chunk - 1) / chunk;
+        cnt[e] = quotient(len[e] + chunk - 1, chunk);
     }
     for (int c = 0; c < ncls; c++) {
         int loc[E], lsum = 0;
@@ -451,7 +461,7 @@ __device__ __forceinline__ int block_view(const AttnArgs &a, int chunk, int64_t 
 #pragma unroll
         for (int e = 0; e < E; e++) {
             const int b = base + tid * E + e;
-            cnt[e] = (len[e] + chunk - 1) / chunk;
+            cnt[e] = quotient(len[e] + chunk - 1, chunk);
             sum += cnt[e];
             if (b < a.n) {
                 len_s[b] = len[e];
@@ -867,7 +877,7 @@ struct Item {
 // back to `chunk` if rounding would leave the last piece empty.
 __device__ __forceinline__ int balanced_chunk_len(int len, int nchunks, int chunk) {
     if (nchunks <= 1) return chunk;
-    const int clen = (len + nchunks - 1) / nchunks;
+    const int clen = quotient(len + nchunks - 1, nchunks);
     return (nchunks - 1) * clen < len ? clen : chunk;
 }
 
@@ -902,7 +912,8 @@ __device__ __forceinline__ int find_sequence(const int *pre, int n, int w) {
 __device__ __forceinline__ Item decode_item(const AttnArgs &a, const BatchView &v, int64_t item, int n_hgb) {
     Item it;
     const int lane = threadIdx.x & 63;
-    int w = (int)(item / n_hgb);
+    // (items beyond 2^24: whole numbers of 32 bits and more, in forty and a hundred instructions)
+    int w = item < (1 << 24) ? quotient((int)item, n_hgb) : (int)(item / n_hgb);
     it.hgb = (int)(item - (int64_t)w * n_hgb);
     it.slot0 = w;
     const int tot = lane < v.ncls ? v.pre[lane * (v.n + 1) + v.n] : 0;

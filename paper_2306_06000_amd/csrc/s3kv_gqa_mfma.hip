@@ -152,15 +152,6 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
     t[3] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);
 }
 
-// Quotients of whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here all out
-// of a cold instruction cache).  x / y rounded down, exact for x below 2^24: the product is off by less than one, which the
-// remainder puts right.  And a whole number not below x / y, by less than 2 above it where x / y is below 2^19.
-__device__ __forceinline__ int quotient(int x, int y) {
-    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y)), r = x - q * y;
-    return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
-}
-__device__ __forceinline__ int not_below(int x, int y) { return (int)((float)x * __builtin_amdgcn_rcpf((float)y) * 1.000001f) + 1; }
-
 // How a launch of few rows divides them (four waves a workgroup): every context by itself, into near-equal
 // chunks of at most `per` tiles, one wave or a team of four waves a chunk, all at once.  Nothing is combined that the
 // lengths do not force: a context of one chunk is finished by its wave or team.  (The figures of few contexts were taken before
