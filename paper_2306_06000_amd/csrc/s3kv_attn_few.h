@@ -1,4 +1,4 @@
-// Attention over few contexts of a multi-head 16-bit cache, gfx950.  Included by s3kv_attn_inst.hip (one translation unit
+// Attention over few contexts of a multi-head cache, 16-bit rows or (KV8) e4m3 codes, gfx950.  Included by s3kv_attn_inst.hip (one translation unit
 // per head dimension).
 //
 // A launch of few rows is a chain of latencies, and most of it instructions that run once.  attn_step_kernel spent, on one
@@ -15,32 +15,70 @@
 // us a layer, attn_step_kernel and this: 16 x 256 fp16, 1 context of 30..40 rows 5.7, 3.9; of 300..400 9.2, 6.6; of 1400..1500
 // 12.9, 9.5; of 8000 28.1, 26.1; 4 of 17..128 9.5, 6.6; 4 of 500..1500 17.4, 16.2; 16 of 32..1000 28.1, 26.8; 12 x 128 bf16, 1
 // of 1400..1500 12.4, 8.5, 24 of 32..1000 18.1, 17.2; 64 x 96 bf16, 1 of 300..400 9.8, 7.1, 8 of 32..1000 20.9, 21.8 (the
-// most it loses); 3 x 128, 8 of 500..1500 12.0, 7.8.
+// most it loses); 3 x 128, 8 of 500..1500 12.0, 7.8.  e4m3 rows (attn_fp8_kernel, whose one wave of eight combines a chunk while
+// the others wait): 16 x 256, 1 of 300..400 13.9, 7.9, of 8000 32.9, 19.4, 8 of 32..1000 17.8, 11.9, 40 of 32..1000 39.0, 34.9; 12 x 128,
+// 4 of 17..128 12.6, 7.0.
 #pragma once
 #include <type_traits>
 
 #include "s3kv_attn.h"
 
-// A wave's share of a chunk's rows, for one head group.
-template <int DT, int D>
+// Lanes of a wave load: a lane holds 16 bytes of a row, EL elements, LPH lanes a head (USED of them in use), GH heads a load.
+template <int D, bool KV8>
+struct FewLanes {
+    static constexpr int EL = KV8 ? 16 : 8, USED = D / EL, LPH = KV8 ? D / 16 : HeadLanes<D>::LPH, GH = 64 / LPH;
+};
+
+// A wave's share of a chunk's rows, for one head group.  DT: the type of q (and of the rows, but for KV8).
+template <int DT, int D, bool KV8>
 struct FewRows {
-    typedef HeadLanes<D> HL;
+    typedef FewLanes<D, KV8> HL;
+    static constexpr int EL = HL::EL;
     const char *kb, *vb;      // the share's first row, this head group (wave-uniform)
-    const char *knew, *vnew;  // the new row, and whether it is the share's last one
+    const char *knew, *vnew;  // the new row, and whether it is the share's last one (KV8: it is not in `rows`)
     bool fresh;
     int64_t rstride;
     unsigned rs32, tail;      // (tail: bytes of a row in front of this head group)
     unsigned lane_byte;       // this lane's bytes of a row
     int rows;                 // rows of the share
     float scale_log2e;
-    u32x4 qv;
+    u32x4 qv;                 // (16-bit rows)
+    float qf[KV8 ? 16 : 1];   // (KV8: q, scaled)
+
+    __device__ __forceinline__ float dot(const u32x4 k) const {
+        if constexpr (!KV8) return dot8<DT>(qv, k);
+        float d = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; w++) {
+            float f[4];
+            const unsigned word = k[w];
+            widen4_e4m3(word, f);
+#pragma unroll
+            for (int e = 0; e < 4; e++) d = fmaf(qf[KV8 ? 4 * w + e : 0], f[e], d);
+        }
+        return d;
+    }
+    __device__ __forceinline__ void axpy(float (&acc)[EL], const float p, const u32x4 v) const {
+        if constexpr (!KV8) {
+            axpy8<DT>(acc, p, v);
+        } else {
+#pragma unroll
+            for (int w = 0; w < 4; w++) {
+                float f[4];
+                const unsigned word = v[w];
+                widen4_e4m3(word, f);
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[4 * w + e] = fmaf(p, f[e], acc[4 * w + e]);
+            }
+        }
+    }
 
     // Rows j .. j+U-1: zeros (and no traffic) past the share's end.
     template <int U>
     __device__ __forceinline__ void load(int j, u32x4 *kk, u32x4 *vv) const {
         const int left = min(rows - j, U);
         const char *kp = kb + j * rstride, *vp = vb + j * rstride;
-        if (__builtin_expect(fresh && left > 0 && j + left == rows, 0)) {  // the last row is the new one
+        if (!KV8 && __builtin_expect(fresh && left > 0 && j + left == rows, 0)) {  // the last row is the new one
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 const bool it = u == left - 1;
@@ -63,26 +101,26 @@ struct FewRows {
 
     // `count` of N rows (or more than N: all).
     template <int N>
-    __device__ __forceinline__ void reduce(int count, const u32x4 *kk, const u32x4 *vv, float &m, float &l, float (&acc)[8]) const {
+    __device__ __forceinline__ void reduce(int count, const u32x4 *kk, const u32x4 *vv, float &m, float &l, float (&acc)[EL]) const {
         float s[N], mb = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < N; u++) s[u] = dot8<DT>(qv, kk[u]);
+        for (int u = 0; u < N; u++) s[u] = dot(kk[u]);
 #pragma unroll
         for (int u = 0; u < N; u++) s[u] = group_sum<HL::LPH>(s[u]);
 #pragma unroll
         for (int u = 0; u < N; u++) {
-            s[u] = u < count ? s[u] * scale_log2e : -INFINITY;
+            s[u] = u < count ? KV8 ? s[u] : s[u] * scale_log2e : -INFINITY;
             mb = fmaxf(mb, s[u]);
         }
         const float mn = fmaxf(m, mb), ref = exp_reference(mn), alpha = fast_exp2(m - ref);
         l *= alpha;
 #pragma unroll
-        for (int i = 0; i < 8; i++) acc[i] *= alpha;
+        for (int i = 0; i < EL; i++) acc[i] *= alpha;
 #pragma unroll
         for (int u = 0; u < N; u++) {
             const float p = fast_exp2(s[u] - ref);
             l += p;
-            axpy8<DT>(acc, p, vv[u]);
+            axpy(acc, p, vv[u]);
         }
         m = mn;
     }
@@ -92,11 +130,12 @@ struct FewRows {
 // (three at 96 elements a head, whose loads bring 12 of 16 bytes): four or eight a set, which leave room for one workgroup
 // only, read level where latencies bound the launch and 5 to 20 % slower where the memory rate does (16 x 256, 8 contexts of
 // 500..1500 rows: 24.7 us with two, 26.4 with four, 30.9 with eight).
-template <int DT, int D>
+template <int DT, int D, bool KV8 = false>
 __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
-    typedef HeadLanes<D> HL;
-    constexpr int LPH = HL::LPH, USED = HL::USED, GH = HL::GH, NW = 8, U = D == 96 ? 3 : 2;
-    constexpr int ELEMS = GH * D;  // elements of a head group's output: at most one per thread
+    typedef FewLanes<D, KV8> HL;
+    constexpr int LPH = HL::LPH, USED = HL::USED, GH = HL::GH, EL = HL::EL, NW = 8, U = D == 96 ? 3 : 2;
+    constexpr int ELEMS = GH * D;        // elements of a head group's output
+    constexpr int EPT = (ELEMS + 511) / 512;  // ... per thread: one, KV8 two
     __shared__ __align__(16) float comb[NW][ELEMS];
     __shared__ float2 comb_ml[NW][GH];
     __shared__ int last_here;
@@ -155,49 +194,65 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
         const int g = lane / LPH, dl = lane % LPH;
         const int h = hg * GH + g;
         const int hc = h < a.H ? g : a.H - 1 - hg * GH, dc = dl < USED ? dl : USED - 1;  // (lanes without bytes of their own: a neighbour's)
-        const int64_t rstride = (int64_t)a.H * D * 2;
+        const int64_t rstride = (int64_t)a.H * D * (KV8 ? 1 : 2);
         const bool fresh = a.k_new && j0 + share == all && share > 0;  // the new row is this share's last one
-        FewRows<DT, D> st;
+        FewRows<DT, D, KV8> st;
         st.rstride = rstride;
         st.rs32 = (unsigned)rstride;
-        st.tail = (unsigned)(hg * GH * D * 2);
-        const unsigned lane_byte = (unsigned)((hc * D + dc * 8) * 2);
+        st.tail = (unsigned)(hg * GH * D * (KV8 ? 1 : 2));
+        const unsigned lane_byte = (unsigned)((hc * D + dc * EL) * (KV8 ? 1 : 2));
         st.lane_byte = lane_byte;
         st.kb = a.kplane + (row0 + j0) * rstride + st.tail;
         st.vb = a.vplane + (row0 + j0) * rstride + st.tail;
-        st.rows = share;
+        st.rows = share - (KV8 && fresh ? 1 : 0);
         st.fresh = fresh;
-        st.knew = a.k_new + (int64_t)seq * rstride + st.tail;
-        st.vnew = a.v_new + (int64_t)seq * rstride + st.tail;
         st.scale_log2e = a.scale_log2e;
-        const int64_t in_byte = (int64_t)seq * rstride + st.tail + lane_byte;
-        st.qv = *(const u32x4 *)(a.q + in_byte);
+        // q and the new row are 16-bit: this lane's elements of them
+        const int64_t in_row = ((int64_t)seq * a.H + hg * GH) * D * 2;
+        const unsigned in_lane = KV8 ? 2 * lane_byte : lane_byte;
+        st.knew = a.k_new + in_row;
+        st.vnew = a.v_new + in_row;
+        u32x4 q1;
+        st.qv = *(const u32x4 *)(a.q + in_row + in_lane);
+        if constexpr (KV8) q1 = *(const u32x4 *)(a.q + in_row + in_lane + 16);
         // (without a branch: what two paths bring into one register is waited for where they meet)
-        const int fresh_bytes = fresh ? (int)(st.rs32 - st.tail) : 0;
-        const u32x4 kn = __builtin_amdgcn_raw_buffer_load_b128(st.rows_of(st.knew, fresh_bytes), lane_byte, 0, 0);
-        const u32x4 vn = __builtin_amdgcn_raw_buffer_load_b128(st.rows_of(st.vnew, fresh_bytes), lane_byte, 0, 0);
-        if (USED < LPH && dl >= USED) st.qv = (u32x4){0u, 0u, 0u, 0u};
-        float m = -INFINITY, l = 0.f, acc[8];
-#pragma unroll
-        for (int i = 0; i < 8; i++) acc[i] = 0.f;
-        // Up to twelve rows: all of them leave at once, in fours (a load past the share's end costs its issue).
-        auto few = [&](auto fours) {
-            constexpr int F = decltype(fours)::value;
-            u32x4 k4[4 * F], v4[4 * F];
-#pragma unroll
-            for (int f = 0; f < F; f++) st.template load<4>(4 * f, k4 + 4 * f, v4 + 4 * f);
-#pragma unroll
-            for (int f = 0; f < F; f++) st.template reduce<4>(st.rows - 4 * f, k4 + 4 * f, v4 + 4 * f, m, l, acc);
-        };
-        if (st.rows <= 8) {
-            if (st.rows > 4) few(std::integral_constant<int, 2>());
-            else if (st.rows > 0) few(std::integral_constant<int, 1>());
-        } else if (st.rows <= 12) {
-            few(std::integral_constant<int, 3>());
+        const int fresh_bytes = fresh ? (int)((a.H - hg * GH) * D * 2) : 0;
+        const __amdgpu_buffer_rsrc_t knr = st.rows_of(st.knew, fresh_bytes), vnr = st.rows_of(st.vnew, fresh_bytes);
+        u32x4 kn, vn;
+        if constexpr (!KV8) {  // (KV8: below, for want of registers)
+            kn = __builtin_amdgcn_raw_buffer_load_b128(knr, in_lane, 0, 0);
+            vn = __builtin_amdgcn_raw_buffer_load_b128(vnr, in_lane, 0, 0);
         } else {
-            float m1 = -INFINITY, l1 = 0.f, acc1[8];  // the runs before
 #pragma unroll
-            for (int i = 0; i < 8; i++) acc1[i] = 0.f;
+            for (int i = 0; i < 8; i++) {
+                const unsigned w = i < 4 ? st.qv[i] : q1[i - 4];
+                st.qf[KV8 ? 2 * i : 0] = widen16<DT>((unsigned short)(w & 0xFFFFu)) * a.scale_log2e;
+                st.qf[KV8 ? 2 * i + 1 : 0] = widen16<DT>((unsigned short)(w >> 16)) * a.scale_log2e;
+            }
+        }
+        if (!KV8 && USED < LPH && dl >= USED) st.qv = (u32x4){0u, 0u, 0u, 0u};
+        float m = -INFINITY, l = 0.f, acc[EL];
+#pragma unroll
+        for (int i = 0; i < EL; i++) acc[i] = 0.f;
+        // Up to twelve rows (KV8: six): all of them leave at once, in fours (threes; a load past the share's end costs its issue).
+        constexpr int FB = KV8 ? 3 : 4;
+        auto few = [&](auto times) {
+            constexpr int F = decltype(times)::value;
+            u32x4 kf[FB * F], vf[FB * F];
+#pragma unroll
+            for (int f = 0; f < F; f++) st.template load<FB>(FB * f, kf + FB * f, vf + FB * f);
+#pragma unroll
+            for (int f = 0; f < F; f++) st.template reduce<FB>(st.rows - FB * f, kf + FB * f, vf + FB * f, m, l, acc);
+        };
+        if (st.rows <= 2 * FB) {
+            if (st.rows > FB) few(std::integral_constant<int, 2>());
+            else if (st.rows > 0) few(std::integral_constant<int, 1>());
+        } else if (!KV8 && st.rows <= 3 * FB) {
+            few(std::integral_constant<int, KV8 ? 2 : 3>());
+        } else {
+            float m1 = -INFINITY, l1 = 0.f, acc1[EL];  // the runs before
+#pragma unroll
+            for (int i = 0; i < EL; i++) acc1[i] = 0.f;
             u32x4 ka[U], va[U], kb[U], vb[U];
             st.template load<U>(0, ka, va);
             st.template load<U>(U, kb, vb);
@@ -214,11 +269,11 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
                     m1 = mm;
                     l1 = f1 * l1 + f * l;
 #pragma unroll
-                    for (int i = 0; i < 8; i++) acc1[i] = f1 * acc1[i] + f * acc[i];
+                    for (int i = 0; i < EL; i++) acc1[i] = f1 * acc1[i] + f * acc[i];
                     m = -INFINITY;
                     l = 0.f;
 #pragma unroll
-                    for (int i = 0; i < 8; i++) acc[i] = 0.f;
+                    for (int i = 0; i < EL; i++) acc[i] = 0.f;
                 }
             }
             st.template reduce<U>(st.rows - j, ka, va, m, l, acc);
@@ -227,7 +282,16 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
             m = mm;
             l = f1 * l1 + f * l;
 #pragma unroll
-            for (int i = 0; i < 8; i++) acc[i] = f1 * acc1[i] + f * acc[i];
+            for (int i = 0; i < EL; i++) acc[i] = f1 * acc1[i] + f * acc[i];
+        }
+        if constexpr (KV8) {  // the new row, rounded to codes as the append kernel rounds it, and attended to as they widen
+            if (fresh) {
+                const u32x4 k0 = __builtin_amdgcn_raw_buffer_load_b128(knr, in_lane, 0, 0), k1 = __builtin_amdgcn_raw_buffer_load_b128(knr, in_lane + 16, 0, 0);
+                const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(vnr, in_lane, 0, 0), v1 = __builtin_amdgcn_raw_buffer_load_b128(vnr, in_lane + 16, 0, 0);
+                kn = quantize16<DT>(k0, k1);
+                vn = quantize16<DT>(v0, v1);
+                st.template reduce<1>(1, &kn, &vn, m, l, acc);
+            }
         }
         if (fresh && h < a.H && dl < USED) {  // the append
             *(u32x4 *)(const_cast<char *>(st.kb) + (share - 1) * rstride + lane_byte) = kn;
@@ -235,41 +299,52 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
         }
         // ---- the shares meet: every thread one element of the head group's output
         if (dl < USED) {
-            *(f32x4 *)&comb[wave][g * D + dl * 8] = (f32x4){acc[0], acc[1], acc[2], acc[3]};
-            *(f32x4 *)&comb[wave][g * D + dl * 8 + 4] = (f32x4){acc[4], acc[5], acc[6], acc[7]};
+#pragma unroll
+            for (int i = 0; i < EL; i += 4) *(f32x4 *)&comb[wave][g * D + dl * EL + i] = (f32x4){acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
             if (dl == 0) comb_ml[wave][g] = make_float2(m, l);
         }
         __syncthreads();
-        const int e = ELEMS == 512 ? tid : min(tid, ELEMS - 1), eh = e / D, head = hg * GH + eh;
-        const bool mine = (ELEMS == 512 || tid < ELEMS) && head < a.H;
-        float2 x[NW];
-        float o[NW], mx = -INFINITY;
+        // (element k of this thread: tid + 512 * k of the head group's)
+        const int heads = min(GH, a.H - hg * GH);
+        const int64_t out0 = (int64_t)seq * a.H * D + hg * ELEMS;
+        const auto combine = [&](auto parts, int e, float &top, float &sum, float &val) {
+            constexpr int N = decltype(parts)::value;
+            float2 x[N];
+            float o[N];
+            top = -INFINITY;
 #pragma unroll
-        for (int s = 0; s < NW; s++) {
-            x[s] = comb_ml[s][eh];
-            o[s] = comb[s][e];
-        }
-#pragma unroll
-        for (int s = 0; s < NW; s++) mx = fmaxf(mx, x[s].x);
-        const float ref = exp_reference(mx);
-        float sum = 0.f, val = 0.f;
-#pragma unroll
-        for (int s = 0; s < NW; s++) {
-            const float f = fast_exp2(x[s].x - ref);
-            sum += f * x[s].y;
-            val += f * o[s];
-        }
-        const int64_t out_e = (int64_t)seq * a.H * D + hg * ELEMS + e;
-        if (nchunks == 1) {
-            if (mine) store_out1(a.out, a.out_dtype, out_e, val / sum);
-        } else {
-            const int64_t stride = (int64_t)a.H;
-            const int64_t p0 = first * stride + hg * GH + eh;  // the context's first piece, this head
-            if (mine) {
-                const int64_t pi = p0 + chunk * stride;
-                put_partial1(a.part_acc + pi * D + (e - eh * D), val);
-                if (e - eh * D == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){mx, sum});
+            for (int s = 0; s < N; s++) {
+                x[s] = comb_ml[s][e / D];
+                o[s] = comb[s][e];
             }
+#pragma unroll
+            for (int s = 0; s < N; s++) top = fmaxf(top, x[s].x);
+            const float ref = exp_reference(top);
+            sum = val = 0.f;
+#pragma unroll
+            for (int s = 0; s < N; s++) {
+                const float f = fast_exp2(x[s].x - ref);
+                sum += f * x[s].y;
+                val += f * o[s];
+            }
+        };
+        const int64_t p0 = (int64_t)first * a.H + hg * GH;  // the context's first piece, this group's first head
+#pragma unroll
+        for (int k = 0; k < EPT; k++) {
+            const int e = ELEMS % 512 == 0 ? tid + 512 * k : min(tid, ELEMS - 1);
+            float top, sum, val;
+            combine(std::integral_constant<int, NW>(), e, top, sum, val);
+            if (e / D < heads && (ELEMS % 512 == 0 || tid < ELEMS)) {
+                if (nchunks == 1) {
+                    store_out1(a.out, a.out_dtype, out0 + e, val / sum);
+                } else {
+                    const int64_t pi = p0 + (int64_t)chunk * a.H + e / D;
+                    put_partial1(a.part_acc + pi * D + e % D, val);
+                    if (e % D == 0) put_partial2<true>((float *)a.part_ml + 2 * pi, (f32x2){top, sum});
+                }
+            }
+        }
+        if (nchunks > 1) {
             if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wave's stores are at the memory side ...
             __syncthreads();                                             // ... and all the others', before one of them counts
@@ -286,29 +361,28 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
             if (last_here) {
                 if (a.merge_sync) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 asm volatile("" ::: "memory");
-                // Two waves take every fourth piece, a thread four elements of it; the four sums meet in LDS.
-                constexpr int QUADS = ELEMS / 4;
-                const int q = min(tid & 127, QUADS - 1), qh = 4 * q / D, part = wave >> 1;
+                // A thread takes four elements of every PARTS-th piece (two waves a piece, KV8 four); the sums meet in LDS.
+                constexpr int QUADS = ELEMS / 4, WIDTH = QUADS <= 128 ? 128 : 256, PARTS = 512 / WIDTH;
+                const int q = min(tid & (WIDTH - 1), QUADS - 1), qh = 4 * q / D, part = __builtin_amdgcn_readfirstlane(tid / WIDTH);
                 const unsigned sml = (unsigned)a.H * 8, sacc = (unsigned)a.H * D * 4;
-                const float *pml = (const float *)a.part_ml + 2 * (first * stride + hg * GH), *pacc = a.part_acc + (first * stride + hg * GH) * D;
-                const int heads = min(GH, a.H - hg * GH);
+                const float *pml = (const float *)a.part_ml + 2 * p0, *pacc = a.part_acc + p0 * D;
                 float mm = -INFINITY, ll = 0.f;
                 f32x4 oo = (f32x4){0.f, 0.f, 0.f, 0.f};
-                auto pieces = [&](int c, auto np) {  // pieces c + part, c + part + 4, ..., one memory round trip
+                auto pieces = [&](int c, auto np) {  // pieces c + part, c + part + PARTS, ..., one memory round trip
                     constexpr int NP = decltype(np)::value;
-                    const int left = min(nchunks - c, 4 * NP);
+                    const int left = min(nchunks - c, PARTS * NP);
                     const __amdgpu_buffer_rsrc_t mls = piece_buffer(pml + (int64_t)c * a.H * 2, (left - 1) * sml + heads * 8);
                     const __amdgpu_buffer_rsrc_t accs = piece_buffer(pacc + (int64_t)c * a.H * D, (left - 1) * sacc + heads * D * 4);
                     f32x2 mv[NP];
                     f32x4 av[NP];
 #pragma unroll
-                    for (int u = 0; u < NP; u++) mv[u] = piece_load2(mls, (part + 4 * u) * sml + 8 * qh);
+                    for (int u = 0; u < NP; u++) mv[u] = piece_load2(mls, (part + PARTS * u) * sml + 8 * qh);
 #pragma unroll
-                    for (int u = 0; u < NP; u++) av[u] = piece_load4(accs, (part + 4 * u) * sacc + 16 * q);
+                    for (int u = 0; u < NP; u++) av[u] = piece_load4(accs, (part + PARTS * u) * sacc + 16 * q);
                     float mn = mm;
 #pragma unroll
                     for (int u = 0; u < NP; u++) {
-                        mv[u][0] = part + 4 * u < left ? mv[u][0] : -INFINITY;
+                        mv[u][0] = part + PARTS * u < left ? mv[u][0] : -INFINITY;
                         mn = fmaxf(mn, mv[u][0]);
                     }
                     const float r = exp_reference(mn), al = fast_exp2(mm - r);
@@ -322,32 +396,23 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
                     }
                     mm = mn;
                 };
-                if (nchunks <= 16) pieces(0, std::integral_constant<int, 4>());
+                if (nchunks <= 16) pieces(0, std::integral_constant<int, 16 / PARTS>());
                 else
 #pragma unroll 1
-                    for (int c = 0; c < nchunks; c += 32) pieces(c, std::integral_constant<int, 8>());
+                    for (int c = 0; c < nchunks; c += 8 * PARTS) pieces(c, std::integral_constant<int, 8>());
                 // (the shares in comb have been read: two barriers ago)
-                if ((tid & 127) < QUADS) {
+                if ((tid & (WIDTH - 1)) < QUADS) {
                     *(f32x4 *)&comb[part][4 * q] = oo;
                     if ((4 * q) % D == 0) comb_ml[part][qh] = make_float2(mm, ll);
                 }
                 __syncthreads();
-                float top = -INFINITY;
-                float2 y[4];
 #pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    y[k] = comb_ml[k][eh];
-                    top = fmaxf(top, y[k].x);
+                for (int k = 0; k < EPT; k++) {
+                    const int e = ELEMS % 512 == 0 ? tid + 512 * k : min(tid, ELEMS - 1);
+                    float top, sum, val;
+                    combine(std::integral_constant<int, PARTS>(), e, top, sum, val);
+                    if (e / D < heads && (ELEMS % 512 == 0 || tid < ELEMS)) store_out1(a.out, a.out_dtype, out0 + e, val / sum);
                 }
-                const float r = exp_reference(top);
-                sum = val = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const float f = fast_exp2(y[k].x - r);
-                    sum += f * y[k].y;
-                    val += f * comb[k][e];
-                }
-                if (mine) store_out1(a.out, a.out_dtype, out_e, val / sum);
             }
         }
     }

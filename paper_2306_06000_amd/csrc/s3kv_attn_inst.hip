@@ -18,8 +18,14 @@ attn_fn S3_CAT(s3i_pick_mha_d, S3_INST_D)(int dt, int variant) {
     return nullptr;
 }
 
-attn_fn S3_CAT(s3i_pick_few_d, S3_INST_D)(int dt) {
-    return dt == S3_F16 ? (attn_fn)attn_few_kernel<S3_F16, S3_INST_D> : dt == S3_BF16 ? (attn_fn)attn_few_kernel<S3_BF16, S3_INST_D> : nullptr;
+// Few contexts; act: the type of q (and of the rows, unless they are e4m3: kv8).
+attn_fn S3_CAT(s3i_pick_few_d, S3_INST_D)(int act, bool kv8) {
+    if (act != S3_F16 && act != S3_BF16) return nullptr;
+#if S3_INST_D != 96
+    if (kv8) return act == S3_F16 ? (attn_fn)attn_few_kernel<S3_F16, S3_INST_D, true> : (attn_fn)attn_few_kernel<S3_BF16, S3_INST_D, true>;
+#endif
+    if (kv8) return nullptr;
+    return act == S3_F16 ? (attn_fn)attn_few_kernel<S3_F16, S3_INST_D> : (attn_fn)attn_few_kernel<S3_BF16, S3_INST_D>;
 }
 
 attn_fn S3_CAT(s3i_pick_merge_d, S3_INST_D)() { return (attn_fn)attn_merge_kernel<S3_INST_D>; }

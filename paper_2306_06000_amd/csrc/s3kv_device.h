@@ -230,6 +230,18 @@ __device__ __forceinline__ u32x4 quantize16(const u32x4 lo, const u32x4 hi) {
     return out;
 }
 
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+
+// e4m3 codes -> fp32, exact, four codes of one 32-bit word (v_cvt_pk_f32_fp8 reads this format on gfx950).
+__device__ __forceinline__ void widen4_e4m3(const unsigned w, float (&f)[4]) {
+    const f32x2v lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
+    const f32x2v hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
+    f[0] = lo[0];
+    f[1] = lo[1];
+    f[2] = hi[0];
+    f[3] = hi[1];
+}
+
 template <bool NT>
 __device__ __forceinline__ u32x4 load16(const char *p) {
     return NT ? __builtin_nontemporal_load((const u32x4 *)p) : *(const u32x4 *)p;

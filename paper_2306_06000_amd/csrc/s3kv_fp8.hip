@@ -13,18 +13,6 @@
 // decode step the kernel quantises and appends the new row itself: one launch per step.
 #include "s3kv_device.h"
 
-typedef float f32x2v __attribute__((ext_vector_type(2)));
-
-// e4m3 codes -> fp32, exact, four codes of one 32-bit word (v_cvt_pk_f32_fp8 reads this format on gfx950).
-__device__ __forceinline__ void widen4_e4m3(const unsigned w, float (&f)[4]) {
-    const f32x2v lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
-    const f32x2v hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
-    f[0] = lo[0];
-    f[1] = lo[1];
-    f[2] = hi[0];
-    f[3] = hi[1];
-}
-
 // grid (n, 2): block (b, which) quantises one new row of H*D 16-bit elements into row off+pos.
 template <int ACT>
 __global__ void __launch_bounds__(256) append_fp8_kernel(char *kplane, char *vplane, const int64_t *slot_off,

@@ -289,10 +289,10 @@ attn_fn s3i_pick_mha_d64(int dt, int variant);
 attn_fn s3i_pick_mha_d96(int dt, int variant);
 attn_fn s3i_pick_mha_d128(int dt, int variant);
 attn_fn s3i_pick_mha_d256(int dt, int variant);
-attn_fn s3i_pick_few_d64(int dt);
-attn_fn s3i_pick_few_d96(int dt);
-attn_fn s3i_pick_few_d128(int dt);
-attn_fn s3i_pick_few_d256(int dt);
+attn_fn s3i_pick_few_d64(int act, bool kv8);
+attn_fn s3i_pick_few_d96(int act, bool kv8);
+attn_fn s3i_pick_few_d128(int act, bool kv8);
+attn_fn s3i_pick_few_d256(int act, bool kv8);
 attn_fn s3i_pick_merge_d64();
 attn_fn s3i_pick_merge_d96();
 attn_fn s3i_pick_merge_d128();
@@ -319,9 +319,9 @@ static attn_fn pick_merge(int d) {
                                                                                        : s3i_pick_merge_d256();
 }
 
-static attn_fn pick_few(int dt, int d) {
-    return d == 64 ? s3i_pick_few_d64(dt) : d == 96 ? s3i_pick_few_d96(dt) : d == 128 ? s3i_pick_few_d128(dt)
-                                                                                      : d == 256 ? s3i_pick_few_d256(dt) : nullptr;
+static attn_fn pick_few(int act, int d, bool kv8) {
+    return d == 64 ? s3i_pick_few_d64(act, kv8) : d == 96 ? s3i_pick_few_d96(act, kv8) : d == 128 ? s3i_pick_few_d128(act, kv8)
+                                                                                       : d == 256 ? s3i_pick_few_d256(act, kv8) : nullptr;
 }
 
 // Heads that one 128-bit wave load of 16-bit elements covers: 512/D, except that a 96-wide head takes a
@@ -698,13 +698,18 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // (unit_rule), and from 4/3 to 7/4 whole contexts (whole_rule), if contexts can be long enough at all.  Batches that the rules
 // leave alone pay 0.2 to 1.0 us for the look (half of them less than 0.6), which is why they are not asked in between, where only few gain.
 //
-// Multi-head 16-bit rows, nothing set by the caller: attn_few_kernel serves batches of up to 3/4 of an item a compute unit
-// (and 64 contexts, a lane each), in up to 2 * cus / n_hg chunks.  Beyond, whole contexts fill most of the chip and the
-// streaming kernel's balance is as good or better: 16 x 256, 26 contexts of 500..1500 rows 87.6 us a layer, 75.7 here, but 40
-// of 32..1000 60.8, 63.8, 48 70.4, 83.5, 64 x 96, 18 of 20..200 12.8, 14.9.
+// Multi-head rows, nothing set by the caller: attn_few_kernel serves batches of up to 3/4 of an item a compute unit, 8-bit rows
+// 4/5 (and 64 contexts, a lane each), in up to 2 * cus / n_hg chunks.  Beyond, whole contexts fill most of the chip and the
+// streaming kernels' balance is as good or better.  us a layer, streaming kernel and this one: 16-bit, 16 x 256, 24 contexts
+// (the last) of 20..200 rows 14.8, 12.2, of 500..1500 73.7, 68.5, of 32..1000 37.6, 37.5; 26 (beyond) of 500..1500 87.6, 75.7,
+// but 40 of 32..1000 60.8, 63.8, 48 70.4, 83.5; 64 x 96, 18 of 20..200 12.8, 14.9.  e4m3, 16 x 256, 50 of 20..100 13.2, 10.2, of
+// 300..600 38.6, 37.3, of 1000..2000 105.7, 107.1; 64 (beyond) of 20..100 13.8, 10.6, but of 32..1000 53.3, 56.8.  Rows of fewer 8-bit
+// heads than a wave load takes, and that divide it, several to a load, stay with attn_fp8_kernel.
 static bool on_few_kernel(const s3_arena *a, int n, int n_hg) {
-    const int64_t cus = a->num_cus > 0 ? a->num_cus : 256;
-    return s3i_kernel_kind(a) == 0 && a->chunk <= 0 && a->variant < 0 && n <= 64 && (int64_t)n * n_hg <= cus * 3 / 4;
+    const int64_t cus = a->num_cus > 0 ? a->num_cus : 256, items = (int64_t)n * n_hg;
+    const int kind = s3i_kernel_kind(a), loads = 1024 / a->cfg.head_dim;  // (8-bit rows: heads a wave load)
+    if (a->chunk > 0 || a->variant >= 0 || n > 64) return false;
+    return kind == 0 ? items <= cus * 3 / 4 : kind == 3 && (a->cfg.n_heads >= loads || loads % a->cfg.n_heads != 0) && items <= cus * 4 / 5;
 }
 static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes, int32_t *few, int32_t *units) {
     const int chunk = a->chunk > 0 ? a->chunk : 1024;
@@ -914,6 +919,17 @@ static int launch_gqa(s3_arena *a, const AttnCall &c) {
     return launch_attn_kernels(a, fn, blocks, threads, dyn_lds, c.stream, args, Hq, !c.static_scratch);
 }
 
+static int launch_few(s3_arena *a, AttnArgs &args, int n_hg, bool kv8, const AttnCall &c) {
+    const int cus = a->num_cus > 0 ? a->num_cus : 256;
+    attn_fn fn = pick_few(a->cfg.act_dtype, a->cfg.head_dim, kv8);
+    if (!fn) return S3_ERR_INVALID;
+    args.few_chunks = cus / n_hg;
+    args.unit_chunks = 2 * cus / n_hg;
+    args.columns = n_hg;
+    args.column_shift = (n_hg & (n_hg - 1)) == 0 ? __builtin_ctz((unsigned)n_hg) : -1;
+    return launch_attn_kernels(a, fn, args.unit_chunks * n_hg, 512, 0, c.stream, args, 0, !c.static_scratch);
+}
+
 // Scratch of a kernel whose chunks meet inside the launch.
 static int place_chunk_scratch(s3_arena *a, AttnArgs &args, int n_hg, const AttnCall &c) {
     const size_t slot_bytes = (size_t)args.Hq * ((size_t)a->cfg.head_dim * sizeof(float) + sizeof(float2));
@@ -932,6 +948,7 @@ static int launch_fp8(s3_arena *a, const AttnCall &c) {
     const int n_hg = (H + 1024 / D - 1) / (1024 / D);  // head groups: 1024/D heads per 128-bit wave load of bytes
     int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
+    if (on_few_kernel(a, c.n, n_hg)) return launch_few(a, args, n_hg, true, c);
     const size_t dyn_lds = batch_view_lds(c.n, args.ncls);
     int blocks = 0;
     rc = stride_grid(a, (const void *)fn, threads, dyn_lds, c.n > 128 ? 2 : 1, &blocks);
@@ -969,14 +986,7 @@ static int launch_attention(s3_arena *a, const AttnCall &c) {
     }
     int rc = place_chunk_scratch(a, args, n_hg, c);
     if (rc != S3_OK) return rc;
-    if (on_few_kernel(a, c.n, n_hg)) {
-        const int cus = a->num_cus > 0 ? a->num_cus : 256;
-        args.few_chunks = cus / n_hg;
-        args.unit_chunks = 2 * cus / n_hg;
-        args.columns = n_hg;
-        args.column_shift = (n_hg & (n_hg - 1)) == 0 ? __builtin_ctz((unsigned)n_hg) : -1;
-        return launch_attn_kernels(a, pick_few(a->cfg.kv_dtype, D), args.unit_chunks * n_hg, 512, 0, c.stream, args, 0, !c.static_scratch);
-    }
+    if (on_few_kernel(a, c.n, n_hg)) return launch_few(a, args, n_hg, false, c);
     if (args.unit_chunks > 0) fn = pick_kernel(a->cfg.kv_dtype, D, S3_UNIT_VARIANT);
     const int threads = s3i_variant_threads(variant);
     const size_t view = batch_view_lds(c.n, args.ncls);

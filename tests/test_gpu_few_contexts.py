@@ -170,18 +170,20 @@ def test_longer_chunks_sum_no_longer_runs(H, D, kvt, n):
     assert off[0] <= 1.03 * off[1], off  # (the division of the rows differs, and with it every rounding: 1 % either way)
 
 
-FEW = [FAMS[0], FAMS[1], FAMS[2], ("3 x 128", 3, 3, 128, s3.S3_BF16, s3.S3_BF16, 0), ("16 x 64", 16, 16, 64, s3.S3_F16, s3.S3_F16, 0)]
+FEW = [FAMS[0], FAMS[1], FAMS[2], ("3 x 128", 3, 3, 128, s3.S3_BF16, s3.S3_BF16, 0), ("16 x 64", 16, 16, 64, s3.S3_F16, s3.S3_F16, 0),
+       FAMS[4], FAMS[5], ("17 x 64 e4m3", 17, 17, 64, s3.S3_E4M3, s3.S3_BF16, 3), ("4 x 128 e4m3", 4, 4, 128, s3.S3_E4M3, s3.S3_F16, 3)]
 
 
 @pytest.mark.parametrize("fam", FEW, ids=[f[0] for f in FEW])
 def test_few_contexts_shares_and_pieces(fam):
-    """The kernel of few contexts at the edges of what a wave takes (a row, fours of them, twelve, thirteen, runs of 128) and of
-    what a merge takes (16 pieces a round trip, 32, more), with the new row first, inside and last in a four; the largest batches
-    of it and the first beyond; empty contexts between.  Attention against the oracle; the step bit for bit against attention over the
-    appended rows, through both of its entry points and with both orderings of the merge."""
+    """The kernel of few contexts at the edges of what a wave takes (a row, fours of them, twelve, thirteen, runs of 128; 8-bit
+    rows: threes, six, seven) and of what a merge takes (16 pieces a round trip, 32, more), with the new row first, inside and last in a
+    four; the largest batches of it and the first beyond; empty contexts between; head groups that are not full, and rows that go several to a
+    load (the streaming kernel's).  Attention and step against the oracle; the step bit for bit the same through both of its entry points and
+    with both orderings of the merge, and, 16-bit rows, as attention over the appended rows (8-bit rows take the new row last)."""
     name, H, Hkv, D, kvt, act, kind = fam
-    n_hg = -(-H // (4 if D == 96 else 512 // D))
-    last = min(64, 192 // n_hg)
+    n_hg = -(-H // (1024 // D if kind == 3 else 4 if D == 96 else 512 // D))
+    last = min(64, (204 if kind == 3 else 192) // n_hg)
     rng = np.random.default_rng(7 * D + H)
     top = 8192
     rows = rng.standard_normal((top + 130, Hkv, D), dtype=np.float32)
@@ -199,8 +201,11 @@ def test_few_contexts_shares_and_pieces(fam):
         qb, step = rig.step(q, k_new, v_new)
         longer = [L + 1 for L in lens]
         assert_close(step, rig.want(qb, longer), f"{name} / {lens[:4]} x {n} / step")
-        assert np.array_equal(rig.attend(q, lens=longer)[1], step), lens
+        again = rig.attend(q, lens=longer)[1]
+        if kind == 0:
+            assert np.array_equal(again, step), lens
+        assert_close(again, rig.want(qb, longer), f"{name} / {lens[:4]} x {n} / appended")
         assert np.array_equal(static_step(rig, q, k_new, v_new), step), lens
         assert s3.s3_kv_set_param(rig.a, "merge_sync", 1) == 0
-        assert np.array_equal(rig.attend(q, lens=longer)[1], step), lens
+        assert np.array_equal(rig.attend(q, lens=longer)[1], again), lens
         rig.close()
