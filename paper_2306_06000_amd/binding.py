@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libs3kv.so: same names as the C ABI, argument marshalling only.
+"""Thin ctypes binding of libs3kv.so: same names as the C ABI, argument marshalling only (that of the per-layer calls in C,
+csrc/s3kv_pycall.cpp, for the argument types a decode loop passes).
 
 Device arrays are passed as torch tensors (their ``data_ptr()`` is used) or raw integer
 addresses; host arrays as numpy arrays / sequences.  Nothing here computes: every step of
@@ -7,6 +8,7 @@ the hot path runs inside the library's kernels.  The library must have been buil
 loudly otherwise - there is no fallback.
 """
 import ctypes
+import importlib.util
 import os
 
 import numpy as np
@@ -18,6 +20,7 @@ S3_STATIC_SCRATCH_BYTES = 32 << 20
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("S3KV_LIB") or os.path.join(_HERE, "libs3kv.so")  # S3KV_LIB: a diagnostic build
 _lib = None
+_call = None  # the extension module of the per-layer calls, connected to the loaded library
 
 
 class s3_kv_config(ctypes.Structure):
@@ -83,6 +86,22 @@ def lib():
             fn.restype, fn.argtypes = res, args
         _lib = handle
     return _lib
+
+
+def _connect():
+    """The call path of the per-layer functions.  Raises if it has not been built."""
+    global _call
+    handle = lib()
+    path = os.path.join(_HERE, "_s3call.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is missing: build it with `python -m paper_2306_06000_amd.build`")
+    spec = importlib.util.spec_from_file_location("_s3call", path)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.connect(*[ctypes.cast(getattr(handle, f), ctypes.c_void_p).value
+                     for f in ("s3_decode_step", "s3_decode_step_static", "s3_kv_append", "s3_decode_attention", "s3_kv_fill_batch")])
+    _call = module
+    return module
 
 
 def _ptr(x):
@@ -166,6 +185,10 @@ def s3_kv_slot_info(arena, slot_id):
 
 
 def s3_kv_append(arena, layer, n, slot_off, pos, k_new, v_new, stream=0, slot_id=None, pos_host=None):
+    if slot_id is None and pos_host is None:
+        st = (_call or _connect()).append(arena, layer, n, slot_off, pos, k_new, v_new, stream)
+        if st is not None:
+            return st
     _a, idp = _host_i32(slot_id)
     _b, php = _host_i32(pos_host)
     return lib().s3_kv_append(arena, int(layer), int(n), idp, php, _ptr(slot_off), _ptr(pos), _ptr(k_new),
@@ -173,12 +196,19 @@ def s3_kv_append(arena, layer, n, slot_off, pos, k_new, v_new, stream=0, slot_id
 
 
 def s3_decode_attention(arena, layer, n, q, slot_off, cur_len, out, out_dtype=S3_F32, scale=0.0, stream=0):
+    st = (_call or _connect()).attention(arena, layer, n, q, slot_off, cur_len, out, out_dtype, scale, stream)
+    if st is not None:
+        return st
     return lib().s3_decode_attention(arena, int(layer), int(n), _ptr(q), _ptr(slot_off), _ptr(cur_len), _ptr(out),
                                      int(out_dtype), float(scale), stream or None)
 
 
 def s3_decode_step(arena, layer, n, slot_off, pos, q, k_new, v_new, out, out_dtype=S3_F32, scale=0.0, len_out=None,
                    stream=0, slot_id=None, pos_host=None):
+    if slot_id is None and pos_host is None:
+        st = (_call or _connect()).step(arena, layer, n, slot_off, pos, q, k_new, v_new, out, out_dtype, scale, len_out, stream)
+        if st is not None:
+            return st
     _a, idp = _host_i32(slot_id)
     _b, php = _host_i32(pos_host)
     return lib().s3_decode_step(arena, int(layer), int(n), idp, php, _ptr(slot_off), _ptr(pos), _ptr(q), _ptr(k_new),
@@ -188,6 +218,10 @@ def s3_decode_step(arena, layer, n, slot_off, pos, q, k_new, v_new, out, out_dty
 def s3_decode_step_static(arena, layer, n, slot_off, pos, q, k_new, v_new, out, out_dtype=S3_F32, scale=0.0, len_out=None,
                           stream=0, slot_id=None, pos_host=None):
     """s3_decode_step for callers that cannot allocate: the library's fixed device scratch is used."""
+    if slot_id is None and pos_host is None:
+        st = (_call or _connect()).step_static(arena, layer, n, slot_off, pos, q, k_new, v_new, out, out_dtype, scale, len_out, stream)
+        if st is not None:
+            return st
     _a, idp = _host_i32(slot_id)
     _b, php = _host_i32(pos_host)
     return lib().s3_decode_step_static(arena, int(layer), int(n), idp, php, _ptr(slot_off), _ptr(pos), _ptr(q),
@@ -287,6 +321,10 @@ def s3_kv_fill(arena, slot_id, layer, first_row, n_rows, k_rows, v_rows, stream=
 def s3_kv_fill_batch(arena, layer, slot_ids, n_rows, k_rows, v_rows, stream=0, slot_off=None, length=None, batch_n=0,
                      batch_idx=None):
     """k_rows / v_rows: sequences of device tensors (or addresses), one per newcomer."""
+    if slot_off is None and length is None and batch_idx is None and batch_n == 0:
+        st = (_call or _connect()).fill(arena, layer, slot_ids, n_rows, k_rows, v_rows, stream)
+        if st is not None:
+            return st
     s_arr, sp = _host_i32(slot_ids)
     r_arr, rp = _host_i32(n_rows)
     n = int(s_arr.size)

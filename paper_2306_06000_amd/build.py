@@ -1,11 +1,13 @@
 """Compile libs3kv.so (HIP kernels + host bookkeeping) for gfx950, in-tree."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libs3kv.so")
+CALL_SRC, CALL_LIB = os.path.join(CSRC, "s3kv_pycall.cpp"), os.path.join(HERE, "_s3call.so")  # the binding's call path
 # (source, extra defines, object name); the multi-head attention kernels are one object per head dimension
 HEAD_DIMS = (64, 96, 128, 256)
 UNITS = [("s3kv_attn_inst.hip", [f"-DS3_INST_D={d}"], f"s3kv_attn_d{d}.o") for d in HEAD_DIMS] + [
@@ -27,7 +29,8 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
 
     srcs = sorted({os.path.join(CSRC, u[0]) for u in UNITS})
     deps = srcs + [os.path.join(CSRC, h) for h in HEADERS] + [os.path.join(ROOT, "include", "s3kv.h")]
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
+    built = os.path.exists(LIB) and os.path.exists(CALL_LIB) and os.path.getmtime(CALL_LIB) >= os.path.getmtime(CALL_SRC)
+    if not force and built and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
         return LIB
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
@@ -50,6 +53,9 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
         if verbose and out.strip():
             print(out, flush=True)
 
+    run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], CALL_SRC,
+         "-o", CALL_LIB + ".tmp"])
+    os.replace(CALL_LIB + ".tmp", CALL_LIB)
     objs = [os.path.join(objdir, u[2]) for u in UNITS]
     with ThreadPoolExecutor(max_workers=min(len(UNITS), int(os.environ.get("MAX_JOBS", "8")))) as pool:
         list(pool.map(lambda u: run([_hipcc()] + flags + u[1] + ["-c", "-x", "hip", os.path.join(CSRC, u[0]), "-o",
