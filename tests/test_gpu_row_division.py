@@ -195,3 +195,26 @@ def test_eight_waves_a_workgroup_and_the_borders_of_their_rule(fam):
         assert_close(step, rig.want(qb, longer), f"{name} / {what} / step")
         assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
         rig.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H", [7, 8, 9, 16, 20])
+@pytest.mark.parametrize("kvt,kind", [(s3.S3_F16, 2), (s3.S3_E4M3, 4)], ids=["f16", "e4m3"])
+def test_eight_waves_combine_one_or_two_quads_a_thread(H, kvt, kind):
+    """Eight waves' parts of a chunk, rows of 256: one quad of elements a thread up to eight query heads, two of one head
+    beyond (20: a column of sixteen and one of four); contexts of one chunk, that are stored, and of several, that merge."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    for lens in ([17, 130, 1, 0, 350], [2000, 40]):
+        rng = np.random.default_rng(len(lens) + H)
+        rig = EdgeRig(("quads", H, 1, 256, kvt, s3.S3_F16, kind), lens, M=2048)
+        rig.put([rng.standard_normal((L, 1, 256), dtype=np.float32) for L in lens],
+                [rng.standard_normal((L, 1, 256), dtype=np.float32) for L in lens])
+        q = rng.standard_normal((len(lens), H, 256), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{H} heads, {lens}")
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, *(rng.standard_normal((len(lens), 1, 256), dtype=np.float32) for _ in range(2)))
+        assert_close(step, rig.want(qb, longer), f"{H} heads, {lens} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step)
+        rig.close()
