@@ -247,8 +247,8 @@ __device__ __forceinline__ u32x4 load16(const char *p) {
     return NT ? __builtin_nontemporal_load((const u32x4 *)p) : *(const u32x4 *)p;
 }
 
-// Quotients of whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here all out
-// of a cold instruction cache).  x / y rounded down, exact for x below 2^24: the product is off by less than one, which the
+// Quotients of whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here on
+// the way to a launch's first load).  x / y rounded down, exact for x below 2^24: the product is off by less than one, which the
 // remainder puts right.  And a whole number not below x / y, by less than 2 above it where x / y is below 2^19.
 __device__ __forceinline__ int quotient(int x, int y) {
     const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y)), r = x - q * y;
@@ -308,7 +308,7 @@ __device__ __forceinline__ int wave_max_nonneg(int v) {
 }
 
 // Rows per chunk of a batch of few contexts (total and longest: their rows).  Two bounds.  (1) `few_chunks` chunks in
-// all, so that every compute unit has an item and none has two (the host says how many, see few_chunks_for).
+// all, so that every compute unit has an item and none has two (the host says how many: chunk_slots).
 // (2) A context's chunks are merged by one wave, a few per memory round trip, while a chunk's rows stream side by
 // side: a chunk of c rows costs about c / 10 of what merging one more chunk costs, so no finer than sqrt(10 * longest).
 // One context, 16 heads x 256 fp16, four layers, best chunk of a sweep: 410 rows 64 (36.6 us; whole 72.1), 1417 rows
@@ -335,7 +335,8 @@ __device__ __forceinline__ int unit_chunk_rows(const AttnArgs &a, int units, int
 // batch beyond the few contexts gets.  chunks: how many those would be; rows, longest: all rows, and those of the longest
 // context.  Two kinds of batch gain:
 // (1) few contexts whose chunks turn out more than the compute units (contexts do not divide evenly), so that some units get
-// two and the launch lasts as long as those: by more than an eighth at 400 rows a context, by any number at 1000.
+// two and the launch lasts as long as those: by more than an eighth at 400 rows a context, by any number at 1000.  (Up to 64
+// such contexts are attn_few_kernel's since; what comes here are 65 and more of one or two head groups.)
 // (2) beyond the few, a longest chunk that outlasts the rest: u items a compute unit (2 * n / units) of r rows on average take
 // the time of u * r rows, a single one streams about twice as fast once the others are done, and the finer division costs as
 // much again where it shares out little: the line, measured, is longest / r = 2 * u^2, and 1.6.
@@ -540,7 +541,7 @@ __device__ __forceinline__ int chunk_prefix(int n, const int *len, int rows, int
 }
 
 // A view with one length class in chunks (tiles) of CHUNK rows; `longest` receives the rows of the longest context.  Kept
-// small: it runs once, out of a cold instruction cache.
+// small: every wave runs it before its first load.
 template <int CHUNK>
 __device__ __forceinline__ BatchView build_tile_view(const AttnArgs &a, char *dyn, int *wave_sums, int &longest) {
     int64_t *off_s = (int64_t *)dyn;

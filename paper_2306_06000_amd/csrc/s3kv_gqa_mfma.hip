@@ -157,7 +157,7 @@ __device__ __forceinline__ void transpose4x4_bytes(const unsigned w0, const unsi
 // lengths do not force: a context of one chunk is finished by its wave or team.  (The figures of few contexts were taken before
 // workgroups of eight took the launches of no more pairs than compute units.)  What bounds such a launch is a chain of
 // latencies (view and plan 2.5 us, rows a tile a microsecond and wave, the team's meeting in LDS 1, write-through and count
-// 1, merge 2 to 3) and, throughout, code that runs once out of a cold instruction cache.  A layer in microseconds, shares
+// 1, merge 2 to 3) and, throughout, instructions that run once.  A layer in microseconds, shares
 // across contexts or chunks by one wave -> this rule: 32q/8kv x 128, 3 contexts of 512..8192 rows 18.9 -> 16.2, 8 of
 // 32..2000 18.9 -> 15.3, 19 of 70..84 9.7 -> 8.1; 12q/2kv x 128, 17 of 1200..1455 19.8 -> 15.8; 16q/1kv x 256, 3 of
 // 700..924 25.0 -> 16.9, 30 of 32..1000 29.0 -> 18.1, 100 30.8 -> 22.8; 64q/8kv x 128 e4m3, 22 of 2000..4793 44.6 -> 41.7,
@@ -400,8 +400,7 @@ __device__ __forceinline__ void pieces_of(const SharePlan &sp, int t0, int t1, i
 // Merge the pieces of query heads hq0 .. hq0+nh-1 of a context and store the final rows; by a wave (nthr 64) or by
 // the four or eight (EIGHT) waves of a workgroup in step (nthr 256, 512).  Four waves with at least a thread per quad of elements
 // take one quad a thread and deals the pieces over what threads are spare, which meet in LDS (6 floats per thread).
-// Kept small: all of this runs once per launch and wave, i.e. out of a cold instruction cache (unrolled for every
-// shape, with the code around it, the kernel was 136 KB and a merge of four pieces took 3 us).
+// Kept small: unrolled for every shape, with the code around it, the kernel was 136 KB and a merge of four pieces took 3 us.
 template <int D, bool EIGHT>
 __device__ __forceinline__ void merge_pieces(const AttnArgs &a, const Pending &p, int hq0, int nh, int tid, int nthr, float *lds) {
     const int64_t row0 = ((int64_t)p.first + p.b) * a.Hq + hq0;

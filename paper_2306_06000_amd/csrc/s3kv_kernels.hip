@@ -685,7 +685,8 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // (the lengths are on the device, so the rows per chunk are chosen there: few_chunk_rows).  Returns the partial slots.
 // n_hg: head groups, i.e. work items per chunk.  3/4 of an item per compute unit while the contexts themselves are
 // fewer than that (pieces do not divide evenly: with a full item per unit some unit would get two); beyond, whole
-// contexts are items enough.  Chunk fixed at 1024 -> this rule, 16 heads x 256 fp16, four layers: one context of 410
+// contexts are items enough.  (Up to 64 such contexts are attn_few_kernel's since, if the caller sets neither chunk nor
+// variant; these figures are the streaming kernels'.)  Chunk fixed at 1024 -> this rule, 16 heads x 256 fp16, four layers: one context of 410
 // rows 74 -> 36 us, of 8050 rows 181 -> 112; 4 contexts of 500..1500 rows 129 -> 68, 8: 143 -> 102, 16: 207 -> 189;
 // 32 contexts of 32..1000 rows: 212, and 217 if the line were drawn above them.
 // As with s3i_gqa_max_shares, what the fixed buffer takes by its documented rule is held to its size.
