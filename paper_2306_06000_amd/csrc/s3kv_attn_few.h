@@ -126,7 +126,7 @@ struct FewRows {
     }
 };
 
-// Two workgroups a compute unit (128 registers).  A share beyond twelve rows is walked with two sets of two rows, alternately
+// Two workgroups a compute unit (128 registers).  A share beyond sixteen (twelve) rows is walked with two sets of two rows, alternately
 // (three at 96 elements a head, whose loads bring 12 of 16 bytes): four or eight a set, which leave room for one workgroup
 // only, read level where latencies bound the launch and 5 to 20 % slower where the memory rate does (16 x 256, 8 contexts of
 // 500..1500 rows: 24.7 us with two, 26.4 with four, 30.9 with eight).
@@ -235,20 +235,26 @@ __global__ void __launch_bounds__(512, 4) attn_few_kernel(const AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < EL; i++) acc[i] = 0.f;
         // Up to twelve rows (KV8: six): all of them leave at once, in fours (threes; a load past the share's end costs its issue).
+        // Up to sixteen, 16-bit heads of less than 256: a second turn of four (the loop below takes four turns of memory for them;
+        // us a layer, with it and this way: 12 x 128, 40 contexts of 100..200 rows 12.26, 11.34, 24 of 60..600 12.54, 11.68, 64 x 96, 8
+        // of 50..128 8.85, 8.50, 16 x 64, one of 8000 13.50, 13.02, one of 4000 10.62, 10.78).  With 256 the loop is the better
+        // one: 16 x 256, 9 of 300..400 13.35, 13.71.  So it is beside a second turn of up to eight: 12 x 128, 24 of 300..400 13.92,
+        // 14.40.
         constexpr int FB = KV8 ? 3 : 4;
-        auto few = [&](auto times) {
+        auto few = [&](auto times, int j) {
             constexpr int F = decltype(times)::value;
             u32x4 kf[FB * F], vf[FB * F];
 #pragma unroll
-            for (int f = 0; f < F; f++) st.template load<FB>(FB * f, kf + FB * f, vf + FB * f);
+            for (int f = 0; f < F; f++) st.template load<FB>(j + FB * f, kf + FB * f, vf + FB * f);
 #pragma unroll
-            for (int f = 0; f < F; f++) st.template reduce<FB>(st.rows - FB * f, kf + FB * f, vf + FB * f, m, l, acc);
+            for (int f = 0; f < F; f++) st.template reduce<FB>(st.rows - j - FB * f, kf + FB * f, vf + FB * f, m, l, acc);
         };
         if (st.rows <= 2 * FB) {
-            if (st.rows > FB) few(std::integral_constant<int, 2>());
-            else if (st.rows > 0) few(std::integral_constant<int, 1>());
-        } else if (!KV8 && st.rows <= 3 * FB) {
-            few(std::integral_constant<int, KV8 ? 2 : 3>());
+            if (st.rows > FB) few(std::integral_constant<int, 2>(), 0);
+            else if (st.rows > 0) few(std::integral_constant<int, 1>(), 0);
+        } else if (!KV8 && st.rows <= (D == 256 ? 3 : 4) * FB) {
+            few(std::integral_constant<int, KV8 ? 2 : 3>(), 0);
+            if (D != 256 && st.rows > 3 * FB) few(std::integral_constant<int, 1>(), 3 * FB);
         } else {
             float m1 = -INFINITY, l1 = 0.f, acc1[EL];  // the runs before
 #pragma unroll

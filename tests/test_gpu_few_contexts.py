@@ -209,3 +209,28 @@ def test_few_contexts_shares_and_pieces(fam):
         assert s3.s3_kv_set_param(rig.a, "merge_sync", 1) == 0
         assert np.array_equal(rig.attend(q, lens=longer)[1], again), lens
         rig.close()
+
+
+TURNS = [FAMS[1], ("64 x 96", 64, 64, 96, s3.S3_BF16, s3.S3_BF16, 0), ("16 x 64", 16, 16, 64, s3.S3_F16, s3.S3_F16, 0), FAMS[0]]
+
+
+@pytest.mark.parametrize("fam", TURNS, ids=[f[0] for f in TURNS])
+def test_shares_of_thirteen_to_sixteen_rows(fam):
+    """Whole contexts of 96 to 128 rows, twelve to sixteen a wave: beyond twelve rows a second turn of four (heads of 256: the
+    loop), with the new row at every place of it."""
+    name, H, Hkv, D, kvt, act, kind = fam
+    last = min(64, 192 // -(-H // (4 if D == 96 else 512 // D)))
+    rng = np.random.default_rng(D)
+    rows = rng.standard_normal((200, Hkv, D), dtype=np.float32)
+    for first in range(0, 32, last):
+        lens = [96 + (first + b) % 32 for b in range(last)]
+        rig = EdgeRig(fam, lens, M=256)
+        rig.put([rows[b:b + L] for b, L in enumerate(lens)], [rows[last - b:last - b + L] for b, L in enumerate(lens)])
+        q, k_new, v_new = (rng.standard_normal((last, h, D), dtype=np.float32) for h in (H, Hkv, Hkv))
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / from {lens[0]}")
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, k_new, v_new)
+        assert_close(step, rig.want(qb, longer), f"{name} / from {lens[0]} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step)
+        rig.close()
