@@ -547,7 +547,7 @@ __host__ __device__ constexpr int gqa_tile_rows(int row_bytes) { return row_byte
 // NW: waves of a workgroup, 4 or 8.
 // GQ: 2 or 3, the query heads per cached head where these are so few: the scores on the matrix cores, the weighted rows on the
 // vector ALU with the weights in fp32 (pick_few_heads); 0: both products on the matrix cores.
-// LOOP: there may be more units than waves (teams); else every wave (team) takes one, and nothing is computed, and spilled, in
+// LOOP: there may be more units than waves (teams), see s3i_gqa_units; else every wave (team) takes one, and nothing is computed, and spilled, in
 // front of a loop for units that do not come (137 to 169 scalar registers spilled with it, 58 to 105 without).
 template <int DT, int D, bool KV8, int NW, int GQ = 0, bool LOOP = false>
 __global__ void __launch_bounds__(NW * 64, NW == 8 || D <= 128 ? 2 : 1) attn_gqa_mfma_kernel(const AttnArgs a) {

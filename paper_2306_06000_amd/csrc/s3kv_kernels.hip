@@ -829,6 +829,18 @@ static int launch_attn_kernels(s3_arena *a, attn_fn fn, int blocks, int threads,
     return S3_OK;
 }
 
+// What the matrix-core kernel's workgroups of four, per_cu of them a compute unit, make of a column: at most so many shares (or
+// chunks) by single waves, or by teams of the four waves of a workgroup.  Returns whether these units can be more than run at
+// once, so that the instance with the loop over units is needed: chunks of the caller's size, grids of the caller's, and more
+// columns than workgroups, since a column has at least one unit and a team's unit takes a whole workgroup.
+// (not for callers of the library: a host test reads it)
+extern "C" int32_t s3i_gqa_units(const s3_arena *a, int32_t per_cu, int32_t *wave_shares, int32_t *team_shares) {
+    const int64_t columns = gqa_columns(a), workgroups = (int64_t)(a->num_cus > 0 ? a->num_cus : 256) * per_cu;
+    *wave_shares = (int32_t)(4 * workgroups > columns ? 4 * workgroups / columns : 1);
+    *team_shares = (int32_t)(workgroups > columns ? workgroups / columns : 1);
+    return a->chunk > 0 || a->grid_blocks > 0 || columns > workgroups;
+}
+
 // Shared key/value heads, matrix-core kernel: one launch (with workgroups of four over 8-bit rows an append before it).
 static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
     const int D = a->cfg.head_dim, Hq = a->cfg.n_heads, Hkv = a->cfg.n_kv_heads;
@@ -879,18 +891,19 @@ static int launch_gqa_mfma(s3_arena *a, const AttnCall &c) {
         rc = launch_append(a, c.layer, c.n, c.slot_off, c.len_or_pos, c.k_new, c.v_new, c.stream);
         if (rc != S3_OK) return rc;
     }
-    // Chunks of the caller's size, grids of the caller's, and more columns than waves: units beyond what runs at once.
-    if (a->chunk > 0 || a->grid_blocks > 0 || columns > 4 * cus) fn = pick(false, true);
-    rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
-    if (rc != S3_OK) return rc;
-    if (per_cu > 2) per_cu = 2;
+    bool loop = false;
+    while (true) {
+        rc = resident_per_cu((const void *)fn, 256, dyn_lds, &per_cu);
+        if (rc != S3_OK) return rc;
+        if (per_cu > 2) per_cu = 2;
+        if (!s3i_gqa_units(a, per_cu, &args.wave_shares, &args.team_shares) || loop) break;
+        loop = true;
+        fn = pick(false, true);
+    }
     // What one more piece costs the wave that merges a context, in tiles streamed by one wave: a memory round trip of
     // about two tiles brings two quads of elements a lane of six pieces (D 256: four quads of three).
     const int eb = D == 256 ? 4 : 2, quads = (int)group16 * (D / 4), passes = (quads + 64 * eb - 1) / (64 * eb);
     args.merge_cost = 2.f * passes / (eb == 4 ? 3 : 6);
-    const int64_t waves = (int64_t)cus * per_cu * 4;
-    args.wave_shares = (int32_t)(waves > columns ? waves / columns : 1);
-    args.team_shares = (int32_t)(waves > 4 * columns ? waves / (4 * columns) : 1);
     const int blocks = a->grid_blocks > 0 ? a->grid_blocks : cus * per_cu;
     return launch_attn_kernels(a, fn, blocks, 256, dyn_lds, c.stream, args, 0, !c.static_scratch);
 }

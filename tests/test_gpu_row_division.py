@@ -218,3 +218,27 @@ def test_eight_waves_combine_one_or_two_quads_a_thread(H, kvt, kind):
         assert_close(step, rig.want(qb, longer), f"{H} heads, {lens} / step")
         assert np.array_equal(rig.attend(q, lens=longer)[1], step)
         rig.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,Hkv,D,kvt,act,kind", [(1028, 257, 256, s3.S3_F16, s3.S3_F16, 2), (1280, 320, 256, s3.S3_BF16, s3.S3_BF16, 2), (960, 320, 256, s3.S3_F16, s3.S3_F16, 1),
+                                                  (1200, 300, 256, s3.S3_E4M3, s3.S3_BF16, 4), (2400, 600, 128, s3.S3_BF16, s3.S3_BF16, 2)])
+def test_more_columns_than_workgroups_run_at_once(H, Hkv, D, kvt, act, kind):
+    """A context that a team of four waves takes in each of more columns than there are workgroups: every head's output and every
+    head's new row."""
+    from tests.test_gpu_numeric_edges import EdgeRig
+
+    for lens in ([600], [600, 7, 0, 90]):
+        n = len(lens)
+        rng = np.random.default_rng(Hkv + n)
+        rows = rng.standard_normal((640, Hkv, D), dtype=np.float32)
+        rig = EdgeRig(("columns", H, Hkv, D, kvt, act, kind), lens, M=640)
+        rig.put([rows[b:b + L] for b, L in enumerate(lens)], [rows[n - b:n - b + L] for b, L in enumerate(lens)])
+        q = rng.standard_normal((n, H, D), dtype=np.float32)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{H}/{Hkv} x {D}, {lens}")
+        longer = [L + 1 for L in lens]
+        qb, step = rig.step(q, *(rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2)))
+        assert_close(step, rig.want(qb, longer), f"{H}/{Hkv} x {D}, {lens} / step")
+        assert np.array_equal(rig.attend(q, lens=longer)[1], step)
+        rig.close()
