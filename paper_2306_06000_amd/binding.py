@@ -98,8 +98,8 @@ def _connect():
     spec = importlib.util.spec_from_file_location("_s3call", path)
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
-    module.connect(*[ctypes.cast(getattr(handle, f), ctypes.c_void_p).value
-                     for f in ("s3_decode_step", "s3_decode_step_static", "s3_kv_append", "s3_decode_attention", "s3_kv_fill_batch")])
+    module.connect(ctypes.c_void_p, *[ctypes.cast(getattr(handle, f), ctypes.c_void_p).value
+                                      for f in ("s3_decode_step", "s3_decode_step_static", "s3_kv_append", "s3_decode_attention", "s3_kv_fill_batch")])
     _call = module
     return module
 

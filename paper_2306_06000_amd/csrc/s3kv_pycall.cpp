@@ -22,6 +22,7 @@ static fill_fn g_fill;
 static append_fn g_append;
 static attention_fn g_attention;
 static PyObject *s_data_ptr, *s_value;
+static PyObject *g_void_p;  // the type ctypes.c_void_p
 
 // 1: converted; 0: a type that is left to the ctypes path; -1: a Python error is set.
 static int address(PyObject *x, void **out) {
@@ -45,15 +46,12 @@ static int address(PyObject *x, void **out) {
     return PyErr_Occurred() ? -1 : ok;
 }
 
-static int handle(PyObject *x, void **out) {  // an arena: a ctypes.c_void_p
-    if (x == Py_None || PyLong_Check(x)) return 0;
+// An arena: a ctypes.c_void_p and nothing else that has a `value` (other ctypes numbers, enum members: the ctypes path refuses them).
+static int handle(PyObject *x, void **out) {
+    if ((PyObject *)Py_TYPE(x) != g_void_p) return 0;
     PyObject *v = PyObject_GetAttr(x, s_value);
-    if (!v) {
-        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return -1;
-        PyErr_Clear();
-        return 0;
-    }
-    const bool ok = PyLong_Check(v);
+    if (!v) return -1;
+    const bool ok = PyLong_Check(v);  // (a null pointer's is None)
     if (ok) *out = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
     Py_DECREF(v);
     return PyErr_Occurred() ? -1 : ok;
@@ -192,10 +190,14 @@ static PyObject *fill(PyObject *, PyObject *const *a, Py_ssize_t count) {
     return PyLong_FromLong(rc);
 }
 
-// Addresses of s3_decode_step, s3_decode_step_static, s3_kv_append, s3_decode_attention and s3_kv_fill_batch of the loaded library.
+// (ctypes.c_void_p, then the addresses of s3_decode_step, s3_decode_step_static, s3_kv_append, s3_decode_attention and
+// s3_kv_fill_batch of the loaded library)
 static PyObject *connect(PyObject *, PyObject *args) {
     unsigned long long s, t, p, q, f;
-    if (!PyArg_ParseTuple(args, "KKKKK", &s, &t, &p, &q, &f)) return nullptr;
+    PyObject *type;
+    if (!PyArg_ParseTuple(args, "O!KKKKK", &PyType_Type, &type, &s, &t, &p, &q, &f)) return nullptr;
+    Py_INCREF(type);
+    Py_XSETREF(g_void_p, type);
     g_step = (step_fn)(uintptr_t)s;
     g_static = (step_fn)(uintptr_t)t;
     g_append = (append_fn)(uintptr_t)p;

@@ -1,6 +1,7 @@
 """The C call path of the per-layer functions hands over what the ctypes path does, for every argument type it takes itself,
 and leaves the others to that path."""
 import ctypes
+import enum
 
 import numpy as np
 import pytest
@@ -42,7 +43,7 @@ def recorder(monkeypatch):
     s3._connect()
     yield r
     lib = ctypes.CDLL(s3.LIB_PATH)  # the extension is one per process: back to the library
-    real.connect(*[ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in SIG])
+    real.connect(ctypes.c_void_p, *[ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in SIG])
 
 
 def calls(arena, ptrs, dtype, scale, stream):
@@ -105,3 +106,26 @@ def test_what_is_no_pointer_is_refused_as_before(recorder):
             with pytest.raises(TypeError):
                 bad[name]()
     assert not recorder.seen
+
+
+class Handle(ctypes.c_void_p):
+    pass
+
+
+NO_ARENA = {"c_int": ctypes.c_int(5), "c_uint64": ctypes.c_uint64(9), "c_size_t": ctypes.c_size_t(16), "enum member": enum.Enum("Colour", {"RED": 5}).RED,
+            "any object with a value": type("Boxed", (), {"value": 16})(), "float": 1.5, "tensor": TENSORS[0]}
+
+
+@pytest.mark.parametrize("what", NO_ARENA, ids=list(NO_ARENA))
+def test_what_is_no_arena_is_refused_as_before(recorder, what):
+    for name, call in calls(NO_ARENA[what], TENSORS, s3.S3_F32, 0.0, 0).items():
+        with pytest.raises(ctypes.ArgumentError):
+            call()
+    assert not recorder.seen
+
+
+@pytest.mark.parametrize("arena,address", [(ctypes.c_void_p(), None), (None, None), (16, 16), (Handle(16), 16)], ids=["null", "none", "number", "subclass"])
+def test_the_arenas_that_ctypes_takes(recorder, arena, address):
+    for name, call in calls(arena, TENSORS, s3.S3_F32, 0.0, 0).items():
+        assert call() == -10 - SIG.index(name)
+        assert recorder.seen[name][0][0] == address
