@@ -10,6 +10,7 @@ loudly otherwise - there is no fallback.
 import ctypes
 import importlib.util
 import os
+import sysconfig
 
 import numpy as np
 
@@ -19,6 +20,7 @@ S3_STATIC_SCRATCH_BYTES = 32 << 20
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("S3KV_LIB") or os.path.join(_HERE, "libs3kv.so")  # S3KV_LIB: a diagnostic build
+CALL_PATH = os.path.join(_HERE, "_s3call" + sysconfig.get_config_var("EXT_SUFFIX"))  # compiled for one interpreter
 _lib = None
 _call = None  # the extension module of the per-layer calls, connected to the loaded library
 
@@ -92,10 +94,9 @@ def _connect():
     """The call path of the per-layer functions.  Raises if it has not been built."""
     global _call
     handle = lib()
-    path = os.path.join(_HERE, "_s3call.so")
-    if not os.path.exists(path):
-        raise RuntimeError(f"{path} is missing: build it with `python -m paper_2306_06000_amd.build`")
-    spec = importlib.util.spec_from_file_location("_s3call", path)
+    if not os.path.exists(CALL_PATH):
+        raise RuntimeError(f"{CALL_PATH} is missing: build it with `python -m paper_2306_06000_amd.build`")
+    spec = importlib.util.spec_from_file_location("_s3call", CALL_PATH)
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
     module.connect(ctypes.c_void_p, *[ctypes.cast(getattr(handle, f), ctypes.c_void_p).value

@@ -7,7 +7,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libs3kv.so")
-CALL_SRC, CALL_LIB = os.path.join(CSRC, "s3kv_pycall.cpp"), os.path.join(HERE, "_s3call.so")  # the binding's call path
+# The binding's call path; its name carries the interpreter it is compiled for (another one finds nothing and says so).
+CALL_SRC, CALL_LIB = os.path.join(CSRC, "s3kv_pycall.cpp"), os.path.join(HERE, "_s3call" + sysconfig.get_config_var("EXT_SUFFIX"))
 # (source, extra defines, object name); the multi-head attention kernels are one object per head dimension
 HEAD_DIMS = (64, 96, 128, 256)
 UNITS = [("s3kv_attn_inst.hip", [f"-DS3_INST_D={d}"], f"s3kv_attn_d{d}.o") for d in HEAD_DIMS] + [

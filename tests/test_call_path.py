@@ -2,6 +2,8 @@
 and leaves the others to that path."""
 import ctypes
 import enum
+import os
+import sysconfig
 
 import numpy as np
 import pytest
@@ -129,3 +131,15 @@ def test_the_arenas_that_ctypes_takes(recorder, arena, address):
     for name, call in calls(arena, TENSORS, s3.S3_F32, 0.0, 0).items():
         assert call() == -10 - SIG.index(name)
         assert recorder.seen[name][0][0] == address
+
+
+def test_the_extension_is_named_for_its_interpreter(recorder, monkeypatch, tmp_path):
+    """Another interpreter does not load it: it looks for a file of its own, and says how to build one."""
+    from paper_2306_06000_amd import build
+
+    assert build.CALL_LIB == s3.CALL_PATH and s3.CALL_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert sysconfig.get_config_var("SOABI") in os.path.basename(s3.CALL_PATH)
+    monkeypatch.setattr(s3, "_call", None)
+    monkeypatch.setattr(s3, "CALL_PATH", str(tmp_path / "_s3call.other.so"))
+    with pytest.raises(RuntimeError, match="is missing: build it"):
+        s3.s3_kv_append(ctypes.c_void_p(16), 0, 1, *TENSORS[:4])
