@@ -1,6 +1,7 @@
-"""Batches of few contexts are cut into chunks by a rule on their total and longest rows that runs on the device: both
-sides of its bounds (the smallest chunk, the longest, the number of contexts at which it ends) against the fp32 oracle,
-and the decode step against append + attention, bit for bit."""
+"""Batches of few contexts are cut into chunks by a rule on their total and longest rows that runs on the device, one rule in
+the kernel of one item a workgroup, which serves up to 64 contexts, and another in the streaming kernels: both sides of their
+bounds (the smallest chunk, the longest, the number of contexts at which they end) against the fp32 oracle, and the decode step
+against append + attention, bit for bit."""
 import numpy as np
 import pytest
 
@@ -22,8 +23,17 @@ FAMS = [
 ]
 
 
+def streaming(rig, kind):
+    """The rig's arena on its streaming kernel: a `variant` of the caller's keeps batches off the kernel of one item a workgroup,
+    whose grid is its own, and leaves the division of few contexts as it is."""
+    variant = s3.s3_kv_get_param(rig.a, "default_variant")[1] if kind == 0 else 2
+    assert s3.s3_kv_set_param(rig.a, "variant", variant) == 0
+
+
 @pytest.mark.parametrize("fam", FAMS, ids=[f[0] for f in FAMS])
 def test_few_contexts_are_cut_by_their_rows(fam):
+    """By the default kernel (one item a workgroup up to 64 contexts, streaming beyond), and by the streaming kernel for every
+    batch, on its own grid and on one of seven workgroups."""
     name, H, Hkv, D, kvt, act, kind = fam
     rng = np.random.default_rng(D + H)
     per_load = 1024 // D if kind == 3 else 4 if D == 96 else 512 // D
@@ -40,14 +50,25 @@ def test_few_contexts_are_cut_by_their_rows(fam):
         assert_close(att, rig.want(qb), f"{name} / {what}")
         assert np.array_equal(rig.attend(q)[1], att)
         longer = [L + 1 for L in lens]
-        qb, step = rig.step(q, rng.standard_normal((n, Hkv, D), dtype=np.float32), rng.standard_normal((n, Hkv, D), dtype=np.float32))
+        k_new, v_new = (rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2))
+        qb, step = rig.step(q, k_new, v_new)
         assert_close(step, rig.want(qb, longer), f"{name} / {what} / step")
         if kind == 0:  # (8-bit rows: the step takes the new row in its last wave, in another order of sums)
+            assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
+        streaming(rig, kind)
+        qb, att = rig.attend(q)
+        assert_close(att, rig.want(qb), f"{name} / {what} / streaming")
+        qb, step = rig.step(q, k_new, v_new)
+        assert_close(step, rig.want(qb, longer), f"{name} / {what} / streaming step")
+        assert s3.s3_kv_set_param(rig.a, "grid_blocks", 7) == 0
+        assert np.array_equal(rig.attend(q)[1], att), (name, what)
+        assert np.array_equal(rig.step(q, k_new, v_new)[1], step), (name, what)
+        if kind == 0:
             assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
         rig.close()
 
 
-@pytest.mark.parametrize("fam,batches", [(FAMS[4], (49, 89, 90)), (FAMS[5], (193, 358, 359))], ids=["16 x 256 e4m3", "3 x 128 e4m3"])
+@pytest.mark.parametrize("fam,batches", [(FAMS[4], (52, 89, 90)), (FAMS[5], (193, 358, 359))], ids=["16 x 256 e4m3", "3 x 128 e4m3"])
 def test_eight_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
     """Beyond the batches above, 8-bit rows are cut until their chunks fill two workgroups a compute unit, by a count on the
     device: the first batch of that rule, the last and the first beyond it, with lengths that divide well and badly."""
@@ -96,7 +117,8 @@ def test_eight_bit_rows_in_the_longest_chunks():
                                          (("16 x 64", 16, 16, 64, s3.S3_F16, s3.S3_F16, 0), (72, 97))], ids=["16 x 256", "12 x 128", "5 x 96", "16 x 64"])
 def test_sixteen_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
     """16-bit rows, 9/16 of an item to one and 4/3 to 7/4 items a compute unit: the first and the last batch of the host's
-    part of the rule, and those beside them, with lengths on either side of the device's part: few contexts whose chunks are
+    part of the rule (up to 64 contexts and 3/4 of an item it is asked no more: these batches are attn_few_kernel's, and are run on the
+    streaming kernel too, whose division of them has no such rule), and those beside them, with lengths on either side of the device's part: few contexts whose chunks are
     more than the units, by a little and by an eighth; a long tail, and lengths without one; contexts whole that would be cut
     at 1024 rows; one longer than any chunk; empty ones between.  Attention against the
     oracle; the step against both it and attention over the appended rows, through both of its entry points, bit for bit."""
@@ -117,9 +139,15 @@ def test_sixteen_bit_rows_fill_the_workgroups_that_run_at_once(fam, batches):
             q = rng.standard_normal((n, H, D), dtype=np.float32)
             qb, att = rig.attend(q)
             assert_close(att, rig.want(qb), f"{name} / {n} / {what}")
+            if n <= 64 and n * -(-H // (4 if D == 96 else 512 // D)) <= 192:
+                streaming(rig, kind)
+                qb, other = rig.attend(q)
+                assert_close(other, rig.want(qb), f"{name} / {n} / {what} / streaming")
+            else:
+                other = att
             assert s3.s3_kv_set_param(rig.a, "grid_blocks", 7) == 0
-            assert np.array_equal(rig.attend(q)[1], att), (n, what)
-            assert s3.s3_kv_set_param(rig.a, "grid_blocks", 0) == 0
+            assert np.array_equal(rig.attend(q)[1], other), (n, what)
+            assert s3.s3_kv_set_param(rig.a, "grid_blocks", 0) == 0 and s3.s3_kv_set_param(rig.a, "variant", -1) == 0
             k_new, v_new = (rng.standard_normal((n, Hkv, D), dtype=np.float32) for _ in range(2))
             qb, step = rig.step(q, k_new, v_new)
             longer = [L + 1 for L in lens]

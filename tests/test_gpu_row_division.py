@@ -48,7 +48,9 @@ def test_even_division_over_batches(fam):
         q = rng.standard_normal((n, H, D), dtype=np.float32)
         qb, att = rig.attend(q)
         assert_close(att, rig.want(qb), f"{name} / {what}")
-        for grid in (1, 7):  # the division does not depend on the grid, nor do the bits
+        # the division does not depend on the grid, nor do the bits (no more contexts and columns than compute units: eight waves a
+        # workgroup, on a grid of their own)
+        for grid in (1, 7) if n * Hkv * -(-(H // Hkv) // 16) > 256 else ():
             assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0
             assert np.array_equal(rig.attend(q)[1], att), (name, what, grid)
         assert s3.s3_kv_set_param(rig.a, "grid_blocks", 0) == 0
@@ -114,7 +116,9 @@ FEW = [
 def test_few_contexts_by_waves_and_teams(fam):
     """Chunks of single contexts, each by one wave or by the four waves of a workgroup: tile and quarter edges, the
     borders of the rule (contexts taken whole, one view entry or four per lane, the largest batch it takes), few and
-    many chunks, in both orderings of the merge and on grids that make a workgroup take many; launch after launch."""
+    many chunks, in both orderings of the merge, launch after launch; on grids that make a workgroup take many, where the launch
+    has a grid of the caller's (more contexts and columns than compute units; fewer go to workgroups of eight waves, one chunk each), and for
+    chunks of the caller's size in every batch."""
     from tests.test_gpu_numeric_edges import EdgeRig
 
     name, H, Hkv, D, kvt, act, kind = fam
@@ -128,7 +132,8 @@ def test_few_contexts_by_waves_and_teams(fam):
         q = rng.standard_normal((len(lens), H, D), dtype=np.float32)
         qb, att = rig.attend(q)
         assert_close(att, rig.want(qb), f"{name} / {what}")
-        for grid, sync in ((1, 0), (5, 1), (0, 1), (0, 0)):
+        columns = Hkv * -(-(H // Hkv) // 16)
+        for grid, sync in ((1, 0), (5, 1), (0, 1), (0, 0)) if len(lens) * columns > 256 else ((0, 1), (0, 0)):
             assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0 and s3.s3_kv_set_param(rig.a, "merge_sync", sync) == 0
             assert np.array_equal(rig.attend(q)[1], att), (name, what, grid, sync)
         longer = [L + 1 for L in lens]
@@ -137,7 +142,11 @@ def test_few_contexts_by_waves_and_teams(fam):
         assert np.array_equal(rig.attend(q, lens=longer)[1], step), (name, what)
         for chunk in (32, 96):
             assert s3.s3_kv_set_param(rig.a, "chunk", chunk) == 0
-            assert_close(rig.attend(q, lens=longer)[1], rig.want(qb, longer), f"{name} / {what} / chunk {chunk}")
+            got = rig.attend(q, lens=longer)[1]
+            assert_close(got, rig.want(qb, longer), f"{name} / {what} / chunk {chunk}")
+            for grid, sync in ((1, 0), (5, 1), (0, 0)):
+                assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0 and s3.s3_kv_set_param(rig.a, "merge_sync", sync) == 0
+                assert np.array_equal(rig.attend(q, lens=longer)[1], got), (name, what, chunk, grid, sync)
         rig.close()
 
 
@@ -187,7 +196,8 @@ def test_eight_waves_a_workgroup_and_the_borders_of_their_rule(fam):
         q = rng.standard_normal((len(lens), H, D), dtype=np.float32)
         qb, att = rig.attend(q)
         assert_close(att, rig.want(qb), f"{name} / {what}")
-        for grid, sync in ((3, 0), (0, 1), (0, 0)):  # the division depends on neither
+        # the bits depend on neither (eight waves: a grid of their own, whatever the caller's)
+        for grid, sync in ((3, 0), (0, 1), (0, 0)) if what == "one more" else ((0, 1), (0, 0)):
             assert s3.s3_kv_set_param(rig.a, "grid_blocks", grid) == 0 and s3.s3_kv_set_param(rig.a, "merge_sync", sync) == 0
             assert np.array_equal(rig.attend(q)[1], att), (name, what, grid, sync)
         longer = [L + 1 for L in lens]
