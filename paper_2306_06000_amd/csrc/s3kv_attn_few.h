@@ -4,7 +4,7 @@
 // A launch of few rows is a chain of latencies, and most of it instructions that run once.  attn_step_kernel spent, on one
 // context of 1450 rows (16 x 256 fp16, MI355X, us from the launch's start): 1.8 until the batch view stood in LDS, 2.7 until a
 // workgroup knew its item, 7.9 with its rows (a wave's fifteen in four dependent rounds), 9.9 when the chunk was counted and 12.7
-// when one wave had merged twelve pieces.  Here:
+// when one wave had merged twelve pieces.  This one: 1.7 until a workgroup knows its chunk, 5.1 with its rows, 6.7 counted, 8.7 merged.  Here:
 //   * one item a workgroup, no loop around it, hence no invariants computed (and spilled) in front of it; the view stays in
 //     every wave's registers (lane b: context b) and the item is found by a ballot and lane reads, without LDS or a barrier;
 //   * all arguments in one round trip (read where they were used, they cost one each): 0.3 us;
@@ -14,8 +14,8 @@
 //   * the arrival counters are a cache line apart (neighbours in one line, the atomics of 200 workgroups took up to 2.5 us).
 // us a layer, attn_step_kernel and this: 16 x 256 fp16, 1 context of 30..40 rows 5.7, 3.9; of 300..400 9.2, 6.6; of 1400..1500
 // 12.9, 9.5; of 8000 28.1, 26.1; 4 of 17..128 9.5, 6.6; 4 of 500..1500 17.4, 16.2; 16 of 32..1000 28.1, 26.8; 12 x 128 bf16, 1
-// of 1400..1500 12.4, 8.5, 24 of 32..1000 18.1, 17.2; 64 x 96 bf16, 1 of 300..400 9.8, 7.1, 8 of 32..1000 20.9, 21.8 (the
-// most it loses); 3 x 128, 8 of 500..1500 12.0, 7.8.  e4m3 rows (attn_fp8_kernel, whose one wave of eight combines a chunk while
+// of 1400..1500 12.4, 8.5, 24 of 32..1000 18.1, 17.2; 64 x 96 bf16, 1 of 300..400 9.8, 7.1, 12 of 32..1000 30.2, 31.7 (the
+// most it loses, see on_few_kernel); 3 x 128, 8 of 500..1500 12.0, 7.8.  e4m3 rows (attn_fp8_kernel, whose one wave of eight combines a chunk while
 // the others wait): 16 x 256, 1 of 300..400 13.9, 7.9, of 8000 32.9, 19.4, 8 of 32..1000 17.8, 11.9, 40 of 32..1000 39.0, 34.9; 12 x 128,
 // 4 of 17..128 12.6, 7.0.
 #pragma once

@@ -87,6 +87,8 @@ __device__ __forceinline__ float dpp_sum_step(float v) {
 
 // Sum, maximum over a lane and those that differ from it in the sixteen (rows of 16 lanes; WIDE: the half) they are in, without the
 // LDS unit: the swap brings the even rows (the lower half) of a value into one register, the odd ones (the upper) into another.
+// Shared heads, through the LDS unit and by swaps, us a layer: 8q/1kv x 64, 250 contexts of 32..1000 rows 13.1, 12.6, 12q/2kv x 128,
+// 100 of 32..1000 17.4, 17.0, 32q/8kv x 128, 1000 of 2..40 29.6, 28.7; 239 launches 0 to 5 % faster, 1.5 % in the mean.  Multi-head rows level.
 template <bool WIDE, typename F>
 __device__ __forceinline__ float swap_rows(float v, F f) {
     const unsigned u = __builtin_bit_cast(unsigned, v);
@@ -250,6 +252,8 @@ __device__ __forceinline__ u32x4 load16(const char *p) {
 // Quotients of whole numbers from the hardware's reciprocal (an exact integer division is forty instructions, here on
 // the way to a launch's first load).  x / y rounded down, exact for x below 2^24: the product is off by less than one, which the
 // remainder puts right.  And a whole number not below x / y, by less than 2 above it where x / y is below 2^19.
+// Multi-head batch views with divisions and with quotients, us a layer: 16 x 256, 26 contexts of 20..60 rows 8.10, 7.87; 3 x 128, 600 of 5..60
+// 16.9, 16.5; 16 x 64, 128 of 20..100 10.9, 10.7; level in longer launches.
 __device__ __forceinline__ int quotient(int x, int y) {
     const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y)), r = x - q * y;
     return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
@@ -576,8 +580,8 @@ __device__ __forceinline__ BatchView build_batch_view(const AttnArgs &a, char *d
         // l*E .. l*E+E-1; a serial prefix inside the lane, one DPP scan across lanes per class) and the
         // workgroup meets at ONE barrier.  The general path below needs four barriers and LDS round trips
         // between them, which cost every workgroup of a small launch about 1.5 us before its first load.
-        // E is a compile-time constant per batch size class: the per-entry work (two integer divisions) is
-        // not spent on entries a small batch does not have.
+        // E is a compile-time constant per batch size class: the per-entry work (quotients for its chunks and its
+        // class) is not spent on entries a small batch does not have.
         if (wave == 0) {
             if (n <= 64) one_wave_view<1, UNITS>(a, off_s, len_s, pre, wave_sums);
             else if (n <= 128) one_wave_view<2, UNITS>(a, off_s, len_s, pre, wave_sums);

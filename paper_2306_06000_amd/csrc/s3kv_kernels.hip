@@ -703,7 +703,9 @@ static size_t gqa_partial_slots(const s3_arena *a, int n) {
 // 4/5 (and 64 contexts, a lane each), in up to 2 * cus / n_hg chunks.  Beyond, whole contexts fill most of the chip and the
 // streaming kernels' balance is as good or better.  us a layer, streaming kernel and this one: 16-bit, 16 x 256, 24 contexts
 // (the last) of 20..200 rows 14.8, 12.2, of 500..1500 73.7, 68.5, of 32..1000 37.6, 37.5; 26 (beyond) of 500..1500 87.6, 75.7,
-// but 40 of 32..1000 60.8, 63.8, 48 70.4, 83.5; 64 x 96, 18 of 20..200 12.8, 14.9.  e4m3, 16 x 256, 50 of 20..100 13.2, 10.2, of
+// but 40 of 32..1000 60.8, 63.8, 48 70.4, 83.5; 64 x 96, 18 of 20..200 12.8, 14.9.  The lengths are not known here, so a batch below the
+// line can be slower where they happen to divide badly (64 x 96, 12 of 32..1000 rows 30.2, 31.7), and one above it could gain; over 60 kinds
+// of batches below it, four draws of the lengths each, a kind takes 0.95 of the time, the worst (32 x 128, 24 of 1000..2000) 1.014.  e4m3, 16 x 256, 50 of 20..100 13.2, 10.2, of
 // 300..600 38.6, 37.3, of 1000..2000 105.7, 107.1; 64 (beyond) of 20..100 13.8, 10.6, but of 32..1000 53.3, 56.8.  Rows of fewer 8-bit
 // heads than a wave load takes, and that divide it, several to a load, stay with attn_fp8_kernel.
 static bool on_few_kernel(const s3_arena *a, int n, int n_hg) {
@@ -733,7 +735,7 @@ static size_t chunk_slots(const s3_arena *a, int n, int n_hg, size_t slot_bytes,
     if (whole <= fixed && fill + n > fixed) fill = 0;
     *units = fill > 0 ? (int32_t)(fill | (eight_bit ? 0 : 1 << 16)) : 0;
     if (fill > want) want = fill;
-    if (on_few_kernel(a, n, n_hg)) want = 2 * cus / n_hg;  // (at most 2 MiB: in the fixed buffer always)
+    if (on_few_kernel(a, n, n_hg)) want = 2 * cus / n_hg;  // (with the n slots below 3 MiB: in the fixed buffer always)
     return (size_t)(want > 0 && want + n > whole ? want + n : whole);
 }
 
